@@ -1,9 +1,11 @@
 // no_select_hot and the embedding cache (Section 4.1.2): hotness = how often a vertex lands in
 // V^1 (the set whose layer-1 embedding could be reused) while pre-sampling the training batches;
 // the hot set is the top floor(fraction * V) by (count descending, id ascending).
+#include <algorithm>
 #include <mutex>
 #include <unordered_set>
 #include "primitives.hpp"
+#include "draw.hpp"
 #include "handles.hpp"
 
 #include <math.h>
@@ -19,6 +21,118 @@ __global__ void count_members_kernel(const int32_t* ids, const int32_t* d_n, int
     const int32_t v = ids[i];
     if (n_vertices > 0 && (uint32_t)v >= (uint32_t)n_vertices) { *bad_flag = 1; return; }
     atomicAdd(&freq[v], 1);       // integer count: order independent
+}
+
+// One workgroup pre-samples one whole batch, all hops in one launch: V^1 is only wanted as a set, so a vertex is a bit of the
+// batch's bitmap (workgroup-scope atomics: they end in the L2 of the die the workgroup runs on) and the order in which the
+// lanes meet it does not matter; the draws themselves depend on nothing but (stream, vertex, slot, hop). Hops above the last
+// also append every vertex they meet for the first time to the batch's list, the destinations of the next hop.
+// Batches are independent, so as many workgroups run as there are batches in a group (train ids job % n_batches).
+// Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
+// unit. Measured (2.4 M vertices, 124 M edges, 1523 batches of 1024 seeds, fanouts 15 and 10): no_select_hot 117 ms with the
+// batches one after another through the training sampler, 5.2 ms like this; a group of 508 batches takes 1.26 ms and moves 3.7 GB (64-byte
+// sectors of column entries, bitmap lines in and out).
+constexpr int PRESAMPLE_THREADS = 1024;
+struct PresampleHops { int32_t fanout[NO_MAX_LAYERS]; int32_t n; };
+template <int G, typename RowT>
+__global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(const RowT* __restrict__ rowptr, const int32_t* __restrict__ col,
+                                                                      const int32_t* __restrict__ train, int64_t n_train,
+                                                                      int32_t batch, int64_t n_batches, int64_t first_job,
+                                                                      uint64_t seed, PresampleHops hops, int32_t n_vertices,
+                                                                      uint32_t* bitmaps, int64_t words, int32_t* lists,
+                                                                      int64_t list_cap, int32_t* bad_flag) {
+    __shared__ int32_t n_list;
+    const int64_t job = first_job + blockIdx.x;
+    const int64_t lo = (job % n_batches) * batch;
+    const int32_t n_seeds = (int32_t)min((int64_t)batch, n_train - lo);
+    uint32_t* bm = bitmaps + (int64_t)blockIdx.x * words;
+    int32_t* list = lists + (int64_t)blockIdx.x * list_cap;
+    const uint64_t key = seed + (uint64_t)job;
+    const uint32_t key0 = (uint32_t)key, key1 = (uint32_t)(key >> 32);
+    const int lane = lane_id();
+    // marks u; where it was not marked before and `keep`, it joins the list (one counter access per wavefront)
+    auto visit = [&](bool on, int32_t u, bool keep) {
+        bool fresh = false;
+        if (on) {
+            const uint32_t bit = 1u << (u & 31);
+            fresh = !(__hip_atomic_fetch_or(&bm[u >> 5], bit, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP) & bit);
+        }
+        if (!keep) return;
+        const uint64_t m = __ballot(fresh);
+        int32_t at = 0;
+        if (m && lane == 0) at = atomicAdd(&n_list, __popcll(m));
+        at = __shfl(at, 0, 64);
+        if (fresh) list[at + __popcll(m & ((1ull << lane) - 1ull))] = u;
+    };
+    if (threadIdx.x == 0) n_list = 0;
+    __syncthreads();
+    for (int32_t i0 = 0; i0 < n_seeds; i0 += PRESAMPLE_THREADS) {
+        const int32_t i = i0 + (int32_t)threadIdx.x;
+        int32_t v = i < n_seeds ? train[lo + i] : 0;
+        const bool ok = i < n_seeds && (uint32_t)v < (uint32_t)n_vertices;
+        if (i < n_seeds && !ok) *bad_flag = 1;       // never followed; the caller gets an error and no cache
+        visit(ok, v, true);
+    }
+    __syncthreads();
+    constexpr int ROWS = PRESAMPLE_THREADS / G;
+    const int32_t j = (int32_t)threadIdx.x % G;
+    for (int32_t h = 0; h < hops.n; ++h) {
+        const int32_t n_dst = n_list, k = hops.fanout[h];
+        const uint32_t c3 = (1u << 8) | (uint32_t)h;
+        const bool keep = h + 1 < hops.n;
+        __syncthreads();                              // (everybody has read the count before it grows)
+        for (int32_t i0 = 0; i0 < n_dst; i0 += ROWS) {
+            const int32_t i = i0 + (int32_t)threadIdx.x / G;
+            const bool row_ok = i < n_dst;
+            int32_t v = 0;
+            int64_t begin = 0, d = 0;
+            if (row_ok) {
+                v = list[i];
+                begin = (int64_t)rowptr[v];
+                d = (int64_t)rowptr[v + 1] - begin;
+            }
+            const int64_t pos = draw_position<G>(row_ok, v, d, k, j, key0, key1, c3);
+            const bool on = row_ok && j < k && (int64_t)j < d;
+            visit(on, on ? col[begin + pos] : 0, keep);
+        }
+        __syncthreads();
+    }
+}
+
+// freq[v] += number of bitmaps that hold v. A thread owns one word (32 vertices) of up to COUNT_MAPS bitmaps and adds them
+// up in bit planes: eighteen operations on a word count 32 vertices at once, and a vertex costs one atomic per COUNT_MAPS batches
+// instead of one per batch.
+constexpr int COUNT_PLANES = 9, COUNT_MAPS = (1 << COUNT_PLANES) - 1;
+__global__ void __launch_bounds__(256) count_bitmaps_kernel(const uint32_t* __restrict__ bitmaps, int64_t words, int32_t n_maps,
+                                                            int64_t n_vertices, int32_t* freq) {
+    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (w >= words) return;
+    const int32_t first = (int32_t)blockIdx.y * COUNT_MAPS, last = min(n_maps, first + COUNT_MAPS);
+    uint32_t plane[COUNT_PLANES] = {0};
+    auto add = [&](uint32_t c) {
+#pragma unroll
+        for (int p = 0; p < COUNT_PLANES; ++p) {
+            const uint32_t carry = plane[p] & c;
+            plane[p] ^= c;
+            c = carry;
+        }
+    };
+    int32_t m = first;
+    for (; m + 8 <= last; m += 8) {
+        uint32_t x[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) x[q] = bitmaps[(int64_t)(m + q) * words + w];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) add(x[q]);
+    }
+    for (; m < last; ++m) add(bitmaps[(int64_t)m * words + w]);
+#pragma unroll
+    for (int b = 0; b < 32; ++b) {
+        int32_t n = 0;
+#pragma unroll
+        for (int p = 0; p < COUNT_PLANES; ++p) n |= (int32_t)((plane[p] >> b) & 1u) << p;
+        if (n && w * 32 + b < n_vertices) atomicAdd(&freq[w * 32 + b], n);      // integer count: order independent
+    }
 }
 
 __global__ void hot_keys_kernel(const int32_t* freq, int64_t n, uint32_t max_count, uint32_t* keys, uint32_t* ids) {
@@ -44,6 +158,14 @@ void cache_register(no_cache_s* c) { std::lock_guard<std::mutex> l(g_cache_mutex
 void cache_unregister(no_cache_s* c) { std::lock_guard<std::mutex> l(g_cache_mutex); g_live_caches.erase(c); }
 bool cache_is_live(no_cache_s* c) { std::lock_guard<std::mutex> l(g_cache_mutex); return g_live_caches.count(c) != 0; }
 }  // namespace no
+
+// Whether whole batches are pre-sampled by one workgroup each, a group of them per launch, or one after the other with the
+// training sampler, every hop spread over the chip. A batch takes the sampler a dozen launches (about 80 us) however small it
+// is, and a workgroup about 2 us per 1024 slots, 512 of them at a time: few but very large batches stay with the sampler.
+static bool presample_by_group(int64_t n_batches, int64_t slots_per_batch) {
+    const double rounds = (double)((n_batches + 511) / 512);
+    return rounds * (20.0 + 2.0 * (double)slots_per_batch / 1024.0) < 80.0 * (double)n_batches;
+}
 
 extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64_t n_train, int32_t batch,
                                  const int32_t* h_fanouts, int32_t n_layers, int32_t presample_epochs,
@@ -86,51 +208,92 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
 
     // pre-sampling: hops 0 .. L-2 of every batch, Philox domain 1
     no_blocks_s* b = nullptr;
-    if (n_layers >= 2) NO_CHECK(blocks_create_impl(g, batch, h_fanouts, n_layers - 1, false, &b));
-    struct BGuard { no_blocks_s* b; ~BGuard() { if (b) { b->release(); delete b; } } } bguard{b};
-    DevBuf<int32_t> bad_flag;          // single-layer models: an id outside [0, V) among the train ids
-    struct FGuard { DevBuf<int32_t>* f; ~FGuard() { f->release(); } } fguard{&bad_flag};
+    struct BGuard { no_blocks_s*& b; ~BGuard() { if (b) { b->release(); delete b; } } } bguard{b};
+    // bad_flag: an id outside [0, V) among the train ids. arena: bitmaps and lists of a group of batches, then the sort's arrays.
+    DevBuf<int32_t> bad_flag, arena;
+    struct FGuard { DevBuf<int32_t>* f[2]; ~FGuard() { f[0]->release(); f[1]->release(); } } fguard{{&bad_flag, &arena}};
     NO_CHECK(bad_flag.alloc(1));
     NO_CHECK(fill_i32(bad_flag.p, 0, 1, st));
-    for (int32_t p = 0; p < presample_epochs; ++p)
-        for (int64_t bi = 0; bi < nb; ++bi) {
-            const int64_t lo = bi * batch;
-            const int32_t n = (int32_t)((lo + batch <= n_train) ? batch : (n_train - lo));
-            if (n_layers >= 2) {
-                NO_CHECK(sample_blocks_impl(g, d_train_ids + lo, n, seed + (uint64_t)p * (uint64_t)nb + (uint64_t)bi, 1u,
-                                            n_layers - 1, nullptr, 0, b, st));
-                const HopBuffers& H = b->hop[n_layers - 2];
-                hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(H.n_src_cap, 256)), dim3(256), 0, st,
-                                   (const int32_t*)H.src_global.p, (const int32_t*)(b->counts.p + 4 * (n_layers - 2) + 1), 0,
-                                   c->freq.p, 0, (int32_t*)nullptr);
-            } else {
-                hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
-                                   d_train_ids + lo, (const int32_t*)nullptr, n, c->freq.p, (int32_t)V, bad_flag.p);
-            }
+    // slots a batch draws at most, and destinations of its last pre-sampled hop at most
+    int64_t slots = 0, dst_cap = batch;
+    int32_t widest = 1;
+    for (int32_t h = 0; h + 1 < n_layers; ++h) {
+        slots += dst_cap * h_fanouts[h];
+        if (h + 2 < n_layers) dst_cap = std::min<int64_t>(V, dst_cap * (h_fanouts[h] + 1));
+        widest = std::max(widest, h_fanouts[h]);
+    }
+    const bool by_group = n_layers >= 2 && presample_by_group(max_count, slots);
+    // A group is as many batches as fit 192 MiB (larger device allocations take the runtime some 250 us to give back), more
+    // where that would make more than 16 groups; groups are of equal size.
+    const int64_t words = ceil_div(V, 32), per_batch = words + dst_cap;       // (32-bit words)
+    int64_t group = 0, arena_words = 0;
+    if (by_group) {
+        const int64_t room = std::max<int64_t>(192ll << 18, std::min<int64_t>(4ll << 28, max_count * per_batch / 16));
+        group = std::max<int64_t>(1, std::min<int64_t>(max_count, room / per_batch));
+        group = ceil_div(max_count, ceil_div(max_count, group));
+        arena_words = group * per_batch;
+    }
+    const int64_t sort_words = c->n_hot > 0 ? 6 * V + (int64_t)(radix_ws_bytes(V) + 15) / 4 : 0;
+    NO_CHECK(arena.alloc((size_t)std::max(arena_words, sort_words)));
+    if (by_group) {
+        uint32_t* bitmaps = (uint32_t*)arena.p;
+        int32_t* lists = arena.p + group * words;
+        PresampleHops hops{};
+        hops.n = n_layers - 1;
+        for (int32_t h = 0; h < hops.n; ++h) hops.fanout[h] = h_fanouts[h];
+        for (int64_t job = 0; job < max_count; job += group) {
+            const int32_t n = (int32_t)std::min<int64_t>(group, max_count - job);
+            NO_CHECK(fill_i32((int32_t*)bitmaps, 0, n * words, st));
+#define NO_LAUNCH_PRESAMPLE(G, RowT, rp)                                                                                        \
+    hipLaunchKernelGGL((presample_kernel<G, RowT>), dim3((unsigned)n), dim3(PRESAMPLE_THREADS), 0, st, rp, g->col.p, d_train_ids, n_train, \
+                       batch, nb, job, seed, hops, (int32_t)V, bitmaps, words, lists, dst_cap, bad_flag.p)
+#define NO_LAUNCH_PRESAMPLE_G(G) \
+    do { if (g->rowptr_bits == 64) NO_LAUNCH_PRESAMPLE(G, int64_t, g->rowptr64.p); else NO_LAUNCH_PRESAMPLE(G, int32_t, g->rowptr32.p); } while (0)
+            if (widest <= 8) NO_LAUNCH_PRESAMPLE_G(8);
+            else if (widest <= 16) NO_LAUNCH_PRESAMPLE_G(16);
+            else if (widest <= 32) NO_LAUNCH_PRESAMPLE_G(32);
+            else NO_LAUNCH_PRESAMPLE_G(64);
+#undef NO_LAUNCH_PRESAMPLE_G
+#undef NO_LAUNCH_PRESAMPLE
+            hipLaunchKernelGGL(count_bitmaps_kernel, dim3((unsigned)ceil_div(words, 256), (unsigned)ceil_div(n, COUNT_MAPS)), dim3(256), 0, st,
+                               (const uint32_t*)bitmaps, words, n, V, c->freq.p);
         }
+    } else {
+        if (n_layers >= 2) NO_CHECK(blocks_create_impl(g, batch, h_fanouts, n_layers - 1, false, &b));
+        for (int32_t p = 0; p < presample_epochs; ++p)
+            for (int64_t bi = 0; bi < nb; ++bi) {
+                const int64_t lo = bi * batch;
+                const int32_t n = (int32_t)((lo + batch <= n_train) ? batch : (n_train - lo));
+                if (n_layers >= 2) {
+                    NO_CHECK(sample_blocks_impl(g, d_train_ids + lo, n, seed + (uint64_t)p * (uint64_t)nb + (uint64_t)bi, 1u,
+                                                n_layers - 1, nullptr, 0, b, st));
+                    const HopBuffers& H = b->hop[n_layers - 2];
+                    hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(H.n_src_cap, 256)), dim3(256), 0, st,
+                                       (const int32_t*)H.src_global.p, (const int32_t*)(b->counts.p + 4 * (n_layers - 2) + 1), 0,
+                                       c->freq.p, 0, (int32_t*)nullptr);
+                } else {
+                    hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
+                                       d_train_ids + lo, (const int32_t*)nullptr, n, c->freq.p, (int32_t)V, bad_flag.p);
+                }
+            }
+    }
     NO_CHECK(launch_status("presample"));
 
     // rank: stable sort of ids by (max_count - freq) keeps ascending id among equal counts
     if (c->n_hot > 0) {
-        DevBuf<uint32_t> k_in, v_in, k_out, v_out, k_tmp, v_tmp;
-        DevBuf<char> ws;
-        struct Tmp { DevBuf<uint32_t>* u[6]; DevBuf<char>* w; ~Tmp() { for (auto p : u) p->release(); w->release(); } }
-            tmp{{&k_in, &v_in, &k_out, &v_out, &k_tmp, &v_tmp}, &ws};
-        NO_CHECK(k_in.alloc((size_t)V)); NO_CHECK(v_in.alloc((size_t)V));
-        NO_CHECK(k_out.alloc((size_t)V)); NO_CHECK(v_out.alloc((size_t)V));
-        NO_CHECK(k_tmp.alloc((size_t)V)); NO_CHECK(v_tmp.alloc((size_t)V));
-        NO_CHECK(ws.alloc(radix_ws_bytes(V)));
+        uint32_t* a = (uint32_t*)arena.p;
+        uint32_t *k_in = a, *v_in = a + V, *k_out = a + 2 * V, *v_out = a + 3 * V, *k_tmp = a + 4 * V, *v_tmp = a + 5 * V;
+        void* ws = (void*)(((uintptr_t)(a + 6 * V) + 15) & ~(uintptr_t)15);
         int64_t blocks = ceil_div(V, 256 * 4);
         if (blocks > 65536) blocks = 65536;
         hipLaunchKernelGGL(hot_keys_kernel, dim3((unsigned)blocks), dim3(256), 0, st, (const int32_t*)c->freq.p, V,
-                           (uint32_t)max_count, k_in.p, v_in.p);
+                           (uint32_t)max_count, k_in, v_in);
         int bits = ilog2_ceil((uint64_t)max_count + 1);
         if (bits < 1) bits = 1;
-        NO_CHECK(radix_sort_pairs(k_in.p, v_in.p, k_out.p, v_out.p, k_tmp.p, v_tmp.p, nullptr, V, bits, ws.p, st));
+        NO_CHECK(radix_sort_pairs(k_in, v_in, k_out, v_out, k_tmp, v_tmp, nullptr, V, bits, ws, st));
         hipLaunchKernelGGL(hot_slots_kernel, dim3((unsigned)ceil_div(c->n_hot, 256)), dim3(256), 0, st,
-                           (const uint32_t*)v_out.p, c->n_hot, c->hot_ids.p, c->slot_of_vertex.p);
+                           (const uint32_t*)v_out, c->n_hot, c->hot_ids.p, c->slot_of_vertex.p);
         NO_CHECK(launch_status("hot ranking"));
-        NO_HIP_CHECK(hipStreamSynchronize(st));
     }
     NO_HIP_CHECK(hipStreamSynchronize(st));
     {

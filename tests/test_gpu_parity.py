@@ -207,6 +207,21 @@ def test_select_hot_matches_oracle(fanouts, frac):
     assert not view["emb"].cpu().numpy().any()
 
 
+@pytest.mark.parametrize("V,E,n_train,batch,fanouts,bits", [
+    (1003, 20_000, 651, 1, (4, 3), 32),            # more batches than a counter of the bitmap count holds, a last word of 11 vertices
+    (1003, 20_000, 650, 3, (33, 5, 2), 64),        # a lane group per row as wide as a wavefront, a ragged last batch
+    (4096, 60_000, 4096, 1500, (17, 9, 4), 64),    # a batch of more seeds than a workgroup has threads
+    (10_000, 100_000, 9_000, 9_000, (10, 5), 32)]) # one large batch: spread over the chip by the training sampler
+def test_select_hot_batch_counts_and_sizes(V, E, n_train, batch, fanouts, bits):
+    b = nb()
+    src, dst, og, gg = make_graph(V, E, 3, bits)
+    train = si.train_split(V, 1.0, 3)[:n_train]
+    oc = ora.select_hot(og, train, batch, fanouts, 1, 0.25, 1, 4, 9)
+    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, fanouts, 1, 0.25, 1, 4, 9), V)
+    assert np.array_equal(view["freq"].cpu().numpy().astype(np.int64), oc.freq)
+    assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
+
+
 def test_sample_blocks_with_cache_lookup():
     b = nb()
     w = si.WORKLOADS["tiny"]
