@@ -62,7 +62,16 @@ inline int32_t launch_status(const char* what) {
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline int ilog2_ceil(uint64_t x) { int b = 0; while ((1ull << b) < x) ++b; return b; }
 
-// A device allocation owned by a handle.
+// Device memory through the library's pool (pool.hip). A free waits for the block's device first; inside a ReleaseScope
+// only the first one does.
+hipError_t device_alloc(void** out, size_t bytes);
+void device_free(void* p);
+struct ReleaseScope { ReleaseScope(); ~ReleaseScope(); };
+// The pool gives everything back when the last handle (graph, blocks, cache, model) is gone.
+void handle_created();
+void handle_destroyed();
+
+// A device allocation owned by a handle or a call.
 template <typename T>
 struct DevBuf {
     T* p = nullptr;
@@ -70,15 +79,15 @@ struct DevBuf {
     int32_t alloc(size_t count) {
         n = count;
         if (count == 0) count = 1;
-        hipError_t e = hipMalloc((void**)&p, count * sizeof(T));
+        hipError_t e = device_alloc((void**)&p, count * sizeof(T));
         if (e != hipSuccess) {
             p = nullptr;
-            set_error("hipMalloc of %zu bytes failed: %s", count * sizeof(T), hipGetErrorString(e));
+            set_error("allocation of %zu bytes of device memory failed: %s", count * sizeof(T), hipGetErrorString(e));
             return NO_ERR_HIP;
         }
         return NO_OK;
     }
-    void release() { if (p) { (void)hipFree(p); p = nullptr; } n = 0; }
+    void release() { if (p) { device_free(p); p = nullptr; } n = 0; }
 };
 
 constexpr int32_t EMPTY = 0x7fffffff;   // vertex -> local id map: no entry
@@ -90,15 +99,11 @@ constexpr int32_t EMPTY = 0x7fffffff;   // vertex -> local id map: no entry
 size_t scan_ws_bytes(int64_t cap);
 int32_t exclusive_scan_i32(const int32_t* d_in, const int32_t* d_n, int64_t cap, int32_t* d_out,
                            int32_t* d_total, void* ws, hipStream_t st);
-int32_t exclusive_scan_i32_to_i64(const int32_t* d_in, int64_t n, int64_t* d_out, void* ws, hipStream_t st);
 
-// Stable LSD radix sort of (key, value) uint32 pairs on the low `bits` bits of the key.
-// n = min(*d_n, cap) if d_n != NULL else cap. Result lands in keys_out/vals_out (which may be the
-// alt buffers or the inputs depending on the pass count: always returned in *_out).
-size_t radix_ws_bytes(int64_t cap);
+// Stable LSD radix sort of (key, value) uint32 pairs on the low `bits` bits of the key (see radix.hpp).
+size_t radix_ws_bytes(int64_t n);
 int32_t radix_sort_pairs(const uint32_t* keys_in, const uint32_t* vals_in, uint32_t* keys_out, uint32_t* vals_out,
-                         uint32_t* keys_tmp, uint32_t* vals_tmp, const int32_t* d_n, int64_t cap, int bits,
-                         void* ws, hipStream_t st);
+                         uint32_t* keys_tmp, uint32_t* vals_tmp, int64_t n, int bits, void* ws, hipStream_t st);
 
 int32_t fill_i32(int32_t* d, int32_t value, int64_t n, hipStream_t st);
 

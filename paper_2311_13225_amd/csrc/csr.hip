@@ -1,30 +1,79 @@
 // no_build_csr: COO -> in-neighbour CSR on the device (input G(V,E) of Algorithm 1; rows are
 // the N_in(v) of Eq. 1). Two stable radix sorts (by src, then by dst) give rows ascending by
-// src with duplicates kept; the row pointers come from a degree histogram and a prefix sum.
+// src with duplicates kept; the row pointers are looked up in the sorted destinations.
+#include <algorithm>
 #include "primitives.hpp"
+#include "radix.hpp"
 #include "handles.hpp"
 
 namespace no {
 
-__global__ void csr_check_and_count_kernel(const int32_t* src, const int32_t* dst, int64_t n_edges, int64_t n_vertices,
-                                           int32_t* degree, int32_t* bad) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n_edges; i += stride) {
-        int32_t s = src[i], d = dst[i];
-        if (s < 0 || s >= n_vertices || d < 0 || d >= n_vertices) { *bad = 1; continue; }
-        atomicAdd(&degree[d], 1);     // integer count: order independent
+// The caller's edge list as the first pass of the sort reads it: the pair of edge i is (src, dst), and with both directions
+// asked for (i >= n_in) edge i - n_in the other way round. Its counting launch also checks both ends of every edge.
+template <typename IdT>
+struct EdgeSource {
+    const IdT* src; const IdT* dst; int64_t n_in, n_vertices; int32_t* bad;
+    __device__ __forceinline__ uint32_t key(int64_t i) const { return (uint32_t)(i < n_in ? src[i] : dst[i - n_in]); }
+    __device__ __forceinline__ uint32_t val(int64_t i) const { return (uint32_t)(i < n_in ? dst[i] : src[i - n_in]); }
+    __device__ __forceinline__ void keys_checked(int64_t i, int here, uint32_t (&k)[RS_ITEMS]) const {
+        if (i + here <= n_in) {
+            IdT s[RS_ITEMS], d[RS_ITEMS];
+            load_run(src, i, here, s);
+            load_run(dst, i, here, d);
+            bool wrong = false;
+#pragma unroll
+            for (int q = 0; q < RS_ITEMS; ++q) {      // (past `here` the ids read as 0)
+                wrong |= s[q] < 0 || (int64_t)s[q] >= n_vertices || d[q] < 0 || (int64_t)d[q] >= n_vertices;
+                k[q] = (uint32_t)s[q];
+            }
+            if (wrong) *bad = 1;
+        } else if (i >= n_in) {                       // the other direction: already checked
+            IdT d[RS_ITEMS];
+            load_run(dst, i - n_in, here, d);
+#pragma unroll
+            for (int q = 0; q < RS_ITEMS; ++q) k[q] = (uint32_t)d[q];
+        } else {
+            for (int q = 0; q < RS_ITEMS; ++q) {
+                k[q] = q < here ? key(i + q) : 0u;
+                if (i + q < n_in && q < here) {
+                    const IdT s = src[i + q], d = dst[i + q];
+                    if (s < 0 || (int64_t)s >= n_vertices || d < 0 || (int64_t)d >= n_vertices) *bad = 1;
+                }
+            }
+        }
     }
-}
+};
 
-// 64-bit ids on input (NO_CSR_IDS_64): narrowed to the library's 32-bit ids; an id outside [0, V) raises *bad (and V < 2^31)
-__global__ void narrow_ids_kernel(const int64_t* in, uint32_t* out, int64_t n, int64_t n_vertices, int32_t* bad) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) {
-        const int64_t v = in[i];
-        if (v < 0 || v >= n_vertices) { *bad = 1; out[i] = 0u; } else out[i] = (uint32_t)v;
+// rowptr[v] = number of entries of the sorted list below v, v in [0, V]. A block looks up the two ends of its 256 vertices
+// (a wavefront each, 64 probes a step: 5 dependent reads for 10^8 entries instead of 27) and every thread searches between
+// them: the reads of a block stay within a few lines, and nothing is counted edge by edge (one atomic per edge took 6.7 ms
+// on 124 M edges: popular vertices queue up on one word).
+template <typename RowT>
+__global__ void __launch_bounds__(256) rowptr_kernel(const uint32_t* __restrict__ sorted_dst, int64_t n, int64_t n_vertices,
+                                                     RowT* __restrict__ rowptr) {
+    __shared__ int64_t ends[2];
+    const int64_t v0 = (int64_t)blockIdx.x * 256, v = v0 + threadIdx.x;
+    const int wave = (int)(threadIdx.x >> 6), lane = lane_id();
+    if (wave < 2) {
+        const int64_t x = v0 + 256 * (int64_t)wave;
+        int64_t lo = 0, hi = n;                        // the answer lies in [lo, hi]
+        while (lo < hi) {
+            const int64_t step = (hi - lo + 63) / 64, at = lo + step * (lane + 1) - 1;      // lane l probes the last entry of its part
+            const uint64_t m = __ballot(at < hi ? (int64_t)sorted_dst[at] < x : false);
+            const int parts = __popcll(m);                              // parts that lie wholly below x
+            lo = min(hi, lo + step * parts);
+            hi = min(hi, lo + step - 1);                                // the next part's last entry is not below x (or is not there)
+        }
+        if (lane == 0) ends[wave] = lo;
     }
+    __syncthreads();
+    if (v > n_vertices) return;
+    int64_t lo = ends[0], hi = ends[1];
+    while (lo < hi) {
+        const int64_t mid = lo + (hi - lo) / 2;
+        if ((int64_t)sorted_dst[mid] < v) lo = mid + 1; else hi = mid;
+    }
+    rowptr[v] = (RowT)lo;
 }
 
 // NO_CSR_DEDUP: entry i of the (dst, src)-sorted edge list is kept iff it differs from entry i - 1
@@ -35,20 +84,14 @@ __global__ void mark_first_of_run_kernel(const uint32_t* dst, const uint32_t* sr
 }
 
 __global__ void compact_edges_kernel(const uint32_t* dst, const uint32_t* src, const int32_t* keep, const int32_t* pos,
-                                     int64_t n, int32_t* col_out, int32_t* degree) {
+                                     int64_t n, int32_t* col_out, uint32_t* dst_out) {
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     int64_t stride = (int64_t)gridDim.x * blockDim.x;
     for (; i < n; i += stride)
         if (keep[i]) {
             col_out[pos[i]] = (int32_t)src[i];
-            atomicAdd(&degree[dst[i]], 1);     // integer count: order independent
+            dst_out[pos[i]] = dst[i];
         }
-}
-
-__global__ void narrow_rowptr_kernel(const int64_t* in, int32_t* out, int64_t n) {
-    int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    int64_t stride = (int64_t)gridDim.x * blockDim.x;
-    for (; i < n; i += stride) out[i] = (int32_t)in[i];
 }
 
 }  // namespace no
@@ -80,99 +123,91 @@ extern "C" int32_t no_build_csr(const void* src, const void* dst, int64_t n_edge
     g->rowptr_bits = rowptr_bits;
     struct Guard { no_graph_s* g; ~Guard() { if (g) { g->release(); delete g; } } } guard{g};
 
-    const size_t ne = (size_t)n_edges, ne_in = (size_t)n_edges_in;
-    DevBuf<uint32_t> a_k, a_v, b_k, b_v, c_k, c_v;
-    DevBuf<int32_t> degree, bad;
-    DevBuf<char> ws;
-    DevBuf<int64_t> rowptr64, wide;
-    struct Tmp { DevBuf<uint32_t>*u[6]; DevBuf<int32_t>* i[2]; DevBuf<char>* w; DevBuf<int64_t>* r[2];
-                 ~Tmp() { for (auto p : u) p->release(); for (auto p : i) p->release(); w->release(); for (auto p : r) p->release(); } }
-        tmp{{&a_k, &a_v, &b_k, &b_v, &c_k, &c_v}, {&degree, &bad}, &ws, {&rowptr64, &wide}};
-
-    NO_CHECK(a_k.alloc(ne)); NO_CHECK(a_v.alloc(ne));
-    NO_CHECK(b_k.alloc(ne)); NO_CHECK(b_v.alloc(ne));
-    NO_CHECK(c_k.alloc(ne)); NO_CHECK(c_v.alloc(ne));
-    NO_CHECK(degree.alloc((size_t)n_vertices)); NO_CHECK(bad.alloc(1));
-    size_t ws_bytes = radix_ws_bytes(n_edges);
-    size_t sb = scan_ws_bytes(n_vertices > n_edges ? n_vertices : n_edges);
-    if (sb > ws_bytes) ws_bytes = sb;
-    NO_CHECK(ws.alloc(ws_bytes));
-    NO_CHECK(rowptr64.alloc((size_t)n_vertices + 1));
+    // One allocation for the temporaries: two sets of pair arrays that the passes alternate between, a fifth array where
+    // duplicates are dropped, and the passes' scratch.
+    const size_t ne = (size_t)n_edges, stride = (ne + 64) & ~(size_t)63;      // (room for one word more than the edges)
+    const RadixPlan plan(n_edges);
+    const size_t ws_words = std::max(plan.ws_words(), (scan_ws_bytes(n_edges) + 3) / 4);
+    DevBuf<uint32_t> arena;
+    DevBuf<int32_t> bad;
+    DevBuf<char> staged;
+    struct Tmp { DevBuf<uint32_t>* a; DevBuf<int32_t>* b; DevBuf<char>* s; ~Tmp() { ReleaseScope scope; a->release(); b->release(); s->release(); } } tmp{&arena, &bad, &staged};
+    NO_CHECK(arena.alloc((dedup ? 5 : 4) * stride + ws_words));
+    NO_CHECK(bad.alloc(1));
     NO_CHECK(g->col.alloc(ne));
-    NO_CHECK(fill_i32(degree.p, 0, n_vertices, st));
     NO_CHECK(fill_i32(bad.p, 0, 1, st));
+    uint32_t* keys[2] = {arena.p, arena.p + 2 * stride};
+    uint32_t* vals[2] = {arena.p + stride, arena.p + 3 * stride};
+    void* ws = arena.p + (dedup ? 5 : 4) * stride;
+    const uint32_t* sorted_dst = keys[0];
 
-    // a_k = src, a_v = dst (32-bit ids)
-    const hipMemcpyKind kind = (flags & NO_CSR_INPUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    auto grid_for = [](int64_t n) { int64_t b = ceil_div(n, 256 * 4); if (b > 65536) b = 65536; if (b < 1) b = 1; return dim3((unsigned)b); };
-    if (n_edges_in > 0) {
-        if (ids64) {
-            NO_CHECK(wide.alloc(ne_in));
-            for (int which = 0; which < 2; ++which) {
-                NO_HIP_CHECK(hipMemcpyAsync(wide.p, which == 0 ? src : dst, ne_in * 8, kind, st));
-                hipLaunchKernelGGL(narrow_ids_kernel, grid_for(n_edges_in), dim3(256), 0, st, (const int64_t*)wide.p,
-                                   which == 0 ? a_k.p : a_v.p, n_edges_in, n_vertices, bad.p);
-            }
-            NO_CHECK(launch_status("narrow_ids"));
-        } else {
-            NO_HIP_CHECK(hipMemcpyAsync(a_k.p, src, ne_in * 4, kind, st));
-            NO_HIP_CHECK(hipMemcpyAsync(a_v.p, dst, ne_in * 4, kind, st));
-        }
-        if (symmetrise) {       // every edge once more the other way round
-            NO_HIP_CHECK(hipMemcpyAsync(a_k.p + ne_in, a_v.p, ne_in * 4, hipMemcpyDeviceToDevice, st));
-            NO_HIP_CHECK(hipMemcpyAsync(a_v.p + ne_in, a_k.p, ne_in * 4, hipMemcpyDeviceToDevice, st));
-        }
-    }
     if (n_edges > 0) {
-        // range check of every endpoint; without NO_CSR_DEDUP this pass also takes the degree histogram
-        hipLaunchKernelGGL(csr_check_and_count_kernel, grid_for(n_edges), dim3(256), 0, st, (const int32_t*)a_k.p,
-                           (const int32_t*)a_v.p, n_edges, n_vertices, degree.p, bad.p);
-        NO_CHECK(launch_status("csr_check_and_count"));
+        // a host list is copied to the device: 32-bit ids into the arrays that the first pass does not write
+        const size_t id_bytes = ids64 ? 8 : 4, list_bytes = (size_t)n_edges_in * id_bytes;
+        if (!(flags & NO_CSR_INPUT_ON_DEVICE)) {
+            char* at[2] = {(char*)keys[1], (char*)vals[1]};
+            if (ids64) {
+                NO_CHECK(staged.alloc(2 * list_bytes));
+                at[0] = staged.p;
+                at[1] = staged.p + list_bytes;
+            }
+            NO_HIP_CHECK(hipMemcpyAsync(at[0], src, list_bytes, hipMemcpyHostToDevice, st));
+            NO_HIP_CHECK(hipMemcpyAsync(at[1], dst, list_bytes, hipMemcpyHostToDevice, st));
+            src = at[0];
+            dst = at[1];
+        }
+        // stable sort by source, then by destination: rows ascending by source
+        const int bits = ilog2_ceil((uint64_t)n_vertices), passes = radix_passes(bits), width = radix_digit_bits(bits);
+        int to = 0;
+        if (ids64)
+            NO_CHECK(radix_pass(EdgeSource<int64_t>{(const int64_t*)src, (const int64_t*)dst, n_edges_in, n_vertices, bad.p}, plan, 0, width,
+                                keys[to], vals[to], ws, st));
+        else
+            NO_CHECK(radix_pass(EdgeSource<int32_t>{(const int32_t*)src, (const int32_t*)dst, n_edges_in, n_vertices, bad.p}, plan, 0, width,
+                                keys[to], vals[to], ws, st));
+        for (int p = 1; p < passes; ++p, to ^= 1)
+            NO_CHECK(radix_pass(PairArrays{keys[to], vals[to]}, plan, p * width, width, keys[to ^ 1], vals[to ^ 1], ws, st));
+        PairArrays in{vals[to], keys[to]};          // from here on the key is the destination
+        for (int p = 0; p < passes; ++p, to ^= 1) {
+            uint32_t* sources = p + 1 == passes && !dedup ? (uint32_t*)g->col.p : vals[to ^ 1];
+            NO_CHECK(radix_pass(in, plan, p * width, width, keys[to ^ 1], sources, ws, st));
+            in = PairArrays{keys[to ^ 1], sources};
+        }
+        sorted_dst = keys[to];
+        if (dedup) {
+            // keep the first of every run of equal pairs
+            auto grid_for = [](int64_t n) { int64_t b = ceil_div(n, 256 * 4); if (b > 65536) b = 65536; return dim3((unsigned)b); };
+            int32_t* keep = (int32_t*)keys[to ^ 1];
+            int32_t* pos = (int32_t*)vals[to ^ 1];
+            uint32_t* kept_dst = arena.p + 4 * stride;
+            hipLaunchKernelGGL(mark_first_of_run_kernel, grid_for(n_edges), dim3(256), 0, st, sorted_dst, (const uint32_t*)vals[to],
+                               n_edges, keep);
+            NO_CHECK(exclusive_scan_i32(keep, nullptr, n_edges, pos, nullptr, ws, st));
+            hipLaunchKernelGGL(compact_edges_kernel, grid_for(n_edges), dim3(256), 0, st, sorted_dst, (const uint32_t*)vals[to],
+                               (const int32_t*)keep, (const int32_t*)pos, n_edges, g->col.p, kept_dst);
+            NO_CHECK(launch_status("csr dedup"));
+            int32_t kept = 0;
+            NO_HIP_CHECK(hipMemcpyAsync(&kept, pos + n_edges, 4, hipMemcpyDeviceToHost, st));
+            NO_HIP_CHECK(hipStreamSynchronize(st));
+            g->n_edges = kept;
+            sorted_dst = kept_dst;
+        }
     }
+    const dim3 rows((unsigned)ceil_div(n_vertices + 1, 256));
+    if (rowptr_bits == 64) {
+        NO_CHECK(g->rowptr64.alloc((size_t)n_vertices + 1));
+        hipLaunchKernelGGL((rowptr_kernel<int64_t>), rows, dim3(256), 0, st, sorted_dst, g->n_edges, n_vertices, g->rowptr64.p);
+    } else {
+        NO_CHECK(g->rowptr32.alloc((size_t)n_vertices + 1));
+        hipLaunchKernelGGL((rowptr_kernel<int32_t>), rows, dim3(256), 0, st, sorted_dst, g->n_edges, n_vertices, g->rowptr32.p);
+    }
+    NO_CHECK(launch_status("rowptr"));
     int32_t h_bad = 0;
     NO_HIP_CHECK(hipMemcpyAsync(&h_bad, bad.p, 4, hipMemcpyDeviceToHost, st));
     NO_HIP_CHECK(hipStreamSynchronize(st));
     NO_REQUIRE(h_bad == 0, NO_ERR_OUT_OF_RANGE, "no_build_csr: an edge endpoint lies outside [0, V)");
-
-    if (n_edges > 0) {
-        int bits = ilog2_ceil((uint64_t)n_vertices);
-        if (bits < 1) bits = 1;
-        // sort by src (key a_k, value a_v=dst) -> b; then by dst (key b_v, value b_k=src) -> (a_k = dst, col or c_v = src)
-        NO_CHECK(radix_sort_pairs(a_k.p, a_v.p, b_k.p, b_v.p, c_k.p, c_v.p, nullptr, n_edges, bits, ws.p, st));
-        if (!dedup) {
-            NO_CHECK(radix_sort_pairs(b_v.p, b_k.p, a_k.p, (uint32_t*)g->col.p, c_k.p, c_v.p, nullptr, n_edges, bits, ws.p, st));
-        } else {
-            // sorted (dst, src) pairs in (a_k, a_v); keep the first of every run of equal pairs
-            NO_CHECK(radix_sort_pairs(b_v.p, b_k.p, a_k.p, a_v.p, c_k.p, c_v.p, nullptr, n_edges, bits, ws.p, st));
-            int32_t* keep = (int32_t*)b_k.p;           // (the first sort's outputs are free again)
-            hipLaunchKernelGGL(mark_first_of_run_kernel, grid_for(n_edges), dim3(256), 0, st, (const uint32_t*)a_k.p,
-                               (const uint32_t*)a_v.p, n_edges, keep);
-            DevBuf<int32_t> pos_buf;
-            struct PGuard { DevBuf<int32_t>* p; ~PGuard() { p->release(); } } pguard{&pos_buf};
-            NO_CHECK(pos_buf.alloc(ne + 1));
-            NO_CHECK(exclusive_scan_i32(keep, nullptr, n_edges, pos_buf.p, bad.p, ws.p, st));      // (total -> the spare word)
-            NO_CHECK(fill_i32(degree.p, 0, n_vertices, st));
-            hipLaunchKernelGGL(compact_edges_kernel, grid_for(n_edges), dim3(256), 0, st, (const uint32_t*)a_k.p,
-                               (const uint32_t*)a_v.p, (const int32_t*)keep, (const int32_t*)pos_buf.p, n_edges, g->col.p, degree.p);
-            NO_CHECK(launch_status("csr dedup"));
-            int32_t kept = 0;
-            NO_HIP_CHECK(hipMemcpyAsync(&kept, bad.p, 4, hipMemcpyDeviceToHost, st));
-            NO_HIP_CHECK(hipStreamSynchronize(st));
-            g->n_edges = kept;
-        }
-    }
-    NO_CHECK(exclusive_scan_i32_to_i64(degree.p, n_vertices, rowptr64.p, ws.p, st));
-    if (rowptr_bits == 64) {
-        g->rowptr64 = rowptr64;          // hand the buffer over
-        rowptr64.p = nullptr;
-    } else {
-        NO_CHECK(g->rowptr32.alloc((size_t)n_vertices + 1));
-        hipLaunchKernelGGL(narrow_rowptr_kernel, dim3((unsigned)ceil_div(n_vertices + 1, 256)), dim3(256), 0, st,
-                           (const int64_t*)rowptr64.p, g->rowptr32.p, n_vertices + 1);
-        NO_CHECK(launch_status("narrow_rowptr"));
-    }
-    NO_HIP_CHECK(hipStreamSynchronize(st));
     guard.g = nullptr;
+    handle_created();
     *out = g;
     return NO_OK;
 }
@@ -194,5 +229,6 @@ extern "C" int32_t no_graph_destroy(no_graph_t g) {
     if (!g) return NO_OK;
     g->release();
     delete g;
+    handle_destroyed();
     return NO_OK;
 }

@@ -8,7 +8,7 @@ struct no_graph_s {
     no::DevBuf<int32_t> rowptr32;
     no::DevBuf<int64_t> rowptr64;
     no::DevBuf<int32_t> col;
-    void release() { rowptr32.release(); rowptr64.release(); col.release(); }
+    void release() { no::ReleaseScope scope; rowptr32.release(); rowptr64.release(); col.release(); }
 };
 
 namespace no {
@@ -73,6 +73,7 @@ struct no_blocks_s {
     hipEvent_t time_ev0 = nullptr, time_ev1 = nullptr;
     int32_t time_hop = -1;
     void release() {
+        no::ReleaseScope scope;
         if (side) { (void)hipStreamSynchronize(side); (void)hipStreamDestroy(side); side = nullptr; }
         for (auto& e : ev_fork) if (e) { (void)hipEventDestroy(e); e = nullptr; }
         if (ev_side_done) { (void)hipEventDestroy(ev_side_done); ev_side_done = nullptr; }
@@ -104,6 +105,7 @@ struct RefreshState {
     hipEvent_t ev_snap = nullptr, ev_done = nullptr;
     bool pending = false;
     void release() {
+        no::ReleaseScope scope;
         if (stream) { (void)hipStreamSynchronize(stream); (void)hipStreamDestroy(stream); stream = nullptr; }
         if (ev_snap) { (void)hipEventDestroy(ev_snap); ev_snap = nullptr; }
         if (ev_done) { (void)hipEventDestroy(ev_done); ev_done = nullptr; }
@@ -127,6 +129,7 @@ struct no_cache_s {
     int32_t gcn_form = NO_ARCH_GCN;    // the GCN-style form a one-matrix bulk refresh computes
     RefreshState* refresh = nullptr;
     void release() {
+        no::ReleaseScope scope;
         if (refresh) { refresh->release(); delete refresh; refresh = nullptr; }
         hot_ids.release(); slot_of_vertex.release(); version.release(); freq.release(); emb.release();
     }

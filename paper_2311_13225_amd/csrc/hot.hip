@@ -30,7 +30,7 @@ __global__ void count_members_kernel(const int32_t* ids, const int32_t* d_n, int
 // Batches are independent, so as many workgroups run as there are batches in a group (train ids job % n_batches).
 // Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
 // unit. Measured (2.4 M vertices, 124 M edges, 1523 batches of 1024 seeds, fanouts 15 and 10): no_select_hot 117 ms with the
-// batches one after another through the training sampler, 5.2 ms like this; a group of 508 batches takes 1.26 ms and moves 3.7 GB (64-byte
+// batches one after another through the training sampler, 4.3 ms like this; a group of 508 batches takes 1.26 ms and moves 3.7 GB (64-byte
 // sectors of column entries, bitmap lines in and out).
 constexpr int PRESAMPLE_THREADS = 1024;
 struct PresampleHops { int32_t fanout[NO_MAX_LAYERS]; int32_t n; };
@@ -211,7 +211,7 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
     struct BGuard { no_blocks_s*& b; ~BGuard() { if (b) { b->release(); delete b; } } } bguard{b};
     // bad_flag: an id outside [0, V) among the train ids. arena: bitmaps and lists of a group of batches, then the sort's arrays.
     DevBuf<int32_t> bad_flag, arena;
-    struct FGuard { DevBuf<int32_t>* f[2]; ~FGuard() { f[0]->release(); f[1]->release(); } } fguard{{&bad_flag, &arena}};
+    struct FGuard { DevBuf<int32_t>* f[2]; ~FGuard() { ReleaseScope scope; f[0]->release(); f[1]->release(); } } fguard{{&bad_flag, &arena}};
     NO_CHECK(bad_flag.alloc(1));
     NO_CHECK(fill_i32(bad_flag.p, 0, 1, st));
     // slots a batch draws at most, and destinations of its last pre-sampled hop at most
@@ -290,7 +290,7 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
                            (uint32_t)max_count, k_in, v_in);
         int bits = ilog2_ceil((uint64_t)max_count + 1);
         if (bits < 1) bits = 1;
-        NO_CHECK(radix_sort_pairs(k_in, v_in, k_out, v_out, k_tmp, v_tmp, nullptr, V, bits, ws, st));
+        NO_CHECK(radix_sort_pairs(k_in, v_in, k_out, v_out, k_tmp, v_tmp, V, bits, ws, st));
         hipLaunchKernelGGL(hot_slots_kernel, dim3((unsigned)ceil_div(c->n_hot, 256)), dim3(256), 0, st,
                            (const uint32_t*)v_out, c->n_hot, c->hot_ids.p, c->slot_of_vertex.p);
         NO_CHECK(launch_status("hot ranking"));
@@ -306,6 +306,7 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
     }
     guard.c = nullptr;
     no::cache_register(c);
+    handle_created();
     *out = c;
     return NO_OK;
 }
@@ -359,5 +360,6 @@ extern "C" int32_t no_cache_destroy(no_cache_t c) {
     no::cache_unregister(c);
     c->release();
     delete c;
+    handle_destroyed();
     return NO_OK;
 }

@@ -1037,7 +1037,9 @@ extern "C" int32_t no_blocks_create(no_graph_t g, int32_t n_seeds_cap, const int
     NO_REQUIRE(n_seeds_cap >= 1, NO_ERR_INVALID_ARG, "no_blocks_create: n_seeds_cap must be positive");
     NO_REQUIRE(n_seeds_cap <= g->n_vertices, NO_ERR_INVALID_ARG, "no_blocks_create: more seeds than vertices");
     NO_CHECK(check_fanouts(h_fanouts, n_layers, "no_blocks_create"));
-    return blocks_create_impl(g, n_seeds_cap, h_fanouts, n_layers, true, out);
+    NO_CHECK(blocks_create_impl(g, n_seeds_cap, h_fanouts, n_layers, true, out));
+    handle_created();
+    return NO_OK;
 }
 
 extern "C" int32_t no_sample_blocks(no_graph_t g, const int32_t* d_seeds, int32_t n_seeds, uint64_t seed, int64_t step,
@@ -1102,5 +1104,6 @@ extern "C" int32_t no_blocks_destroy(no_blocks_t blocks) {
     if (!blocks) return NO_OK;
     blocks->release();
     delete blocks;
+    handle_destroyed();
     return NO_OK;
 }

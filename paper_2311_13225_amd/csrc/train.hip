@@ -130,6 +130,7 @@ struct no_model_s {
     const void* ahead_features = nullptr;
     no::StageProfiler prof;
     void release() {
+        no::ReleaseScope scope;
         if (prof.created) { for (auto& e : prof.ev) (void)hipEventDestroy(e); prof.created = false; }
         if (ev_dw_join) { (void)hipEventDestroy(ev_dw_join); ev_dw_join = nullptr; }
         if (worker) { worker->shutdown(); delete worker; worker = nullptr; }
@@ -252,6 +253,7 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
     NO_HIP_CHECK(hipMemset(m->stats.p, 0, sizeof(no_step_stats)));
     NO_HIP_CHECK(hipDeviceSynchronize());
     guard.m = nullptr;
+    handle_created();
     *out = m;
     return NO_OK;
 }
@@ -751,6 +753,7 @@ extern "C" int32_t no_model_destroy(no_model_t m) {
     if (!m) return NO_OK;
     m->release();
     delete m;
+    handle_destroyed();
     return NO_OK;
 }
 

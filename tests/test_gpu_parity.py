@@ -70,6 +70,46 @@ def test_build_csr_matches_oracle(V, E, bits):
         assert np.array_equal(col.cpu().numpy(), og.col)
 
 
+@pytest.mark.parametrize("V,E,symmetrise,ids64", [
+    (2, 8191, False, False), (513, 8192, False, True), (512, 8193, True, False),      # tiles of 8192 edges, digits of up to 9 bits
+    (600_000, 4_300_001, False, False),     # more tiles than chunks, three passes a key
+    (70_001, 2_150_003, True, True)])       # the two directions meet inside a thread's run, off 16-byte alignment
+def test_build_csr_tile_and_digit_edges(V, E, symmetrise, ids64):
+    rng = np.random.default_rng(5)
+    src = rng.integers(0, V, E).astype(np.int32)
+    dst = (rng.integers(0, V, E) * rng.integers(0, 2, E)).astype(np.int32)       # half of all edges meet in vertex 0
+    og = ora.build_csr(src, dst, V, symmetrise=symmetrise)
+    ids = np.int64 if ids64 else np.int32
+    rowptr, col = nb().no_graph_view(nb().no_build_csr(dev(src.astype(ids)), dev(dst.astype(ids)), V, 64, symmetrise=symmetrise))[3:]
+    assert np.array_equal(rowptr.cpu().numpy(), og.rowptr)
+    assert np.array_equal(col.cpu().numpy(), og.col)
+
+
+def test_graphs_built_and_destroyed_by_several_threads():
+    """The library's memory is reused across calls: threads with streams of their own must never share a block in use."""
+    import threading
+    wrong = []
+
+    def work(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            for k in range(6):
+                V, E = 3000 + 997 * i, 40_000 + 9001 * k
+                src, dst = si.random_graph_small(V, E, 10 * i + k)
+                og = ora.build_csr(src, dst, V)
+                gg = nb().no_build_csr(dev(src), dev(dst), V, 64)
+                rowptr, col = nb().no_graph_view(gg)[3:]
+                if not (np.array_equal(rowptr.cpu().numpy(), og.rowptr) and np.array_equal(col.cpu().numpy(), og.col)):
+                    wrong.append((i, k))
+                del rowptr, col, gg
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not wrong
+
+
 def test_build_csr_from_device_and_rejects_bad_ids():
     src, dst = si.rmat_edges(500, 5000, 2)
     og = ora.build_csr(src, dst, 500)
