@@ -1,7 +1,138 @@
-// LDS-tiled fp32 MFMA matrix products (see gemm.hpp). Block tile BM x BN x 32 with BM, BN in
-// {64, 128}, 256 threads = 2 x 2 wavefronts, each owning a (BM/2) x (BN/2) sub-tile as
-// v_mfma_f32_32x32x2_f32 accumulators. The tile shape is picked per call so that tall-skinny
-// problems whose row count is a device scalar still spread over the 256 compute units.
+// The fp32 products on the fp32 matrix instruction (forward products, and small ones of either kind) and the reduction of the split
+// weight-gradient products. Large gradient products: gemm_cut.hip.
+#include "gemm_tile.hpp"
+
+namespace no {
+
+// ------------------------------------------------------------------------------------------ NN, small
+
+// Small products (few output tiles, e.g. the classifier layer over the seeds and its input gradient): a block owns a 32x32 output
+// tile and its four wavefronts split the reduction, chunk c of 32 indices going to wave c % 4. Operands go
+// from memory straight into MFMA registers with several chunks of loads in flight, so the product takes a
+// few memory round trips instead of one per 32 indices; the four partial tiles are summed in wave order
+// through LDS. Out-of-range rows and columns are clamped to valid addresses and dropped at the store.
+template <bool B_KC>
+__global__ void __launch_bounds__(256) gemm_nn_small_kernel(GemmNNArgs g) {
+    __shared__ float red[4][16][64];
+    int M = *g.d_M;
+    if (M > g.M_cap) M = g.M_cap;
+    const int m0 = (int)blockIdx.y * 32, n0 = (int)blockIdx.x * 32;
+    if (m0 >= M) return;
+    const int prob = g.accumulate ? 0 : (int)blockIdx.z;
+    const int n_phases = g.accumulate ? g.n_problems : 1;
+    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
+    const int half = lane >> 5, l32 = lane & 31;
+    const int row_c = min(m0 + l32, M - 1), col_c = min(n0 + l32, g.N - 1);
+    float* C = g.C[prob];
+    const int64_t ldc = g.ldc[prob];
+    const int32_t* sp = g.row_scale_indptr[prob];
+    const int32_t* c_rows = prob == 0 ? g.c_rows : nullptr;
+    const int32_t* c_keep_rows = prob == 0 ? g.c_keep_rows : nullptr;
+    int32_t crow[4], krow[4];
+    float scale[4], bias_v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {       // indices and scales of this thread's four output elements, requested before the
+                                        // operands so that they arrive behind them instead of after the products
+        const int e = (int)threadIdx.x + 256 * i;
+        const int r = e >> 6, ln = e & 63;
+        const int row = min(m0 + acc_row(r, ln), M - 1), col = min(n0 + (ln & 31), g.N - 1);
+        crow[i] = c_rows ? c_rows[row] : row;
+        krow[i] = c_keep_rows ? c_keep_rows[row] : -1;
+        bias_v[i] = g.bias ? g.bias[col] : 0.f;
+        scale[i] = 1.f;
+        if (sp) {
+            const int len = sp[row + 1] - sp[row] + g.row_scale_plus;
+            scale[i] = len > 0 ? (g.row_scale_rsqrt ? 1.f / sqrtf((float)len) : 1.f / (float)len) : 0.f;
+        }
+    }
+    floatx16 acc, acc2;                       // two sets, so consecutive MFMAs of a round do not depend on each other
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
+    int chunk_base = 0;                       // chunks of earlier phases
+    for (int ph = 0; ph < n_phases; ++ph) {
+        const int q = g.accumulate ? ph : prob;
+        const int K = g.K[q];
+        const float* A = g.A[q] + (int64_t)(g.a_rows[q] ? g.a_rows[q][row_c] : row_c) * g.lda[q];
+        const float* B = g.B[q];
+        const int64_t ldb = g.ldb[q];
+        const int n_chunks = (K + 31) / 32;
+        // first chunk of this phase that belongs to this wave
+        int c = ((wave - chunk_base) % 4 + 4) % 4;
+        for (; c + 4 < n_chunks && (c + 4) * 32 + 32 <= K; c += 8) {     // two full chunks per round
+            float4 av[2][4];
+            float bv[2][4][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int sc = 0; sc < 4; ++sc) {
+                    const int k = (c + 4 * u) * 32 + sc * 8 + half * 4;
+                    av[u][sc] = load4_fast(A + k);
+                    if (B_KC) {
+                        const float4 t = load4_fast(B + (int64_t)col_c * ldb + k);
+                        bv[u][sc][0] = t.x; bv[u][sc][1] = t.y; bv[u][sc][2] = t.z; bv[u][sc][3] = t.w;
+                    } else {
+#pragma unroll
+                        for (int kk = 0; kk < 4; ++kk) bv[u][sc][kk] = B[(int64_t)(k + kk) * ldb + col_c];
+                    }
+                }
+#pragma unroll
+            for (int sc = 0; sc < 4; ++sc) {
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].x, bv[0][sc][0], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].x, bv[1][sc][0], acc2, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].y, bv[0][sc][1], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].y, bv[1][sc][1], acc2, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].z, bv[0][sc][2], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].z, bv[1][sc][2], acc2, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].w, bv[0][sc][3], acc, 0, 0, 0);
+                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].w, bv[1][sc][3], acc2, 0, 0, 0);
+            }
+        }
+        for (; c < n_chunks; c += 4) {                                    // remaining chunks, guarded in k
+#pragma unroll
+            for (int sc = 0; sc < 4; ++sc) {
+                const int k = c * 32 + sc * 8 + half * 4;
+                const float4 a4 = load4_guarded(A + k, K - k);
+                float b4[4];
+                if (B_KC) {
+                    const float4 t = load4_guarded(B + (int64_t)col_c * ldb + k, K - k);
+                    b4[0] = t.x; b4[1] = t.y; b4[2] = t.z; b4[3] = t.w;
+                } else {
+#pragma unroll
+                    for (int kk = 0; kk < 4; ++kk) b4[kk] = k + kk < K ? B[(int64_t)(k + kk) * ldb + col_c] : 0.f;
+                }
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4[0], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4[1], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4[2], acc, 0, 0, 0);
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4[3], acc, 0, 0, 0);
+            }
+        }
+        chunk_base += n_chunks;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r] + acc2[r];
+    __syncthreads();
+    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt 0: see gemm_nn_kernel
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int e = (int)threadIdx.x + 256 * i;
+        const int r = e >> 6, ln = e & 63;
+        const int row = m0 + acc_row(r, ln), col = n0 + (ln & 31);
+        if (row >= M || col >= g.N) continue;
+        float v = ((red[0][r][ln] + red[1][r][ln]) + red[2][r][ln]) + red[3][r][ln] + bias_v[i];
+        if (g.relu) v = v > 0.f ? v : 0.f;
+        C[(int64_t)crow[i] * ldc + col] = v * scale[i];
+        if (krow[i] >= 0) {
+            g.c_keep[(int64_t)krow[i] * ldc + col] = v * scale[i];
+            if (col == 0 && g.c_keep_stamp) g.c_keep_stamp[krow[i]] = g.stamp;
+        }
+    }
+}
+
+// ------------------------------------------------------------------------------------------ NN, forward
+
+// LDS-tiled forward products. Block tile 64 x 64 x 32, 256 threads = 2 x 2 wavefronts, each owning a 32 x 32 sub-tile as
+// v_mfma_f32_32x32x2_f32 accumulators. They stay on the fp32 instruction and sum every output element in one fixed order,
+// because the ReLU decisions of a step hang on the last bits of these sums.
 //
 // Operand tiles sit in LDS in one of two layouts, chosen by how the operand lies in memory:
 //   KC (reduction index contiguous in memory): T[x][k], pitch 36 floats; a lane fetches the four
@@ -9,14 +140,6 @@
 //   XC (tile row/column index contiguous): T[k][x], pitch = tile width; four 4-byte LDS reads.
 // Within each group of 8 reduction indices lanes 0-31 take indices 0-3 and lanes 32-63 take 4-7
 // for MFMA 0-3; both operands use the same assignment, so every index is summed exactly once.
-#include "gemm.hpp"
-
-#include <stdlib.h>
-
-namespace no {
-
-typedef float floatx16 __attribute__((ext_vector_type(16)));
-
 constexpr int BK = 32;
 constexpr int PITCH_KC = 36;
 
@@ -25,31 +148,14 @@ template <bool KC, int BX> struct TileShape {
     static constexpr int PASSES = BX / 32;
 };
 
-// 16-byte load from a 4-byte aligned address (rows of 602 floats start on 8-byte boundaries only).
-typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 load4_fast(const float* p) {
-    float4_a4 v = *reinterpret_cast<const float4_a4*>(p);
-    return make_float4(v.x, v.y, v.z, v.w);
-}
-__device__ __forceinline__ float4 load4_guarded(const float* p, int valid) {
-    if (valid >= 4) return load4_fast(p);      // only the lanes that straddle an edge go element by element
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (valid > 0) v.x = p[0];
-    if (valid > 1) v.y = p[1];
-    if (valid > 2) v.z = p[2];
-    return v;
-}
-
 // Global -> registers for one BX x 32 operand tile. x = tile row/column index, k = reduction index.
 // FAST: the whole tile lies inside the operand (no guards, no branches: the hot path).
-// Otherwise every element is guarded and out-of-range elements read as zero; ones_col >= 0 (XC only)
-// adds a virtual column of ones at index `ones_col`, which makes row `ones_col` of the product the
-// column sums of the other operand (the bias gradient).
+// Otherwise every element is guarded and out-of-range elements read as zero.
 // KC tiles take the memory row of tile row (xr + 32 * pass) from xrow[pass] (the tile row itself, or an entry
 // of a row index when the operand is a set of rows of a larger table).
 template <bool KC, int BX, bool FAST>
 __device__ __forceinline__ void tile_fetch(float4 (&reg)[BX / 32], const float* src, int64_t ld, int x0, int x_lim, int k0,
-                                           int k_lim, const int32_t (&xrow)[BX / 32], int ones_col = -1) {
+                                           int k_lim, const int32_t (&xrow)[BX / 32]) {
     const int tid = (int)threadIdx.x;
     if (KC) {
         const int kq = tid & 7, xr = tid >> 3;
@@ -68,10 +174,6 @@ __device__ __forceinline__ void tile_fetch(float4 (&reg)[BX / 32], const float* 
             if (FAST) reg[pass] = load4_fast(src + (int64_t)gk * ld + gx);
             else {
                 float4 v = load4_guarded(src + (int64_t)gk * ld + gx, gk < k_lim ? x_lim - gx : 0);
-                if (ones_col >= 0 && gk < k_lim && ones_col >= gx && ones_col < gx + 4) {
-                    const int c = ones_col - gx;
-                    if (c == 0) v.x = 1.f; else if (c == 1) v.y = 1.f; else if (c == 2) v.z = 1.f; else v.w = 1.f;
-                }
                 reg[pass] = v;
             }
         }
@@ -155,8 +257,33 @@ __device__ __forceinline__ void tile_mma(const float* As, const float* Bs,
     }
 }
 
-// Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.
-__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+// The first `chunks` of a step's four (a step that sticks out of the reduction holds zeros in the others).
+template <bool A_KC, bool B_KC, int BM, int BN>
+__device__ __forceinline__ void tile_mma_part(const float* As, const float* Bs,
+                                              floatx16 (&acc)[AccSets<BM, BN>::N][BM / 64][BN / 64], int wm, int wn, int chunks) {
+    constexpr int MI = BM / 64, NI = BN / 64, SETS = AccSets<BM, BN>::N;
+    const int lane = (int)(threadIdx.x & 63);
+    const int half = lane >> 5, l32 = lane & 31;
+#pragma unroll
+    for (int chunk = 0; chunk < BK / 8; ++chunk) {
+        if (chunk >= chunks) break;
+        float4 a[MI], b[NI];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a[i] = tile_frag<A_KC, BM>(As, wm * (BM / 2) + i * 32 + l32, chunk, half);
+#pragma unroll
+        for (int i = 0; i < NI; ++i) b[i] = tile_frag<B_KC, BN>(Bs, wn * (BN / 2) + i * 32 + l32, chunk, half);
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+#pragma unroll
+            for (int mi = 0; mi < MI; ++mi)
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni) {
+                    const float av = kk == 0 ? a[mi].x : kk == 1 ? a[mi].y : kk == 2 ? a[mi].z : a[mi].w;
+                    const float bv = kk == 0 ? b[ni].x : kk == 1 ? b[ni].y : kk == 2 ? b[ni].z : b[ni].w;
+                    acc[kk % SETS][mi][ni] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[kk % SETS][mi][ni], 0, 0, 0);
+                }
+    }
+}
 
 template <int SETS, int MI, int NI>
 __device__ __forceinline__ void acc_zero(floatx16 (&acc)[SETS][MI][NI]) {
@@ -187,7 +314,6 @@ struct StepSource {
     const int32_t* a_rows;   // KC layout only: tile row x of A is memory row a_rows[x] (NULL: row x)
     int k_begin, k_lim;      // reduction range of this phase
     int n_steps, n_fast;     // steps in this phase; the first n_fast lie wholly inside the reduction range
-    int ones_col;            // virtual column of ones in A (XC layout only), or -1
 };
 
 // Guarded or unguarded fetch of step t of the flat list (any step; used outside the pipelined loop).
@@ -206,7 +332,7 @@ __device__ __forceinline__ void fetch_step(float4 (&ra)[BM / 32], float4 (&rb)[B
         tile_fetch<A_KC, BM, true>(ra, p.A, p.lda, am0, a_lim, k0, p.k_lim, ar);
         tile_fetch<B_KC, BN, true>(rb, p.B, p.ldb, bn0, b_lim, k0, p.k_lim, brow);
     } else {
-        tile_fetch<A_KC, BM, false>(ra, p.A, p.lda, am0, a_lim, k0, p.k_lim, ar, p.ones_col);
+        tile_fetch<A_KC, BM, false>(ra, p.A, p.lda, am0, a_lim, k0, p.k_lim, ar);
         tile_fetch<B_KC, BN, false>(rb, p.B, p.ldb, bn0, b_lim, k0, p.k_lim, brow);
     }
 }
@@ -368,7 +494,8 @@ __device__ __forceinline__ void run_steps(StepSource p0, StepSource p1, int am0,
             tile_store<A_KC, BM>(rta[i], As + (i % C) * A_FLOATS);
             tile_store<B_KC, BN>(rtb[i], Bs + (i % C) * B_FLOATS);
             __syncthreads();
-            tile_mma<A_KC, B_KC, BM, BN>(As + (i % C) * A_FLOATS, Bs + (i % C) * B_FLOATS, acc, wm, wn);
+            const int t = tail_step(i), k_left = t < p0.n_steps ? p0.k_lim - t * BK : p1.k_lim - (t - p0.n_steps) * BK;
+            tile_mma_part<A_KC, B_KC, BM, BN>(As + (i % C) * A_FLOATS, Bs + (i % C) * B_FLOATS, acc, wm, wn, (k_left + 7) / 8);
         }
 }
 
@@ -394,19 +521,6 @@ __device__ __forceinline__ void acc_to_lds(float* Cs, const floatx16 (&acc)[AccS
                     acc_get<SETS, MI, NI>(acc, mi, ni, r);
     __syncthreads();
 }
-
-// Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by linear
-// id. The tiles that share an operand panel (all column tiles of one row tile; all tiles of one
-// reduction slice) get consecutive *logical* ids, and logical ids are dealt out in chunks per XCD, so
-// a panel is fetched into one L2 once instead of into several.
-constexpr int N_XCD = 8;
-__device__ __forceinline__ int64_t xcd_logical_id(int64_t total_padded) {
-    const int64_t id = blockIdx.x;
-    return (id % N_XCD) * (total_padded / N_XCD) + id / N_XCD;
-}
-static inline unsigned xcd_padded(int64_t total) { return (unsigned)(ceil_div(total, N_XCD) * N_XCD); }
-
-// ------------------------------------------------------------------------------------------ NN
 
 template <bool B_KC, int BM, int BN, int GRP = 1, int STG = 2, int OCC = 2>
 __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
@@ -467,9 +581,9 @@ __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
     {
         const int q0 = g.accumulate ? 0 : prob, q1 = g.accumulate && n_phases > 1 ? 1 : q0;
         StepSource p0{g.A[q0], g.lda[q0], g.B[q0], g.ldb[q0], g.a_rows[q0], 0, g.K[q0], (g.K[q0] + BK - 1) / BK,
-                      g.K[q0] / BK, -1};
+                      g.K[q0] / BK};
         StepSource p1{g.A[q1], g.lda[q1], g.B[q1], g.ldb[q1], g.a_rows[q1], 0, g.K[q1],
-                      n_phases > 1 ? (g.K[q1] + BK - 1) / BK : 0, n_phases > 1 ? g.K[q1] / BK : 0, -1};
+                      n_phases > 1 ? (g.K[q1] + BK - 1) / BK : 0, n_phases > 1 ? g.K[q1] / BK : 0};
         run_steps<true, B_KC, BM, BN, GRP, STG>(p0, p1, m0, M, n0, g.N, As, Bs, acc, wm, wn);
     }
     acc_to_lds<BM, BN>(smem, acc, wm, wn);
@@ -504,264 +618,40 @@ __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
     }
 }
 
-// Small products (few output tiles, e.g. the classifier layer over the seeds and its input gradient): a block owns a 32x32 output
-// tile and its four wavefronts split the reduction, chunk c of 32 indices going to wave c % 4. Operands go
-// from memory straight into MFMA registers with several chunks of loads in flight, so the product takes a
-// few memory round trips instead of one per 32 indices; the four partial tiles are summed in wave order
-// through LDS. Out-of-range rows and columns are clamped to valid addresses and dropped at the store.
-template <bool B_KC>
-__global__ void __launch_bounds__(256) gemm_nn_small_kernel(GemmNNArgs g) {
-    __shared__ float red[4][16][64];
-    int M = *g.d_M;
-    if (M > g.M_cap) M = g.M_cap;
-    const int m0 = (int)blockIdx.y * 32, n0 = (int)blockIdx.x * 32;
-    if (m0 >= M) return;
-    const int prob = g.accumulate ? 0 : (int)blockIdx.z;
-    const int n_phases = g.accumulate ? g.n_problems : 1;
-    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
-    const int half = lane >> 5, l32 = lane & 31;
-    const int row_c = min(m0 + l32, M - 1), col_c = min(n0 + l32, g.N - 1);
-    float* C = g.C[prob];
-    const int64_t ldc = g.ldc[prob];
-    const int32_t* sp = g.row_scale_indptr[prob];
-    const int32_t* c_rows = prob == 0 ? g.c_rows : nullptr;
-    const int32_t* c_keep_rows = prob == 0 ? g.c_keep_rows : nullptr;
-    int32_t crow[4], krow[4];
-    float scale[4], bias_v[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {       // indices and scales of this thread's four output elements, requested before the
-                                        // operands so that they arrive behind them instead of after the products
-        const int e = (int)threadIdx.x + 256 * i;
-        const int r = e >> 6, ln = e & 63;
-        const int row = min(m0 + acc_row(r, ln), M - 1), col = min(n0 + (ln & 31), g.N - 1);
-        crow[i] = c_rows ? c_rows[row] : row;
-        krow[i] = c_keep_rows ? c_keep_rows[row] : -1;
-        bias_v[i] = g.bias ? g.bias[col] : 0.f;
-        scale[i] = 1.f;
-        if (sp) {
-            const int len = sp[row + 1] - sp[row] + g.row_scale_plus;
-            scale[i] = len > 0 ? (g.row_scale_rsqrt ? 1.f / sqrtf((float)len) : 1.f / (float)len) : 0.f;
-        }
-    }
-    floatx16 acc, acc2;                       // two sets, so consecutive MFMAs of a round do not depend on each other
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = acc2[r] = 0.f;
-    int chunk_base = 0;                       // chunks of earlier phases
-    for (int ph = 0; ph < n_phases; ++ph) {
-        const int q = g.accumulate ? ph : prob;
-        const int K = g.K[q];
-        const float* A = g.A[q] + (int64_t)(g.a_rows[q] ? g.a_rows[q][row_c] : row_c) * g.lda[q];
-        const float* B = g.B[q];
-        const int64_t ldb = g.ldb[q];
-        const int n_chunks = (K + 31) / 32;
-        // first chunk of this phase that belongs to this wave
-        int c = ((wave - chunk_base) % 4 + 4) % 4;
-        for (; c + 4 < n_chunks && (c + 4) * 32 + 32 <= K; c += 8) {     // two full chunks per round
-            float4 av[2][4];
-            float bv[2][4][4];
-#pragma unroll
-            for (int u = 0; u < 2; ++u)
-#pragma unroll
-                for (int sc = 0; sc < 4; ++sc) {
-                    const int k = (c + 4 * u) * 32 + sc * 8 + half * 4;
-                    av[u][sc] = load4_fast(A + k);
-                    if (B_KC) {
-                        const float4 t = load4_fast(B + (int64_t)col_c * ldb + k);
-                        bv[u][sc][0] = t.x; bv[u][sc][1] = t.y; bv[u][sc][2] = t.z; bv[u][sc][3] = t.w;
-                    } else {
-#pragma unroll
-                        for (int kk = 0; kk < 4; ++kk) bv[u][sc][kk] = B[(int64_t)(k + kk) * ldb + col_c];
-                    }
-                }
-#pragma unroll
-            for (int sc = 0; sc < 4; ++sc) {
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].x, bv[0][sc][0], acc, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].x, bv[1][sc][0], acc2, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].y, bv[0][sc][1], acc, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].y, bv[1][sc][1], acc2, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].z, bv[0][sc][2], acc, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].z, bv[1][sc][2], acc2, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[0][sc].w, bv[0][sc][3], acc, 0, 0, 0);
-                acc2 = __builtin_amdgcn_mfma_f32_32x32x2f32(av[1][sc].w, bv[1][sc][3], acc2, 0, 0, 0);
-            }
-        }
-        for (; c < n_chunks; c += 4) {                                    // remaining chunks, guarded in k
-#pragma unroll
-            for (int sc = 0; sc < 4; ++sc) {
-                const int k = c * 32 + sc * 8 + half * 4;
-                const float4 a4 = load4_guarded(A + k, K - k);
-                float b4[4];
-                if (B_KC) {
-                    const float4 t = load4_guarded(B + (int64_t)col_c * ldb + k, K - k);
-                    b4[0] = t.x; b4[1] = t.y; b4[2] = t.z; b4[3] = t.w;
-                } else {
-#pragma unroll
-                    for (int kk = 0; kk < 4; ++kk) b4[kk] = k + kk < K ? B[(int64_t)(k + kk) * ldb + col_c] : 0.f;
-                }
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.x, b4[0], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.y, b4[1], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.z, b4[2], acc, 0, 0, 0);
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a4.w, b4[3], acc, 0, 0, 0);
-            }
-        }
-        chunk_base += n_chunks;
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) red[wave][r][lane] = acc[r] + acc2[r];
-    __syncthreads();
-    __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt 0: see gemm_nn_kernel
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int e = (int)threadIdx.x + 256 * i;
-        const int r = e >> 6, ln = e & 63;
-        const int row = m0 + acc_row(r, ln), col = n0 + (ln & 31);
-        if (row >= M || col >= g.N) continue;
-        float v = ((red[0][r][ln] + red[1][r][ln]) + red[2][r][ln]) + red[3][r][ln] + bias_v[i];
-        if (g.relu) v = v > 0.f ? v : 0.f;
-        C[(int64_t)crow[i] * ldc + col] = v * scale[i];
-        if (krow[i] >= 0) {
-            g.c_keep[(int64_t)krow[i] * ldc + col] = v * scale[i];
-            if (col == 0 && g.c_keep_stamp) g.c_keep_stamp[krow[i]] = g.stamp;
-        }
-    }
+int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);      // gemm_cut.hip
+
+static int32_t launch_small_nn(const GemmNNArgs& a, bool b_transposed, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    dim3 grid((unsigned)ceil_div(a.N, 32), (unsigned)ceil_div(a.M_cap, 32), (unsigned)(a.accumulate ? 1 : a.n_problems));
+    if (b_transposed) NO_LAUNCH_TIMED((gemm_nn_small_kernel<true>), grid, dim3(256), st, ev0, ev1, a);
+    else NO_LAUNCH_TIMED((gemm_nn_small_kernel<false>), grid, dim3(256), st, ev0, ev1, a);
+    return launch_status("gemm_nn_small");
 }
 
-// 64 x 64 tiles at every size: with the branch-free pipeline and the scattered epilogue they measured as fast as or
-// faster than 64 x 128 and 128 x 64 from 8 K to 70 K rows (e.g. 27 K rows: 151 vs 165 us), and they quantise best;
-// register budget for three blocks per compute unit.
-template <bool B_KC>
-static void launch_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    const int64_t z = a.accumulate ? 1 : a.n_problems;
-    dim3 grid(xcd_padded(ceil_div(a.N, 64) * ceil_div(a.M_cap, 64) * z));
-    NO_LAUNCH_TIMED((gemm_nn_kernel<B_KC, 64, 64, 1, 2, 3>), grid, dim3(256), st, ev0, ev1, a);
-}
-
-int32_t gemm_nn(const GemmNNArgs& a, bool b_transposed, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
-    const int64_t z = a.accumulate ? 1 : a.n_problems;
-    if (ceil_div(a.M_cap, 64) * ceil_div(a.N, 64) * z <= 128) {
-        dim3 grid((unsigned)ceil_div(a.N, 32), (unsigned)ceil_div(a.M_cap, 32), (unsigned)z);
-        if (b_transposed) NO_LAUNCH_TIMED((gemm_nn_small_kernel<true>), grid, dim3(256), st, ev0, ev1, a);
-        else NO_LAUNCH_TIMED((gemm_nn_small_kernel<false>), grid, dim3(256), st, ev0, ev1, a);
-        return launch_status("gemm_nn_small");
-    }
-    if (b_transposed) launch_nn<true>(a, st, ev0, ev1);
-    else launch_nn<false>(a, st, ev0, ev1);
+    const int64_t tiles = ceil_div(a.M_cap, 64) * ceil_div(a.N, 64);
+    if (tiles <= 128) return launch_small_nn(a, false, st, ev0, ev1);
+    NO_LAUNCH_TIMED((gemm_nn_kernel<false, 64, 64, 1, 2, 3>), dim3(xcd_padded(tiles)), dim3(256), st, ev0, ev1, a);
     return launch_status("gemm_nn");
 }
 
-// ------------------------------------------------------------------------------------------ TN
-
-// The jobs of one launch (by value in the kernel arguments): job j owns the linear block ids [end_block[j-1], end_block[j]).
-struct TNLaunch { GemmTNArgs job[NO_MAX_LAYERS]; uint32_t end_block[NO_MAX_LAYERS]; int32_t n; };
-
-template <int BM, int BN, int GRP = 1, int STG = 2, int OCC = 2>
-__global__ void __launch_bounds__(256, OCC) gemm_tn_kernel(TNLaunch launch) {
-    int job = 0;
-    uint32_t first = 0;
-    while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
-    const GemmTNArgs& g = launch.job[job];
-    constexpr int MI = BM / 64, NI = BN / 64;
-    constexpr int A_TOTAL = 2 * GRP * TileShape<false, BM>::FLOATS, B_TOTAL = 2 * GRP * TileShape<false, BN>::FLOATS;
-    // the output tile is staged over the operand copies
-    constexpr int SMEM = A_TOTAL + B_TOTAL > OutTile<BM, BN>::FLOATS ? A_TOTAL + B_TOTAL : OutTile<BM, BN>::FLOATS;
-    __shared__ __attribute__((aligned(16))) float smem[SMEM];
-    float* As = smem;
-    float* Bs = smem + A_TOTAL;
-    int R = *g.d_R;
-    if (R > g.R_cap) R = g.R_cap;
-    // a job's blocks in the order of a plain 3-D grid (column tile fastest, then row tile, then problem x slice): dealing
-    // the slices out per XCD measured slower here (the partial tiles are written once and the operand slices are small),
-    // so the tiles of a slice stay spread over the dies
-    const uint32_t id = blockIdx.x - first;
-    const uint32_t gx = (uint32_t)((g.N + BN - 1) / BN), gy = (uint32_t)((g.Kp + 1 + BM - 1) / BM);
-    const int bx = (int)(id % gx), by = (int)((id / gx) % gy), bz = (int)(id / (gx * gy));
-    const int prob = bz / g.splits, split = bz % g.splits;
-    const int used = tn_used_splits(R, g.splits, g.rows_per_split);
-    if (split >= used) return;                 // (the reduction reads the first `used` partials only)
-    int chunk = (R + used - 1) / used;
-    chunk = (chunk + BK - 1) / BK * BK;
-    const int r0 = split * chunk;
-    const int r1 = min(R, r0 + chunk);
-    const int m0 = by * BM, n0 = bx * BN;
-    if (m0 >= g.Kp) {
-        // Kp is a multiple of the tile height: this row tile holds nothing but row Kp, the column sums of G that product
-        // 0 carries (the bias gradient). A tile of matrix products for one row would be a third of the launch's work at
-        // Kp = 128: the sums are taken directly, in a fixed order (row r0 + i by thread group i mod 4, groups combined in
-        // order). Product 1 has no such row (the reduction never reads it).
-        if (prob != 0) return;
-        float* red = smem;                                   // [4][BN]
-        const int c = (int)(threadIdx.x % BN), part = (int)(threadIdx.x / BN);
-        constexpr int PARTS = 256 / BN;
-        float s = 0.f;
-        if (n0 + c < g.N)
-            for (int r = r0 + part; r < r1; r += PARTS) s += g.G[(int64_t)r * g.ldg + n0 + c];
-        red[part * BN + c] = s;
-        __syncthreads();
-        if (part == 0 && n0 + c < g.N) {
-            float t = red[c];
-#pragma unroll
-            for (int q = 1; q < PARTS; ++q) t += red[q * BN + c];
-            g.P[((int64_t)prob * g.splits + split) * (int64_t)(g.Kp + 1) * g.N + (int64_t)g.Kp * g.N + n0 + c] = t;
-        }
-        return;
+int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
+    GemmNNArgs a = args;
+    if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
+    if (ceil_div(a.M_cap, 64) * ceil_div(a.N, 64) * a.n_problems <= 128 || a.K[0] < 8) return launch_small_nn(a, true, st, nullptr, nullptr);
+    if (!a.cut_B[0]) {
+        const bool one = a.B[1] == a.B[0];
+        const size_t each = cut_weights_elements(a.N, a.K[0], true);
+        if (!a.cut_scratch || (one ? 1 : 2) * each * 2 > a.cut_scratch_bytes) return launch_small_nn(a, true, st, nullptr, nullptr);
+        uint16_t* planes = (uint16_t*)a.cut_scratch;
+        NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], true, planes, st));
+        a.cut_B[0] = planes;
+        a.cut_B[1] = one ? planes : planes + each;
     }
-    const int wave = (int)(threadIdx.x >> 6), wm = wave >> 1, wn = wave & 1;
-    constexpr int SETS = AccSets<BM, BN>::N;
-    floatx16 acc[SETS][MI][NI];
-    acc_zero<SETS, MI, NI>(acc);
-    const float* A = g.A[prob];
-    const int64_t lda = g.lda[prob];
-    const int ones_col = prob == 0 ? g.Kp : -1;       // product 0 carries the column sums of G in row Kp
-    if (r0 < r1) {
-        StepSource p0{A, lda, g.G, g.ldg, nullptr, r0, r1, (r1 - r0 + BK - 1) / BK, (r1 - r0) / BK, ones_col};
-        StepSource p1 = p0;
-        p1.n_steps = p1.n_fast = 0;
-        run_steps<false, false, BM, BN, GRP, STG>(p0, p1, m0, g.Kp, n0, g.N, As, Bs, acc, wm, wn);
-    }
-    using OT = OutTile<BM, BN>;
-    acc_to_lds<BM, BN>(smem, acc, wm, wn);
-    const int rows_out = g.Kp + 1;
-    float* P = g.P + ((int64_t)prob * g.splits + split) * (int64_t)rows_out * g.N;
-    const int tid = (int)threadIdx.x, cq = tid % OT::QC, tr = tid / OT::QC;
-    const int col = n0 + cq * 4;
-    const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && col + 4 <= g.N;
-#pragma unroll
-    for (int j = 0; j < OT::PASSES; ++j) {
-        const int lr = tr + OT::ROWS_PER_PASS * j, row = m0 + lr;
-        if (row >= rows_out || col >= g.N) continue;
-        const float4 t = *reinterpret_cast<const float4*>(&smem[lr * OT::PITCH + cq * 4]);
-        float* dst = P + (int64_t)row * g.N + col;
-        if (vec) *reinterpret_cast<float4*>(dst) = t;
-        else {
-            const float v[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (col + i < g.N) dst[i] = v[i];
-        }
-    }
+    return cut_nn(a, st, nullptr, nullptr);
 }
 
-int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    // 64x64 tiles: the output of one split is small, so the chip is filled by many small blocks over a
-    // moderate number of splits rather than by few large blocks over many splits (fewer partials to reduce).
-    constexpr int bm = 64, bn = 64;
-    TNLaunch launch{};
-    uint64_t blocks = 0;
-    for (int32_t j = 0; j < n_jobs && launch.n < NO_MAX_LAYERS; ++j) {
-        const GemmTNArgs& a = jobs[j];
-        if (a.Kp <= 0 || a.N <= 0) continue;
-        blocks += (uint64_t)ceil_div(a.N, bn) * (uint64_t)ceil_div(a.Kp + 1, bm) * (uint64_t)(a.n_problems * a.splits);
-        NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");
-        launch.job[launch.n] = a;
-        launch.end_block[launch.n] = (uint32_t)blocks;
-        ++launch.n;
-    }
-    if (launch.n == 0) return NO_OK;
-    dim3 grid((unsigned)blocks);
-    NO_LAUNCH_TIMED((gemm_tn_kernel<64, 64, 1, 2, 3>), grid, dim3(256), st, ev0, ev1, launch);
-    return launch_status("gemm_tn");
-}
+// ------------------------------------------------------------------------------------------ gradient reduction
 
 // Sums the split partial products in split order: g_self = rows [0,Kp) of product 0, g_bias = row Kp of
 // product 0, g_neigh = rows [0,Kp) of product 1. With lr != 0 the parameters take their SGD step in the
@@ -844,6 +734,18 @@ __global__ void __launch_bounds__(256) reduce_grads_kernel(ReduceLaunch launch, 
         const uint32_t u = __float_as_uint(*w);
         const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
         (q == 0 ? a.wt_self : a.wt_neigh)[(int64_t)n * a.Kpad + k] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    }
+    if (a.cut_bwd[q] && w && !bias_row) {
+        // and its planes for the next step's input gradients (cut_weights' layout, transposed)
+        const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
+        const int64_t plane_b = (int64_t)cut_pad(N) * Kp;
+        float v = *w;
+#pragma unroll
+        for (int p = 0; p < 3; ++p) {
+            const uint32_t h = bf16_pair(v, 0.f) & 0xffffu;
+            v -= __uint_as_float(h << 16);
+            a.cut_bwd[q][p * plane_b + ((int64_t)(n >> 3) * Kp + k) * 8 + (n & 7)] = (uint16_t)h;
+        }
     }
 }
 

@@ -1,5 +1,5 @@
 // fp32 matrix products for the dense UPDATE of Eq. 2 and its gradients, on the gfx950 matrix
-// cores (v_mfma_f32_32x32x2_f32). Two shapes:
+// cores (gemm_cut.hip; gemm.hip for small ones). Two shapes:
 //   NN: C[M,N] = sum_p A_p[M,K_p] * B_p[K_p,N] (+ bias, ReLU, optional 1/len row scale); M is a
 //       device scalar (rows past it are skipped); B may be given transposed; the rows of A_p may be
 //       picked out of a larger table by an index (gather fused into the operand load).
@@ -15,6 +15,10 @@ struct GemmNNArgs {
     const int32_t* a_rows[2];             // per problem: row m of the operand is row a_rows[m] of A (NULL: row m)
     const float* B[2]; int64_t ldb[2]; int b_align[2];
     int32_t K[2];
+    // large input gradients take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch (where
+    // there is no room for them, the kernel for small products takes over)
+    const uint16_t* cut_B[2];
+    void* cut_scratch; size_t cut_scratch_bytes;
     float* C[2]; int64_t ldc[2];
     const int32_t* row_scale_indptr[2];   // per problem: multiply row m by 1/(indptr[m+1]-indptr[m]+row_scale_plus) (0 if that is 0)
     int32_t row_scale_plus;               // 1 when the row itself counts in the average (Eq. 1 over N_in(v) U {v})
@@ -67,6 +71,13 @@ struct GemmBf16TNArgs {
     float* P; int32_t Kp, N;                                 // partials in the layout of GemmTNArgs
     const int32_t* d_R; int32_t R_cap; int32_t splits; int32_t rows_per_split;
 };
+// Weights cut for the large gradient products (gemm_cut.hip): planes of one matrix [K][N], reduction index padded to 32.
+__host__ __device__ inline int32_t cut_pad(int32_t K) { return (K + 31) / 32 * 32; }
+inline size_t cut_weights_elements(int32_t K, int32_t N, bool transposed) {
+    return (size_t)3 * (transposed ? (size_t)cut_pad(N) * K : (size_t)cut_pad(K) * N);
+}
+// w1 may be NULL; the second matrix's planes follow the first's (cut_weights_elements apart)
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st);
 inline int32_t bf16_kpad(int32_t K) { return (K + 15) / 16 * 16; }
 int32_t weights_to_bf16_t(const float* w, int32_t K, int32_t N, int32_t Kpad, uint16_t* out, hipStream_t st);
 int32_t gemm_bf16_nn(const GemmBf16NNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -93,6 +104,8 @@ struct ReduceArgs {
     const int32_t* d_R = nullptr; int32_t R_cap = 0; int32_t rows_per_split = 0;   // as in the product: the slices it used
     // bf16 copies of the two matrices ([N][Kpad], weights_to_bf16_t's layout), rewritten with the updated values (or NULL)
     uint16_t* wt_self = nullptr; uint16_t* wt_neigh = nullptr; int32_t Kpad = 0;
+    // planes of the two transposed matrices for the layer's input gradient, rewritten too (or NULL)
+    uint16_t* cut_bwd[2] = {nullptr, nullptr};
 };
 
 // Weight-gradient work of several layers carried by one product launch and one reduction launch: the gradients of an
@@ -111,7 +124,9 @@ struct GradJobs {
 };
 
 // ev0 / ev1 (optional): events that take the product kernel's own start and end times
-int32_t gemm_nn(const GemmNNArgs& a, bool b_transposed, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// forward: one result, the sum of the products; input gradient: independent results, B transposed
+int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+int32_t gemm_nn_input_grad(const GemmNNArgs& a, hipStream_t st);
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
 int32_t reduce_grads(const ReduceArgs* jobs, int32_t n_jobs, hipStream_t st, const StatsJob* stats_job = nullptr);

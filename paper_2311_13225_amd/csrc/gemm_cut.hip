@@ -1,0 +1,564 @@
+// The gradients' fp32 matrix products on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16, 16 times the rate of the fp32
+// instruction).
+//
+// Every fp32 operand value is cut into three bf16 values, high + middle + low, each the nearest bf16 of what the ones
+// before it left over: 3 x 8 significand bits hold all 24 of an fp32 number, so nothing of the input is lost. A product of two
+// such sums is nine partial products, each exact in fp32; the six largest are accumulated in fp32 (high x high, high x
+// middle, middle x high, middle x middle, high x low, low x high). The three left out are below 2^-9 2^-18 + 2^-18 2^-9 +
+// 2^-36 < 2^-25.9 of the product, less than a quarter of the 2^-24 by which one fp32 rounding may be off. The largest partial
+// product has an accumulator of its own, which is therefore rounded once per 16 terms (the fp32 instruction: 8 times).
+// Measured against fp64 on random operands, relative 2-norm error of a weight gradient over 25 K rows / an input gradient over
+// 256 columns: fp32 instruction 3.0e-7 / 2.1e-7, this 1.9e-7 / 1.0e-7 (with one accumulator for all six 3.8e-7 / 2.4e-7).
+// (A value within 2^-9 of the largest fp32 number rounds to infinity in its high part: sums with such terms were about to
+// overflow.)
+//
+// Bound: 6 bf16 products per term are 416 TFLOP/s of fp32 products against the fp32 instruction's 157; next to them stand
+// the vector instructions that cut the operands (5.5 an element). So an element is cut as few times as possible: weights
+// once per update (or call), into the order in which the matrix cores take them; rows once per 128 output columns.
+// Measured, fp32 instruction -> this: input gradient of 60 K x 256 rows by two 256 x 256 matrices 176 -> 108 us, 5.5 K rows 21 -> 16;
+// weight gradients of 25 K rows, 2 x 100 x 256: 47 -> 35 us, of 60 K rows, 2 x 256 x 256: 194 -> 130.
+// (Forward products stay on the fp32 instruction: see gemm.hip.)
+#include <algorithm>
+
+#include "gemm_tile.hpp"
+
+namespace no {
+
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+
+constexpr int SK = 32;              // reduction indices per step
+constexpr int SPITCH = SK + 8;      // bf16 elements per LDS row: rows start 20 banks apart
+
+// eight values, cut into the three planes (packed in pairs)
+__device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = f[2 * i], b = f[2 * i + 1];
+        h[i] = bf16_pair(a, b);
+        a -= __uint_as_float(h[i] << 16);
+        b -= __uint_as_float(h[i] & 0xffff0000u);
+        m[i] = bf16_pair(a, b);
+        a -= __uint_as_float(m[i] << 16);
+        b -= __uint_as_float(m[i] & 0xffff0000u);
+        l[i] = bf16_pair(a, b);
+    }
+    p[0] = make_uint4(h[0], h[1], h[2], h[3]);
+    p[1] = make_uint4(m[0], m[1], m[2], m[3]);
+    p[2] = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+__device__ __forceinline__ bf16x8_t cut_fragment(const uint16_t* p) {
+    bf16x8_t v;
+    __builtin_memcpy(&v, __builtin_assume_aligned(p, 16), 16);
+    return v;
+}
+
+// The partial products of one pair of fragments, smallest first, and the accumulator each goes to.
+constexpr int CUT_TERMS = 6;
+struct CutTerm { int a, b, acc; };
+__device__ constexpr CutTerm CUT_TERM[CUT_TERMS] = {{2, 0, 0}, {0, 2, 0}, {1, 1, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+
+// ------------------------------------------------------------------------------------------ weights
+
+// Both matrices of a layer ([K][N] fp32, row-major) cut into planes: out[matrix][plane][K/8][N][8] with the reduction index
+// fastest, zeros from K to the next multiple of 32. transposed: the operand is W^T, so the reduction runs over the columns:
+// out[matrix][plane][N/8][K][8].
+__global__ void __launch_bounds__(256) cut_weights_kernel(const float* __restrict__ w0, const float* __restrict__ w1, int32_t K, int32_t N,
+                                                          int32_t transposed, uint16_t* __restrict__ out, int64_t matrix_stride) {
+    const float* w = blockIdx.y ? w1 : w0;
+    const int32_t R = transposed ? N : K, X = transposed ? K : N;       // reduction indices, columns of the operand
+    const int64_t plane = (int64_t)cut_pad(R) * X;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= plane / 8) return;
+    const int32_t rb = (int32_t)(i / X), x = (int32_t)(i - (int64_t)rb * X);
+    float f[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int32_t r = rb * 8 + j;
+        f[j] = r < R ? (transposed ? w[(int64_t)x * N + r] : w[(int64_t)r * N + x]) : 0.f;
+    }
+    uint4 p[3];
+    cut8(f, p);
+    uint16_t* o = out + blockIdx.y * matrix_stride + i * 8;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(o + q * plane) = p[q];
+}
+
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st) {
+    const int64_t stride = (int64_t)cut_weights_elements(K, N, transposed), units = stride / 24;
+    hipLaunchKernelGGL(cut_weights_kernel, dim3((unsigned)ceil_div(units, 256), w1 ? 2u : 1u), dim3(256), 0, st, w0, w1, K, N,
+                       transposed ? 1 : 0, out, stride);
+    return launch_status("cut_weights");
+}
+
+// ------------------------------------------------------------------------------------------ NN
+
+// Block: WM x WN wavefronts (WM * WN = 4), each 32 MI rows x 32 NJ columns. Rows of A are cut once per block, into one of two
+// LDS copies while the other is multiplied (one barrier per 32 indices), two steps ahead in registers; fragments of B come
+// straight from their planes (a lane's eight indices are 16 contiguous bytes, the 32 lanes of a fragment 512: L2 reads, one
+// step ahead). What is left at 60 K rows is memory next to the products: without the loads of B the launch takes 81 of 101 us,
+// without either operand's 70.
+template <int MI, int NJ, int WN, int OCC>
+__global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
+    constexpr int WM = 4 / WN, BM = 32 * MI * WM, BN = 32 * NJ * WN, PLANE = BM * SPITCH, COPY = 3 * PLANE;
+    constexpr int UNITS = BM >= 64 ? BM / 64 : 1, CW = 32 * NJ, CPITCH = CW + 4;
+    constexpr int BYTES = 2 * COPY * 2 > 4 * 32 * CPITCH * 4 ? 2 * COPY * 2 : 4 * 32 * CPITCH * 4;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
+    __shared__ int32_t crow_sh[BM], krow_sh[BM];
+    __shared__ float scale_sh[BM];
+    uint16_t* As = reinterpret_cast<uint16_t*>(smem);
+    int M = *g.d_M;
+    if (M > g.M_cap) M = g.M_cap;
+    // the grid covers the row capacity; only the tiles of the actual M rows are dealt out to the XCDs
+    const int gx = (g.N + BN - 1) / BN, gy = (M + BM - 1) / BM, gz = g.accumulate ? 1 : g.n_problems;
+    const int64_t total = (int64_t)gx * gy * gz, padded = (total + N_XCD - 1) / N_XCD * N_XCD;
+    if ((int64_t)blockIdx.x >= padded) return;
+    const int64_t lid = xcd_logical_id(padded);
+    if (lid >= total) return;
+    const int bx = (int)(lid % gx), by = (int)((lid / gx) % gy), bz = (int)(lid / ((int64_t)gx * gy));
+    const int m0 = by * BM, prob = g.accumulate ? 0 : bz, n_phases = g.accumulate ? g.n_problems : 1;
+    const int tid = (int)threadIdx.x, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
+    const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    const int c0 = bx * BN + wn * CW;                  // this wavefront's columns
+    const bool wave_on = c0 < g.N;                     // (one without columns multiplies the last ones again and stores nothing)
+    floatx16 acc[2][MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = acc[1][i][j][r] = 0.f;
+    // this thread's rows of A (rows past the operand repeat the last one and are never stored)
+    const bool loads = BM >= 64 || tid < BM * 4;
+    const int kq = (tid & 3) * 8;
+    const float* arow[2][UNITS];
+#pragma unroll
+    for (int i = 0; i < UNITS; ++i) {
+        const int m = min(m0 + ((tid + 256 * i) >> 2) % BM, M - 1);
+        arow[0][i] = g.A[prob] + (int64_t)(g.a_rows[prob] ? g.a_rows[prob][m] : m) * g.lda[prob];
+        arow[1][i] = n_phases > 1 ? g.A[1] + (int64_t)(g.a_rows[1] ? g.a_rows[1][m] : m) * g.lda[1] : arow[0][i];
+    }
+    // what the epilogue needs per row
+    if (tid < BM) {
+        const int row = min(m0 + tid, M - 1);
+        const int32_t* sp = g.row_scale_indptr[prob];
+        float s = 1.f;
+        if (sp) {
+            const int len = sp[row + 1] - sp[row] + g.row_scale_plus;
+            s = len > 0 ? (g.row_scale_rsqrt ? 1.f / sqrtf((float)len) : 1.f / (float)len) : 0.f;
+        }
+        scale_sh[tid] = s;
+        crow_sh[tid] = prob == 0 && g.c_rows ? g.c_rows[row] : row;
+        krow_sh[tid] = prob == 0 && g.c_keep_rows ? g.c_keep_rows[row] : -1;
+    }
+    const int K0 = g.K[prob], K1 = n_phases > 1 ? g.K[1] : K0, N = g.N;
+    const int steps0 = cut_pad(K0) / SK, steps = steps0 + (n_phases > 1 ? cut_pad(K1) / SK : 0);
+    RowUnit ta[2][UNITS];
+    auto request_a = [&](RowUnit (&t)[UNITS], int s) {      // (past the last step: that one again, not used)
+        const int q = min(s, steps - 1);
+        const bool second = q >= steps0;
+#pragma unroll
+        for (int i = 0; i < UNITS; ++i)
+            t[i].request(second ? arow[1][i] : arow[0][i], (second ? q - steps0 : q) * SK + kq, second ? K1 : K0);
+    };
+    auto store_a = [&](RowUnit (&t)[UNITS], int s, uint16_t* S) {
+        const bool second = s >= steps0;
+        const int k0 = (second ? s - steps0 : s) * SK, K = second ? K1 : K0;
+        if (k0 + SK > K) {
+#pragma unroll
+            for (int i = 0; i < UNITS; ++i) t[i].trim(k0 + kq, K);
+        }
+        if (loads) {
+#pragma unroll
+            for (int i = 0; i < UNITS; ++i) {
+                uint4 p[3];
+                cut8(t[i].f, p);
+                uint16_t* at = S + ((tid + 256 * i) >> 2) * SPITCH + kq;
+#pragma unroll
+                for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(at + q * PLANE) = p[q];
+            }
+        }
+    };
+    // Fragments of B for step s (two halves of 16 indices) of the flat list: uniform base, this lane's offset within two blocks of eight.
+    int cols[NJ];
+    uint32_t boff[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        cols[j] = min(c0 + j * 32 + l32, N - 1);
+        boff[j] = (uint32_t)(half * N + cols[j]) * 16u;
+    }
+    const char* const B0 = reinterpret_cast<const char*>(g.cut_B[prob]);
+    const char* const B1 = n_phases > 1 ? reinterpret_cast<const char*>(g.cut_B[1]) : B0;
+    const int64_t plane0 = (int64_t)cut_pad(K0) * N * 2, plane1 = (int64_t)cut_pad(K1) * N * 2;
+    auto request_b = [&](bf16x8_t (&b)[2][NJ][3], int s) {
+        const int q = min(s, steps - 1);
+        const bool second = q >= steps0;
+        const char* base = (second ? B1 : B0) + (int64_t)(second ? q - steps0 : q) * N * 64;
+        const int64_t plane = second ? plane1 : plane0;
+#pragma unroll
+        for (int p = 0; p < 3; ++p, base += plane)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j) b[h][j][p] = cut_fragment(reinterpret_cast<const uint16_t*>(base + (int64_t)h * N * 32 + boff[j]));
+    };
+    auto multiply = [&](const uint16_t* S, const bf16x8_t (&b)[NJ][3], int ks) {
+        bf16x8_t a[MI][3];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) a[i][p] = cut_fragment(S + p * PLANE + ((wm * MI + i) * 32 + l32) * SPITCH + ks * 16 + half * 8);
+#pragma unroll
+        for (int t = 0; t < CUT_TERMS; ++t)
+#pragma unroll
+            for (int i = 0; i < MI; ++i)
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    acc[CUT_TERM[t].acc][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][CUT_TERM[t].a], b[j][CUT_TERM[t].b],
+                                                                                          acc[CUT_TERM[t].acc][i][j], 0, 0, 0);
+    };
+    bf16x8_t b0[2][NJ][3], b1[2][NJ][3];
+    request_a(ta[0], 0);
+    request_a(ta[1], 1);
+    request_b(b0, 0);
+    store_a(ta[0], 0, As);
+    request_a(ta[0], 2);
+    __syncthreads();
+    auto step = [&](int s, uint16_t* cur, uint16_t* nxt, RowUnit (&t)[UNITS], bf16x8_t (&b)[2][NJ][3], bf16x8_t (&next_b)[2][NJ][3]) {
+        request_b(next_b, s + 1);
+        multiply(cur, b[0], 0);
+        if (s + 1 < steps) store_a(t, s + 1, nxt);
+        request_a(t, s + 3);
+        multiply(cur, b[1], 1);
+        __syncthreads();
+    };
+    for (int s = 0; s < steps; s += 2) {
+        step(s, As, As + COPY, ta[1], b0, b1);
+        if (s + 1 < steps) step(s + 1, As + COPY, As, ta[0], b1, b0);
+    }
+    // Epilogue: a wavefront's 32 x 64 tiles go through LDS (its own part, over the operand copies) so that a lane stores 16
+    // contiguous bytes of an output row: whole 256-byte row segments per 16 lanes.
+    float* Ct = reinterpret_cast<float*>(smem) + wave * 32 * CPITCH;
+    float* C = g.C[prob];
+    const int64_t ldc = g.ldc[prob];
+    constexpr int QL = CW / 4, RL = 64 / QL;             // lanes to a row, rows to an instruction
+    const int c4 = lane % QL * 4, col = c0 + c4;
+    const bool vec = (ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(C) & 15) == 0) &&
+                     (!(prob == 0 && g.c_keep_rows) || (reinterpret_cast<uintptr_t>(g.c_keep) & 15) == 0) && col + 4 <= g.N;
+#pragma unroll
+    for (int i = 0; i < MI; ++i) {
+        if (wave_on) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                const float bias = g.bias ? g.bias[cols[j]] : 0.f;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    float v = acc[1][i][j][r] + acc[0][i][j][r] + bias;
+                    if (g.relu) v = v > 0.f ? v : 0.f;
+                    Ct[acc_row(r, lane) * CPITCH + j * 32 + l32] = v;
+                }
+            }
+        }
+        __syncthreads();
+        if (wave_on) {
+#pragma unroll
+            for (int q = 0; q < 32 / RL; ++q) {
+                const int lr = q * RL + lane / QL, row = (wm * MI + i) * 32 + lr;
+                if (m0 + row >= M || col >= g.N) continue;
+                float4 t = *reinterpret_cast<const float4*>(Ct + lr * CPITCH + c4);
+                const float s = scale_sh[row];
+                t.x *= s; t.y *= s; t.z *= s; t.w *= s;
+                float* dst = C + (int64_t)crow_sh[row] * ldc + col;
+                const int kr = krow_sh[row];
+                float* keep = kr >= 0 ? g.c_keep + (int64_t)kr * ldc + col : nullptr;
+                if (vec) {
+                    *reinterpret_cast<float4*>(dst) = t;
+                    if (keep) *reinterpret_cast<float4*>(keep) = t;
+                } else {
+                    const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (col + e < g.N) { dst[e] = v[e]; if (keep) keep[e] = v[e]; }
+                }
+                if (keep && col == 0 && g.c_keep_stamp) g.c_keep_stamp[kr] = g.stamp;
+            }
+        }
+        if (i + 1 < MI) __syncthreads();
+    }
+}
+
+template <int MI, int NJ, int WN, int OCC>
+static void launch_cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    constexpr int BM = 32 * MI * (4 / WN), BN = 32 * NJ * WN;
+    const int64_t z = a.accumulate ? 1 : a.n_problems;
+    dim3 grid(xcd_padded(ceil_div(a.N, BN) * ceil_div(a.M_cap, BM) * z));
+    NO_LAUNCH_TIMED((cut_nn_kernel<MI, NJ, WN, OCC>), grid, dim3(256), st, ev0, ev1, a);
+}
+
+int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    // Few rows: 32-row blocks (twice as many; measured at 3.4 K / 5.5 K rows x 256 columns: 12.9 / 15.8 us against 15.2 / 18.9 with 64-row
+    // blocks, at 25 K rows 37 against 31). Narrow outputs: all four wavefronts below each other.
+    if (a.N <= 64) launch_cut_nn<1, 2, 1, 2>(a, st, ev0, ev1);
+    else if (a.M_cap <= 20000) launch_cut_nn<1, 1, 4, 2>(a, st, ev0, ev1);
+    else launch_cut_nn<2, 1, 4, 2>(a, st, ev0, ev1);
+    return launch_status("cut_nn");
+}
+
+// ------------------------------------------------------------------------------------------ TN
+
+// W neighbouring columns (2 or 4) of eight consecutive rows, on their way from memory to LDS: eight loads of 4 W bytes, turned in
+// registers into W units of eight reduction indices.
+template <int W>
+struct ColumnUnit {
+    typedef float vec __attribute__((ext_vector_type(W)));
+    typedef float vec_a4 __attribute__((ext_vector_type(W), aligned(4)));
+    vec f[8];
+    __device__ __forceinline__ void request(const float* p, int64_t ld) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[j] = *reinterpret_cast<const vec_a4*>(p + (int64_t)j * ld);
+    }
+    __device__ __forceinline__ void request_short(const float* p, int64_t ld, int rows, int cols) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int c = 0; c < W; ++c) f[j][c] = j < rows && c < cols ? p[(int64_t)j * ld + c] : 0.f;
+    }
+};
+
+// The jobs of one launch (by value in the kernel arguments): job j owns the linear block ids [end_block[j-1], end_block[j]).
+struct CutTNLaunch { GemmTNArgs job[NO_MAX_LAYERS]; uint32_t end_block[NO_MAX_LAYERS]; int32_t n; };
+
+constexpr uint32_t TN_LARGE_BLOCKS = 160;      // a job with fewer large-tile blocks takes small tiles
+constexpr int tn_shared_bytes(int T) { return 6 * T * SPITCH * 2 > T * (T + 4) * 4 ? 6 * T * SPITCH * 2 : T * (T + 4) * 4; }
+
+// Block `id` of a job: a T x T tile of one product over one slice; 2 x 2 wavefronts. Half of the threads bring a tile of A, the
+// other half one of G, each W = T / 32 columns x eight rows. Column W q + c of a tile stands in LDS row 32 c + q (a
+// wavefront then writes neighbouring rows); the output tile is put back in order on its way through LDS.
+template <int T>
+__device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, int R, int used, unsigned char* smem) {
+    constexpr int W = T / 32, Q = 32, PLANE = T * SPITCH, OPITCH = T + 4, I = T / 64;
+    uint16_t* As = reinterpret_cast<uint16_t*>(smem);
+    uint16_t* Gs = As + 3 * PLANE;
+    // in the order of a plain 3-D grid (column tile fastest, then row tile, then problem x slice)
+    const uint32_t gx = (uint32_t)((g.N + T - 1) / T), gy = (uint32_t)((g.Kp + 1 + T - 1) / T);
+    const int bx = (int)(id % gx), by = (int)((id / gx) % gy), bz = (int)(id / (gx * gy));
+    const int prob = bz / used, split = bz % used;
+    if (prob >= g.n_problems) return;
+    int chunk = (R + used - 1) / used;
+    chunk = (chunk + SK - 1) / SK * SK;
+    const int r0 = split * chunk, r1 = min(R, r0 + chunk);
+    const int m0 = by * T, n0 = bx * T, tid = (int)threadIdx.x;
+    float* P = g.P + ((int64_t)prob * g.splits + split) * (int64_t)(g.Kp + 1) * g.N;
+    if (m0 >= g.Kp) {
+        // Kp is a multiple of the tile height: this row tile holds nothing but row Kp, the column sums of G that product
+        // 0 carries (the bias gradient). The sums are taken directly, in a fixed order (row r0 + i by thread group i mod PARTS,
+        // groups combined in order). Product 1 has no such row (the reduction never reads it).
+        if (prob != 0) return;
+        float* red = reinterpret_cast<float*>(smem);         // [PARTS][T]
+        const int c = tid % T, part = tid / T;
+        constexpr int PARTS = 256 / T;
+        float s = 0.f;
+        if (n0 + c < g.N) {
+            int r = r0 + part;
+            for (; r + 7 * PARTS < r1; r += 8 * PARTS) {
+                float v[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) v[q] = g.G[(int64_t)(r + q * PARTS) * g.ldg + n0 + c];
+#pragma unroll
+                for (int q = 0; q < 8; ++q) s += v[q];
+            }
+            for (; r < r1; r += PARTS) s += g.G[(int64_t)r * g.ldg + n0 + c];
+        }
+        red[part * T + c] = s;
+        __syncthreads();
+        if (part == 0 && n0 + c < g.N) {
+            float t = red[c];
+#pragma unroll
+            for (int q = 1; q < PARTS; ++q) t += red[q * T + c];
+            P[(int64_t)g.Kp * g.N + n0 + c] = t;
+        }
+        return;
+    }
+    const int wave = tid >> 6, wm = wave >> 1, wn = wave & 1, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
+    floatx16 acc[2][I][I];
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+#pragma unroll
+        for (int j = 0; j < I; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = acc[1][i][j][r] = 0.f;
+    // this thread's W columns and its eight rows of a step
+    const bool mine_a = wave < 2;
+    const float* src = mine_a ? g.A[prob] : g.G;
+    const int64_t ld = mine_a ? g.lda[prob] : g.ldg;
+    const int q = tid % Q, k8 = (tid % 128) / Q * 8;
+    const int col = (mine_a ? m0 : n0) + q * W, lim = mine_a ? g.Kp : g.N;
+    const int ones = mine_a && prob == 0 ? g.Kp - col : -1;        // which of them is the column of ones, if 0 .. W - 1
+    const bool with_ones = prob == 0 && g.Kp < m0 + T;
+    // Columns past the operand are never stored, but must be read inside it: a unit that sticks out is read where it ends with
+    // the row and shifted.
+    const bool edge = m0 + T > g.Kp || n0 + T > g.N;
+    const int col_r = max(0, min(col, lim - W)), sh = col - col_r;
+    uint16_t* S = (mine_a ? As : Gs) + q * SPITCH + k8;
+    auto store = [&](ColumnUnit<W>& u, int lo, int hi, int shift) {       // rows [lo, hi) of the 32 count
+        if (edge) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int c = 0; c < W; ++c) {
+                    float v = u.f[j][c];
+#pragma unroll
+                    for (int b = 1; c + b < W; ++b) v = shift == b ? u.f[j][c + b] : v;
+                    u.f[j][c] = v;
+                }
+        }
+        if (lo > 0 || hi < SK) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int c = 0; c < W; ++c) u.f[j][c] = k8 + j >= lo && k8 + j < hi ? u.f[j][c] : 0.f;
+        }
+#pragma unroll
+        for (int c = 0; c < W; ++c) {
+            float f[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) f[j] = u.f[j][c];
+            if (with_ones && ones == c) {
+#pragma unroll
+                for (int j = 0; j < 8; ++j) f[j] = k8 + j >= lo && k8 + j < hi ? 1.f : 0.f;
+            }
+            uint4 p[3];
+            cut8(f, p);
+#pragma unroll
+            for (int e = 0; e < 3; ++e) *reinterpret_cast<uint4*>(S + e * PLANE + c * Q * SPITCH) = p[e];
+        }
+    };
+    auto multiply = [&]() {
+#pragma unroll
+        for (int ks = 0; ks < SK / 16; ++ks) {
+            bf16x8_t a[I][3], b[I][3];
+#pragma unroll
+            for (int i = 0; i < I; ++i)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) {
+                    a[i][p] = cut_fragment(As + p * PLANE + (wm * (T / 2) + i * 32 + l32) * SPITCH + ks * 16 + half * 8);
+                    b[i][p] = cut_fragment(Gs + p * PLANE + (wn * (T / 2) + i * 32 + l32) * SPITCH + ks * 16 + half * 8);
+                }
+#pragma unroll
+            for (int t = 0; t < CUT_TERMS; ++t)
+#pragma unroll
+                for (int i = 0; i < I; ++i)
+#pragma unroll
+                    for (int j = 0; j < I; ++j)
+                        acc[CUT_TERM[t].acc][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][CUT_TERM[t].a], b[j][CUT_TERM[t].b],
+                                                                                              acc[CUT_TERM[t].acc][i][j], 0, 0, 0);
+        }
+    };
+    const int steps = r0 < r1 ? (r1 - r0 + SK - 1) / SK : 0;
+    if (r1 - r0 >= SK && g.Kp >= W && g.N >= W) {
+        // the last step is moved back to end with the slice, and the rows it shares with the step before it count nothing
+        const float* p = src + col_r + (int64_t)k8 * ld;
+        ColumnUnit<W> u0, u1;
+        auto request = [&](ColumnUnit<W>& u, int s) { u.request(p + (int64_t)min(r0 + s * SK, r1 - SK) * ld, ld); };
+        auto step = [&](ColumnUnit<W>& u, int s) {
+            if (s > 0) __syncthreads();
+            store(u, max(0, r0 + (s + 1) * SK - r1), SK, sh);
+            __syncthreads();
+            request(u, s + 2);                   // two steps ahead (past the end: the last rows again, not used)
+            multiply();
+        };
+        request(u0, 0);
+        request(u1, 1);
+        for (int s = 0; s < steps; s += 2) {
+            step(u0, s);
+            if (s + 1 < steps) step(u1, s + 1);
+        }
+    } else {
+        ColumnUnit<W> u;
+        auto request = [&](int s) {
+            u.request_short(src + col + (int64_t)(r0 + s * SK + k8) * ld, ld, r1 - (r0 + s * SK + k8), lim - col);
+        };
+        if (steps > 0) request(0);
+        for (int s = 0; s < steps; ++s) {
+            if (s > 0) __syncthreads();
+            store(u, 0, min(SK, r1 - (r0 + s * SK)), 0);
+            __syncthreads();
+            if (s + 1 < steps) request(s + 1);
+            multiply();
+        }
+    }
+    // the output tile through LDS, its rows and columns back in order
+    float* Cs = reinterpret_cast<float*>(smem);
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+#pragma unroll
+        for (int j = 0; j < I; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int x = wm * (T / 2) + i * 32 + acc_row(r, lane), y = wn * (T / 2) + j * 32 + l32;
+                Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = acc[1][i][j][r] + acc[0][i][j][r];
+            }
+    __syncthreads();
+    constexpr int C4 = T / 4;
+    const int rows_out = g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
+    const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && n + 4 <= g.N;
+#pragma unroll 4
+    for (int lr = tid / C4; lr < T; lr += 256 / C4) {
+        const int row = m0 + lr;
+        if (row >= rows_out || n >= g.N) continue;
+        const float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
+        float* dst = P + (int64_t)row * g.N + n;
+        if (vec) *reinterpret_cast<float4*>(dst) = t;
+        else {
+            const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (n + e < g.N) dst[e] = v[e];
+        }
+    }
+}
+
+static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) {
+    return (uint32_t)((g.N + T - 1) / T) * (uint32_t)((g.Kp + 1 + T - 1) / T) * (uint32_t)g.n_problems;
+}
+
+// A job takes the larger tiles (fewer cuts per product) where they make blocks for most compute units, a function of the batch's row
+// count (112 blocks, 3.4 K rows: 21.8 us in large tiles, 15.9 in small ones; 176 blocks, 5.5 K rows: 23.1 and 23.6; 256 blocks, 25 K rows:
+// 34.5 and 44.7); its share of the grid is sized for either.
+__global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
+    int job = 0;
+    uint32_t first = 0;
+    while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
+    const GemmTNArgs& g = launch.job[job];
+    int R = *g.d_R;
+    if (R > g.R_cap) R = g.R_cap;
+    const int used = tn_used_splits(R, g.splits, g.rows_per_split);      // (the reduction reads the first `used` partials only)
+    const uint32_t id = blockIdx.x - first;
+    if (tn_tiles(g, 128) * used >= TN_LARGE_BLOCKS) cut_tn_tile<128>(g, id, R, used, smem);
+    else cut_tn_tile<64>(g, id, R, used, smem);
+}
+
+int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    CutTNLaunch launch{};
+    uint64_t blocks = 0;
+    for (int32_t j = 0; j < n_jobs && launch.n < NO_MAX_LAYERS; ++j) {
+        const GemmTNArgs& a = jobs[j];
+        if (a.Kp <= 0 || a.N <= 0) continue;
+        // (small tiles are only taken while there are few large ones)
+        const uint64_t small = (uint64_t)tn_tiles(a, 64), large = (uint64_t)tn_tiles(a, 128);
+        const uint64_t most_small = std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / large);
+        blocks += std::max(small * most_small, large * (uint64_t)a.splits);
+        NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");
+        launch.job[launch.n] = a;
+        launch.end_block[launch.n] = (uint32_t)blocks;
+        ++launch.n;
+    }
+    if (launch.n == 0) return NO_OK;
+    NO_LAUNCH_TIMED(cut_tn_kernel, dim3((unsigned)blocks), dim3(256), st, ev0, ev1, launch);
+    return launch_status("gemm_tn");
+}
+
+}  // namespace no

@@ -1,0 +1,75 @@
+// What the matrix-product kernels share: 4-byte-aligned 16-byte loads, rounding to bf16, the accumulator's
+// layout and the dealing of tiles to the dies.
+#pragma once
+#include "gemm.hpp"
+
+namespace no {
+
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+
+// 16-byte load from a 4-byte aligned address (rows of 602 floats start on 8-byte boundaries only).
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_fast(const float* p) {
+    float4_a4 v = *reinterpret_cast<const float4_a4*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ float4 load4_guarded(const float* p, int valid) {
+    if (valid >= 4) return load4_fast(p);      // only the lanes that straddle an edge go element by element
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (valid > 0) v.x = p[0];
+    if (valid > 1) v.y = p[1];
+    if (valid > 2) v.z = p[2];
+    return v;
+}
+
+// Two values rounded to bf16, nearest-even, one instruction.
+typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+    const f32x2_t f = {a, b};
+    const bf16x2_t r = __builtin_convertvector(f, bf16x2_t);
+    uint32_t u;
+    __builtin_memcpy(&u, &r, 4);
+    return u;
+}
+
+// Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.
+__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
+
+// Eight consecutive reduction indices of one row of A, on their way from memory to LDS.
+struct RowUnit {
+    float f[8];
+    // indices [k, k + 8) of a row of K >= 8 values. Always two loads and no branch around them (the wait before the values are
+    // used then counts exactly the loads behind them): a unit that sticks out is read where it ends with the row, or, wholly
+    // outside, at the row's start, and put right by trim().
+    __device__ __forceinline__ void request(const float* row, int k, int K) {
+        const float* p = row + (k + 8 <= K ? k : (k < K ? K - 8 : 0));
+        const float4 a = load4_fast(p), b = load4_fast(p + 4);
+        f[0] = a.x; f[1] = a.y; f[2] = a.z; f[3] = a.w; f[4] = b.x; f[5] = b.y; f[6] = b.z; f[7] = b.w;
+    }
+    __device__ __forceinline__ void trim(int k, int K) {
+        const int sh = k + 8 <= K ? 0 : (k < K ? k + 8 - K : 8);      // values to shift out
+#pragma unroll
+        for (int b = 4; b >= 1; b >>= 1)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float from = j + b < 8 ? f[j + b < 8 ? j + b : 0] : 0.f;
+                f[j] = (sh & b) ? from : f[j];
+            }
+#pragma unroll
+        for (int j = 0; j < 8; ++j) f[j] = sh >= 8 ? 0.f : f[j];
+    }
+};
+
+// Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by linear
+// id. The tiles that share an operand panel (all column tiles of one row tile; all tiles of one
+// reduction slice) get consecutive *logical* ids, and logical ids are dealt out in chunks per XCD, so
+// a panel is fetched into one L2 once instead of into several.
+constexpr int N_XCD = 8;
+__device__ __forceinline__ int64_t xcd_logical_id(int64_t total_padded) {
+    const int64_t id = blockIdx.x;
+    return (id % N_XCD) * (total_padded / N_XCD) + id / N_XCD;
+}
+static inline unsigned xcd_padded(int64_t total) { return (unsigned)(ceil_div(total, N_XCD) * N_XCD); }
+
+}  // namespace no

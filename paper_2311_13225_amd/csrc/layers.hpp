@@ -41,7 +41,8 @@ struct LayerWorkspace {
     float* gz = nullptr;             // [n_dst_cap, d_out] masked output gradient
     float* gmean = nullptr;          // [n_dst_cap, d_in]  gradient of the mean, pre-divided by the row length
     float* x_dst_f32 = nullptr;      // [n_dst_cap, d_in]  fp32 copy of bf16 destination rows
-    float* partials = nullptr;       // [2, splits, d_in + 1, d_out]
+    float* partials = nullptr;       // [2, splits, d_in + 1, d_out]; before that, planes of the weights
+    size_t partials_bytes = 0;
     int32_t splits = 1;
     size_t bytes = 0;
 };
@@ -117,6 +118,8 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      int32_t arch = NO_ARCH_SAGE_MEAN, const Layer1Reuse* reuse = nullptr, bool aggregate_done = false,
                      const SourceWeights* weights = nullptr, const PaddedSlots* padded = nullptr,
                      const Bf16Products* bf = nullptr);
+// cut_bwd: the layer's two matrices cut for the input gradient (kept by a model, rewritten by the reduction); without them the
+// product cuts them itself
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,
                       const float* h, const float* grad_h, const float* w_self, const float* w_neigh, int32_t d_out,
                       int32_t relu, float* gw_self, float* gw_neigh, float* gbias, float* grad_x_src,
@@ -126,7 +129,8 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
                       float* w_neigh_rw = nullptr, float* bias_rw = nullptr, int32_t arch = NO_ARCH_SAGE_MEAN,
                       const StatsJob* stats_job = nullptr, const float* gz_in = nullptr,
                       const BelowLayer* below = nullptr, GradJobs* pending = nullptr, bool defer = false,
-                      const SourceWeights* weights = nullptr, const Bf16Products* bf = nullptr);
+                      const SourceWeights* weights = nullptr, const Bf16Products* bf = nullptr,
+                      uint16_t* const* cut_bwd = nullptr);
 int32_t gather_rows(const void* d_table, int32_t row_bytes, int64_t table_stride, const int32_t* d_ids,
                     const int32_t* d_n, int32_t n_cap, void* d_out, int64_t out_stride, hipStream_t st);
 

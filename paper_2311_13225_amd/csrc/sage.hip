@@ -535,7 +535,9 @@ LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_
     w.gz = (float*)(base + off);        off += align256((size_t)n_dst_cap * d_out * 4);
     w.gmean = (float*)(base + off);     off += align256((size_t)n_dst_cap * d_in * 4);
     w.x_dst_f32 = (float*)(base + off); off += align256((size_t)n_dst_cap * d_in * 4);
-    w.partials = (float*)(base + off);  off += align256((size_t)2 * w.splits * (d_in + 1) * d_out * 4);
+    w.partials = (float*)(base + off);
+    w.partials_bytes = align256((size_t)2 * w.splits * (d_in + 1) * d_out * 4);
+    off += w.partials_bytes;
     w.bytes = off;
     return w;
 }
@@ -582,7 +584,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         scatter(a);
         e0 = e1 = nullptr;
         if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
-        return gemm_nn(a, false, st, e0, e1);
+        return gemm_nn_forward(a, st, e0, e1);
     }
     // agg_table != NULL: the rows to average are rows of that table addressed by blk.d_indices (global ids),
     // while x_src holds only the destination rows (fused gather + aggregate of the bottom layer). An fp32
@@ -632,7 +634,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     scatter(a);
     e0 = e1 = nullptr;
     if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
-    return gemm_nn(a, false, st, e0, e1);
+    return gemm_nn_forward(a, st, e0, e1);
 }
 
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,
@@ -642,7 +644,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
                       int reduce_stage, int dx_stage, const int32_t* grad_rows, float lr, float* w_self_rw,
                       float* w_neigh_rw, float* bias_rw, int32_t arch, const StatsJob* stats_job, const float* gz_in,
                       const BelowLayer* below, GradJobs* pending, bool defer, const SourceWeights* weights,
-                      const Bf16Products* bf) {
+                      const Bf16Products* bf, uint16_t* const* cut_bwd) {
     const bool gcn = arch_is_gcn(arch);
     if (arch == NO_ARCH_GCN_SYM && grad_x_src && !(weights && weights->cnt)) {
         set_error("GCN-style layer with symmetric normalisation: the block has no per-source edge counts");
@@ -686,8 +688,12 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
             if (arch == NO_ARCH_GCN_SUM) a.row_scale_indptr[0] = a.row_scale_indptr[1] = nullptr;
         }
         a.n_problems = 2; a.accumulate = 0;
+        a.cut_B[0] = cut_bwd ? cut_bwd[0] : nullptr;
+        a.cut_B[1] = cut_bwd ? cut_bwd[gcn ? 0 : 1] : nullptr;
+        a.cut_scratch = w.partials;       // (free until this layer's weight gradients)
+        a.cut_scratch_bytes = w.partials_bytes;
         a.d_M = blk.d_n_dst; a.M_cap = n_cap; a.N = d_in;
-        NO_CHECK(gemm_nn(a, true, st));
+        NO_CHECK(gemm_nn_input_grad(a, st));
         NO_CHECK(transpose_aggregate(w.gmean, d_in, blk.d_csc_indptr, blk.d_csc_dst, blk.d_n_src, blk.n_src_cap,
                                      blk.d_n_dst, grad_x_src, st, below ? below->h : nullptr, below ? below->out_rows : nullptr,
                                      below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr));
@@ -709,6 +715,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     t.rows_per_split = 256;
     ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
     r.d_R = t.d_R; r.R_cap = t.R_cap; r.rows_per_split = t.rows_per_split;
+    for (int q = 0; cut_bwd && q < 2; ++q) r.cut_bwd[q] = cut_bwd[q];
     if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
     if (pending && defer) {
         // an upper layer inside a step: its product and reduction ride on the bottom layer's launches

@@ -98,6 +98,9 @@ struct no_model_s {
     // caller may have changed them: weights_dirty)
     no::DevBuf<uint16_t> wt1;
     int32_t wt1_kpad = 0;
+    // the matrices of the layers above layer 1 cut for their input gradients (cut_weights), rewritten like wt1
+    no::DevBuf<uint16_t> planes;
+    uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
     hipEvent_t ev_dw_join = nullptr;
     bool weights_dirty = true;
     no::DevBuf<float> mean[NO_MAX_LAYERS];           // layer l (index l-1): [n_dst_cap, d_{l-1}]
@@ -144,7 +147,7 @@ struct no_model_s {
         mean_alt.release();
         h0_alt.release();
         if (blocks_alt) { blocks_alt->release(); delete blocks_alt; blocks_alt = nullptr; }
-        x0_alt.release(); wt1.release();
+        x0_alt.release(); wt1.release(); planes.release();
         if (blocks) { blocks->release(); delete blocks; blocks = nullptr; }
         params.release(); grads.release(); x0.release();
         for (auto& b : mean) b.release();
@@ -237,6 +240,12 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
         NO_CHECK(m->wt1.alloc((size_t)2 * m->dims[1] * m->wt1_kpad));
         NO_HIP_CHECK(hipEventCreateWithFlags(&m->ev_dw_join, NO_SYNC_EVENT_FLAGS));
     }
+    size_t n_planes = 0;
+    for (int32_t l = 1; l < L; ++l) n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1], true);
+    NO_CHECK(m->planes.alloc(n_planes));
+    uint16_t* at = m->planes.p;
+    for (int32_t l = 1; l < L; ++l)
+        for (int q = 0; q < 2; ++q, at += cut_weights_elements(m->dims[l], m->dims[l + 1], true)) m->cut_bwd[l][q] = at;
     size_t ws_bytes = 0;
     for (int32_t l = 1; l <= L; ++l) {
         const HopBuffers& H = m->blocks->hop[L - l];
@@ -405,9 +414,14 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
     uint16_t* wt_self = m->wt1.p;
     uint16_t* wt_neigh = m->wt1.p ? m->wt1.p + (size_t)m->dims[1] * m->wt1_kpad : nullptr;
-    if (bf16_products && m->weights_dirty) {
-        NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_self, st));
-        NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_neigh, st));
+    if (m->weights_dirty) {
+        if (bf16_products) {
+            NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_self, st));
+            NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_neigh, st));
+        }
+        for (int32_t l = 1; l < L; ++l)
+            NO_CHECK(cut_weights(m->params.p + m->off_w_self[l], m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], true,
+                                 m->cut_bwd[l][0], st));
         m->weights_dirty = false;
     }
     hipEvent_t sev0 = nullptr, sev1 = nullptr;
@@ -642,7 +656,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                l == 1 ? &prof : nullptr, NO_STAGE_BWD_L1_PREP, NO_STAGE_GEMM_DW_L1, NO_STAGE_BWD_L1_REDUCE,
                                -1, grad_rows, lr, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                                m->params.p + m->off_bias[l - 1], m->arch, l == 1 ? &stats_job : nullptr, gz_in,
-                               l >= 2 ? &below : nullptr, &pending, l >= 2, &sw, (bf16_products && l == 1) ? &bfp : nullptr));
+                               l >= 2 ? &below : nullptr, &pending, l >= 2, &sw, (bf16_products && l == 1) ? &bfp : nullptr, l >= 2 ? m->cut_bwd[l - 1] : nullptr));
         if (launch_beside && pending.n > 0) {
             NO_HIP_CHECK(hipStreamWaitEvent(pending.side, pending.fork, 0));
             NO_CHECK(gemm_tn_partials(pending.tn, pending.n, pending.side, nullptr, nullptr));

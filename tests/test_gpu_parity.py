@@ -332,6 +332,33 @@ def test_sage_layer_forward_backward(F, d_out, relu, bf16):
     check_layer_forward_backward(layer_case(4000, 60_000, F, d_out, (7, 6), 300, 11, bf16), F, d_out, relu, bf16)
 
 
+@pytest.mark.parametrize("n,cap,F,d_out", [
+    (0, 5000, 64, 64), (1, 5000, 8, 256), (31, 5000, 9, 100), (33, 9000, 33, 48), (63, 5000, 128, 128),      # fewer rows than a step or a tile
+    (257, 5000, 129, 65), (1000, 30_000, 100, 256), (5001, 30_000, 66, 7),                                   # remainders of every tile size
+    (4097, 4097, 127, 129), (9000, 9000, 3, 130), (20_100, 30_000, 130, 172)])                              # large tiles; a layer of 3 columns
+def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
+    """Weight and input gradients against exact sums. Bound: every term of a sum of K products may be off by the rounding of
+    one fp32 product and every addition by that of its partial sum, together below (K + 8) 2^-24 sum |a b|."""
+    b = nb()
+    rng = np.random.default_rng(n + F)
+    f32 = lambda *s: rng.standard_normal(s).astype(np.float32)
+    x, mean, gh, w_self, w_neigh = f32(cap, F), f32(cap, F), f32(cap, d_out), f32(F, d_out), f32(F, d_out)
+    i32 = lambda a: dev(np.asarray(a, np.int32))
+    # row v samples itself once; source u is sampled by row u
+    blk = b.block_view_from_tensors(i32([n]), i32([n]), i32(np.minimum(np.arange(cap + 1), n)), i32(np.arange(cap)), cap, cap,
+                                    i32(np.minimum(np.arange(cap + 1), n)), i32(np.arange(cap)))
+    ws = torch.empty(b.no_sage_layer_ws_bytes(cap, cap, F, d_out), dtype=torch.uint8, device="cuda")
+    gs, gn, gb, gx = (torch.full(s, float("nan"), device="cuda") for s in ((F, d_out), (F, d_out), (d_out,), (cap, F)))
+    b.no_sage_layer_bwd(blk, dev(x), dev(mean), dev(gh), dev(gh), dev(w_self), dev(w_neigh), False, gs, gn, gb, gx, ws)
+    x, mean, gh = (a[:n].astype(np.float64) for a in (x, mean, gh))
+    w = w_self.astype(np.float64) + w_neigh.astype(np.float64)
+    w_abs = np.abs(w_self).astype(np.float64) + np.abs(w_neigh)
+    for got, ref, mag, terms in ((gs, x.T @ gh, np.abs(x).T @ np.abs(gh), n), (gn, mean.T @ gh, np.abs(mean).T @ np.abs(gh), n),
+                                 (gb, gh.sum(0), np.abs(gh).sum(0), n), (gx[:n], gh @ w.T, np.abs(gh) @ w_abs.T, 2 * d_out)):
+        assert (np.abs(got.cpu().numpy() - ref) <= (terms + 8) * 2.0 ** -24 * mag).all()
+    assert torch.isnan(gx[n:]).all()
+
+
 def test_sage_layer_backward_with_a_popular_source():
     """One source that every destination samples: its transposed segment has several hundred entries (more than the 64
     indices a wavefront reads at a time, and a tail that is no multiple of 16), next to ordinary short segments."""
