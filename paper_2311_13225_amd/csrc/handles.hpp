@@ -21,13 +21,19 @@ struct HopBuffers {
     const int32_t* d_dst = nullptr;     // alias: seeds copy, previous hop's src_global, or compute list
     const int32_t* d_n_dst = nullptr;   // alias into counts
     DevBuf<int32_t> src_global, indptr, nbr_pad, nbr_global, indices, edge_row;
-    DevBuf<int32_t> csc_indptr, csc_cnt, csc_cur, csc_dst, csc_eid;
+    DevBuf<int32_t> csc_indptr, csc_cnt, csc_dst, csc_eid;
+    DevBuf<int32_t> csc_fill;           // the columns in order of arrival
+    DevBuf<int32_t> csc_tiles;          // tile sums of the counts (hops with many sources)
     void release() {
         src_global.release(); indptr.release(); nbr_pad.release(); nbr_global.release(); indices.release();
-        edge_row.release(); csc_indptr.release(); csc_cnt.release(); csc_cur.release(); csc_dst.release();
-        csc_eid.release();
+        edge_row.release(); csc_indptr.release(); csc_cnt.release(); csc_dst.release();
+        csc_eid.release(); csc_fill.release(); csc_tiles.release();
     }
 };
+
+// Dense copy of the last hop's destination feature rows (out[i,:] = table[dst[i],:]) to be made among a call's side tasks.
+struct SideGather { const void* table = nullptr; int32_t row_bytes = 0; void* out = nullptr; };
+struct SideTasks;
 
 }  // namespace no
 
@@ -47,7 +53,6 @@ struct no_blocks_s {
     int32_t call_id = 0;               // id of the last sampling call into these blocks (1, 2, ...; never 0)
     no::DevBuf<int32_t> seeds;          // copy of the seed ids (hop 0 destinations)
     no::DevBuf<int32_t> map;            // vertex -> local id, EMPTY between calls, [V]
-    no::DevBuf<int32_t> tmp_a;          // unordered transpose fill [max nnz_cap with a transpose]
     no::DevBuf<char> ws;                // tile sums of the scans
     // bottom hop with a cache
     no::DevBuf<int32_t> compute_list, compute_pos, hit_pos, hit_slot, probe_slot, probe_ver;
@@ -59,29 +64,20 @@ struct no_blocks_s {
     bool scan_two_pass = false;              // the edge compaction of the next sampling call: two launches instead of one
     no::DevBuf<int32_t> compute_inv;         // [|V^1|]: index in the compute list of position i of V^1, -1 if served from the cache
     bool last_used_cache = false;
-    // The transposes and the final wipe of the id map do not feed the forward pass: they run on a side
-    // stream (same priority) and are joined where their results are first needed.
-    hipStream_t side = nullptr;
-    hipEvent_t ev_fork[NO_MAX_LAYERS] = {nullptr};
-    hipEvent_t ev_side_done = nullptr;
-    hipEvent_t ev_gather_done = nullptr;
-    hipEvent_t ev_indices_done = nullptr;    // side stream: local indices of every hop written
-    bool upper_indices_deferred = false;     // the last call left the upper hops' indices to the side stream
-    bool side_pending = false;
-    no::DevBuf<char> ws_side;
+    // Side tasks (side.hpp) of the last call not launched yet: the next one of each hop (-1: none), the wipe of the id map
+    // after hop wipe_hop, and the copy of that hop's destination rows.
+    int32_t side_next[NO_MAX_LAYERS];
+    bool wipe_pending = false;
+    int32_t wipe_hop = 0;
+    no::SideGather rows_pending;
     // measurement only: a pair of events for the next call's sampling kernel of hop time_hop (taken by that call)
     hipEvent_t time_ev0 = nullptr, time_ev1 = nullptr;
     int32_t time_hop = -1;
+    no_blocks_s() { for (auto& n : side_next) n = -1; }
     void release() {
         no::ReleaseScope scope;
-        if (side) { (void)hipStreamSynchronize(side); (void)hipStreamDestroy(side); side = nullptr; }
-        for (auto& e : ev_fork) if (e) { (void)hipEventDestroy(e); e = nullptr; }
-        if (ev_side_done) { (void)hipEventDestroy(ev_side_done); ev_side_done = nullptr; }
-        if (ev_gather_done) { (void)hipEventDestroy(ev_gather_done); ev_gather_done = nullptr; }
-        if (ev_indices_done) { (void)hipEventDestroy(ev_indices_done); ev_indices_done = nullptr; }
-        ws_side.release();
         for (auto& h : hop) h.release();
-        counts.release(); seeds.release(); map.release(); tmp_a.release(); ws.release(); compute_list.release(); compute_pos.release(); hit_pos.release(); hit_slot.release();
+        counts.release(); seeds.release(); map.release(); ws.release(); compute_list.release(); compute_pos.release(); hit_pos.release(); hit_slot.release();
         probe_slot.release(); probe_ver.release(); compute_inv.release(); refresh_slot.release(); refresh_old.release();
     }
 };
@@ -137,16 +133,16 @@ struct no_cache_s {
 
 namespace no {
 // Internal entry used by no_sample_blocks and no_select_hot.
-// With join == false the caller must call blocks_join(b, st) before anything on `st` reads a transpose
-// or starts another sampling call on the same blocks.
-// Optional job run first on the side stream: dense copy of the last hop's destination feature rows
-// (out[i,:] = table[dst[i],:]); the caller waits on b->ev_gather_done before reading `out`.
-struct SideGather { const void* table = nullptr; int32_t row_bytes = 0; void* out = nullptr; bool needed_by_forward = true; };
+// With finish == false the call leaves its last side tasks to the launches that follow (mean_aggregate takes them along);
+// blocks_finish(b, st), on a stream ordered after the call's, launches what is left of them. Until they are done nothing may
+// read a local index of the last hop, a transpose or the copied rows (gather).
 int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seeds, uint64_t stream_key,
                            uint32_t domain, int32_t n_hops, no_cache_s* cache, int64_t step, no_blocks_s* b,
-                           hipStream_t st, bool join = true, const SideGather* gather = nullptr,
+                           hipStream_t st, bool finish = true, const SideGather* gather = nullptr,
                            bool stamp_refresh = false);
-int32_t blocks_join(no_blocks_s* b, hipStream_t st);
+int32_t blocks_finish(no_blocks_s* b, hipStream_t st);
+// The side tasks that may run in the next launch (of own_blocks blocks and the tasks' own) on the call's stream; they count as launched.
+void side_take(no_blocks_s* b, uint32_t own_blocks, SideTasks* side);
 // stamp_refresh: the split writes `step` into the version of every cache slot the batch will recompute (training
 // calls; the row follows with the layer-1 product). blocks_unstamp takes the stamps back for a batch that is dropped.
 int32_t blocks_unstamp(no_blocks_s* b, hipStream_t st);

@@ -79,7 +79,6 @@ extern "C" int32_t no_refresh_hot_begin(no_cache_t c, no_graph_t g, const void* 
     sg.table = d_features;
     sg.row_bytes = feat_dim * (dt == NO_BF16 ? 2 : 4);
     sg.out = r->x0.p;
-    sg.needed_by_forward = true;
     r->blocks->count_sources = arch == NO_ARCH_GCN_SYM;
     NO_CHECK(sample_blocks_impl(g, c->hot_ids.p, n_hot, seed + (uint64_t)version, 2u, 1, nullptr, 0, r->blocks, r->stream, true,
                                 bf16 ? &sg : nullptr));
@@ -93,7 +92,7 @@ extern "C" int32_t no_refresh_hot_begin(no_cache_t c, no_graph_t g, const void* 
     if (arch == NO_ARCH_GCN_SYM) { sw.cnt = r->blocks->hop[0].csc_cnt.p; sw.local = r->blocks->hop[0].indices.p; }
     NO_CHECK(sage_forward(view, bf16 ? (const void*)r->x0.p : d_features, dt, feat_dim, w_self, w_neigh, bias, d_out, 1,
                           r->mean.p, r->emb_pending.p, w, r->stream, nullptr, -1, -1, d_features,
-                          bf16 ? r->blocks->ev_gather_done : nullptr, arch, nullptr, false, &sw, &slots));
+                          arch, nullptr, false, &sw, &slots));
     NO_CHECK(fill_i32(r->version_pending.p, (int32_t)version, n_hot, r->stream));
     NO_HIP_CHECK(hipEventRecord(r->ev_done, r->stream));
     r->pending = true;

@@ -4,9 +4,12 @@
 // above the bottom one, the input gradient through the transposed block (segment sums in a fixed
 // order, no float atomics). The bottom layer needs only the saved mean and the new embedding.
 #include "layers.hpp"
+#include "handles.hpp"
+#include "side.hpp"
 
 #include <stdlib.h>
 #include <mutex>
+#include <type_traits>
 
 namespace no {
 
@@ -97,7 +100,8 @@ __device__ __forceinline__ void accum_unit(float (&acc)[1], const uint16_t& b) {
 // wavefronts, so a wide row keeps many short independent load chains in flight instead of one long one;
 // the items of a row are consecutive, which keeps the reads of a source row next to each other in time.
 // Up to eight source rows are loaded before the first add; the adds stay in segment order.
-template <typename T, int VEC, bool MEAN, bool WEIGHTED>
+// Side: SideTasks where the launch carries some, else NoSideTasks (the tasks' code costs the widest forms 2 to 34 registers).
+template <typename T, int VEC, bool MEAN, bool WEIGHTED, typename Side>
 __global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const T* __restrict__ src, int64_t ld_src,
                                                            const int32_t* __restrict__ seg, const int32_t* __restrict__ idx,
                                                            const int32_t* d_n_rows, int32_t n_rows_cap,
@@ -105,13 +109,14 @@ __global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const
                                                            int32_t units, int32_t g_log2, int32_t n_chunks,
                                                            const int32_t* __restrict__ self_idx, int32_t agg_mode,
                                                            const float* __restrict__ mask_h, const int32_t* __restrict__ out_rows,
-                                                           float* __restrict__ masked_out, SourceWeights sw) {
+                                                           float* __restrict__ masked_out, SourceWeights sw, Side side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (job.dst && blockIdx.x >= job.first_block) {
         // extra blocks of the launch: dst[dst_rows[i], :] = src[src_rows[i], :], one wavefront per row (rows that are
         // ready before this kernel's own output is, e.g. the cached layer-1 rows of the reused vertices)
         const int32_t nj = *job.d_n;
         const int64_t w0 = (((int64_t)(blockIdx.x - job.first_block)) * blockDim.x + threadIdx.x) >> 6;
-        const int64_t nw = ((int64_t)(gridDim.x - job.first_block) * blockDim.x) >> 6;
+        const int64_t nw = ((int64_t)(side.first_block - job.first_block) * blockDim.x) >> 6;
         const int ln = (int)(threadIdx.x & 63);
         for (int64_t i = w0; i < nj; i += nw) {
             const float* s_ = job.src + (int64_t)job.src_rows[i] * job.dim;
@@ -125,7 +130,7 @@ __global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const
     const int32_t n_init = (!MEAN && d_n_init) ? *d_n_init : 0;
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t n_waves = ((int64_t)(job.dst ? job.first_block : gridDim.x) * blockDim.x) >> 6;
+    const int64_t n_waves = ((int64_t)(job.dst ? job.first_block : side.first_block) * blockDim.x) >> 6;
     const int32_t items_per_pass = 64 >> g_log2;
     const int32_t sub = lane >> g_log2, u0 = lane & ((1 << g_log2) - 1);
     const int64_t n_items = (int64_t)n * n_chunks;
@@ -274,7 +279,7 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
                            int32_t n_cap, const int32_t* d_n_init, float* out, int64_t ld_out, int32_t dim, hipStream_t st,
                            const int32_t* self_idx = nullptr, int32_t agg_mode = AGG_NEIGH_MEAN, const float* mask_h = nullptr,
                            const int32_t* out_rows = nullptr, float* masked_out = nullptr, const RowCopyJob* copy = nullptr,
-                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr) {
+                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr, no_blocks_s* side_of = nullptr) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -292,12 +297,26 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
         if (copy_blocks < 1) copy_blocks = 1;
     }
     const SourceWeights sw = weights ? *weights : SourceWeights{};
-    if (sw.cnt)
-        NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, true>), dim3((unsigned)(blocks + copy_blocks)), dim3(256), st, ev0, ev1, job, src, ld_src, seg, idx, d_n,
-                        n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask_h, out_rows, masked_out, sw);
-    else
-        NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, false>), dim3((unsigned)(blocks + copy_blocks)), dim3(256), st, ev0, ev1, job, src, ld_src, seg, idx, d_n,
-                        n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask_h, out_rows, masked_out, sw);
+    const uint32_t own = (uint32_t)(blocks + copy_blocks);
+    auto launch = [&](auto weighted, const auto& side, uint32_t grid) {
+        using Side = std::decay_t<decltype(side)>;
+        NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, decltype(weighted)::value, Side>), dim3(grid), dim3(256), st, ev0, ev1, job, src,
+                        ld_src, seg, idx, d_n, n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask_h, out_rows,
+                        masked_out, sw, side);
+    };
+    if constexpr (MEAN) {
+        SideTasks side;
+        if (side_of) side_take(side_of, own, &side);
+        if (side.n > 0) {
+            if (sw.cnt) launch(std::true_type{}, side, own + side.side_blocks());
+            else launch(std::false_type{}, side, own + side.side_blocks());
+            return;
+        }
+    }
+    NoSideTasks none;
+    none.first_block = own;
+    if (sw.cnt) launch(std::true_type{}, none, own);
+    else launch(std::false_type{}, none, own);
 }
 
 // The layer-1 aggregate straight from the sampler's fixed-stride slot array: row r's sampled neighbours are the
@@ -307,17 +326,18 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
 // -> rows -> store" instead of "row count -> row pointers -> indices -> rows -> store": the kernel is bound by that chain
 // (every wave handles one or two items), not by bytes in flight. NS (8 or 16) slots and their rows are in flight at a time. Same sums in the same order as segment_rows_kernel<MEAN>.
 // agg_mode as there (no per-source weights here).
-template <typename T, int VEC, int NS>
+template <typename T, int VEC, int NS, typename Side>
 __global__ void __launch_bounds__(256) padded_rows_kernel(RowCopyJob job, const T* __restrict__ src, int64_t ld_src,
                                                           const int32_t* __restrict__ pad, int32_t k,
                                                           const int32_t* d_n_rows, int32_t n_rows_cap,
                                                           float* __restrict__ out, int64_t ld_out, int32_t units,
                                                           int32_t g_log2, int32_t n_chunks,
-                                                          const int32_t* __restrict__ self_idx, int32_t agg_mode) {
+                                                          const int32_t* __restrict__ self_idx, int32_t agg_mode, Side side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (job.dst && blockIdx.x >= job.first_block) {
         const int32_t nj = *job.d_n;
         const int64_t w0 = (((int64_t)(blockIdx.x - job.first_block)) * blockDim.x + threadIdx.x) >> 6;
-        const int64_t nw = ((int64_t)(gridDim.x - job.first_block) * blockDim.x) >> 6;
+        const int64_t nw = ((int64_t)(side.first_block - job.first_block) * blockDim.x) >> 6;
         const int ln = (int)(threadIdx.x & 63);
         for (int64_t i = w0; i < nj; i += nw) {
             const float* s_ = job.src + (int64_t)job.src_rows[i] * job.dim;
@@ -331,7 +351,7 @@ __global__ void __launch_bounds__(256) padded_rows_kernel(RowCopyJob job, const 
     if (n > n_rows_cap) n = n_rows_cap;
     const int32_t lane = (int32_t)(threadIdx.x & 63);
     const int64_t wave = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int64_t n_waves = ((int64_t)(job.dst ? job.first_block : gridDim.x) * blockDim.x) >> 6;
+    const int64_t n_waves = ((int64_t)(job.dst ? job.first_block : side.first_block) * blockDim.x) >> 6;
     const int32_t items_per_pass = 64 >> g_log2;
     const int32_t sub = lane >> g_log2, u0 = lane & ((1 << g_log2) - 1);
     const int64_t n_items = (int64_t)n * n_chunks;
@@ -379,7 +399,7 @@ __global__ void __launch_bounds__(256) padded_rows_kernel(RowCopyJob job, const 
 template <typename T, int VEC>
 static void launch_padded(const T* src, int64_t ld_src, const int32_t* pad, int32_t k, const int32_t* d_n, int32_t n_cap,
                           float* out, int64_t ld_out, int32_t dim, hipStream_t st, const int32_t* self_idx, int32_t agg_mode,
-                          const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1) {
+                          const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1, no_blocks_s* side_of) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -396,25 +416,38 @@ static void launch_padded(const T* src, int64_t ld_src, const int32_t* pad, int3
         if (copy_blocks > 1024) copy_blocks = 1024;
         if (copy_blocks < 1) copy_blocks = 1;
     }
-    if (k <= 8)
-        NO_LAUNCH_TIMED((padded_rows_kernel<T, VEC, 8>), dim3((unsigned)(blocks + copy_blocks)), dim3(256), st, ev0, ev1, job, src,
-                        ld_src, pad, k, d_n, n_cap, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode);
-    else
-        NO_LAUNCH_TIMED((padded_rows_kernel<T, VEC, 16>), dim3((unsigned)(blocks + copy_blocks)), dim3(256), st, ev0, ev1, job, src,
-                        ld_src, pad, k, d_n, n_cap, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode);
+    const uint32_t own = (uint32_t)(blocks + copy_blocks);
+    auto launch = [&](auto slots, const auto& side, uint32_t grid) {
+        using Side = std::decay_t<decltype(side)>;
+        NO_LAUNCH_TIMED((padded_rows_kernel<T, VEC, decltype(slots)::value, Side>), dim3(grid), dim3(256), st, ev0, ev1, job, src, ld_src,
+                        pad, k, d_n, n_cap, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, side);
+    };
+    using Few = std::integral_constant<int, 8>;
+    using Many = std::integral_constant<int, 16>;
+    SideTasks side;
+    if (side_of) side_take(side_of, own, &side);
+    NoSideTasks none;
+    none.first_block = own;
+    if (side.n > 0) {
+        if (k <= 8) launch(Few{}, side, own + side.side_blocks());
+        else launch(Many{}, side, own + side.side_blocks());
+    } else {
+        if (k <= 8) launch(Few{}, none, own);
+        else launch(Many{}, none, own);
+    }
 }
 
 int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_t* indptr, const int32_t* indices,
                        const int32_t* d_n_dst, int32_t n_dst_cap, float* mean, hipStream_t st, int32_t agg_mode,
                        const int32_t* self_idx, const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1,
-                       const SourceWeights* weights, const PaddedSlots* padded) {
+                       const SourceWeights* weights, const PaddedSlots* padded, no_blocks_s* side_of) {
     if (n_dst_cap <= 0) return NO_OK;
     if (padded && padded->pad && !(weights && weights->cnt)) {
         // the rows are addressed through the sampler's slot array (global ids): two memory round trips fewer per item
         const int32_t* pad = padded->pad;
         const int32_t k = padded->k;
 #define NO_PAD_FWD(T, V, ptr) \
-    launch_padded<T, V>(ptr, dim, pad, k, d_n_dst, n_dst_cap, mean, dim, dim, st, self_idx, agg_mode, copy, ev0, ev1)
+    launch_padded<T, V>(ptr, dim, pad, k, d_n_dst, n_dst_cap, mean, dim, dim, st, self_idx, agg_mode, copy, ev0, ev1, side_of)
         if (dt == NO_F32) {
             const float* x = (const float*)x_src;
             const bool a16 = (((uintptr_t)x | (uintptr_t)mean) & 15) == 0, a8 = (((uintptr_t)x | (uintptr_t)mean) & 7) == 0;
@@ -432,7 +465,7 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
     }
 #define NO_SEG_FWD(T, V, ptr) \
     launch_segment<T, V, true>(ptr, dim, indptr, indices, d_n_dst, n_dst_cap, nullptr, mean, dim, dim, st, self_idx, agg_mode, \
-                               nullptr, nullptr, nullptr, copy, ev0, ev1, weights)
+                               nullptr, nullptr, nullptr, copy, ev0, ev1, weights, side_of)
     if (dt == NO_F32) {
         const float* x = (const float*)x_src;
         const bool a16 = (((uintptr_t)x | (uintptr_t)mean) & 15) == 0, a8 = (((uintptr_t)x | (uintptr_t)mean) & 7) == 0;
@@ -547,9 +580,9 @@ LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_
 int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* w_self,
                      const float* w_neigh, const float* bias, int32_t d_out, int32_t relu, float* mean, float* h,
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof, int agg_stage, int gemm_stage,
-                     const void* agg_table, hipEvent_t wait_before_gemm, int32_t arch, const Layer1Reuse* reuse,
+                     const void* agg_table, int32_t arch, const Layer1Reuse* reuse,
                      bool aggregate_done, const SourceWeights* weights, const PaddedSlots* padded,
-                     const Bf16Products* bf) {
+                     const Bf16Products* bf, no_blocks_s* side_of) {
     // aggregate_done: `mean` (and the reused rows of H^1) were already written by an earlier launch of the same
     // aggregation (a batch prepared ahead); only the product runs
     // reuse: the output rows are scattered into H^1, recomputed hot rows also refresh the cache, and the reused
@@ -572,7 +605,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         }
         NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
                                 blk.n_dst_cap, mean, st, mode, agg_table ? blk.d_src_global : nullptr, hits, e0, e1,
-                                arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr));
+                                arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr, side_of));
         GemmNNArgs a{};
         a.A[0] = mean; a.lda[0] = d_in; a.a_align[0] = ptr_align(mean, d_in);
         a.B[0] = w_self; a.ldb[0] = d_out; a.b_align[0] = ptr_align(w_self, d_out);
@@ -589,17 +622,17 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     // agg_table != NULL: the rows to average are rows of that table addressed by blk.d_indices (global ids),
     // while x_src holds only the destination rows (fused gather + aggregate of the bottom layer). An fp32
     // table also feeds the self product directly, row m = table row src_global[m], so the forward pass
-    // does not wait for the dense copy of the destination rows at all.
+    // does not need the dense copy of the destination rows at all.
     const bool direct_self = agg_table && dt == NO_F32 && blk.d_src_global;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (prof && agg_stage >= 0 && !aggregate_done) prof->kernel_pair(agg_stage, &e0, &e1);
     if (!aggregate_done)
         NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
                                 blk.n_dst_cap, mean, st, AGG_NEIGH_MEAN, nullptr, hits, e0, e1, nullptr,
-                                agg_table ? padded : nullptr));
+                                agg_table ? padded : nullptr, side_of));
     if (bf) {
         // bf16 operands on the matrix cores: the destinations' rows straight from the table (bf16 as stored), the mean
-        // rounded on load, the weights from their bf16 copies; nothing to wait for on another stream
+        // rounded on load, the weights from their bf16 copies
         GemmBf16NNArgs a{};
         a.X = bf->x_table; a.ldx = bf->ldx; a.x_rows = bf->x_rows;
         a.Mn = mean; a.ldm = d_in;
@@ -613,8 +646,6 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
         return gemm_bf16_nn(a, st, e0, e1);
     }
-    if (wait_before_gemm && !direct_self)
-        NO_HIP_CHECK(hipStreamWaitEvent(st, wait_before_gemm, 0));   // x_src rows come from another stream
     const float* x_dst = direct_self ? (const float*)agg_table : (const float*)x_src;
     if (dt == NO_BF16) {
         NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, blk.n_dst_cap, d_in, w.x_dst_f32, st));
@@ -731,9 +762,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     rj[n_jobs++] = r;
     if (!bf) tj[n_tn++] = t;
     for (int32_t i = 0; pending && i < pending->n && n_jobs < NO_MAX_LAYERS; ++i) { tj[n_tn++] = pending->tn[i]; rj[n_jobs++] = pending->red[i]; }
-    const bool beside = pending && pending->launched_beside;      // the deferred products already run on the side stream
-    if (beside) n_tn = bf ? 0 : 1;
-    if (pending) { pending->n = 0; pending->launched_beside = false; }
+    if (pending) pending->n = 0;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     if (bf) {
         // this layer's two products take bf16 operands (their own launch); the deferred fp32 products of the layers
@@ -753,7 +782,6 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
         NO_CHECK(gemm_tn_partials(tj, n_tn, st, e0, e1));
     }
-    if (beside) NO_HIP_CHECK(hipStreamWaitEvent(st, pending->join, 0));      // only the reduction needs the products beside
     if (prof && reduce_stage >= 0) prof->begin(reduce_stage);
     NO_CHECK(reduce_grads(rj, n_jobs, st, stats_job));
     if (prof && reduce_stage >= 0) prof->end();
@@ -890,7 +918,7 @@ extern "C" int32_t no_gcn_layer_fwd(const no_block_view* blk, no_arch form, cons
     NO_REQUIRE(d_ws != nullptr && ws_bytes >= w.bytes, NO_ERR_CAPACITY, "no_gcn_layer_fwd: workspace too small (%zu < %zu)",
                ws_bytes, w.bytes);
     return sage_forward(*blk, d_x_src, dt_x, d_in, d_w, nullptr, d_bias, d_out, relu, d_agg, d_h, w, (hipStream_t)stream,
-                        nullptr, -1, -1, nullptr, nullptr, form, nullptr, false, &sw);
+                        nullptr, -1, -1, nullptr, form, nullptr, false, &sw);
 }
 
 extern "C" int32_t no_gcn_layer_bwd(const no_block_view* blk, no_arch form, int32_t d_in, const float* d_agg, const float* d_h,

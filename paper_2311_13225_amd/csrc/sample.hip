@@ -16,12 +16,15 @@
 // `map` is a direct-address table int32[V] (HBM is plentiful; no hashing, no probing order to
 // reason about). It carries the local ids from one hop to the next and is wiped after the last.
 // The transpose (hops above the bottom one) is a counting sort: scan of the per-source counts,
-// unordered fill through atomic cursors, then every edge ranks itself inside its (short) column so
+// unordered fill in order of arrival at the counts, then every edge ranks itself inside its (short) column so
 // that columns end up in ascending edge id regardless of the fill order.
-#include "primitives.hpp"
+// 4 and the transpose are side tasks: extra blocks of the launches that follow (side.hpp).
+#include "side.hpp"
 #include "draw.hpp"
 #include "handles.hpp"
 #include "layers.hpp"
+
+#include <algorithm>
 
 namespace no {
 
@@ -40,12 +43,17 @@ __global__ void __launch_bounds__(256) sample_rows_kernel(const RowT* __restrict
                                                           int32_t* __restrict__ src_global, int32_t* map,
                                                           int32_t insert_dst, int32_t* seeds_copy, int32_t* count_out,
                                                           int32_t n_vertices, int32_t* bad_id_flag, int32_t flag_value,
-                                                          unsigned long long* scan_status, int32_t n_status) {
+                                                          unsigned long long* scan_status, int32_t n_status,
+                                                          int32_t* zero_extra, SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     // the tile status words of the scan that follows this launch start out empty
-    for (int32_t t = (int32_t)(blockIdx.x * 256 + threadIdx.x); t < n_status; t += (int32_t)(gridDim.x * 256)) scan_status[t] = 0ull;
+    for (int32_t t = (int32_t)(blockIdx.x * 256 + threadIdx.x); t < n_status; t += (int32_t)(side.first_block * 256)) scan_status[t] = 0ull;
     int32_t n_dst = d_n_dst ? *d_n_dst : n_fixed;
     if (n_dst > n_cap) n_dst = n_cap;
-    if (blockIdx.x == 0 && threadIdx.x == 0) *count_out = n_dst;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *count_out = n_dst;
+        if (zero_extra) zero_extra[0] = zero_extra[1] = zero_extra[4] = 0;      // no cache: nothing computed, reused, refreshed
+    }
     const int32_t i = (int32_t)(blockIdx.x * (256 / G) + threadIdx.x / G);
     const int32_t j = (int32_t)(threadIdx.x % G);
     const bool row_ok = i < n_dst;
@@ -101,11 +109,9 @@ __device__ __forceinline__ int64_t slot_flags_marked(const int32_t* __restrict__
 
 __global__ void __launch_bounds__(ETHREADS) edge_tile_sums_kernel(int32_t* __restrict__ nbr_pad, const int32_t* map,
                                                                   const int32_t* d_n_dst, int32_t k, int64_t* tile_sums,
-                                                                  int32_t* zero_a, int32_t* zero_b, int32_t n_zero) {
-    for (int64_t t = (int64_t)blockIdx.x * ETHREADS + threadIdx.x; t < n_zero; t += (int64_t)gridDim.x * ETHREADS) {
-        zero_a[t] = 0;
-        zero_b[t] = 0;
-    }
+                                                                  int32_t* csc_cnt, int32_t n_zero, SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
+    for (int64_t t = (int64_t)blockIdx.x * ETHREADS + threadIdx.x; t < n_zero; t += (int64_t)side.first_block * ETHREADS) csc_cnt[t] = 0;
     const int32_t n_dst = *d_n_dst;
     const int64_t n_pad = (int64_t)n_dst * k;
     const int64_t base = (int64_t)blockIdx.x * ETILE;
@@ -131,7 +137,9 @@ __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __
                                                                const int64_t* __restrict__ tile_sums,
                                                                int32_t* __restrict__ indptr, int32_t* __restrict__ nbr,
                                                                int32_t* __restrict__ edge_row, int32_t* __restrict__ src_global,
-                                                               int32_t* counts /* [0]=n_dst (in), [1]=n_src, [2]=nnz */) {
+                                                               int32_t* counts /* [0]=n_dst (in), [1]=n_src, [2]=nnz */,
+                                                               SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     __shared__ int64_t smem[ETHREADS / 64 + 1];
     const int32_t n_dst = *d_n_dst;
     const int64_t n_pad = (int64_t)n_dst * k;
@@ -211,16 +219,14 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
                                                              int32_t* __restrict__ nbr, int32_t* __restrict__ edge_row,
                                                              int32_t* __restrict__ src_global,
                                                              int32_t* counts /* [0]=n_dst (in), [1]=n_src, [2]=nnz */,
-                                                             int32_t* zero_a, int32_t* zero_b, int32_t n_zero, int32_t* fail_flag,
+                                                             int32_t* csc_cnt, int32_t n_zero, int32_t* fail_flag,
                                                              int32_t flag_value, int32_t spin_limit, int32_t withhold_first,
-                                                             unsigned int* done) {
+                                                             unsigned int* done, SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     __shared__ int64_t smem[ETHREADS / 64 + 1];
     __shared__ int64_t prefix_sh;
     __shared__ int cleanup_sh;
-    for (int64_t t = (int64_t)blockIdx.x * ETHREADS + threadIdx.x; t < n_zero; t += (int64_t)gridDim.x * ETHREADS) {
-        zero_a[t] = 0;
-        zero_b[t] = 0;
-    }
+    for (int64_t t = (int64_t)blockIdx.x * ETHREADS + threadIdx.x; t < n_zero; t += (int64_t)side.first_block * ETHREADS) csc_cnt[t] = 0;
     const int32_t n_dst = *d_n_dst;
     const int64_t n_pad = (int64_t)n_dst * k;
     if (n_pad == 0) {
@@ -332,55 +338,6 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
     }
 }
 
-// ---------------------------------------------------------------------------- 4. local indices (+ transpose)
-
-__global__ void edge_indices_kernel(const int32_t* d_nnz, const int32_t* __restrict__ nbr, const int32_t* __restrict__ map,
-                                    int32_t* __restrict__ indices, int32_t* csc_cnt) {
-    const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= *d_nnz) return;
-    const int32_t local = map[nbr[e]];
-    indices[e] = local;
-    if (csc_cnt) atomicAdd(&csc_cnt[local], 1);     // integer count: order independent
-}
-
-__global__ void csc_fill_kernel(const int32_t* d_nnz, const int32_t* __restrict__ indices,
-                                const int32_t* __restrict__ csc_indptr, int32_t* cursor, int32_t* __restrict__ unordered) {
-    const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= *d_nnz) return;
-    const int32_t u = indices[e];
-    unordered[csc_indptr[u] + atomicAdd(&cursor[u], 1)] = e;
-}
-
-// Every edge finds its rank among the edges of its column; columns are short (a source is sampled by
-// few destinations), so the quadratic work is small and needs no sort network or shared memory.
-__global__ void csc_rank_kernel(const int32_t* d_nnz, const int32_t* __restrict__ indices,
-                                const int32_t* __restrict__ csc_indptr, const int32_t* __restrict__ unordered,
-                                const int32_t* __restrict__ edge_row, int32_t* __restrict__ csc_eid,
-                                int32_t* __restrict__ csc_dst) {
-    const int32_t e = blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= *d_nnz) return;
-    const int32_t u = indices[e];
-    const int32_t b = csc_indptr[u], len = csc_indptr[u + 1] - b;
-    int32_t r = 0;
-    if (len > 1) {
-        const int32_t* col = unordered + b;
-        int32_t t = 0;
-        for (; t + 8 <= len; t += 8) {       // independent loads: eight compares in flight
-            const int32_t x0 = col[t], x1 = col[t + 1], x2 = col[t + 2], x3 = col[t + 3];
-            const int32_t x4 = col[t + 4], x5 = col[t + 5], x6 = col[t + 6], x7 = col[t + 7];
-            r += (x0 < e) + (x1 < e) + (x2 < e) + (x3 < e) + (x4 < e) + (x5 < e) + (x6 < e) + (x7 < e);
-        }
-        for (; t < len; ++t) r += col[t] < e ? 1 : 0;
-    }
-    csc_eid[b + r] = e;
-    csc_dst[b + r] = edge_row[e];
-}
-
-__global__ void map_wipe_kernel(const int32_t* src_global, const int32_t* d_n_src, int32_t* map) {
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < *d_n_src) map[src_global[i]] = EMPTY;
-}
-
 // ---------------------------------------------------------------------------- hot lookup on V^1
 
 struct CacheProbe {
@@ -405,13 +362,18 @@ __global__ void __launch_bounds__(ETHREADS) v1_tile_sums_kernel(CacheProbe probe
                                                                 int32_t* __restrict__ probe_ver /* [n]: the version the probe read (hot vertices) */,
                                                                 uint32_t v1_blocks, const int32_t* d_nnz,
                                                                 const int32_t* __restrict__ nbr, const int32_t* map,
-                                                                int32_t* __restrict__ indices, int32_t* csc_cnt) {
+                                                                int32_t* __restrict__ indices, int32_t* csc_cnt, int32_t* csc_pos,
+                                                                SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (blockIdx.x >= v1_blocks) {
         const int32_t e = (int32_t)((blockIdx.x - v1_blocks) * ETHREADS + threadIdx.x);
         if (e >= *d_nnz) return;
         const int32_t local = map[nbr[e]];
         indices[e] = local;
-        if (csc_cnt) atomicAdd(&csc_cnt[local], 1);     // integer count: order independent
+        if (csc_cnt) {      // integer count: order independent
+            const int32_t pos = atomicAdd(&csc_cnt[local], 1);
+            if (csc_pos) csc_pos[e] = pos;
+        }
         return;
     }
     const int64_t n = *d_n_v1;
@@ -450,7 +412,8 @@ __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* _
                                                                 int32_t* compute_list, int32_t* compute_pos, int32_t* compute_inv,
                                                                 int32_t* refresh_slot, int32_t* hit_pos,
                                                                 int32_t* hit_slot, int32_t* extra /* n_compute, n_hit, -, -, n_refresh */,
-                                                                int32_t* version, int32_t stamp, int32_t* refresh_old) {
+                                                                int32_t* version, int32_t stamp, int32_t* refresh_old, SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     // version != NULL: the slot of a hot vertex that will be recomputed is stamped with the step right here (the row
     // itself arrives with the step's layer-1 product), so that the split of the next batch depends on this split only
     // and not on that product; the version it replaces is kept, in case the batch is never trained on.
@@ -528,7 +491,7 @@ __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* _
 __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, const int32_t* d_n_v1, unsigned long long* status,
                                                             uint32_t idx_blocks, const int32_t* d_nnz,
                                                             const int32_t* __restrict__ nbr, int32_t* map,
-                                                            int32_t* __restrict__ indices, int32_t* csc_cnt,
+                                                            int32_t* __restrict__ indices, int32_t* csc_cnt, int32_t* csc_pos,
                                                             unsigned int* idx_done, int32_t* compute_list,
                                                             int32_t* compute_pos, int32_t* compute_inv, int32_t* refresh_slot,
                                                             int32_t* hit_pos, int32_t* hit_slot,
@@ -537,7 +500,8 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
                                                             int32_t* fail_flag, int32_t flag_value, int32_t spin_limit,
                                                             int32_t withhold_first, unsigned int* done, int32_t csc_len,
                                                             int32_t* above_nnz, int32_t* above_indptr,
-                                                            const int32_t* above_n_dst) {
+                                                            const int32_t* above_n_dst, SideTasks side) {
+    if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (blockIdx.x < idx_blocks) {
         const int64_t e = (int64_t)blockIdx.x * ETHREADS + threadIdx.x;
         const int32_t nnz = *d_nnz;
@@ -546,7 +510,10 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
             const int32_t local = map[nbr[e]];
             indices[e] = local;
             // (the range check only matters after an expired wait, when the split may have re-keyed the map already)
-            if (csc_cnt && (uint32_t)local < (uint32_t)csc_len) atomicAdd(&csc_cnt[local], 1);     // integer count: order independent
+            if (csc_cnt && (uint32_t)local < (uint32_t)csc_len) {      // integer count: order independent
+                const int32_t pos = atomicAdd(&csc_cnt[local], 1);
+                if (csc_pos) csc_pos[e] = pos;
+            }
         }
         __syncthreads();      // every map read of the block has returned (its value went into a store)
         if (threadIdx.x == 0) __hip_atomic_fetch_add(idx_done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
@@ -679,7 +646,7 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
     }
 }
 
-__global__ void set_counts_kernel(int32_t* p, int32_t a, int32_t b, int32_t c) { p[0] = a; p[1] = b; p[4] = c; }
+__global__ void __launch_bounds__(SIDE_THREADS) side_tasks_kernel(SideTasks side) { run_side_tasks(side); }
 
 // Takes back the stamps of a split whose batch is not trained on.
 __global__ void unstamp_kernel(const int32_t* __restrict__ refresh_slot, const int32_t* __restrict__ refresh_old,
@@ -697,14 +664,95 @@ static inline int64_t edge_tiles(int64_t n_pad_cap) { int64_t t = ceil_div(n_pad
 // does this hop count the edges that leave each source (for its transpose, or for the symmetric normalisation)?
 static inline bool counts_sources(const no_blocks_s* b, const HopBuffers& H) { return H.has_csc || b->count_sources; }
 
+// ---- side tasks: what is due, in the order it becomes so
+
+static inline bool side_pending(const no_blocks_s* b) {
+    for (int32_t h = 0; h < b->n_layers; ++h) if (b->side_next[h] >= 0) return true;
+    return b->wipe_pending || b->rows_pending.table;
+}
+
+void side_take(no_blocks_s* b, uint32_t own_blocks, SideTasks* side) {
+    side->first_block = own_blocks;
+    side->n = 0;
+    bool indices_left = false;
+    for (int32_t h = 0; h < b->n_layers; ++h) indices_left = indices_left || b->side_next[h] == SIDE_INDICES;
+    auto blocks_for = [](int64_t items) { return (uint32_t)std::min<int64_t>(std::max<int64_t>(ceil_div(items, SIDE_THREADS), 1), 8192); };
+    for (int32_t h = 0; h < b->n_layers && side->n < MAX_SIDE_TASKS; ++h) {
+        HopBuffers& H = b->hop[h];
+        const int32_t* cnt = b->counts.p + 4 * h;
+        if (b->side_next[h] < 0) continue;
+        SideTask& t = side->t[side->n++];
+        t = SideTask{};
+        t.kind = b->side_next[h];
+        t.d_n = cnt + 2;
+        t.n_blocks = blocks_for(H.nnz_cap);
+        switch (t.kind) {
+            case SIDE_INDICES:
+                t.in0 = H.nbr_global.p; t.in1 = b->map.p; t.out0 = H.indices.p;
+                t.out1 = counts_sources(b, H) ? H.csc_cnt.p : nullptr;
+                t.out2 = H.has_csc ? H.csc_dst.p : nullptr;      // (arrivals: the ranking, which writes csc_dst, is two tasks away)
+                b->side_next[h] = !H.has_csc ? -1 : H.csc_tiles.p ? SIDE_TILE_SUMS : SIDE_SCAN;
+                break;
+            case SIDE_TILE_SUMS:
+            case SIDE_SCAN:
+                t.d_n = cnt + 1; t.d_nnz = cnt + 2; t.n_cap = H.n_src_cap;
+                t.n_blocks = (uint32_t)std::max<int64_t>(ceil_div(H.n_src_cap, SIDE_SCAN_TILE), 1);
+                t.in0 = H.csc_cnt.p; t.in1 = H.csc_tiles.p;
+                t.out0 = t.kind == SIDE_SCAN ? H.csc_indptr.p : H.csc_tiles.p;
+                b->side_next[h] = t.kind == SIDE_SCAN ? SIDE_FILL : SIDE_SCAN;
+                break;
+            case SIDE_FILL:
+                t.in0 = H.indices.p; t.in1 = H.csc_indptr.p; t.in2 = H.csc_dst.p; t.out0 = H.csc_fill.p;
+                b->side_next[h] = SIDE_RANK;
+                break;
+            default:
+                t.in0 = H.indices.p; t.in1 = H.csc_indptr.p; t.in2 = H.csc_fill.p; t.in3 = H.edge_row.p;
+                t.out0 = H.csc_eid.p; t.out1 = H.csc_dst.p;
+                b->side_next[h] = -1;
+                break;
+        }
+    }
+    if (b->wipe_pending && !indices_left && side->n < MAX_SIDE_TASKS) {
+        SideTask& t = side->t[side->n++];
+        t = SideTask{};
+        t.kind = SIDE_WIPE;
+        const HopBuffers& last = b->hop[b->wipe_hop];
+        t.d_n = b->counts.p + 4 * b->wipe_hop + 1; t.n_blocks = blocks_for(last.n_src_cap);
+        t.in0 = last.src_global.p; t.out0 = b->map.p;
+        b->wipe_pending = false;
+    }
+    if (b->rows_pending.table && side->n < MAX_SIDE_TASKS) {
+        SideTask& t = side->t[side->n++];
+        t = SideTask{};
+        t.kind = SIDE_ROWS;
+        const HopBuffers& last = b->hop[b->wipe_hop];
+        const SideGather& g = b->rows_pending;
+        t.d_n = b->counts.p + 4 * b->wipe_hop; t.n_cap = last.n_dst_cap; t.in0 = last.src_global.p;
+        t.table = (const char*)g.table; t.rows_out = (char*)g.out; t.row_bytes = g.row_bytes;
+        const uintptr_t mix = (uintptr_t)g.table | (uintptr_t)g.out | (uintptr_t)g.row_bytes;
+        t.unit = (mix & 15) == 0 ? 16 : (mix & 7) == 0 ? 8 : (mix & 3) == 0 ? 4 : 2;
+        // (8192 wavefronts: the chip's wave slots once)
+        t.n_blocks = (uint32_t)std::min<int64_t>(std::max<int64_t>(ceil_div(last.n_dst_cap, SIDE_THREADS / 64), 1), 2048);
+        b->rows_pending = SideGather{};
+    }
+}
+
+int32_t blocks_finish(no_blocks_s* b, hipStream_t st) {
+    while (side_pending(b)) {
+        SideTasks side;
+        side_take(b, 0, &side);
+        hipLaunchKernelGGL(side_tasks_kernel, dim3(side.side_blocks()), dim3(SIDE_THREADS), 0, st, side);
+    }
+    return launch_status("side tasks");
+}
+
 template <typename RowT>
 static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b, int32_t h, const int32_t* d_dst,
                           const int32_t* d_n_dst_in, int32_t n_fixed, bool insert_dst, uint32_t key0, uint32_t key1,
-                          uint32_t domain, hipStream_t st, bool indices_now, int32_t extra_status = 0) {
+                          uint32_t domain, hipStream_t st, int32_t* zero_extra, int32_t extra_status) {
     HopBuffers& H = b->hop[h];
     int32_t* cnt = b->counts.p + 4 * h;              // n_dst, n_src, nnz
     const int32_t k = H.fanout;
-    const int T = 256;
     H.d_dst = d_dst;
     H.d_n_dst = cnt;
     int64_t* tile_sums = (int64_t*)b->ws.p;
@@ -712,16 +760,19 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
     int32_t* seeds_copy = (h == 0) ? b->seeds.p : nullptr;
     hipEvent_t tev0 = nullptr, tev1 = nullptr;
     if (b->time_hop == h && b->time_ev0) { tev0 = b->time_ev0; tev1 = b->time_ev1; b->time_ev0 = b->time_ev1 = nullptr; b->time_hop = -1; }
+    SideTasks side;
+    if (tev0) NO_CHECK(blocks_finish(b, st));      // (the timed kernel does its own work only)
 #define NO_LAUNCH_SAMPLE(G)                                                                                            \
-    NO_LAUNCH_TIMED((sample_rows_kernel<G, RowT>), dim3((unsigned)ceil_div(H.n_dst_cap, 256 / G)), dim3(256), st, tev0, tev1, \
+    side_take(b, (uint32_t)ceil_div(H.n_dst_cap, 256 / G), &side);                                                       \
+    NO_LAUNCH_TIMED((sample_rows_kernel<G, RowT>), dim3(side.first_block + side.side_blocks()), dim3(256), st, tev0, tev1, \
                        rowptr, col, d_dst, d_n_dst_in, n_fixed, H.n_dst_cap, k, key0, key1, c3, H.nbr_pad.p,               \
                        H.src_global.p, b->map.p, insert_dst ? 1 : 0, seeds_copy, cnt, (int32_t)b->n_vertices,               \
                        b->counts.p + 4 * b->n_layers + 5, b->call_id, (unsigned long long*)b->ws.p,                          \
-                       (int32_t)edge_tiles(H.nnz_cap) + 1 + extra_status)
-    if (k <= 8) NO_LAUNCH_SAMPLE(8);
-    else if (k <= 16) NO_LAUNCH_SAMPLE(16);
-    else if (k <= 32) NO_LAUNCH_SAMPLE(32);
-    else NO_LAUNCH_SAMPLE(64);
+                       (int32_t)edge_tiles(H.nnz_cap) + 1 + extra_status, zero_extra, side)
+    if (k <= 8) { NO_LAUNCH_SAMPLE(8); }
+    else if (k <= 16) { NO_LAUNCH_SAMPLE(16); }
+    else if (k <= 32) { NO_LAUNCH_SAMPLE(32); }
+    else { NO_LAUNCH_SAMPLE(64); }
 #undef NO_LAUNCH_SAMPLE
     const unsigned tiles = (unsigned)edge_tiles(H.nnz_cap);
     const uint64_t k_magic = k > 1 ? (~0ull / (uint64_t)k) + 1ull : 0ull;     // ceil(2^64 / k)
@@ -730,87 +781,23 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
     // measured slower than two short launches.
     const bool two_pass = b->scan_two_pass;
     const ScanWaitDebug dbg = scan_wait_debug();
+    const int32_t n_zero = counts_sources(b, H) ? H.n_src_cap + 1 : 0;
+    side_take(b, tiles, &side);
     if (two_pass) {
-        hipLaunchKernelGGL(edge_tile_sums_kernel, dim3(tiles), dim3(ETHREADS), 0, st, H.nbr_pad.p,
-                           (const int32_t*)b->map.p, (const int32_t*)cnt, k, tile_sums, H.csc_cnt.p, H.csc_cur.p,
-                           counts_sources(b, H) ? H.n_src_cap + 1 : 0);
-        hipLaunchKernelGGL(edge_assign_kernel, dim3(tiles), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p, b->map.p,
-                           (const int32_t*)cnt, k, k_magic, (const int64_t*)tile_sums, H.indptr.p, H.nbr_global.p, H.edge_row.p,
-                           H.src_global.p, cnt);
+        hipLaunchKernelGGL(edge_tile_sums_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, H.nbr_pad.p,
+                           (const int32_t*)b->map.p, (const int32_t*)cnt, k, tile_sums, H.csc_cnt.p, n_zero, side);
+        side_take(b, tiles, &side);
+        hipLaunchKernelGGL(edge_assign_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p,
+                           b->map.p, (const int32_t*)cnt, k, k_magic, (const int64_t*)tile_sums, H.indptr.p, H.nbr_global.p,
+                           H.edge_row.p, H.src_global.p, cnt, side);
     } else {
-        hipLaunchKernelGGL(edge_scan_kernel, dim3(tiles), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p, b->map.p,
-                           (const int32_t*)cnt, k, k_magic, (unsigned long long*)b->ws.p, H.indptr.p, H.nbr_global.p,
-                           H.edge_row.p, H.src_global.p, cnt, H.csc_cnt.p, H.csc_cur.p, counts_sources(b, H) ? H.n_src_cap + 1 : 0,
-                           b->counts.p + 4 * b->n_layers + 6, b->call_id, dbg.spin_limit, dbg.withhold_first_tile,
-                           (unsigned int*)((unsigned long long*)b->ws.p + tiles));
+        hipLaunchKernelGGL(edge_scan_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p,
+                           b->map.p, (const int32_t*)cnt, k, k_magic, (unsigned long long*)b->ws.p, H.indptr.p, H.nbr_global.p,
+                           H.edge_row.p, H.src_global.p, cnt, H.csc_cnt.p, n_zero, b->counts.p + 4 * b->n_layers + 6, b->call_id,
+                           dbg.spin_limit, dbg.withhold_first_tile, (unsigned int*)((unsigned long long*)b->ws.p + tiles), side);
     }
-    if (indices_now)
-        hipLaunchKernelGGL(edge_indices_kernel, dim3((unsigned)ceil_div(H.nnz_cap, T)), dim3(T), 0, st,
-                           (const int32_t*)(cnt + 2), (const int32_t*)H.nbr_global.p, (const int32_t*)b->map.p, H.indices.p,
-                           counts_sources(b, H) ? H.csc_cnt.p : nullptr);
+    b->side_next[h] = SIDE_INDICES;
     return launch_status("sample_hop");
-}
-
-// Work that nothing on the caller's stream needs before the join, queued on the side stream behind ONE
-// fork event recorded after the last hop's ids are final: the local indices of the hops that do not have
-// them yet (the bottom layer aggregates through the global ids; a vertex keeps its local id from the hop
-// that first saw it, so the map still answers for the hops above unless the cache split re-keyed it),
-// the transposes of the upper hops, and the wipe of the id map.
-static int32_t launch_side_work(no_blocks_s* b, int32_t n_hops, const int32_t* d_n_src_last, hipStream_t st,
-                                const SideGather* gather, const bool* indices_done) {
-    const int T = 256;
-    hipStream_t sd = b->side;
-    NO_HIP_CHECK(hipEventRecord(b->ev_fork[0], st));
-    NO_HIP_CHECK(hipStreamWaitEvent(sd, b->ev_fork[0], 0));
-    // the dense copy of the bottom destinations' rows goes first when the forward pass waits for it, else last
-    // (then it runs next to the matrix products instead of next to the bandwidth-bound aggregation)
-    auto copy_rows = [&]() -> int32_t {
-        const HopBuffers& lastg = b->hop[n_hops - 1];
-        NO_CHECK(gather_rows(gather->table, gather->row_bytes, gather->row_bytes, lastg.src_global.p,
-                             b->counts.p + 4 * (n_hops - 1), lastg.n_dst_cap, gather->out, gather->row_bytes, sd));
-        NO_HIP_CHECK(hipEventRecord(b->ev_gather_done, sd));
-        return NO_OK;
-    };
-    const bool have_copy = gather && gather->table;
-    if (have_copy && gather->needed_by_forward) NO_CHECK(copy_rows());
-    // local indices first: the forward pass of the layers above the bottom one aggregates through them, so it
-    // waits for ev_indices_done (not for the whole side stream) when they were left to this stream
-    b->upper_indices_deferred = false;
-    for (int32_t h = 0; h < n_hops; ++h) {
-        HopBuffers& H = b->hop[h];
-        int32_t* cnt = b->counts.p + 4 * h;
-        if (indices_done[h]) continue;
-        hipLaunchKernelGGL(edge_indices_kernel, dim3((unsigned)ceil_div(H.nnz_cap, T)), dim3(T), 0, sd,
-                           (const int32_t*)(cnt + 2), (const int32_t*)H.nbr_global.p, (const int32_t*)b->map.p,
-                           H.indices.p, counts_sources(b, H) ? H.csc_cnt.p : nullptr);
-        if (h < n_hops - 1) b->upper_indices_deferred = true;
-    }
-    NO_HIP_CHECK(hipEventRecord(b->ev_indices_done, sd));
-    for (int32_t h = 0; h < n_hops; ++h) {
-        HopBuffers& H = b->hop[h];
-        int32_t* cnt = b->counts.p + 4 * h;
-        if (!H.has_csc) continue;
-        NO_CHECK(exclusive_scan2(ArrayLoader{H.csc_cnt.p}, cnt + 1, H.n_src_cap, H.csc_indptr.p, nullptr, b->ws_side.p, sd));
-        hipLaunchKernelGGL(csc_fill_kernel, dim3((unsigned)ceil_div(H.nnz_cap, T)), dim3(T), 0, sd, (const int32_t*)(cnt + 2),
-                           (const int32_t*)H.indices.p, (const int32_t*)H.csc_indptr.p, H.csc_cur.p, b->tmp_a.p);
-        hipLaunchKernelGGL(csc_rank_kernel, dim3((unsigned)ceil_div(H.nnz_cap, T)), dim3(T), 0, sd, (const int32_t*)(cnt + 2),
-                           (const int32_t*)H.indices.p, (const int32_t*)H.csc_indptr.p, (const int32_t*)b->tmp_a.p,
-                           (const int32_t*)H.edge_row.p, H.csc_eid.p, H.csc_dst.p);
-    }
-    HopBuffers& last = b->hop[n_hops - 1];
-    hipLaunchKernelGGL(map_wipe_kernel, dim3((unsigned)ceil_div(last.n_src_cap, T)), dim3(T), 0, sd,
-                       (const int32_t*)last.src_global.p, d_n_src_last, b->map.p);
-    if (have_copy && !gather->needed_by_forward) NO_CHECK(copy_rows());
-    b->side_pending = true;
-    return launch_status("side work");
-}
-
-int32_t blocks_join(no_blocks_s* b, hipStream_t st) {
-    if (!b->side_pending) return NO_OK;
-    NO_HIP_CHECK(hipEventRecord(b->ev_side_done, b->side));
-    NO_HIP_CHECK(hipStreamWaitEvent(st, b->ev_side_done, 0));
-    b->side_pending = false;
-    return NO_OK;
 }
 
 // One launch for the V^1 split where the sampling has the chip to itself, two launches where it runs beside another
@@ -822,9 +809,9 @@ static bool v1_one_launch(const no_blocks_s* b, unsigned tiles) {
 }
 
 int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seeds, uint64_t stream_key, uint32_t domain,
-                           int32_t n_hops, no_cache_s* cache, int64_t step, no_blocks_s* b, hipStream_t st, bool join,
+                           int32_t n_hops, no_cache_s* cache, int64_t step, no_blocks_s* b, hipStream_t st, bool finish,
                            const SideGather* gather, bool stamp_refresh) {
-    NO_CHECK(blocks_join(b, st));      // a previous call that was never joined
+    NO_CHECK(blocks_finish(b, st));      // a previous call that was never finished
     b->stamped_cache = nullptr;
     b->call_id = b->call_id % 0x3fffffff + 1;      // flag words written by this call's kernels carry this value
     const int32_t L = b->n_layers;
@@ -834,12 +821,16 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
     const int32_t* d_n = nullptr;
     const bool use_cache = cache != nullptr && L >= 2 && n_hops == L && cache->n_hot > 0;
     b->last_used_cache = use_cache;
-    bool indices_done[NO_MAX_LAYERS] = {};
     for (int32_t h = 0; h < n_hops; ++h) {
         if (h == L - 1 && use_cache) {
             // split V^1 (= sources of hop L-2) into reusable rows and rows to compute; the same launch writes
-            // hop L-2's local indices, which the re-keyed map could no longer give
+            // hop L-2's local indices, which the re-keyed map could no longer give (the hops above have theirs: they went
+            // with the sampling of the hop after)
             HopBuffers& P = b->hop[h - 1];
+            b->side_next[h - 1] = -1;
+            for (int32_t up = 0; up < h - 1; ++up)
+                if (b->side_next[up] == SIDE_INDICES) { NO_CHECK(blocks_finish(b, st)); break; }
+            SideTasks side;
             CacheProbe probe{d_dst, cache->slot_of_vertex.p, cache->version.p, step, cache->staleness};
             const unsigned tiles = (unsigned)edge_tiles(P.n_src_cap);
             const unsigned idx_blocks = (unsigned)ceil_div(P.nnz_cap, ETHREADS);
@@ -849,53 +840,53 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
                 // (status words and the counter behind them: emptied by the sampling launch of hop L-2, past its own)
                 // (word edge_tiles(P.nnz_cap) is the completion counter of hop L-2's edge scan)
                 unsigned long long* v1_status = (unsigned long long*)b->ws.p + edge_tiles(P.nnz_cap) + 1;
-                hipLaunchKernelGGL(v1_split_kernel, dim3(idx_blocks + tiles), dim3(ETHREADS), 0, st, probe, d_n, v1_status,
+                side_take(b, idx_blocks + tiles, &side);
+                hipLaunchKernelGGL(v1_split_kernel, dim3(side.first_block + side.side_blocks()), dim3(ETHREADS), 0, st, probe, d_n, v1_status,
                                    idx_blocks, (const int32_t*)(b->counts.p + 4 * (h - 1) + 2), (const int32_t*)P.nbr_global.p,
-                                   b->map.p, P.indices.p, counts_sources(b, P) ? P.csc_cnt.p : nullptr, (unsigned int*)(v1_status + tiles),
+                                   b->map.p, P.indices.p, counts_sources(b, P) ? P.csc_cnt.p : nullptr,
+                                   P.has_csc ? P.csc_dst.p : nullptr, (unsigned int*)(v1_status + tiles),
                                    b->compute_list.p, b->compute_pos.p, b->compute_inv.p, b->refresh_slot.p, b->hit_pos.p,
                                    b->hit_slot.p, extra, stamp_refresh ? cache->version.p : nullptr, (int32_t)step,
                                    b->refresh_old.p, b->counts.p + 4 * b->n_layers + 6, b->call_id, dbg.spin_limit,
                                    dbg.withhold_first_tile, (unsigned int*)(v1_status + tiles + 1), P.n_src_cap + 1,
-                                   b->counts.p + 4 * (h - 1) + 2, P.indptr.p, (const int32_t*)(b->counts.p + 4 * (h - 1)));
+                                   b->counts.p + 4 * (h - 1) + 2, P.indptr.p, (const int32_t*)(b->counts.p + 4 * (h - 1)), side);
             } else {
-            hipLaunchKernelGGL(v1_tile_sums_kernel, dim3(tiles + idx_blocks), dim3(ETHREADS), 0, st, probe, d_n, tile_sums,
+            side_take(b, tiles + idx_blocks, &side);
+            hipLaunchKernelGGL(v1_tile_sums_kernel, dim3(side.first_block + side.side_blocks()), dim3(ETHREADS), 0, st, probe, d_n, tile_sums,
                                b->probe_slot.p, b->probe_ver.p, tiles, (const int32_t*)(b->counts.p + 4 * (h - 1) + 2),
                                (const int32_t*)P.nbr_global.p, (const int32_t*)b->map.p, P.indices.p,
-                               counts_sources(b, P) ? P.csc_cnt.p : nullptr);
-            indices_done[h - 1] = true;
-            hipLaunchKernelGGL(v1_partition_kernel, dim3(tiles), dim3(ETHREADS), 0, st, d_dst,
+                               counts_sources(b, P) ? P.csc_cnt.p : nullptr, P.has_csc ? P.csc_dst.p : nullptr, side);
+            side_take(b, tiles, &side);
+            hipLaunchKernelGGL(v1_partition_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, d_dst,
                                (const int32_t*)b->probe_slot.p, (const int32_t*)b->probe_ver.p, d_n, (const int64_t*)tile_sums, b->map.p, b->compute_list.p, b->compute_pos.p, b->compute_inv.p, b->refresh_slot.p, b->hit_pos.p,
                                b->hit_slot.p, extra, stamp_refresh ? cache->version.p : nullptr, (int32_t)step,
-                               b->refresh_old.p);
+                               b->refresh_old.p, side);
             }
-            indices_done[h - 1] = true;
+            if (P.has_csc) b->side_next[h - 1] = P.csc_tiles.p ? SIDE_TILE_SUMS : SIDE_SCAN;
             b->stamped_cache = stamp_refresh ? cache : nullptr;
             b->stamped_uid = cache->uid;
             b->stamped_contents = cache->contents;
             d_dst = b->compute_list.p;
             d_n = extra + 0;
         }
-        // with the cache split ahead, the hops above L-2 read the map before the split re-keys it; every other
-        // hop's indices wait for the side stream
-        const bool indices_now = use_cache && h < L - 2;
+        int32_t* zero_extra = h == 0 && !use_cache ? extra : nullptr;
         // the hop above the bottom one also empties the status words of the V^1 split that follows it
         const int32_t extra_status = (use_cache && h == L - 2 && v1_one_launch(b, (unsigned)edge_tiles(b->hop[h].n_src_cap)))
                                          ? (int32_t)edge_tiles(b->hop[h].n_src_cap) + 2 : 0;
         if (g->rowptr_bits == 64)
             NO_CHECK(sample_hop<int64_t>(g->rowptr64.p, g->col.p, b, h, d_dst, d_n, n_seeds, h == 0, key0, key1, domain, st,
-                                         indices_now, extra_status));
+                                         zero_extra, extra_status));
         else
             NO_CHECK(sample_hop<int32_t>(g->rowptr32.p, g->col.p, b, h, d_dst, d_n, n_seeds, h == 0, key0, key1, domain, st,
-                                         indices_now, extra_status));
-        if (indices_now) indices_done[h] = true;
+                                         zero_extra, extra_status));
         d_dst = b->hop[h].src_global.p;
         d_n = b->counts.p + 4 * h + 1;
     }
-    if (!use_cache) hipLaunchKernelGGL(set_counts_kernel, dim3(1), dim3(1), 0, st, extra, 0, 0, 0);
-    NO_CHECK(launch_side_work(b, n_hops, d_n, st, gather, indices_done));
+    b->wipe_pending = true;
+    b->wipe_hop = n_hops - 1;
+    if (gather && gather->table) b->rows_pending = *gather;
     NO_CHECK(launch_status("sample_blocks"));
-    if (join) NO_CHECK(blocks_join(b, st));
-    return NO_OK;
+    return finish ? blocks_finish(b, st) : NO_OK;
 }
 
 int32_t blocks_unstamp(no_blocks_s* b, hipStream_t st) {
@@ -926,7 +917,7 @@ int32_t blocks_create_impl(no_graph_s* g, int32_t n_seeds_cap, const int32_t* fa
     b->n_vertices = g->n_vertices;
     b->build_csc = build_csc;
     int64_t dst_cap = n_seeds_cap;
-    int64_t max_pad = 1, max_sort = 1, max_src = 1;
+    int64_t max_pad = 1, max_src = 1;
     for (int32_t h = 0; h < n_layers; ++h) {
         HopBuffers& H = b->hop[h];
         int64_t nnz_cap = dst_cap * fanouts[h];
@@ -944,13 +935,13 @@ int32_t blocks_create_impl(no_graph_s* g, int32_t n_seeds_cap, const int32_t* fa
         NO_CHECK(H.nbr_global.alloc((size_t)nnz_cap));
         NO_CHECK(H.indices.alloc((size_t)nnz_cap));
         NO_CHECK(H.edge_row.alloc((size_t)nnz_cap));
-        NO_CHECK(H.csc_cnt.alloc((size_t)src_cap + 1));       // (every hop: the bottom hop's counts serve the symmetric
-        NO_CHECK(H.csc_cur.alloc((size_t)src_cap + 1));       //  normalisation; the two arrays are emptied together)
+        NO_CHECK(H.csc_cnt.alloc((size_t)src_cap + 1));       // (every hop: the bottom hop's counts serve the symmetric normalisation)
         if (H.has_csc) {
             NO_CHECK(H.csc_indptr.alloc((size_t)src_cap + 1));
             NO_CHECK(H.csc_dst.alloc((size_t)nnz_cap));
             NO_CHECK(H.csc_eid.alloc((size_t)nnz_cap));
-            if (nnz_cap > max_sort) max_sort = nnz_cap;
+            NO_CHECK(H.csc_fill.alloc((size_t)nnz_cap));
+            if (src_cap > SIDE_SCAN_ONE_LAUNCH) NO_CHECK(H.csc_tiles.alloc((size_t)ceil_div(src_cap, SIDE_SCAN_TILE)));
         }
         if (nnz_cap > max_pad) max_pad = nnz_cap;
         if (src_cap > max_src) max_src = src_cap;
@@ -961,15 +952,8 @@ int32_t blocks_create_impl(no_graph_s* g, int32_t n_seeds_cap, const int32_t* fa
     NO_CHECK(b->seeds.alloc((size_t)n_seeds_cap));
     NO_CHECK(b->map.alloc((size_t)g->n_vertices));
     NO_CHECK(fill_i32(b->map.p, EMPTY, g->n_vertices, nullptr));
-    NO_CHECK(b->tmp_a.alloc((size_t)max_sort));
     const int64_t max_items = max_pad > max_src ? max_pad : max_src;
     NO_CHECK(b->ws.alloc((size_t)(2 * edge_tiles(max_items + 1) + 8) * sizeof(int64_t)));      // two sets of status words and their counters
-    NO_CHECK(b->ws_side.alloc((size_t)(edge_tiles(max_items + 1) + 2) * sizeof(int64_t)));
-    NO_HIP_CHECK(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
-    for (int32_t h = 0; h < n_layers; ++h) NO_HIP_CHECK(hipEventCreateWithFlags(&b->ev_fork[h], NO_SYNC_EVENT_FLAGS));
-    NO_HIP_CHECK(hipEventCreateWithFlags(&b->ev_side_done, NO_SYNC_EVENT_FLAGS));
-    NO_HIP_CHECK(hipEventCreateWithFlags(&b->ev_gather_done, NO_SYNC_EVENT_FLAGS));
-    NO_HIP_CHECK(hipEventCreateWithFlags(&b->ev_indices_done, NO_SYNC_EVENT_FLAGS));
     if (n_layers >= 2) {
         size_t v1_cap = (size_t)b->hop[n_layers - 2].n_src_cap;
         NO_CHECK(b->compute_list.alloc(v1_cap));

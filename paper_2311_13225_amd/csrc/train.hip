@@ -101,7 +101,6 @@ struct no_model_s {
     // the matrices of the layers above layer 1 cut for their input gradients (cut_weights), rewritten like wt1
     no::DevBuf<uint16_t> planes;
     uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
-    hipEvent_t ev_dw_join = nullptr;
     bool weights_dirty = true;
     no::DevBuf<float> mean[NO_MAX_LAYERS];           // layer l (index l-1): [n_dst_cap, d_{l-1}]
     no::DevBuf<float> h[NO_MAX_LAYERS];              // layer l output [rows, d_l]; h[0] holds all of V^1
@@ -135,7 +134,6 @@ struct no_model_s {
     void release() {
         no::ReleaseScope scope;
         if (prof.created) { for (auto& e : prof.ev) (void)hipEventDestroy(e); prof.created = false; }
-        if (ev_dw_join) { (void)hipEventDestroy(ev_dw_join); ev_dw_join = nullptr; }
         if (worker) { worker->shutdown(); delete worker; worker = nullptr; }
         // a batch prepared ahead and never trained on: its split's stamps leave the cache with the model
         if (ahead_valid && blocks_alt && sample_stream) (void)no::blocks_unstamp(blocks_alt, sample_stream);
@@ -238,7 +236,6 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
     if (feat_dtype == NO_BF16) {
         m->wt1_kpad = bf16_kpad(m->dims[0]);
         NO_CHECK(m->wt1.alloc((size_t)2 * m->dims[1] * m->wt1_kpad));
-        NO_HIP_CHECK(hipEventCreateWithFlags(&m->ev_dw_join, NO_SYNC_EVENT_FLAGS));
     }
     size_t n_planes = 0;
     for (int32_t l = 1; l < L; ++l) n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1], true);
@@ -386,7 +383,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                 aggregated = true;
             }
         } else {
-            NO_CHECK(blocks_join(m->blocks_alt, st));
+            NO_CHECK(blocks_finish(m->blocks_alt, st));
             NO_CHECK(blocks_unstamp(m->blocks_alt, st));      // the batch prepared ahead is not the one asked for
         }
         m->ahead_valid = false;
@@ -399,17 +396,16 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     prof.st = st;
     prof.n = 0;
 
-    // Sample. Only the destination rows of the bottom hop are gathered densely (the self path of layer 1 and
-    // its weight gradient read them); that copy runs on the blocks' side stream next to the layer-1 aggregation,
-    // which reads the neighbour rows from the feature table itself through the sampled global ids, so those
-    // rows are never written and re-read.
+    // Sample. Only the destination rows of the bottom hop are gathered densely (layer 1's weight gradient reads them;
+    // the forward product reads the table rows itself); that copy is one of the sampling call's side tasks and goes with
+    // the layer-1 aggregation, which reads the neighbour rows from the feature table itself through the sampled global
+    // ids, so those rows are never written and re-read.
     const int32_t es = m->feat_dtype == NO_F32 ? 4 : 2;
     const int32_t row_bytes = m->dims[0] * es;
     SideGather sg;
     sg.table = arch_is_gcn(m->arch) ? nullptr : d_features;    // GCN-style layers read every row inside the aggregation
     sg.row_bytes = row_bytes;
     sg.out = m->x0.p;
-    sg.needed_by_forward = false;    // the forward product reads the destinations' table rows itself (fp32 and bf16)
     // bf16 table: layer 1's products take bf16 operands (features as stored; mean, weights, output gradient rounded)
     const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
     uint16_t* wt_self = m->wt1.p;
@@ -431,15 +427,13 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     if (!presampled) {
         B->time_ev0 = sev0; B->time_ev1 = sev1; B->time_hop = sev0 ? L - 1 : -1;
         NO_CHECK(sample_blocks_impl(g, d_seeds, n_seeds, seed + (uint64_t)step, 0u, L, cache, step, B, st, false, &sg, true));
-        // measurement passes count the side stream's share of the sampling (local indices, transposes, map wipe) too
-        if (prof.enabled) NO_CHECK(blocks_join(B, st));
+        // measurement passes count the side tasks (local indices, transposes, map wipe, copied rows) with the sampling
+        if (prof.enabled) NO_CHECK(blocks_finish(B, st));
     }
     prof.end();
     const bool used_cache = B->last_used_cache;
     m->last_used_cache = used_cache;
     const int32_t* extra = B->counts.p + 4 * L;
-    const HopBuffers& bottom = B->hop[L - 1];
-    (void)bottom;
 
     // The next batch is prepared on the sampling stream in two parts. Part one: sampling and the dense copy of its
     // destination rows. Its split into reused and computed rows reads the cache's versions only, and those are
@@ -450,9 +444,8 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     // layers), which depends on no weight, into a second aggregate buffer; with it the batch's reused rows are copied
     // from the cache (they may be rows this step's layer 1 has just refreshed) into a second H^1, so this step's
     // buffers stay as the step leaves them. Both run beside this step's matrix-bound kernels.
-    // (The transposes, the local indices of the upper hops and the dense copy go to that batch's own side stream: they
-    // are needed by its backward pass and upper layers only, and would otherwise sit between its sampling and its
-    // aggregation on the sampling stream, which is the longer of the two chains.)
+    // (The side tasks that the sampling leaves go with that aggregation and one launch after it.)
+    const bool aggregate_ahead = L >= 2 && m->arch == NO_ARCH_SAGE_MEAN;
     auto launch_sampling_ahead = [=]() -> int32_t {
         NO_HIP_CHECK(hipStreamWaitEvent(m->sample_stream, m->ev_can_sample, 0));
         SideGather sg2 = sg;
@@ -460,6 +453,8 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         m->blocks_alt->scan_two_pass = true;      // this sampling shares the chip with the step's products
         NO_CHECK(sample_blocks_impl(g, d_next_seeds, n_next_seeds, seed + (uint64_t)(step + 1), 0u, L, cache, step + 1,
                                     m->blocks_alt, m->sample_stream, false, &sg2, true));
+        // (the aggregation, if there will be one, takes side tasks along; its event replaces this one)
+        if (!aggregate_ahead) NO_CHECK(blocks_finish(m->blocks_alt, m->sample_stream));
         NO_HIP_CHECK(hipEventRecord(m->ev_sampled, m->sample_stream));
         m->ahead_valid = true;
         m->ahead_step = step + 1;
@@ -474,7 +469,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     };
     // (ev_l1_done is recorded on the step's stream, by the calling thread, after layer 1's launch)
     auto launch_aggregate_ahead = [=]() -> int32_t {
-        if (L < 2 || m->arch != NO_ARCH_SAGE_MEAN) return NO_OK;
+        if (!aggregate_ahead) return NO_OK;
         no_blocks_s* NB = m->blocks_alt;
         no_block_view nv;
         fill_block_view(NB, L - 1, &nv);
@@ -489,7 +484,8 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         const PaddedSlots next_slots{NB->hop[L - 1].nbr_pad.p, NB->hop[L - 1].fanout};
         NO_CHECK(mean_aggregate(d_features, m->feat_dtype, m->dims[0], nv.d_indptr, nv.d_nbr_global, nv.d_n_dst, nv.n_dst_cap,
                                 m->mean_alt.p, m->sample_stream, AGG_NEIGH_MEAN, nullptr, next_cache ? &next_hits : nullptr,
-                                nullptr, nullptr, nullptr, &next_slots));
+                                nullptr, nullptr, nullptr, &next_slots, NB));
+        NO_CHECK(blocks_finish(NB, m->sample_stream));
         NO_HIP_CHECK(hipEventRecord(m->ev_sampled, m->sample_stream));
         m->ahead_aggregated = true;
         return NO_OK;
@@ -536,20 +532,17 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         }
         LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out);
         // symmetric normalisation: the column sums of the block's adjacency are the per-source edge counts of the hop
-        // (written with the local indices on the blocks' side stream); the fused layer-1 aggregate reads global ids,
+        // (written with the local indices); the fused layer-1 aggregate reads global ids,
         // so it also takes the local index of every entry
         SourceWeights sw;
         if (m->arch == NO_ARCH_GCN_SYM) {
             sw.cnt = B->hop[L - l].csc_cnt.p;
-            if (l == 1) { sw.local = B->hop[L - 1].indices.p; NO_HIP_CHECK(hipStreamWaitEvent(st, B->ev_indices_done, 0)); }
+            if (l == 1) { sw.local = B->hop[L - 1].indices.p; NO_CHECK(blocks_finish(B, st)); }
         }
         if (l == 2) prof.begin(NO_STAGE_FWD_UPPER);
-        // layers above the bottom one aggregate through local indices; without the cache split those are written
-        // on the blocks' side stream
-        if (l == 2 && B->upper_indices_deferred) NO_HIP_CHECK(hipStreamWaitEvent(st, B->ev_indices_done, 0));
+        // (the layers above the bottom one aggregate through local indices: those came with the sampling of the hop below)
         if (l == 1) {
-            // fused gather + aggregate: rows of the table addressed by the sampled neighbours' global ids; the
-            // dense product then waits for the destination rows copied on the side stream
+            // fused gather + aggregate: rows of the table addressed by the sampled neighbours' global ids
             no_block_view fused = blk;
             fused.d_indices = blk.d_nbr_global;
             const PaddedSlots slots{B->hop[L - 1].nbr_pad.p, B->hop[L - 1].fanout};
@@ -560,15 +553,13 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             }
             NO_CHECK(sage_forward(fused, x, dt, d_in, m->params.p + m->off_w_self[0], m->params.p + m->off_w_neigh[0],
                                   m->params.p + m->off_bias[0], d_out, l < L ? 1 : 0, m->mean[0].p, h_out, w, st, &prof,
-                                  NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features,
-                                  arch_is_gcn(m->arch) ? nullptr : B->ev_gather_done, m->arch,
+                                  NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
-                                  bf16_products ? &bfp : nullptr));
+                                  bf16_products ? &bfp : nullptr, B));
         } else
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,
-                              l == 1 ? &prof : nullptr, NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, nullptr, nullptr, m->arch,
-                              nullptr, false, &sw));
+                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B));
         if (l == L && L >= 2) prof.end();
         if (l == 1 && d_next_seeds) {
             if (next_uses_cache && L >= 2 && m->arch == NO_ARCH_SAGE_MEAN) NO_HIP_CHECK(hipEventRecord(m->ev_l1_done, st));
@@ -599,20 +590,12 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     stats_job.emb_row_bytes = (L >= 2 && used_cache) ? m->dims[1] * 4 : 0;
     stats_job.stats = stats;
 
-    // backward (first joins the side stream: the transposes are needed from here on)
-    NO_CHECK(blocks_join(B, st));
+    // backward (the transposes and the copied rows are needed from here on)
+    NO_CHECK(blocks_finish(B, st));
     // The weight gradients of the layers above the bottom one (and their SGD step) are nobody's input within the step:
     // their products and reductions are carried by the bottom layer's two launches, which end the step, instead of
     // adding two launches per layer to the chain of dependent kernels.
     GradJobs pending;
-    if (bf16_products) {
-        // the bottom layer's products are of another kind (bf16 operands) and cannot carry the upper layers' fp32 ones in
-        // their launch: those run on the blocks' side stream (joined above, idle from here on), launched once layer 2
-        // has handed over its job, beside layer 2's input gradient and the bottom layer's products
-        pending.side = B->side;
-        pending.fork = B->ev_fork[0];
-        pending.join = m->ev_dw_join;
-    }
     for (int32_t l = L; l >= 1; --l) {
         const no_block_view& blk = view[L - l];
         const int32_t d_in = m->dims[l - 1], d_out = m->dims[l];
@@ -647,8 +630,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             bfp.x_dense = (const uint16_t*)m->x0.p;
             bfp.wt_self = wt_self; bfp.wt_neigh = wt_neigh; bfp.Kpad = m->wt1_kpad;
         }
-        const bool launch_beside = pending.side && l == 2;
-        if (launch_beside) NO_HIP_CHECK(hipEventRecord(pending.fork, st));      // (every deferred job's inputs are ready here)
         NO_CHECK(sage_backward(blk, x, dt, d_in, m->mean[l - 1].p, h_l, gh_l, m->params.p + m->off_w_self[l - 1],
                                m->params.p + m->off_w_neigh[l - 1], d_out, l < L ? 1 : 0,
                                m->grads.p + m->off_w_self[l - 1], m->grads.p + m->off_w_neigh[l - 1],
@@ -657,12 +638,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                -1, grad_rows, lr, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                                m->params.p + m->off_bias[l - 1], m->arch, l == 1 ? &stats_job : nullptr, gz_in,
                                l >= 2 ? &below : nullptr, &pending, l >= 2, &sw, (bf16_products && l == 1) ? &bfp : nullptr, l >= 2 ? m->cut_bwd[l - 1] : nullptr));
-        if (launch_beside && pending.n > 0) {
-            NO_HIP_CHECK(hipStreamWaitEvent(pending.side, pending.fork, 0));
-            NO_CHECK(gemm_tn_partials(pending.tn, pending.n, pending.side, nullptr, nullptr));
-            NO_HIP_CHECK(hipEventRecord(pending.join, pending.side));
-            pending.launched_beside = true;
-        }
     }
 
     // (the SGD step ran inside each layer's gradient reduction, after every kernel that read the weights;
