@@ -41,6 +41,7 @@ struct GemmTNArgs {
     int32_t Kp, N;
     const int32_t* d_R; int32_t R_cap; int32_t splits;   // splits: the most row slices (the partials' layout is sized for it)
     int32_t n_problems = 2;                              // 1: only A[0]
+    const uint16_t* A16 = nullptr;                       // products with bf16 operands: the first one's rows in place of A[0]
     int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer
 };
 
@@ -64,13 +65,6 @@ struct GemmBf16NNArgs {
     const float* bias; int32_t relu;
     const int32_t* c_rows; float* c_keep; const int32_t* c_keep_rows;   // as in GemmNNArgs
 };
-struct GemmBf16TNArgs {
-    const uint16_t* X; int64_t ldx;                          // [R, Kp] bf16 (product 0)
-    const float* Mn; int64_t ldm;                            // [R, Kp] fp32, rounded on load (product 1)
-    const float* G; int64_t ldg;                             // [R, N] fp32, rounded on load
-    float* P; int32_t Kp, N;                                 // partials in the layout of GemmTNArgs
-    const int32_t* d_R; int32_t R_cap; int32_t splits; int32_t rows_per_split;
-};
 // Weights cut for the large gradient products (gemm_cut.hip): planes of one matrix [K][N], reduction index padded to 32.
 __host__ __device__ inline int32_t cut_pad(int32_t K) { return (K + 31) / 32 * 32; }
 inline size_t cut_weights_elements(int32_t K, int32_t N, bool transposed) {
@@ -81,7 +75,6 @@ int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool
 inline int32_t bf16_kpad(int32_t K) { return (K + 15) / 16 * 16; }
 int32_t weights_to_bf16_t(const float* w, int32_t K, int32_t N, int32_t Kpad, uint16_t* out, hipStream_t st);
 int32_t gemm_bf16_nn(const GemmBf16NNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-int32_t gemm_bf16_tn_partials(const GemmBf16TNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 
 // Statistics of a training step, written by one extra block of the last gradient reduction of the step (they are
 // nobody's input, so they do not get a launch of their own on the step's dependency chain): mean of the per-seed

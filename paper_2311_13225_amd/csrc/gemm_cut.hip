@@ -324,7 +324,43 @@ struct ColumnUnit {
 #pragma unroll
             for (int c = 0; c < W; ++c) f[j][c] = j < rows && c < cols ? p[(int64_t)j * ld + c] : 0.f;
     }
+    // Columns of a bf16 operand: two to a float's place until spread() is called, which waits for them.
+    typedef uint32_t raw __attribute__((ext_vector_type(W / 2)));
+    typedef uint32_t raw_a2 __attribute__((ext_vector_type(W / 2), aligned(2)));
+    __device__ __forceinline__ void request(const uint16_t* p, int64_t ld) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const raw v = *reinterpret_cast<const raw_a2*>(p + (int64_t)j * ld);
+#pragma unroll
+            for (int c = 0; c < W / 2; ++c) f[j][c] = __uint_as_float(v[c]);
+        }
+    }
+    __device__ __forceinline__ void request_short(const uint16_t* p, int64_t ld, int rows, int cols) {
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            uint32_t v[W];
+#pragma unroll
+            for (int c = 0; c < W; ++c) v[c] = j < rows && c < cols ? p[(int64_t)j * ld + c] : 0u;
+#pragma unroll
+            for (int c = 0; c < W / 2; ++c) f[j][c] = __uint_as_float(v[2 * c] | (v[2 * c + 1] << 16));
+        }
+    }
+    __device__ __forceinline__ void spread() {
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+#pragma unroll
+            for (int c = W / 2 - 1; c >= 0; --c) {
+                const uint32_t v = __float_as_uint(f[j][c]);
+                f[j][2 * c + 1] = __uint_as_float(v & 0xffff0000u);
+                f[j][2 * c] = __uint_as_float(v << 16);
+            }
+    }
 };
+
+// Row tiles of a product: with the row of column sums, which a bf16 job keeps in a tile of its own.
+static __host__ __device__ inline uint32_t tn_row_tiles(const GemmTNArgs& g, int T) {
+    return g.A16 ? (uint32_t)((g.Kp + T - 1) / T) + 1u : (uint32_t)((g.Kp + 1 + T - 1) / T);
+}
 
 // The jobs of one launch (by value in the kernel arguments): job j owns the linear block ids [end_block[j-1], end_block[j]).
 struct CutTNLaunch { GemmTNArgs job[NO_MAX_LAYERS]; uint32_t end_block[NO_MAX_LAYERS]; int32_t n; };
@@ -335,16 +371,31 @@ constexpr int tn_shared_bytes(int T) { return 6 * T * SPITCH * 2 > T * (T + 4) *
 // Block `id` of a job: a T x T tile of one product over one slice; 2 x 2 wavefronts. Half of the threads bring a tile of A, the
 // other half one of G, each W = T / 32 columns x eight rows. Column W q + c of a tile stands in LDS row 32 c + q (a
 // wavefront then writes neighbouring rows); the output tile is put back in order on its way through LDS.
-template <int T>
+// BF16: the operands are taken in bf16 instead (the first as it is stored, the others rounded to nearest-even), so there is one
+// plane and one partial product; the bias gradient stays the fp32 column sum, always by a row tile of its own.
+template <int T, bool BF16>
 __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, int R, int used, unsigned char* smem) {
-    constexpr int W = T / 32, Q = 32, PLANE = T * SPITCH, OPITCH = T + 4, I = T / 64;
+    constexpr int W = T / 32, Q = 32, PLANE = T * SPITCH, OPITCH = T + 4, I = T / 64, PLANES = BF16 ? 1 : 3;
     uint16_t* As = reinterpret_cast<uint16_t*>(smem);
-    uint16_t* Gs = As + 3 * PLANE;
-    // in the order of a plain 3-D grid (column tile fastest, then row tile, then problem x slice)
-    const uint32_t gx = (uint32_t)((g.N + T - 1) / T), gy = (uint32_t)((g.Kp + 1 + T - 1) / T);
-    const int bx = (int)(id % gx), by = (int)((id / gx) % gy), bz = (int)(id / (gx * gy));
-    const int prob = bz / used, split = bz % used;
-    if (prob >= g.n_problems) return;
+    uint16_t* Gs = As + PLANES * PLANE;
+    const uint32_t gx = (uint32_t)((g.N + T - 1) / T), gy = (uint32_t)tn_row_tiles(g, T);
+    int bx, by, prob, split;
+    if (BF16) {
+        // These products are bound by their operands' bytes: the tiles of a slice read the same rows, so they get consecutive
+        // logical ids, dealt to the dies in chunks (the job stands first in its launch), and a slice is fetched into one L2.
+        const uint32_t per = gx * gy * (uint32_t)g.n_problems, total = per * (uint32_t)used, padded = (total + N_XCD - 1) / N_XCD * N_XCD;
+        if (id >= padded) return;
+        const uint32_t lid = id % N_XCD * (padded / N_XCD) + id / N_XCD, rem = lid % per;
+        if (lid >= total) return;
+        split = (int)(lid / per);
+        bx = (int)(rem % gx); by = (int)((rem / gx) % gy); prob = (int)(rem / (gx * gy));
+    } else {
+        // in the order of a plain 3-D grid (column tile fastest, then row tile, then problem x slice)
+        const int bz = (int)(id / (gx * gy));
+        bx = (int)(id % gx); by = (int)((id / gx) % gy);
+        prob = bz / used; split = bz % used;
+        if (prob >= g.n_problems) return;
+    }
     int chunk = (R + used - 1) / used;
     chunk = (chunk + SK - 1) / SK * SK;
     const int r0 = split * chunk, r1 = min(R, r0 + chunk);
@@ -381,27 +432,29 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
         return;
     }
     const int wave = tid >> 6, wm = wave >> 1, wn = wave & 1, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
-    floatx16 acc[2][I][I];
+    floatx16 acc[BF16 ? 1 : 2][I][I];
 #pragma unroll
     for (int i = 0; i < I; ++i)
 #pragma unroll
         for (int j = 0; j < I; ++j)
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = acc[1][i][j][r] = 0.f;
+            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = acc[BF16 ? 0 : 1][i][j][r] = 0.f;
     // this thread's W columns and its eight rows of a step
     const bool mine_a = wave < 2;
     const float* src = mine_a ? g.A[prob] : g.G;
+    const bool src16 = BF16 && mine_a && prob == 0;               // (uniform in a wavefront)
     const int64_t ld = mine_a ? g.lda[prob] : g.ldg;
     const int q = tid % Q, k8 = (tid % 128) / Q * 8;
     const int col = (mine_a ? m0 : n0) + q * W, lim = mine_a ? g.Kp : g.N;
-    const int ones = mine_a && prob == 0 ? g.Kp - col : -1;        // which of them is the column of ones, if 0 .. W - 1
-    const bool with_ones = prob == 0 && g.Kp < m0 + T;
+    const int ones = !BF16 && mine_a && prob == 0 ? g.Kp - col : -1;        // which of them is the column of ones, if 0 .. W - 1
+    const bool with_ones = !BF16 && prob == 0 && g.Kp < m0 + T;
     // Columns past the operand are never stored, but must be read inside it: a unit that sticks out is read where it ends with
     // the row and shifted.
     const bool edge = m0 + T > g.Kp || n0 + T > g.N;
     const int col_r = max(0, min(col, lim - W)), sh = col - col_r;
     uint16_t* S = (mine_a ? As : Gs) + q * SPITCH + k8;
     auto store = [&](ColumnUnit<W>& u, int lo, int hi, int shift) {       // rows [lo, hi) of the 32 count
+        if (src16) u.spread();
         if (edge) {
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -428,31 +481,36 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
                 for (int j = 0; j < 8; ++j) f[j] = k8 + j >= lo && k8 + j < hi ? 1.f : 0.f;
             }
-            uint4 p[3];
-            cut8(f, p);
+            if (BF16) {
+                *reinterpret_cast<uint4*>(S + c * Q * SPITCH) =
+                    make_uint4(bf16_pair(f[0], f[1]), bf16_pair(f[2], f[3]), bf16_pair(f[4], f[5]), bf16_pair(f[6], f[7]));
+            } else {
+                uint4 p[3];
+                cut8(f, p);
 #pragma unroll
-            for (int e = 0; e < 3; ++e) *reinterpret_cast<uint4*>(S + e * PLANE + c * Q * SPITCH) = p[e];
+                for (int e = 0; e < 3; ++e) *reinterpret_cast<uint4*>(S + e * PLANE + c * Q * SPITCH) = p[e];
+            }
         }
     };
     auto multiply = [&]() {
 #pragma unroll
         for (int ks = 0; ks < SK / 16; ++ks) {
-            bf16x8_t a[I][3], b[I][3];
+            bf16x8_t a[I][PLANES], b[I][PLANES];
 #pragma unroll
             for (int i = 0; i < I; ++i)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) {
+                for (int p = 0; p < PLANES; ++p) {
                     a[i][p] = cut_fragment(As + p * PLANE + (wm * (T / 2) + i * 32 + l32) * SPITCH + ks * 16 + half * 8);
                     b[i][p] = cut_fragment(Gs + p * PLANE + (wn * (T / 2) + i * 32 + l32) * SPITCH + ks * 16 + half * 8);
                 }
 #pragma unroll
-            for (int t = 0; t < CUT_TERMS; ++t)
+            for (int t = BF16 ? CUT_TERMS - 1 : 0; t < CUT_TERMS; ++t)       // (the last: high x high)
 #pragma unroll
                 for (int i = 0; i < I; ++i)
 #pragma unroll
                     for (int j = 0; j < I; ++j)
-                        acc[CUT_TERM[t].acc][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][CUT_TERM[t].a], b[j][CUT_TERM[t].b],
-                                                                                              acc[CUT_TERM[t].acc][i][j], 0, 0, 0);
+                        acc[BF16 ? 0 : CUT_TERM[t].acc][i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i][CUT_TERM[t].a], b[j][CUT_TERM[t].b],
+                                                                                              acc[BF16 ? 0 : CUT_TERM[t].acc][i][j], 0, 0, 0);
         }
     };
     const int steps = r0 < r1 ? (r1 - r0 + SK - 1) / SK : 0;
@@ -460,7 +518,12 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
         // the last step is moved back to end with the slice, and the rows it shares with the step before it count nothing
         const float* p = src + col_r + (int64_t)k8 * ld;
         ColumnUnit<W> u0, u1;
-        auto request = [&](ColumnUnit<W>& u, int s) { u.request(p + (int64_t)min(r0 + s * SK, r1 - SK) * ld, ld); };
+        const uint16_t* p16 = BF16 ? g.A16 + col_r + (int64_t)k8 * ld : nullptr;
+        auto request = [&](ColumnUnit<W>& u, int s) {
+            const int64_t at = (int64_t)min(r0 + s * SK, r1 - SK) * ld;
+            if (src16) u.request(p16 + at, ld);
+            else u.request(p + at, ld);
+        };
         auto step = [&](ColumnUnit<W>& u, int s) {
             if (s > 0) __syncthreads();
             store(u, max(0, r0 + (s + 1) * SK - r1), SK, sh);
@@ -477,7 +540,10 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     } else {
         ColumnUnit<W> u;
         auto request = [&](int s) {
-            u.request_short(src + col + (int64_t)(r0 + s * SK + k8) * ld, ld, r1 - (r0 + s * SK + k8), lim - col);
+            const int64_t at = col + (int64_t)(r0 + s * SK + k8) * ld;
+            const int rows = r1 - (r0 + s * SK + k8);
+            if (src16) u.request_short(g.A16 + at, ld, rows, lim - col);
+            else u.request_short(src + at, ld, rows, lim - col);
         };
         if (steps > 0) request(0);
         for (int s = 0; s < steps; ++s) {
@@ -498,11 +564,11 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int x = wm * (T / 2) + i * 32 + acc_row(r, lane), y = wn * (T / 2) + j * 32 + l32;
-                Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = acc[1][i][j][r] + acc[0][i][j][r];
+                Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = BF16 ? acc[0][i][j][r] : acc[BF16 ? 0 : 1][i][j][r] + acc[0][i][j][r];
             }
     __syncthreads();
     constexpr int C4 = T / 4;
-    const int rows_out = g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
+    const int rows_out = BF16 ? g.Kp : g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
     const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && n + 4 <= g.N;
 #pragma unroll 4
     for (int lr = tid / C4; lr < T; lr += 256 / C4) {
@@ -521,7 +587,7 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 }
 
 static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) {
-    return (uint32_t)((g.N + T - 1) / T) * (uint32_t)((g.Kp + 1 + T - 1) / T) * (uint32_t)g.n_problems;
+    return (uint32_t)((g.N + T - 1) / T) * tn_row_tiles(g, T) * (uint32_t)g.n_problems;
 }
 
 // A job takes the larger tiles (fewer cuts per product) where they make blocks for most compute units, a function of the batch's row
@@ -537,8 +603,14 @@ __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
     if (R > g.R_cap) R = g.R_cap;
     const int used = tn_used_splits(R, g.splits, g.rows_per_split);      // (the reduction reads the first `used` partials only)
     const uint32_t id = blockIdx.x - first;
-    if (tn_tiles(g, 128) * used >= TN_LARGE_BLOCKS) cut_tn_tile<128>(g, id, R, used, smem);
-    else cut_tn_tile<64>(g, id, R, used, smem);
+    const bool large = tn_tiles(g, 128) * used >= TN_LARGE_BLOCKS;
+    if (g.A16) {
+        if (large) cut_tn_tile<128, true>(g, id, R, used, smem);
+        else cut_tn_tile<64, true>(g, id, R, used, smem);
+    } else {
+        if (large) cut_tn_tile<128, false>(g, id, R, used, smem);
+        else cut_tn_tile<64, false>(g, id, R, used, smem);
+    }
 }
 
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
@@ -551,6 +623,7 @@ int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st,
         const uint64_t small = (uint64_t)tn_tiles(a, 64), large = (uint64_t)tn_tiles(a, 128);
         const uint64_t most_small = std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / large);
         blocks += std::max(small * most_small, large * (uint64_t)a.splits);
+        if (a.A16) blocks = (uint64_t)ceil_div((int64_t)blocks, N_XCD) * N_XCD;
         NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");
         launch.job[launch.n] = a;
         launch.end_block[launch.n] = (uint32_t)blocks;

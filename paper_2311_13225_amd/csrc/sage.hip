@@ -760,28 +760,13 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     ReduceArgs rj[NO_MAX_LAYERS];
     int32_t n_jobs = 0, n_tn = 0;
     rj[n_jobs++] = r;
-    if (!bf) tj[n_tn++] = t;
+    if (bf) t.A16 = bf->x_dense;      // this layer's two products take bf16 operands
+    tj[n_tn++] = t;
     for (int32_t i = 0; pending && i < pending->n && n_jobs < NO_MAX_LAYERS; ++i) { tj[n_tn++] = pending->tn[i]; rj[n_jobs++] = pending->red[i]; }
     if (pending) pending->n = 0;
     hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (bf) {
-        // this layer's two products take bf16 operands (their own launch); the deferred fp32 products of the layers
-        // above go first
-        if (n_tn > 0) {
-            if (prof && prep_stage >= 0) prof->begin(prep_stage);
-            NO_CHECK(gemm_tn_partials(tj, n_tn, st, nullptr, nullptr));
-            if (prof && prep_stage >= 0) prof->end();
-        }
-        GemmBf16TNArgs b{};
-        b.X = bf->x_dense; b.ldx = d_in; b.Mn = mean; b.ldm = d_in; b.G = gz; b.ldg = d_out;
-        b.P = w.partials; b.Kp = d_in; b.N = d_out;
-        b.d_R = t.d_R; b.R_cap = t.R_cap; b.splits = t.splits; b.rows_per_split = t.rows_per_split;
-        if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
-        NO_CHECK(gemm_bf16_tn_partials(b, st, e0, e1));
-    } else {
-        if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
-        NO_CHECK(gemm_tn_partials(tj, n_tn, st, e0, e1));
-    }
+    if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
+    NO_CHECK(gemm_tn_partials(tj, n_tn, st, e0, e1));
     if (prof && reduce_stage >= 0) prof->begin(reduce_stage);
     NO_CHECK(reduce_grads(rj, n_jobs, st, stats_job));
     if (prof && reduce_stage >= 0) prof->end();

@@ -625,6 +625,13 @@ def test_train_steps_three_layers_with_reuse():
     assert run_steps(w, 4, use_cache=True, lr=0.02, bits=64) > 0
 
 
+@pytest.mark.parametrize("feat_dim,hidden", [(1, 16), (3, 64), (5, 33), (70, 129), (128, 256), (130, 300), (258, 300)])
+def test_bf16_weight_gradient_products_at_tile_edges(feat_dim, hidden):
+    """Rows that start on odd halves of a word, fewer columns than a unit, remainders of the 64- and the 128-wide tiles."""
+    w = dataclasses.replace(si.WORKLOADS["tiny"], feat_dtype="bf16", feat_dim=feat_dim, hidden=hidden, staleness=2, hot_fraction=0.1)
+    run_steps(w, 2, True)
+
+
 def test_train_step_single_layer_and_bf16_features():
     import dataclasses
     w1 = dataclasses.replace(si.WORKLOADS["tiny"], fanouts=(6,), batch=200)
