@@ -2,6 +2,8 @@
 inputs. Integer outputs (CSR, sampled blocks, transposes, hot sets, cache versions, gathered
 bytes) must match bit for bit; fp32 activations and gradients must satisfy
 |gpu - ora| <= 1e-4 * |ora| + 1e-4 * max|ora| per tensor."""
+import dataclasses
+
 import numpy as np
 import pytest
 import torch
