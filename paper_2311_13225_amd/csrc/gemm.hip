@@ -638,7 +638,7 @@ int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hip
 int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
     GemmNNArgs a = args;
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
-    if (ceil_div(a.M_cap, 64) * ceil_div(a.N, 64) * a.n_problems <= 128 || a.K[0] < 8) return launch_small_nn(a, true, st, nullptr, nullptr);
+    if (!input_grad_takes_planes(a.M_cap, a.K[0], a.N, a.n_problems)) return launch_small_nn(a, true, st, nullptr, nullptr);
     if (!a.cut_B[0]) {
         const bool one = a.B[1] == a.B[0];
         const size_t each = cut_weights_elements(a.N, a.K[0], true);
@@ -734,18 +734,6 @@ __global__ void __launch_bounds__(256) reduce_grads_kernel(ReduceLaunch launch, 
         const uint32_t u = __float_as_uint(*w);
         const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
         (q == 0 ? a.wt_self : a.wt_neigh)[(int64_t)n * a.Kpad + k] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-    }
-    if (a.cut_bwd[q] && w && !bias_row) {
-        // and its planes for the next step's input gradients (cut_weights' layout, transposed)
-        const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
-        const int64_t plane_b = (int64_t)cut_pad(N) * Kp;
-        float v = *w;
-#pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            const uint32_t h = bf16_pair(v, 0.f) & 0xffffu;
-            v -= __uint_as_float(h << 16);
-            a.cut_bwd[q][p * plane_b + ((int64_t)(n >> 3) * Kp + k) * 8 + (n & 7)] = (uint16_t)h;
-        }
     }
 }
 

@@ -72,6 +72,23 @@ inline size_t cut_weights_elements(int32_t K, int32_t N, bool transposed) {
 }
 // w1 may be NULL; the second matrix's planes follow the first's (cut_weights_elements apart)
 int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st);
+// Whether an input gradient of M_cap x N (reduction over K columns) reads planes: more output tiles than compute units for the
+// kernel for small products to keep busy by splitting the reduction.
+inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
+    return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
+}
+// Matrices cut (transposed) by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
+// blocks [end_block[j-1], end_block[j]) of them.
+struct CutJobs {
+    const float* w[2 * NO_MAX_LAYERS]; uint16_t* out[2 * NO_MAX_LAYERS]; int32_t K[2 * NO_MAX_LAYERS], N[2 * NO_MAX_LAYERS];
+    uint32_t end_block[2 * NO_MAX_LAYERS]; int32_t n = 0;
+    void add(const float* matrix, int32_t rows, int32_t cols, uint16_t* planes) {
+        w[n] = matrix; out[n] = planes; K[n] = rows; N[n] = cols;
+        end_block[n] = blocks() + (uint32_t)ceil_div((int64_t)cut_weights_elements(rows, cols, true) / 24, 256);
+        ++n;
+    }
+    uint32_t blocks() const { return n ? end_block[n - 1] : 0u; }
+};
 inline int32_t bf16_kpad(int32_t K) { return (K + 15) / 16 * 16; }
 int32_t weights_to_bf16_t(const float* w, int32_t K, int32_t N, int32_t Kpad, uint16_t* out, hipStream_t st);
 int32_t gemm_bf16_nn(const GemmBf16NNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
@@ -97,8 +114,6 @@ struct ReduceArgs {
     const int32_t* d_R = nullptr; int32_t R_cap = 0; int32_t rows_per_split = 0;   // as in the product: the slices it used
     // bf16 copies of the two matrices ([N][Kpad], weights_to_bf16_t's layout), rewritten with the updated values (or NULL)
     uint16_t* wt_self = nullptr; uint16_t* wt_neigh = nullptr; int32_t Kpad = 0;
-    // planes of the two transposed matrices for the layer's input gradient, rewritten too (or NULL)
-    uint16_t* cut_bwd[2] = {nullptr, nullptr};
 };
 
 // Weight-gradient work of several layers carried by one product launch and one reduction launch: the gradients of an

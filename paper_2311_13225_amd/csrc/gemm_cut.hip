@@ -14,7 +14,7 @@
 //
 // Bound: 6 bf16 products per term are 416 TFLOP/s of fp32 products against the fp32 instruction's 157; next to them stand
 // the vector instructions that cut the operands (5.5 an element). So an element is cut as few times as possible: weights
-// once per update (or call), into the order in which the matrix cores take them; rows once per 128 output columns.
+// once per step (or call), into the order in which the matrix cores take them; rows once per 128 output columns.
 // Measured, fp32 instruction -> this: input gradient of 60 K x 256 rows by two 256 x 256 matrices 176 -> 108 us, 5.5 K rows 21 -> 16;
 // weight gradients of 25 K rows, 2 x 100 x 256: 47 -> 35 us, of 60 K rows, 2 x 256 x 256: 194 -> 130.
 // (Forward products stay on the fp32 instruction: see gemm.hip.)
@@ -28,25 +28,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
 constexpr int SK = 32;              // reduction indices per step
 constexpr int SPITCH = SK + 8;      // bf16 elements per LDS row: rows start 20 banks apart
-
-// eight values, cut into the three planes (packed in pairs)
-__device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
-    uint32_t h[4], m[4], l[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float a = f[2 * i], b = f[2 * i + 1];
-        h[i] = bf16_pair(a, b);
-        a -= __uint_as_float(h[i] << 16);
-        b -= __uint_as_float(h[i] & 0xffff0000u);
-        m[i] = bf16_pair(a, b);
-        a -= __uint_as_float(m[i] << 16);
-        b -= __uint_as_float(m[i] & 0xffff0000u);
-        l[i] = bf16_pair(a, b);
-    }
-    p[0] = make_uint4(h[0], h[1], h[2], h[3]);
-    p[1] = make_uint4(m[0], m[1], m[2], m[3]);
-    p[2] = make_uint4(l[0], l[1], l[2], l[3]);
-}
 
 __device__ __forceinline__ bf16x8_t cut_fragment(const uint16_t* p) {
     bf16x8_t v;
@@ -66,23 +47,8 @@ __device__ constexpr CutTerm CUT_TERM[CUT_TERMS] = {{2, 0, 0}, {0, 2, 0}, {1, 1,
 // out[matrix][plane][N/8][K][8].
 __global__ void __launch_bounds__(256) cut_weights_kernel(const float* __restrict__ w0, const float* __restrict__ w1, int32_t K, int32_t N,
                                                           int32_t transposed, uint16_t* __restrict__ out, int64_t matrix_stride) {
-    const float* w = blockIdx.y ? w1 : w0;
-    const int32_t R = transposed ? N : K, X = transposed ? K : N;       // reduction indices, columns of the operand
-    const int64_t plane = (int64_t)cut_pad(R) * X;
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= plane / 8) return;
-    const int32_t rb = (int32_t)(i / X), x = (int32_t)(i - (int64_t)rb * X);
-    float f[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int32_t r = rb * 8 + j;
-        f[j] = r < R ? (transposed ? w[(int64_t)x * N + r] : w[(int64_t)r * N + x]) : 0.f;
-    }
-    uint4 p[3];
-    cut8(f, p);
-    uint16_t* o = out + blockIdx.y * matrix_stride + i * 8;
-#pragma unroll
-    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(o + q * plane) = p[q];
+    if (i < matrix_stride / 24) cut_weights_unit(blockIdx.y ? w1 : w0, K, N, transposed != 0, out + blockIdx.y * matrix_stride, i);
 }
 
 int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st) {

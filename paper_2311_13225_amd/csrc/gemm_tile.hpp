@@ -33,6 +33,42 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
     return u;
 }
 
+// Eight values, each cut into three bf16 values (gemm_cut.hip): the three planes (packed in pairs)
+__device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = f[2 * i], b = f[2 * i + 1];
+        h[i] = bf16_pair(a, b);
+        a -= __uint_as_float(h[i] << 16);
+        b -= __uint_as_float(h[i] & 0xffff0000u);
+        m[i] = bf16_pair(a, b);
+        a -= __uint_as_float(m[i] << 16);
+        b -= __uint_as_float(m[i] & 0xffff0000u);
+        l[i] = bf16_pair(a, b);
+    }
+    p[0] = make_uint4(h[0], h[1], h[2], h[3]);
+    p[1] = make_uint4(m[0], m[1], m[2], m[3]);
+    p[2] = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// One unit of a matrix's planes (see cut_weights; i < cut_weights_elements / 24): eight reduction indices of one column.
+__device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int32_t N, bool transposed, uint16_t* out, int64_t i) {
+    const int32_t R = transposed ? N : K, X = transposed ? K : N;       // reduction indices, columns of the operand
+    const int64_t plane = (int64_t)cut_pad(R) * X;
+    const int32_t rb = (int32_t)(i / X), x = (int32_t)(i - (int64_t)rb * X);
+    float f[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int32_t r = rb * 8 + j;
+        f[j] = r < R ? (transposed ? w[(int64_t)x * N + r] : w[(int64_t)r * N + x]) : 0.f;
+    }
+    uint4 p[3];
+    cut8(f, p);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(out + i * 8 + q * plane) = p[q];
+}
+
 // Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

@@ -746,7 +746,6 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     t.rows_per_split = 256;
     ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
     r.d_R = t.d_R; r.R_cap = t.R_cap; r.rows_per_split = t.rows_per_split;
-    for (int q = 0; cut_bwd && q < 2; ++q) r.cut_bwd[q] = cut_bwd[q];
     if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
     if (pending && defer) {
         // an upper layer inside a step: its product and reduction ride on the bottom layer's launches

@@ -2,6 +2,7 @@
 // sample -> gather -> forward -> loss -> backward -> SGD, with hot-vertex embedding reuse
 // (Section 4.1.2): layer-1 rows of reusable hot vertices come from the cache, take no gradient,
 // and every computed hot vertex refreshes its slot with version = step.
+#include "gemm_tile.hpp"
 #include "handles.hpp"
 #include "layers.hpp"
 
@@ -98,7 +99,8 @@ struct no_model_s {
     // caller may have changed them: weights_dirty)
     no::DevBuf<uint16_t> wt1;
     int32_t wt1_kpad = 0;
-    // the matrices of the layers above layer 1 cut for their input gradients (cut_weights), rewritten like wt1
+    // the matrices of the layers above layer 1 cut for their input gradients (cut_weights): made again in every step, by
+    // extra blocks of the loss launch, since a caller may write its parameters at any time between two steps
     no::DevBuf<uint16_t> planes;
     uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
     bool weights_dirty = true;
@@ -161,7 +163,17 @@ namespace no {
 __global__ void __launch_bounds__(256) softmax_xent_kernel(const float* __restrict__ logits, const int32_t* __restrict__ labels,
                                                            const int32_t* __restrict__ seeds, int32_t n, int32_t n_classes,
                                                            float* __restrict__ grad, float* __restrict__ row_loss,
-                                                           int32_t* bad_label_flag, int32_t flag_value) {
+                                                           int32_t* bad_label_flag, int32_t flag_value, CutJobs cut) {
+    const uint32_t own = (uint32_t)(n + 3) / 4;
+    if (blockIdx.x >= own) {
+        uint32_t block = blockIdx.x - own;
+        int j = 0;
+        while (block >= cut.end_block[j]) ++j;
+        if (j > 0) block -= cut.end_block[j - 1];
+        const int64_t i = (int64_t)block * 256 + threadIdx.x;
+        if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], true, cut.out[j], i);
+        return;
+    }
     const int lane = (int)(threadIdx.x & 63);
     const int row = (int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
     if (row >= n) return;
@@ -188,8 +200,6 @@ __global__ void __launch_bounds__(256) softmax_xent_kernel(const float* __restri
     }
     if (lane == 0) row_loss[row] = -(z[y] - mx - logf(s));
 }
-
-static inline unsigned wave_rows_blocks(int64_t rows) { int64_t b = ceil_div(rows, 4); return (unsigned)(b < 1 ? 1 : b); }
 
 }  // namespace no
 
@@ -415,9 +425,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_self, st));
             NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_neigh, st));
         }
-        for (int32_t l = 1; l < L; ++l)
-            NO_CHECK(cut_weights(m->params.p + m->off_w_self[l], m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], true,
-                                 m->cut_bwd[l][0], st));
         m->weights_dirty = false;
     }
     hipEvent_t sev0 = nullptr, sev1 = nullptr;
@@ -577,9 +584,16 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     // loss on the seeds
     const int32_t C = m->dims[L];
     prof.begin(NO_STAGE_LOSS);
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3(wave_rows_blocks(n_seeds)), dim3(256), 0, st, (const float*)m->h[L - 1].p,
-                       d_labels, (const int32_t*)B->seeds.p, n_seeds, C, m->gh[L - 1].p, m->row_loss.p,
-                       B->counts.p + 4 * L + 7, B->call_id);
+    CutJobs cut;
+    for (int32_t l = 1; l < L; ++l) {
+        const int32_t K = m->dims[l], N = m->dims[l + 1];
+        if (!input_grad_takes_planes(view[L - 1 - l].n_dst_cap, N, K, 2)) continue;
+        cut.add(m->params.p + m->off_w_self[l], K, N, m->cut_bwd[l][0]);
+        if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], K, N, m->cut_bwd[l][1]);
+    }
+    hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)ceil_div(n_seeds, 4) + cut.blocks()), dim3(256), 0, st,
+                       (const float*)m->h[L - 1].p, d_labels, (const int32_t*)B->seeds.p, n_seeds, C, m->gh[L - 1].p, m->row_loss.p,
+                       B->counts.p + 4 * L + 7, B->call_id, cut);
     prof.end();
     // (mean loss and block sizes are written by an extra block of the step's last kernel, the layer-1 reduction)
     StatsJob stats_job;

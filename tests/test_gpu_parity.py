@@ -361,6 +361,28 @@ def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     assert torch.isnan(gx[n:]).all()
 
 
+def test_parameters_written_through_kept_views_between_steps():
+    """A caller with an optimiser of its own keeps the views of the parameters and writes them between two steps."""
+    b = nb()
+    V, dims, batch, fanouts = 4000, [24, 256, 250, 16], 1100, [5, 4, 3]
+    src, dst, og, gg = make_graph(V, 40_000, 3, 32)
+    feat, lab = dev(si.features(V, dims[0], 3)), dev(si.labels(V, dims[-1], 3))
+    seeds = dev(si.batch_seeds(si.train_split(V, 0.65, 3), batch, 0))
+
+    def grads_after(*weight_seeds):
+        model = b.no_model_create(gg, dims, batch, fanouts)
+        views = [b.no_model_params(model, l + 1) for l in range(3)]
+        for s in weight_seeds:
+            for three, new in zip(views, si.init_weights(dims, s)):
+                for t, a in zip(three, new):
+                    t.copy_(dev(a))
+            b.no_train_step(model, gg, feat, lab, seeds, None, 0, 3, 0.0)
+        return [t.clone() for l in range(3) for t in b.no_model_grads(model, l + 1)]
+
+    for got, ref in zip(grads_after(1, 2), grads_after(2)):
+        assert torch.equal(got, ref)
+
+
 def test_sage_layer_backward_with_a_popular_source():
     """One source that every destination samples: its transposed segment has several hundred entries (more than the 64
     indices a wavefront reads at a time, and a tail that is no multiple of 16), next to ordinary short segments."""
