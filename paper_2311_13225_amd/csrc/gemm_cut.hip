@@ -9,8 +9,8 @@
 // product has an accumulator of its own, which is therefore rounded once per 16 terms (the fp32 instruction: 8 times).
 // Measured against fp64 on random operands, relative 2-norm error of a weight gradient over 25 K rows / an input gradient over
 // 256 columns: fp32 instruction 3.0e-7 / 2.1e-7, this 1.9e-7 / 1.0e-7 (with one accumulator for all six 3.8e-7 / 2.4e-7).
-// (A value within 2^-9 of the largest fp32 number rounds to infinity in its high part: sums with such terms were about to
-// overflow.)
+// (The middle part of an infinity, or of a value within 2^-9 of the largest fp32 number, is NaN, and so is every output it
+// takes part in: an output that comes out as NaN is summed again from the uncut operands, plain_dot.)
 //
 // Bound: 6 bf16 products per term are 416 TFLOP/s of fp32 products against the fp32 instruction's 157; next to them stand
 // the vector instructions that cut the operands (5.5 an element). So an element is cut as few times as possible: weights
@@ -34,6 +34,15 @@ __device__ __forceinline__ bf16x8_t cut_fragment(const uint16_t* p) {
     __builtin_memcpy(&v, __builtin_assume_aligned(p, 16), 16);
     return v;
 }
+
+// sum a[i lda] b[i ldb] as the fp32 instruction would have it (without b: sum a[i lda])
+__device__ __forceinline__ float plain_dot(const float* a, int64_t lda, const float* b, int64_t ldb, int n) {
+    float s = 0.f;
+#pragma unroll 1
+    for (int i = 0; i < n; ++i) s = fmaf(a[(int64_t)i * lda], b ? b[(int64_t)i * ldb] : 1.f, s);
+    return s;
+}
+__device__ __forceinline__ bool any_nan(const float4& t) { return t.x != t.x || t.y != t.y || t.z != t.z || t.w != t.w; }
 
 // The partial products of one pair of fragments, smallest first, and the accumulator each goes to.
 constexpr int CUT_TERMS = 6;
@@ -71,19 +80,18 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
     constexpr int UNITS = BM >= 64 ? BM / 64 : 1, CW = 32 * NJ, CPITCH = CW + 4;
     constexpr int BYTES = 2 * COPY * 2 > 4 * 32 * CPITCH * 4 ? 2 * COPY * 2 : 4 * 32 * CPITCH * 4;
     __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
-    __shared__ int32_t crow_sh[BM], krow_sh[BM];
     __shared__ float scale_sh[BM];
     uint16_t* As = reinterpret_cast<uint16_t*>(smem);
     int M = *g.d_M;
     if (M > g.M_cap) M = g.M_cap;
     // the grid covers the row capacity; only the tiles of the actual M rows are dealt out to the XCDs
-    const int gx = (g.N + BN - 1) / BN, gy = (M + BM - 1) / BM, gz = g.accumulate ? 1 : g.n_problems;
+    const int gx = (g.N + BN - 1) / BN, gy = (M + BM - 1) / BM, gz = g.n_problems;
     const int64_t total = (int64_t)gx * gy * gz, padded = (total + N_XCD - 1) / N_XCD * N_XCD;
     if ((int64_t)blockIdx.x >= padded) return;
     const int64_t lid = xcd_logical_id(padded);
     if (lid >= total) return;
     const int bx = (int)(lid % gx), by = (int)((lid / gx) % gy), bz = (int)(lid / ((int64_t)gx * gy));
-    const int m0 = by * BM, prob = g.accumulate ? 0 : bz, n_phases = g.accumulate ? g.n_problems : 1;
+    const int m0 = by * BM, prob = bz;
     const int tid = (int)threadIdx.x, wave = tid >> 6, wm = wave / WN, wn = wave % WN;
     const int lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     const int c0 = bx * BN + wn * CW;                  // this wavefront's columns
@@ -98,14 +106,9 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
     // this thread's rows of A (rows past the operand repeat the last one and are never stored)
     const bool loads = BM >= 64 || tid < BM * 4;
     const int kq = (tid & 3) * 8;
-    const float* arow[2][UNITS];
+    const float* arow[UNITS];
 #pragma unroll
-    for (int i = 0; i < UNITS; ++i) {
-        const int m = min(m0 + ((tid + 256 * i) >> 2) % BM, M - 1);
-        arow[0][i] = g.A[prob] + (int64_t)(g.a_rows[prob] ? g.a_rows[prob][m] : m) * g.lda[prob];
-        arow[1][i] = n_phases > 1 ? g.A[1] + (int64_t)(g.a_rows[1] ? g.a_rows[1][m] : m) * g.lda[1] : arow[0][i];
-    }
-    // what the epilogue needs per row
+    for (int i = 0; i < UNITS; ++i) arow[i] = g.A[prob] + (int64_t)min(m0 + ((tid + 256 * i) >> 2) % BM, M - 1) * g.lda[prob];
     if (tid < BM) {
         const int row = min(m0 + tid, M - 1);
         const int32_t* sp = g.row_scale_indptr[prob];
@@ -115,22 +118,15 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
             s = len > 0 ? (g.row_scale_rsqrt ? 1.f / sqrtf((float)len) : 1.f / (float)len) : 0.f;
         }
         scale_sh[tid] = s;
-        crow_sh[tid] = prob == 0 && g.c_rows ? g.c_rows[row] : row;
-        krow_sh[tid] = prob == 0 && g.c_keep_rows ? g.c_keep_rows[row] : -1;
     }
-    const int K0 = g.K[prob], K1 = n_phases > 1 ? g.K[1] : K0, N = g.N;
-    const int steps0 = cut_pad(K0) / SK, steps = steps0 + (n_phases > 1 ? cut_pad(K1) / SK : 0);
+    const int K = g.K[prob], N = g.N, steps = cut_pad(K) / SK;
     RowUnit ta[2][UNITS];
     auto request_a = [&](RowUnit (&t)[UNITS], int s) {      // (past the last step: that one again, not used)
-        const int q = min(s, steps - 1);
-        const bool second = q >= steps0;
 #pragma unroll
-        for (int i = 0; i < UNITS; ++i)
-            t[i].request(second ? arow[1][i] : arow[0][i], (second ? q - steps0 : q) * SK + kq, second ? K1 : K0);
+        for (int i = 0; i < UNITS; ++i) t[i].request(arow[i], min(s, steps - 1) * SK + kq, K);
     };
     auto store_a = [&](RowUnit (&t)[UNITS], int s, uint16_t* S) {
-        const bool second = s >= steps0;
-        const int k0 = (second ? s - steps0 : s) * SK, K = second ? K1 : K0;
+        const int k0 = s * SK;
         if (k0 + SK > K) {
 #pragma unroll
             for (int i = 0; i < UNITS; ++i) t[i].trim(k0 + kq, K);
@@ -146,22 +142,14 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
             }
         }
     };
-    // Fragments of B for step s (two halves of 16 indices) of the flat list: uniform base, this lane's offset within two blocks of eight.
-    int cols[NJ];
+    // Fragments of B for step s (two halves of 16 indices): uniform base, this lane's offset within two blocks of eight.
     uint32_t boff[NJ];
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-        cols[j] = min(c0 + j * 32 + l32, N - 1);
-        boff[j] = (uint32_t)(half * N + cols[j]) * 16u;
-    }
-    const char* const B0 = reinterpret_cast<const char*>(g.cut_B[prob]);
-    const char* const B1 = n_phases > 1 ? reinterpret_cast<const char*>(g.cut_B[1]) : B0;
-    const int64_t plane0 = (int64_t)cut_pad(K0) * N * 2, plane1 = (int64_t)cut_pad(K1) * N * 2;
+    for (int j = 0; j < NJ; ++j) boff[j] = (uint32_t)(half * N + min(c0 + j * 32 + l32, N - 1)) * 16u;
+    const char* const B = reinterpret_cast<const char*>(g.cut_B[prob]);
+    const int64_t plane = (int64_t)cut_pad(K) * N * 2;
     auto request_b = [&](bf16x8_t (&b)[2][NJ][3], int s) {
-        const int q = min(s, steps - 1);
-        const bool second = q >= steps0;
-        const char* base = (second ? B1 : B0) + (int64_t)(second ? q - steps0 : q) * N * 64;
-        const int64_t plane = second ? plane1 : plane0;
+        const char* base = B + (int64_t)min(s, steps - 1) * N * 64;
 #pragma unroll
         for (int p = 0; p < 3; ++p, base += plane)
 #pragma unroll
@@ -210,44 +198,42 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
     const int64_t ldc = g.ldc[prob];
     constexpr int QL = CW / 4, RL = 64 / QL;             // lanes to a row, rows to an instruction
     const int c4 = lane % QL * 4, col = c0 + c4;
-    const bool vec = (ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(C) & 15) == 0) &&
-                     (!(prob == 0 && g.c_keep_rows) || (reinterpret_cast<uintptr_t>(g.c_keep) & 15) == 0) && col + 4 <= g.N;
+    const bool vec = (ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(C) & 15) == 0) && col + 4 <= N;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         if (wave_on) {
 #pragma unroll
-            for (int j = 0; j < NJ; ++j) {
-                const float bias = g.bias ? g.bias[cols[j]] : 0.f;
+            for (int j = 0; j < NJ; ++j)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    float v = acc[1][i][j][r] + acc[0][i][j][r] + bias;
-                    if (g.relu) v = v > 0.f ? v : 0.f;
-                    Ct[acc_row(r, lane) * CPITCH + j * 32 + l32] = v;
-                }
-            }
+                for (int r = 0; r < 16; ++r) Ct[acc_row(r, lane) * CPITCH + j * 32 + l32] = acc[1][i][j][r] + acc[0][i][j][r];
         }
         __syncthreads();
         if (wave_on) {
 #pragma unroll
             for (int q = 0; q < 32 / RL; ++q) {
                 const int lr = q * RL + lane / QL, row = (wm * MI + i) * 32 + lr;
-                if (m0 + row >= M || col >= g.N) continue;
+                if (m0 + row >= M || col >= N) continue;
                 float4 t = *reinterpret_cast<const float4*>(Ct + lr * CPITCH + c4);
+                if (any_nan(t)) {
+                    const float* a = g.A[prob] + (int64_t)(m0 + row) * g.lda[prob];
+                    const float* b = g.B[prob];
+                    const int64_t ldb = g.ldb[prob];
+                    t.x = plain_dot(a, 1, b + col * ldb, 1, K);
+                    t.y = plain_dot(a, 1, b + min(col + 1, N - 1) * ldb, 1, K);
+                    t.z = plain_dot(a, 1, b + min(col + 2, N - 1) * ldb, 1, K);
+                    t.w = plain_dot(a, 1, b + min(col + 3, N - 1) * ldb, 1, K);
+                }
                 const float s = scale_sh[row];
                 t.x *= s; t.y *= s; t.z *= s; t.w *= s;
-                float* dst = C + (int64_t)crow_sh[row] * ldc + col;
-                const int kr = krow_sh[row];
-                float* keep = kr >= 0 ? g.c_keep + (int64_t)kr * ldc + col : nullptr;
+                float* dst = C + (int64_t)(m0 + row) * ldc + col;
                 if (vec) {
                     *reinterpret_cast<float4*>(dst) = t;
-                    if (keep) *reinterpret_cast<float4*>(keep) = t;
                 } else {
                     const float v[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
-                        if (col + e < g.N) { dst[e] = v[e]; if (keep) keep[e] = v[e]; }
+                        if (col + e < N) dst[e] = v[e];
                 }
-                if (keep && col == 0 && g.c_keep_stamp) g.c_keep_stamp[kr] = g.stamp;
             }
         }
         if (i + 1 < MI) __syncthreads();
@@ -257,8 +243,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
 template <int MI, int NJ, int WN, int OCC>
 static void launch_cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     constexpr int BM = 32 * MI * (4 / WN), BN = 32 * NJ * WN;
-    const int64_t z = a.accumulate ? 1 : a.n_problems;
-    dim3 grid(xcd_padded(ceil_div(a.N, BN) * ceil_div(a.M_cap, BM) * z));
+    dim3 grid(xcd_padded(ceil_div(a.N, BN) * ceil_div(a.M_cap, BM) * a.n_problems));
     NO_LAUNCH_TIMED((cut_nn_kernel<MI, NJ, WN, OCC>), grid, dim3(256), st, ev0, ev1, a);
 }
 
@@ -540,7 +525,16 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     for (int lr = tid / C4; lr < T; lr += 256 / C4) {
         const int row = m0 + lr;
         if (row >= rows_out || n >= g.N) continue;
-        const float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
+        float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
+        if (!BF16 && any_nan(t)) {
+            const float* b = row < g.Kp ? g.A[prob] + (int64_t)r0 * g.lda[prob] + row : nullptr;
+            const float* a = g.G + (int64_t)r0 * g.ldg;
+            const int64_t ldb = g.lda[prob];
+            t.x = plain_dot(a + n, g.ldg, b, ldb, r1 - r0);
+            t.y = plain_dot(a + min(n + 1, g.N - 1), g.ldg, b, ldb, r1 - r0);
+            t.z = plain_dot(a + min(n + 2, g.N - 1), g.ldg, b, ldb, r1 - r0);
+            t.w = plain_dot(a + min(n + 3, g.N - 1), g.ldg, b, ldb, r1 - r0);
+        }
         float* dst = P + (int64_t)row * g.N + n;
         if (vec) *reinterpret_cast<float4*>(dst) = t;
         else {

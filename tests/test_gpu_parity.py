@@ -361,6 +361,33 @@ def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     assert torch.isnan(gx[n:]).all()
 
 
+def test_sage_layer_gradient_products_of_infinities_and_the_largest_numbers():
+    """An infinite gradient gives infinite products (NaN where infinities of both signs meet, and there only), one near the end of
+    the fp32 range finite ones, as sums of fp32 products do."""
+    b = nb()
+    rng = np.random.default_rng(5)
+    n, cap, F, d_out = 300, 5000, 100, 64
+    f32 = lambda *s: (rng.standard_normal(s) * 1e-3).astype(np.float32)
+    x, mean, gh, w_self, w_neigh = f32(cap, F), f32(cap, F), f32(cap, d_out), f32(F, d_out), f32(F, d_out)
+    gh[5, 3], gh[40, 9], gh[299, 9], gh[120, 33] = np.inf, -np.inf, np.inf, 3.4e38
+    x[17, 99], mean[200, 0] = 3.4e38, -np.inf
+    i32 = lambda a: dev(np.asarray(a, np.int32))
+    ptr = i32(np.minimum(np.arange(cap + 1), n))
+    blk = b.block_view_from_tensors(i32([n]), i32([n]), ptr, i32(np.arange(cap)), cap, cap, ptr, i32(np.arange(cap)))
+    ws = torch.empty(b.no_sage_layer_ws_bytes(cap, cap, F, d_out), dtype=torch.uint8, device="cuda")
+    gs, gn, gb, gx = (torch.empty(s, device="cuda") for s in ((F, d_out), (F, d_out), (d_out,), (cap, F)))
+    b.no_sage_layer_bwd(blk, dev(x), dev(mean), dev(gh), dev(gh), dev(w_self), dev(w_neigh), False, gs, gn, gb, gx, ws)
+    x, mean, gh = (a[:n].astype(np.float64) for a in (x, mean, gh))
+    ws64, wn64 = w_self.astype(np.float64), w_neigh.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        refs = (x.T @ gh, mean.T @ gh, gh.sum(0), gh @ ws64.T + gh @ wn64.T)
+    for got, ref in zip((gs, gn, gb, gx[:n]), refs):
+        got = got.cpu().numpy()
+        assert np.isfinite(ref).any() and not np.isfinite(ref).all()
+        assert np.array_equal(np.isnan(got), np.isnan(ref))
+        assert np.array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(ref), np.sign(ref), 0))
+
+
 def test_parameters_written_through_kept_views_between_steps():
     """A caller with an optimiser of its own keeps the views of the parameters and writes them between two steps."""
     b = nb()
