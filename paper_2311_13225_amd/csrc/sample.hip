@@ -811,7 +811,9 @@ static bool v1_one_launch(const no_blocks_s* b, unsigned tiles) {
 int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seeds, uint64_t stream_key, uint32_t domain,
                            int32_t n_hops, no_cache_s* cache, int64_t step, no_blocks_s* b, hipStream_t st, bool finish,
                            const SideGather* gather, bool stamp_refresh) {
-    NO_CHECK(blocks_finish(b, st));      // a previous call that was never finished
+    // a previous call that was never finished (an error behind it): its rows are nobody's, and its table may be gone
+    b->rows_pending = SideGather{};
+    NO_CHECK(blocks_finish(b, st));
     b->stamped_cache = nullptr;
     b->call_id = b->call_id % 0x3fffffff + 1;      // flag words written by this call's kernels carry this value
     const int32_t L = b->n_layers;
