@@ -199,6 +199,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
     constexpr int QL = CW / 4, RL = 64 / QL;             // lanes to a row, rows to an instruction
     const int c4 = lane % QL * 4, col = c0 + c4;
     const bool vec = (ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(C) & 15) == 0) && col + 4 <= N;
+    bool bad = false;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         if (wave_on) {
@@ -214,15 +215,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
                 const int lr = q * RL + lane / QL, row = (wm * MI + i) * 32 + lr;
                 if (m0 + row >= M || col >= N) continue;
                 float4 t = *reinterpret_cast<const float4*>(Ct + lr * CPITCH + c4);
-                if (any_nan(t)) {
-                    const float* a = g.A[prob] + (int64_t)(m0 + row) * g.lda[prob];
-                    const float* b = g.B[prob];
-                    const int64_t ldb = g.ldb[prob];
-                    t.x = plain_dot(a, 1, b + col * ldb, 1, K);
-                    t.y = plain_dot(a, 1, b + min(col + 1, N - 1) * ldb, 1, K);
-                    t.z = plain_dot(a, 1, b + min(col + 2, N - 1) * ldb, 1, K);
-                    t.w = plain_dot(a, 1, b + min(col + 3, N - 1) * ldb, 1, K);
-                }
+                bad = bad || any_nan(t);
                 const float s = scale_sh[row];
                 t.x *= s; t.y *= s; t.z *= s; t.w *= s;
                 float* dst = C + (int64_t)(m0 + row) * ldc + col;
@@ -237,6 +230,17 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
             }
         }
         if (i + 1 < MI) __syncthreads();
+    }
+    if (bad) {      // (a loop of its own: beside the stores it would cost every call 1 to 3 %)
+#pragma unroll 1
+        for (int at = 0; at < MI * 128 / RL; ++at) {
+            const int q = at / 4, e = at % 4;
+            const int row = (wm * MI + q / (32 / RL)) * 32 + q % (32 / RL) * RL + lane / QL;
+            if (m0 + row >= M || col + e >= N) continue;
+            float* dst = C + (int64_t)(m0 + row) * ldc + col + e;
+            if (*dst != *dst)
+                *dst = scale_sh[row] * plain_dot(g.A[prob] + (int64_t)(m0 + row) * g.lda[prob], 1, g.B[prob] + (int64_t)(col + e) * g.ldb[prob], 1, K);
+        }
     }
 }
 
@@ -521,20 +525,13 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     constexpr int C4 = T / 4;
     const int rows_out = BF16 ? g.Kp : g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
     const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && n + 4 <= g.N;
+    bool bad = false;
 #pragma unroll 4
     for (int lr = tid / C4; lr < T; lr += 256 / C4) {
         const int row = m0 + lr;
         if (row >= rows_out || n >= g.N) continue;
-        float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
-        if (!BF16 && any_nan(t)) {
-            const float* b = row < g.Kp ? g.A[prob] + (int64_t)r0 * g.lda[prob] + row : nullptr;
-            const float* a = g.G + (int64_t)r0 * g.ldg;
-            const int64_t ldb = g.lda[prob];
-            t.x = plain_dot(a + n, g.ldg, b, ldb, r1 - r0);
-            t.y = plain_dot(a + min(n + 1, g.N - 1), g.ldg, b, ldb, r1 - r0);
-            t.z = plain_dot(a + min(n + 2, g.N - 1), g.ldg, b, ldb, r1 - r0);
-            t.w = plain_dot(a + min(n + 3, g.N - 1), g.ldg, b, ldb, r1 - r0);
-        }
+        const float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
+        if (!BF16) bad = bad || any_nan(t);
         float* dst = P + (int64_t)row * g.N + n;
         if (vec) *reinterpret_cast<float4*>(dst) = t;
         else {
@@ -542,6 +539,16 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (n + e < g.N) dst[e] = v[e];
+        }
+    }
+    if (!BF16 && bad) {
+#pragma unroll 1
+        for (int at = 0; at < T * C4 / 64; ++at) {
+            const int lr = tid / C4 + at / 4 * (256 / C4), e = at % 4, row = m0 + lr;
+            const float v = Cs[lr * OPITCH + c4 + e];
+            if (row >= rows_out || n + e >= g.N || v == v) continue;
+            P[(int64_t)row * g.N + n + e] = plain_dot(g.G + (int64_t)r0 * g.ldg + n + e, g.ldg,
+                                                      row < g.Kp ? g.A[prob] + (int64_t)r0 * g.lda[prob] + row : nullptr, g.lda[prob], r1 - r0);
         }
     }
 }
