@@ -100,9 +100,11 @@ __device__ __forceinline__ void accum_unit(float (&acc)[1], const uint16_t& b) {
 // wavefronts, so a wide row keeps many short independent load chains in flight instead of one long one;
 // the items of a row are consecutive, which keeps the reads of a source row next to each other in time.
 // Up to eight source rows are loaded before the first add; the adds stay in segment order.
+// MASKED: the result goes to masked_out (backward inside a step), a variant of its own because the registers it holds cost the plain
+// form 3 us of the 84 of a layer's forward and backward pass (3.4 K rows, 256 x 256).
 // Side: SideTasks where the launch carries some, else NoSideTasks (the tasks' code costs the widest forms 2 to 34 registers).
-template <typename T, int VEC, bool MEAN, bool WEIGHTED, typename Side>
-__global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const T* __restrict__ src, int64_t ld_src,
+template <typename T, int VEC, bool MEAN, bool WEIGHTED, bool MASKED, typename Side>
+__global__ void __launch_bounds__(256, MEAN ? 1 : WEIGHTED ? 4 : 5) segment_rows_kernel(RowCopyJob job, const T* __restrict__ src, int64_t ld_src,
                                                            const int32_t* __restrict__ seg, const int32_t* __restrict__ idx,
                                                            const int32_t* d_n_rows, int32_t n_rows_cap,
                                                            const int32_t* d_n_init, float* __restrict__ out, int64_t ld_out,
@@ -142,6 +144,17 @@ __global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const
         const int32_t b = seg[row], e = seg[row + 1];
         float scale = MEAN ? (e > b ? 1.f / (float)(e - b) : 0.f) : 1.f;
         const T* col = src + (int64_t)u * VEC;
+        // Backward, the consumer is the layer below: its ReLU decision (its output h, row `row`) is applied and the row placed where
+        // that layer's gradient rows live (out_rows[row], -1 = the row takes no gradient, and nothing of it is read). Both
+        // are asked for before the segment: the kernel is bound by its chain of dependent round trips, which they would make two
+        // longer at the end (step of 4096 seeds, 256 columns: 774 -> 752 us; super-batch with most rows served by the cache: 1477 -> 1437).
+        int64_t masked_row = row;
+        typename RawUnit<float, MASKED ? VEC : 1>::type decision{};
+        if (MASKED) {
+            if (out_rows) masked_row = out_rows[row];
+            if (masked_row < 0) continue;
+            decision = *reinterpret_cast<const decltype(decision)*>(mask_h + row * ld_out + (int64_t)u * VEC);
+        }
         float acc[VEC];
 #pragma unroll
         for (int c = 0; c < VEC; ++c) acc[c] = 0.f;
@@ -257,16 +270,12 @@ __global__ void __launch_bounds__(256) segment_rows_kernel(RowCopyJob job, const
 #pragma unroll
             for (int c = 0; c < VEC; ++c) acc[c] *= ws;
         }
-        if (!MEAN && masked_out) {
-            // the consumer is the layer below: apply its ReLU decision (its output h, row `row`) and place the row
-            // where that layer's gradient rows live (out_rows[row], -1 = the row takes no gradient)
-            const int64_t r = out_rows ? (int64_t)out_rows[row] : row;
-            if (r >= 0) {
-                const float* hm = mask_h + row * ld_out + (int64_t)u * VEC;
-                float* mo = masked_out + r * ld_out + (int64_t)u * VEC;
+        if (MASKED) {
+            float hm[VEC];
+            __builtin_memcpy(hm, &decision, MASKED ? sizeof(hm) : 0);
+            float* mo = masked_out + masked_row * ld_out + (int64_t)u * VEC;
 #pragma unroll
-                for (int c = 0; c < VEC; ++c) mo[c] = hm[c] > 0.f ? acc[c] : 0.f;
-            }
+            for (int c = 0; c < VEC; ++c) mo[c] = hm[c] > 0.f ? acc[c] : 0.f;
             continue;
         }
 #pragma unroll
@@ -298,11 +307,17 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
     }
     const SourceWeights sw = weights ? *weights : SourceWeights{};
     const uint32_t own = (uint32_t)(blocks + copy_blocks);
-    auto launch = [&](auto weighted, const auto& side, uint32_t grid) {
+    auto launch_as = [&](auto weighted, auto masked, const auto& side, uint32_t grid) {
         using Side = std::decay_t<decltype(side)>;
-        NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, decltype(weighted)::value, Side>), dim3(grid), dim3(256), st, ev0, ev1, job, src,
+        NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, decltype(weighted)::value, decltype(masked)::value, Side>), dim3(grid), dim3(256), st, ev0, ev1, job, src,
                         ld_src, seg, idx, d_n, n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask_h, out_rows,
                         masked_out, sw, side);
+    };
+    auto launch = [&](auto weighted, const auto& side, uint32_t grid) {
+        if constexpr (!MEAN) {
+            if (masked_out) { launch_as(weighted, std::true_type{}, side, grid); return; }
+        }
+        launch_as(weighted, std::false_type{}, side, grid);
     };
     if constexpr (MEAN) {
         SideTasks side;
