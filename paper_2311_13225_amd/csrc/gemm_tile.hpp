@@ -69,6 +69,15 @@ __device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int3
     for (int q = 0; q < 3; ++q) *reinterpret_cast<uint4*>(out + i * 8 + q * plane) = p[q];
 }
 
+// Block `block` of the extra blocks that carry these jobs (256 threads).
+__device__ __forceinline__ void run_cut_jobs(const CutJobs& cut, uint32_t block) {
+    int j = 0;
+    while (block >= cut.end_block[j]) ++j;
+    if (j > 0) block -= cut.end_block[j - 1];
+    const int64_t i = (int64_t)block * 256 + threadIdx.x;
+    if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], true, cut.out[j], i);
+}
+
 // Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

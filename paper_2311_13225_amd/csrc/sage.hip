@@ -5,6 +5,7 @@
 // order, no float atomics). The bottom layer needs only the saved mean and the new embedding.
 #include "layers.hpp"
 #include "handles.hpp"
+#include "gemm_tile.hpp"
 #include "side.hpp"
 
 #include <stdlib.h>
@@ -522,12 +523,21 @@ int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_
 // (the computed vertices when hot rows were reused) and applies the activation's derivative in one pass.
 __global__ void mask_rows_kernel(const float* __restrict__ grad_h, const int32_t* __restrict__ rows,
                                  const float* __restrict__ h, const int32_t* d_n, int32_t n_cap, int32_t dim, int32_t relu,
-                                 float* __restrict__ gz) {
+                                 float* __restrict__ gz, uint32_t own_blocks, CutJobs cut) {
+    if (blockIdx.x >= own_blocks) { run_cut_jobs(cut, blockIdx.x - own_blocks); return; }
     int32_t n = *d_n;
     if (n > n_cap) n = n_cap;
     const int64_t total = (int64_t)n * dim;
     int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t stride = (int64_t)own_blocks * blockDim.x;
+    if (!rows && (((uintptr_t)grad_h | (uintptr_t)h | (uintptr_t)gz) & 15) == 0) {      // (relu: without rows and without it there is no launch)
+        const int64_t quads = total / 4;
+        for (int64_t q = i; q < quads; q += stride) {
+            const float4 g = reinterpret_cast<const float4*>(grad_h)[q], v = reinterpret_cast<const float4*>(h)[q];
+            reinterpret_cast<float4*>(gz)[q] = make_float4(v.x > 0.f ? g.x : 0.f, v.y > 0.f ? g.y : 0.f, v.z > 0.f ? g.z : 0.f, v.w > 0.f ? g.w : 0.f);
+        }
+        i += quads * 4;
+    }
     for (; i < total; i += stride) {
         const int64_t r = i / dim, c = i - r * dim;
         const float g = rows ? grad_h[(int64_t)rows[r] * dim + c] : grad_h[i];
@@ -700,9 +710,22 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     if (prof && prep_stage >= 0) prof->begin(prep_stage);
     // gz_in: the layer above already applied this layer's ReLU decision and row selection while it wrote the gradient
     const float* gz = gz_in ? gz_in : grad_h;
+    uint16_t* own_planes[2];
     if (!gz_in && (relu || grad_rows)) {
-        hipLaunchKernelGGL(mask_rows_kernel, dim3(ew_blocks((int64_t)n_cap * d_out)), dim3(256), 0, st, grad_h, grad_rows, h,
-                           blk.d_n_dst, n_cap, d_out, relu, w.gz);
+        // The weights of a large input gradient are cut beside the masking (a launch of their own: 3 us of the 80 of a layer of 3.4 K
+        // rows, 256 x 256), into the partials' place, which is free until this layer's weight gradients.
+        CutJobs cut;
+        const size_t plane = cut_weights_elements(d_in, d_out, true);
+        if (grad_x_src && !cut_bwd && input_grad_takes_planes(n_cap, d_out, d_in, 2) && (gcn ? 1 : 2) * plane * 2 <= w.partials_bytes) {
+            own_planes[0] = (uint16_t*)w.partials;
+            own_planes[1] = own_planes[0] + plane;
+            cut.add(w_self, d_in, d_out, own_planes[0]);
+            if (!gcn) cut.add(w_neigh, d_in, d_out, own_planes[1]);
+            cut_bwd = own_planes;
+        }
+        const uint32_t own = ew_blocks((int64_t)n_cap * d_out);
+        hipLaunchKernelGGL(mask_rows_kernel, dim3(own + cut.blocks()), dim3(256), 0, st, grad_h, grad_rows, h, blk.d_n_dst, n_cap, d_out,
+                           relu, w.gz, own, cut);
         gz = w.gz;
     }
     const float* x_dst = (const float*)x_src;

@@ -166,12 +166,7 @@ __global__ void __launch_bounds__(256) softmax_xent_kernel(const float* __restri
                                                            int32_t* bad_label_flag, int32_t flag_value, CutJobs cut) {
     const uint32_t own = (uint32_t)(n + 3) / 4;
     if (blockIdx.x >= own) {
-        uint32_t block = blockIdx.x - own;
-        int j = 0;
-        while (block >= cut.end_block[j]) ++j;
-        if (j > 0) block -= cut.end_block[j - 1];
-        const int64_t i = (int64_t)block * 256 + threadIdx.x;
-        if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], true, cut.out[j], i);
+        run_cut_jobs(cut, blockIdx.x - own);
         return;
     }
     const int lane = (int)(threadIdx.x & 63);
