@@ -278,7 +278,7 @@ def main():
     n_hit = mean([s_.n_hit for s_ in stats])
     n_v1 = mean([s_.n_v1 for s_ in stats])
     loss_last = stats[-1].loss
-    # Gather: inside the step only the bottom destinations' rows are copied (on the side stream; the aggregation
+    # Gather: inside the step only the bottom destinations' rows are copied (beside the aggregation, which
     # reads the neighbour rows in place), so the step has no gather stage to time. The gather figure is
     # no_gather_features on the FULL source lists of the bottom hop (what an unfused step would collect), rotating
     # over the lists of the last 16 steps and over 16 output buffers so that the rows read and written between two
@@ -332,7 +332,7 @@ def main():
     csc_bytes = lambda h: hop("nnz", h) * 16 if h < L - 1 else 0.0
     sampling_bytes = sum(sample_rows_bytes(h) + relabel_bytes(h) + csc_bytes(h) for h in range(L))
     ms = per_step
-    AGG, FWD, DW = "padded_rows_kernel(mean,l1)", "gemm_nn_kernel(l1 fwd)", "gemm_tn_kernel(l1 dW)"
+    AGG, FWD, DW = "padded_rows_kernel(mean,l1)", "gemm_nn_kernel(l1 fwd)", "cut_tn_kernel(dW, all layers)"
     if args.arch == "gcn_sym":
         AGG = "segment_rows_kernel(sym,l1)"        # per-source weights: through the compacted indices
     kern = {
@@ -346,9 +346,10 @@ def main():
     if bf16_products:
         # Layer 1 on a bf16 table: bf16 operands on the matrix cores. At 16x the fp32 matrix rate these two launches are
         # bound by their operands' bytes: bf16 rows + fp32 mean in, fp32 rows out (and the refreshed cache rows); for the
-        # weight gradients bf16 rows + fp32 mean + fp32 output gradient in, the partial tiles out. Their matrix-core
+        # weight gradients bf16 rows + fp32 mean + fp32 output gradient in, the partial tiles out (the launch, and so its time,
+        # carries the upper layers' fp32 weight gradients too, whose bytes and flops are not counted). Their matrix-core
         # share is reported beside (flops over the bf16 peak).
-        FWD, DW = "gemm_bf16_nn_kernel(l1 fwd)", "gemm_bf16_tn_kernel(l1 dW)"
+        FWD = "gemm_bf16_nn_kernel(l1 fwd)"
         n_refresh = mean([s_.n_refresh for s_ in stats]) if L >= 2 else 0.0
         H1 = w.dims[1]
         fwd_bytes = n_dst_bottom * (F * 2 + F * 4) + n_dst_bottom * H1 * 4 + n_refresh * H1 * 4
@@ -361,7 +362,8 @@ def main():
                      DW: round(l1_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4)}
     else:
         kern[FWD] = ("mfma", gemm_fwd_flops / 1e12 / (ms["gemm_fwd_l1"] / 1e3), MFMA_F32_PEAK_TFLOPS, "TFLOP/s", ms["gemm_fwd_l1"])
-        kern[DW] = ("mfma", gemm_dw_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3), MFMA_F32_PEAK_TFLOPS, "TFLOP/s", ms["gemm_dw_l1"])
+        # (six bf16 products per fp32 one)
+        kern[DW] = ("mfma", gemm_dw_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3), MFMA_BF16_PEAK_TFLOPS / 6, "TFLOP/s", ms["gemm_dw_l1"])
     dominant = max(kern, key=lambda k: kern[k][4])
     bound, achieved, peak, unit, dur = kern[dominant]
     # HBM bytes per launch from rocprofv3 --pmc runs of this workload (FETCH_SIZE + WRITE_SIZE, scaled by a copy of
@@ -399,7 +401,7 @@ def main():
     agg_frac = kern[AGG][1] / HBM_PEAK_GBPS
     extra = {
         # every hop's sampled edges over the whole sampling stage: sampling, relabelling, hot lookup, local indices,
-        # transposes and the wipe of the id map (the measurement pass joins the side stream inside the stage)
+        # transposes and the wipe of the id map (the measurement pass runs them all inside the stage)
         "sampled_edges_per_s": round(nnz_total / (ms["sample"] / 1e3), 1),
         "sampled_edges_per_step": round(nnz_total, 1),
         "sampling_algorithmic_bytes_per_step": round(sampling_bytes, 1),
