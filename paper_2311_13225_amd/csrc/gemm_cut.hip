@@ -2,15 +2,17 @@
 // instruction).
 //
 // Every fp32 operand value is cut into three bf16 values, high + middle + low, each the nearest bf16 of what the ones
-// before it left over: 3 x 8 significand bits hold all 24 of an fp32 number, so nothing of the input is lost. A product of two
-// such sums is nine partial products, each exact in fp32; the six largest are accumulated in fp32 (high x high, high x
-// middle, middle x high, middle x middle, high x low, low x high). The three left out are below 2^-9 2^-18 + 2^-18 2^-9 +
-// 2^-36 < 2^-25.9 of the product, less than a quarter of the 2^-24 by which one fp32 rounding may be off. The largest partial
-// product has an accumulator of its own, which is therefore rounded once per 16 terms (the fp32 instruction: 8 times).
+// before it left over: 3 x 8 significand bits hold all 24 of an fp32 number, so nothing of an input from 2^-110 on is lost. A product of two such sums is nine partial products, each exact in fp32; the six largest are accumulated
+// in fp32 (high x high, high x middle, middle x high, middle x middle, high x low, low x high). With |middle| <= 2^-8 and |low| <= 2^-17
+// of a value, the three left out are at most 2^-24.0 of the product together, what one fp32 rounding may be off (2^-27.5 in the
+// root mean square over random significands). The largest partial product has an accumulator of its own, which is therefore
+// rounded once per 16 terms (the fp32 instruction: 8 times).
 // Measured against fp64 on random operands, relative 2-norm error of a weight gradient over 25 K rows / an input gradient over
 // 256 columns: fp32 instruction 3.0e-7 / 2.1e-7, this 1.9e-7 / 1.0e-7 (with one accumulator for all six 3.8e-7 / 2.4e-7).
-// (The middle part of an infinity, or of a value within 2^-9 of the largest fp32 number, is NaN, and so is every output it
-// takes part in: an output that comes out as NaN is summed again from the uncut operands, plain_dot.)
+//
+// Outputs that do not come out finite (an infinite or NaN operand, one that left the range when it was rounded to its high piece, or a sum that did) are summed again on the fp32 instruction from the uncut operands, by the wavefront that owns them
+// and in the same launch: such an output is what the fp32 instruction makes of it, whatever it is. (Backward pass of a layer of
+// 3.4 K rows, 256 x 256: 48 us; with NaN everywhere 150, with one NaN in the gradient 118. Summed one by one: 2594 and 632.)
 //
 // Bound: 6 bf16 products per term are 416 TFLOP/s of fp32 products against the fp32 instruction's 157; next to them stand
 // the vector instructions that cut the operands (5.5 an element). So an element is cut as few times as possible: weights
@@ -35,14 +37,9 @@ __device__ __forceinline__ bf16x8_t cut_fragment(const uint16_t* p) {
     return v;
 }
 
-// sum a[i lda] b[i ldb] as the fp32 instruction would have it (without b: sum a[i lda])
-__device__ __forceinline__ float plain_dot(const float* a, int64_t lda, const float* b, int64_t ldb, int n) {
-    float s = 0.f;
-#pragma unroll 1
-    for (int i = 0; i < n; ++i) s = fmaf(a[(int64_t)i * lda], b ? b[(int64_t)i * ldb] : 1.f, s);
-    return s;
-}
-__device__ __forceinline__ bool any_nan(const float4& t) { return t.x != t.x || t.y != t.y || t.z != t.z || t.w != t.w; }
+__device__ __forceinline__ bool finite(float v) { return fabsf(v) < INFINITY; }
+// z stays 0 while every value that was added is finite, and is NaN from then on (one instruction a value, no lane mask)
+__device__ __forceinline__ void note_not_finite(float& z, float v) { z = fmaf(v, 0.f, z); }
 
 // The partial products of one pair of fragments, smallest first, and the accumulator each goes to.
 constexpr int CUT_TERMS = 6;
@@ -199,7 +196,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
     constexpr int QL = CW / 4, RL = 64 / QL;             // lanes to a row, rows to an instruction
     const int c4 = lane % QL * 4, col = c0 + c4;
     const bool vec = (ldc % 4 == 0) && ((reinterpret_cast<uintptr_t>(C) & 15) == 0) && col + 4 <= N;
-    bool bad = false;
+    float bad = 0.f;
 #pragma unroll
     for (int i = 0; i < MI; ++i) {
         if (wave_on) {
@@ -215,7 +212,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
                 const int lr = q * RL + lane / QL, row = (wm * MI + i) * 32 + lr;
                 if (m0 + row >= M || col >= N) continue;
                 float4 t = *reinterpret_cast<const float4*>(Ct + lr * CPITCH + c4);
-                bad = bad || any_nan(t);
+                note_not_finite(bad, t.x); note_not_finite(bad, t.y); note_not_finite(bad, t.z); note_not_finite(bad, t.w);
                 const float s = scale_sh[row];
                 t.x *= s; t.y *= s; t.z *= s; t.w *= s;
                 float* dst = C + (int64_t)(m0 + row) * ldc + col;
@@ -231,17 +228,65 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
         }
         if (i + 1 < MI) __syncthreads();
     }
-    if (bad) {      // (a loop of its own: beside the stores it would cost every call 1 to 3 %)
-#pragma unroll 1
-        for (int at = 0; at < MI * 128 / RL; ++at) {
-            const int q = at / 4, e = at % 4;
-            const int row = (wm * MI + q / (32 / RL)) * 32 + q % (32 / RL) * RL + lane / QL;
-            if (m0 + row >= M || col + e >= N) continue;
-            float* dst = C + (int64_t)(m0 + row) * ldc + col + e;
-            if (*dst != *dst)
-                *dst = scale_sh[row] * plain_dot(g.A[prob] + (int64_t)(m0 + row) * g.lda[prob], 1, g.B[prob] + (int64_t)(col + e) * g.ldb[prob], 1, K);
+    if (!__any(bad != 0.f)) return;      // (a loop of its own: beside the stores it would cost every call 1 to 3 %)
+    __threadfence_block();        // (the lanes read each other's stores)
+    // Some output of this wavefront is not finite: its products once more on the fp32 instruction, from memory (a lane brings four
+    // consecutive indices of a row of A and of a column of B, lanes 0-31 the first four of eight, as in gemm_nn_small_kernel).
+    const float *pa[MI], *pb[NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i) pa[i] = g.A[prob] + (int64_t)min(m0 + (wm * MI + i) * 32 + l32, M - 1) * g.lda[prob];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) pb[j] = g.B[prob] + (int64_t)min(c0 + j * 32 + l32, N - 1) * g.ldb[prob];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = 0.f;
+    auto add = [&](const float4 (&a)[MI], const float4 (&b)[NJ]) {
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].x, b[j].x, acc[0][i][j], 0, 0, 0);
+                acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].y, b[j].y, acc[0][i][j], 0, 0, 0);
+                acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].z, b[j].z, acc[0][i][j], 0, 0, 0);
+                acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i].w, b[j].w, acc[0][i][j], 0, 0, 0);
+            }
+    };
+    constexpr int U = 4;      // loads of so many groups of eight indices in flight
+    int k = half * 4;
+    for (; k - half * 4 + 8 * U <= K; k += 8 * U) {
+        float4 a[U][MI], b[U][NJ];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+#pragma unroll
+            for (int i = 0; i < MI; ++i) a[u][i] = load4_fast(pa[i] + k + 8 * u);
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) b[u][j] = load4_fast(pb[j] + k + 8 * u);
         }
+#pragma unroll
+        for (int u = 0; u < U; ++u) add(a[u], b[u]);
     }
+    for (; k - half * 4 < K; k += 8) {
+        float4 a[MI], b[NJ];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) a[i] = load4_guarded(pa[i] + k, K - k);
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) b[j] = load4_guarded(pb[j] + k, K - k);
+        add(a, b);
+    }
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int row = (wm * MI + i) * 32 + acc_row(r, lane), n = c0 + j * 32 + l32;
+                if (m0 + row >= M || n >= N) continue;
+                float* dst = C + (int64_t)(m0 + row) * ldc + n;
+                if (!finite(*dst)) *dst = acc[0][i][j][r] * scale_sh[row];
+            }
 }
 
 template <int MI, int NJ, int WN, int OCC>
@@ -511,6 +556,7 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     }
     // the output tile through LDS, its rows and columns back in order
     float* Cs = reinterpret_cast<float*>(smem);
+    float bad = 0.f;
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < I; ++i)
@@ -519,19 +565,19 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int x = wm * (T / 2) + i * 32 + acc_row(r, lane), y = wn * (T / 2) + j * 32 + l32;
-                Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = BF16 ? acc[0][i][j][r] : acc[BF16 ? 0 : 1][i][j][r] + acc[0][i][j][r];
+                const float v = BF16 ? acc[0][i][j][r] : acc[BF16 ? 0 : 1][i][j][r] + acc[0][i][j][r];
+                Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = v;
+                if (!BF16) note_not_finite(bad, v);
             }
     __syncthreads();
     constexpr int C4 = T / 4;
     const int rows_out = BF16 ? g.Kp : g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
     const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && n + 4 <= g.N;
-    bool bad = false;
 #pragma unroll 4
     for (int lr = tid / C4; lr < T; lr += 256 / C4) {
         const int row = m0 + lr;
         if (row >= rows_out || n >= g.N) continue;
         const float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
-        if (!BF16) bad = bad || any_nan(t);
         float* dst = P + (int64_t)row * g.N + n;
         if (vec) *reinterpret_cast<float4*>(dst) = t;
         else {
@@ -541,16 +587,54 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
                 if (n + e < g.N) dst[e] = v[e];
         }
     }
-    if (!BF16 && bad) {
-#pragma unroll 1
-        for (int at = 0; at < T * C4 / 64; ++at) {
-            const int lr = tid / C4 + at / 4 * (256 / C4), e = at % 4, row = m0 + lr;
-            const float v = Cs[lr * OPITCH + c4 + e];
-            if (row >= rows_out || n + e >= g.N || v == v) continue;
-            P[(int64_t)row * g.N + n + e] = plain_dot(g.G + (int64_t)r0 * g.ldg + n + e, g.ldg,
-                                                      row < g.Kp ? g.A[prob] + (int64_t)r0 * g.lda[prob] + row : nullptr, g.lda[prob], r1 - r0);
-        }
+    if (BF16 || !__any(bad != 0.f)) return;
+    // Some output of this wavefront is not finite: its products once more on the fp32 instruction, from memory (two rows of the
+    // operands at a time, lanes 0-31 the first of them, a column a lane: the one whose LDS row the lane's fragment was).
+    auto column = [](int x) { return x % Q * W + x / Q; };
+    const float *pa[I], *pg[I];
+    bool one[I];
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+        const int m = m0 + column(wm * (T / 2) + i * 32 + l32);
+        one[i] = prob == 0 && m == g.Kp;
+        pa[i] = g.A[prob] + min(m, g.Kp - 1);
+        pg[i] = g.G + min(n0 + column(wn * (T / 2) + i * 32 + l32), g.N - 1);
+#pragma unroll
+        for (int j = 0; j < I; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[0][i][j][r] = 0.f;
     }
+    constexpr int U = 8;      // pairs of rows in flight
+    for (int r = r0; r < r1; r += 2 * U) {
+        float a[U][I], b[U][I];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int at = r + 2 * u + half;
+            const bool in = at < r1;
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                const float va = pa[i][(int64_t)min(at, r1 - 1) * g.lda[prob]], vb = pg[i][(int64_t)min(at, r1 - 1) * g.ldg];
+                a[u][i] = in ? (one[i] ? 1.f : va) : 0.f;
+                b[u][i] = in ? vb : 0.f;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int i = 0; i < I; ++i)
+#pragma unroll
+                for (int j = 0; j < I; ++j) acc[0][i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u][i], b[u][j], acc[0][i][j], 0, 0, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < I; ++i)
+#pragma unroll
+        for (int j = 0; j < I; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int x = column(wm * (T / 2) + i * 32 + acc_row(r, lane)), y = column(wn * (T / 2) + j * 32 + l32);
+                if (m0 + x >= rows_out || n0 + y >= g.N || finite(Cs[x * OPITCH + y])) continue;
+                P[(int64_t)(m0 + x) * g.N + n0 + y] = acc[0][i][j][r];
+            }
 }
 
 static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) {
