@@ -2,7 +2,8 @@
 // instruction).
 //
 // Every fp32 operand value is cut into three bf16 values, high + middle + low, each the nearest bf16 of what the ones
-// before it left over: 3 x 8 significand bits hold all 24 of an fp32 number, so nothing of an input from 2^-110 on is lost. A product of two such sums is nine partial products, each exact in fp32; the six largest are accumulated
+// before it left over: 3 x 8 significand bits hold all 24 of an fp32 number, so nothing of a finite input is lost (at the ends of the
+// range either: CUT_SCALE). A product of two such sums is nine partial products, each exact in fp32; the six largest are accumulated
 // in fp32 (high x high, high x middle, middle x high, middle x middle, high x low, low x high). With |middle| <= 2^-8 and |low| <= 2^-17
 // of a value, the three left out are at most 2^-24.0 of the product together, what one fp32 rounding may be off (2^-27.5 in the
 // root mean square over random significands). The largest partial product has an accumulator of its own, which is therefore
@@ -10,7 +11,8 @@
 // Measured against fp64 on random operands, relative 2-norm error of a weight gradient over 25 K rows / an input gradient over
 // 256 columns: fp32 instruction 3.0e-7 / 2.1e-7, this 1.9e-7 / 1.0e-7 (with one accumulator for all six 3.8e-7 / 2.4e-7).
 //
-// Outputs that do not come out finite (an infinite or NaN operand, one that left the range when it was rounded to its high piece, or a sum that did) are summed again on the fp32 instruction from the uncut operands, by the wavefront that owns them
+// Outputs that do not come out finite (an infinite or NaN operand, one that left the range when it was scaled or rounded to its high
+// piece, or a sum that did) are summed again on the fp32 instruction from the uncut operands, by the wavefront that owns them
 // and in the same launch: such an output is what the fp32 instruction makes of it, whatever it is. (Backward pass of a layer of
 // 3.4 K rows, 256 x 256: 48 us; with NaN everywhere 150, with one NaN in the gradient 118. Summed one by one: 2594 and 632.)
 //
@@ -114,7 +116,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
             const int len = sp[row + 1] - sp[row] + g.row_scale_plus;
             s = len > 0 ? (g.row_scale_rsqrt ? 1.f / sqrtf((float)len) : 1.f / (float)len) : 0.f;
         }
-        scale_sh[tid] = s;
+        scale_sh[tid] = s * CUT_UNSCALE;
     }
     const int K = g.K[prob], N = g.N, steps = cut_pad(K) / SK;
     RowUnit ta[2][UNITS];
@@ -285,7 +287,7 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
                 const int row = (wm * MI + i) * 32 + acc_row(r, lane), n = c0 + j * 32 + l32;
                 if (m0 + row >= M || n >= N) continue;
                 float* dst = C + (int64_t)(m0 + row) * ldc + n;
-                if (!finite(*dst)) *dst = acc[0][i][j][r] * scale_sh[row];
+                if (!finite(*dst)) *dst = acc[0][i][j][r] * (scale_sh[row] * (1.f / CUT_UNSCALE));
             }
 }
 
@@ -565,7 +567,7 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int x = wm * (T / 2) + i * 32 + acc_row(r, lane), y = wn * (T / 2) + j * 32 + l32;
-                const float v = BF16 ? acc[0][i][j][r] : acc[BF16 ? 0 : 1][i][j][r] + acc[0][i][j][r];
+                const float v = BF16 ? acc[0][i][j][r] : (acc[BF16 ? 0 : 1][i][j][r] + acc[0][i][j][r]) * CUT_UNSCALE;
                 Cs[(x % Q * W + x / Q) * OPITCH + y % Q * W + y / Q] = v;
                 if (!BF16) note_not_finite(bad, v);
             }

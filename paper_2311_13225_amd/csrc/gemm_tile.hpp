@@ -33,12 +33,17 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
     return u;
 }
 
+// Operands are cut at 2^24 times their size, and the sums brought back (exactly) by 2^-48: the last bit of the smallest fp32 number,
+// 2^-149, is then no smaller than the smallest normal bf16 number, so that no piece of any finite operand is lost below the range.
+// (An operand from 2^104 or a sum from 2^79 on leaves it at the top: gemm_cut.hip sums those outputs on the fp32 instruction.)
+constexpr float CUT_SCALE = 16777216.f, CUT_UNSCALE = 1.f / (CUT_SCALE * CUT_SCALE);
+
 // Eight values, each cut into three bf16 values (gemm_cut.hip): the three planes (packed in pairs)
 __device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
     uint32_t h[4], m[4], l[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-        float a = f[2 * i], b = f[2 * i + 1];
+        float a = f[2 * i] * CUT_SCALE, b = f[2 * i + 1] * CUT_SCALE;
         h[i] = bf16_pair(a, b);
         a -= __uint_as_float(h[i] << 16);
         b -= __uint_as_float(h[i] & 0xffff0000u);

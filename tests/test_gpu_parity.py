@@ -388,6 +388,29 @@ def test_sage_layer_gradient_products_of_infinities_and_the_largest_numbers():
         assert np.array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(ref), np.sign(ref), 0))
 
 
+@pytest.mark.parametrize("e_rows,e_grad", [(-116, 0), (-124, 0), (0, -132), (-145, 60), (10, -147), (60, 58), (110, -20)])
+def test_sage_layer_gradient_products_at_the_ends_of_the_range(e_rows, e_grad):
+    """Operands around 2^e (down to subnormal ones) whose results are ordinary numbers, against exact sums of them: the bound of
+    test_sage_layer_gradient_products_at_tile_edges, which does not depend on where the operands lie. n = 70 rows keep it tight."""
+    b = nb()
+    rng = np.random.default_rng(7)
+    n, cap, F, d_out = 70, 5000, 100, 64
+    f32 = lambda e, *s: (rng.standard_normal(s) * 2.0 ** e).astype(np.float32)
+    x, mean, gh, w_self, w_neigh = f32(e_rows, cap, F), f32(e_rows, cap, F), f32(e_grad, cap, d_out), f32(e_rows, F, d_out), f32(e_rows, F, d_out)
+    i32 = lambda a: dev(np.asarray(a, np.int32))
+    ptr = i32(np.minimum(np.arange(cap + 1), n))
+    blk = b.block_view_from_tensors(i32([n]), i32([n]), ptr, i32(np.arange(cap)), cap, cap, ptr, i32(np.arange(cap)))
+    ws = torch.empty(b.no_sage_layer_ws_bytes(cap, cap, F, d_out), dtype=torch.uint8, device="cuda")
+    gs, gn, gb, gx = (torch.full(s, float("nan"), device="cuda") for s in ((F, d_out), (F, d_out), (d_out,), (cap, F)))
+    b.no_sage_layer_bwd(blk, dev(x), dev(mean), dev(gh), dev(gh), dev(w_self), dev(w_neigh), False, gs, gn, gb, gx, ws)
+    x, mean, gh = (a[:n].astype(np.float64) for a in (x, mean, gh))
+    w = w_self.astype(np.float64) + w_neigh.astype(np.float64)
+    w_abs = np.abs(w_self).astype(np.float64) + np.abs(w_neigh)
+    for got, ref, mag, terms in ((gs, x.T @ gh, np.abs(x).T @ np.abs(gh), n), (gn, mean.T @ gh, np.abs(mean).T @ np.abs(gh), n),
+                                 (gb, gh.sum(0), np.abs(gh).sum(0), n), (gx[:n], gh @ w.T, np.abs(gh) @ w_abs.T, 2 * d_out)):
+        assert (np.abs(got.cpu().numpy() - ref) <= (terms + 8) * 2.0 ** -24 * mag).all()
+
+
 def test_sage_layer_gradient_products_that_end_just_inside_the_range():
     """Products of two finite numbers that stay below the largest one are finite, though their operands round up to a product above it."""
     b = nb()
