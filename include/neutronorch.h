@@ -285,7 +285,9 @@ typedef struct no_step_stats {
 } no_step_stats;
 
 /* dims = [F, hidden.., C] (n_layers+1 entries). Weights live inside the handle; the caller
- * fills them through no_model_params before the first step. */
+ * fills them through no_model_params before the first step. A caller that writes layer 1's parameters of a model on a
+ * bf16 feature table between two steps calls no_model_params for a layer again before the next one (the returned
+ * pointers never change): layer 1's products read bf16 copies of its matrices, which that call marks as out of date. */
 int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t* h_dims, int32_t n_seeds_cap,
                         const int32_t* h_fanouts, no_dtype feat_dtype, no_model_t* out);
 int32_t no_model_params(no_model_t m, int32_t layer /*1-based*/, float** d_w_self, float** d_w_neigh,

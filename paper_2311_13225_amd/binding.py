@@ -463,7 +463,8 @@ def _three(fn, m: Model, layer: int):
 
 
 def no_model_params(m: Model, layer: int):
-    """(w_self, w_neigh, bias) tensor views of layer `layer` (1-based); write initial values into them."""
+    """(w_self, w_neigh, bias) tensor views of layer `layer` (1-based); write initial values into them. After writing layer 1's of a
+    model on a bf16 table between two steps, call this again before the next one."""
     return _three(lib().no_model_params, m, layer)
 
 

@@ -95,12 +95,12 @@ struct no_model_s {
     size_t n_params = 0;
     no::DevBuf<char> x0;                             // gathered rows of the bottom hop's destinations [n_dst_cap, F]
     // bf16 tables with GraphSAGE-mean layers: layer 1's products take bf16 operands; its two matrices as bf16 copies
-    // [2][d_1][Kpad] in the product's layout, rewritten by every step's update (and from the parameters when the
-    // caller may have changed them: weights_dirty)
+    // [2][d_1][Kpad] in the product's layout, rewritten by the update of every step that reads them (and from the parameters when
+    // they may not match them: weights_dirty, raised by no_model_params, through which a caller writes, and by a change of form)
     no::DevBuf<uint16_t> wt1;
     int32_t wt1_kpad = 0;
     // the matrices of the layers above layer 1 cut for their input gradients (cut_weights): made again in every step, by
-    // extra blocks of the loss launch, since a caller may write its parameters at any time between two steps
+    // extra blocks of the loss launch, so that no copy of them outlives a step
     no::DevBuf<uint16_t> planes;
     uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
     bool weights_dirty = true;
@@ -290,6 +290,7 @@ extern "C" int32_t no_model_set_arch(no_model_t m, no_arch arch) {
     NO_REQUIRE(m != nullptr, NO_ERR_INVALID_ARG, "no_model_set_arch: model is NULL");
     NO_REQUIRE(arch == NO_ARCH_SAGE_MEAN || arch_is_gcn(arch), NO_ERR_INVALID_ARG, "no_model_set_arch: unknown layer form");
     m->arch = arch;
+    m->weights_dirty = true;      // steps of another form do not rewrite layer 1's bf16 copies
     // the symmetric normalisation needs the number of edges that leave each source, in the bottom hop too
     m->blocks->count_sources = arch == NO_ARCH_GCN_SYM;
     if (m->blocks_alt) m->blocks_alt->count_sources = arch == NO_ARCH_GCN_SYM;
@@ -415,11 +416,9 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
     uint16_t* wt_self = m->wt1.p;
     uint16_t* wt_neigh = m->wt1.p ? m->wt1.p + (size_t)m->dims[1] * m->wt1_kpad : nullptr;
-    if (m->weights_dirty) {
-        if (bf16_products) {
-            NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_self, st));
-            NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_neigh, st));
-        }
+    if (bf16_products && m->weights_dirty) {
+        NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_self, st));
+        NO_CHECK(weights_to_bf16_t(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->wt1_kpad, wt_neigh, st));
         m->weights_dirty = false;
     }
     hipEvent_t sev0 = nullptr, sev1 = nullptr;

@@ -463,26 +463,64 @@ def test_sage_layer_gradients_of_a_diverged_run_keep_their_pace():
     assert diverged < 10 * ordinary
 
 
-def test_parameters_written_through_kept_views_between_steps():
-    """A caller with an optimiser of its own keeps the views of the parameters and writes them between two steps."""
+@pytest.mark.parametrize("bf16", [False, True])
+def test_parameters_written_through_kept_views_between_steps(bf16):
+    """A caller with an optimiser of its own keeps the views of the parameters and writes them between two steps (and says so by
+    asking for them again, which layer 1's copies on a bf16 table need)."""
     b = nb()
     V, dims, batch, fanouts = 4000, [24, 256, 250, 16], 1100, [5, 4, 3]
     src, dst, og, gg = make_graph(V, 40_000, 3, 32)
-    feat, lab = dev(si.features(V, dims[0], 3)), dev(si.labels(V, dims[-1], 3))
+    feat = si.features(V, dims[0], 3, "bf16" if bf16 else "f32")
+    feat, lab = dev(feat.view(np.int16) if bf16 else feat), dev(si.labels(V, dims[-1], 3))
     seeds = dev(si.batch_seeds(si.train_split(V, 0.65, 3), batch, 0))
 
     def grads_after(*weight_seeds):
-        model = b.no_model_create(gg, dims, batch, fanouts)
+        model = b.no_model_create(gg, dims, batch, fanouts, b.NO_BF16 if bf16 else b.NO_F32)
         views = [b.no_model_params(model, l + 1) for l in range(3)]
         for s in weight_seeds:
             for three, new in zip(views, si.init_weights(dims, s)):
                 for t, a in zip(three, new):
                     t.copy_(dev(a))
+            if bf16:
+                b.no_model_params(model, 1)
             b.no_train_step(model, gg, feat, lab, seeds, None, 0, 3, 0.0)
         return [t.clone() for l in range(3) for t in b.no_model_grads(model, l + 1)]
 
     for got, ref in zip(grads_after(1, 2), grads_after(2)):
         assert torch.equal(got, ref)
+
+
+def test_layer_form_changed_between_steps_on_a_bf16_table():
+    """Layer 1's bf16 copies of its matrices belong to GraphSAGE-mean steps: the first of them after steps of another form makes them
+    from the parameters as those left them."""
+    b = nb()
+    V, dims, batch, fanouts, lr = 3000, [40, 64, 16], 200, [5, 4], 0.1
+    src, dst, og, gg = make_graph(V, 30_000, 3, 32)
+    feat, lab = dev(si.features(V, dims[0], 3, "bf16").view(np.int16)), dev(si.labels(V, dims[-1], 3))
+    seeds = dev(si.batch_seeds(si.train_split(V, 0.65, 3), batch, 0))
+    weights = si.init_weights(dims, 3)
+
+    def new_model(values):
+        model = b.no_model_create(gg, dims, batch, fanouts, b.NO_BF16)
+        for l in range(2):
+            for t, a in zip(b.no_model_params(model, l + 1), values[l]):
+                t.copy_(a if torch.is_tensor(a) else dev(a))
+        return model
+
+    def step(model, form):
+        b.no_model_set_arch(model, form)
+        b.no_train_step(model, gg, feat, lab, seeds, None, 0, 3, lr)
+        return [t.clone() for l in range(2) for t in b.no_model_grads(model, l + 1)]
+
+    views = lambda model: [b.no_model_params(model, l + 1) for l in range(2)]
+    for forms in ((b.NO_ARCH_GCN,), (b.NO_ARCH_SAGE_MEAN, b.NO_ARCH_GCN)):
+        ran, still = new_model(weights), new_model(weights)
+        for form in forms:
+            step(ran, form)
+            step(still, form)
+        still = new_model(views(still))               # the same parameters, and no copies yet
+        for got, ref in zip(step(ran, b.NO_ARCH_SAGE_MEAN), step(still, b.NO_ARCH_SAGE_MEAN)):
+            assert torch.equal(got, ref)
 
 
 def test_sage_layer_backward_with_a_popular_source():
