@@ -389,6 +389,8 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                 aggregated = true;
             }
         } else {
+            // (its rows, not copied yet where an error ended the call that prepared it, are nobody's, and their table may be gone)
+            m->blocks_alt->rows_pending = SideGather{};
             NO_CHECK(blocks_finish(m->blocks_alt, st));
             NO_CHECK(blocks_unstamp(m->blocks_alt, st));      // the batch prepared ahead is not the one asked for
         }

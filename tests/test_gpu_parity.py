@@ -1067,6 +1067,36 @@ def test_sampling_ahead_dropped_when_not_consumed():
     assert np.array_equal(caches[2][0][untouched], caches[0][0][untouched])
 
 
+def test_batch_prepared_ahead_and_dropped_after_an_error_copies_no_rows():
+    """A call that ends in an error may leave a batch sampled ahead whose destination rows are not copied yet. The call that drops it
+    must not copy them late: the table they come from may be gone."""
+    b = nb()
+    w = si.WORKLOADS["tiny"]
+    src, dst, og, gg = make_graph(w.n_vertices, w.n_edges, w.seed, 32)
+    train = si.train_split(w.n_vertices, 0.65, w.seed)
+    lab = dev(si.labels(w.n_vertices, w.n_classes, w.seed))
+    model = b.no_model_create(gg, w.dims, w.batch, w.fanouts)
+    for l in range(w.n_layers):
+        for t in b.no_model_params(model, l + 1):
+            t.zero_()
+    seeds = [dev(si.batch_seeds(train, w.batch, t)) for t in range(4)]
+    one = seeds[3][:1].clone()
+    table, other = (torch.full((w.n_vertices, w.feat_dim), v, device="cuda") for v in (1.0, 3.0))
+    n_rows = b.no_train_step_ahead(model, gg, table, lab, seeds[0], seeds[1], False, None, 0, 7, 0.0).n_dst[-1 + w.n_layers]
+    torch.cuda.synchronize()
+    table.fill_(2.0)                              # (the rows of batches 0 and 1 are copied)
+    # an error of the caller's, not asked for yet, is what the step's first check of a launch finds: batch 2 is left sampled
+    assert b.lib().hipSetDevice(1 << 20) != 0
+    with pytest.raises(b.NoError) as ei:
+        b.no_train_step_ahead(model, gg, table, lab, seeds[1], seeds[2], False, None, 1, 7, 0.0)
+    assert ei.value.code == -5
+    b.no_train_step(model, gg, other, lab, seeds[0], None, 2, 7, 0.0)                               # drops it
+    b.no_train_step_ahead(model, gg, other, lab, seeds[0], one, False, None, 3, 7, 0.0)             # one seed: few rows, written over
+    few = b.no_train_step(model, gg, other, lab, one, None, 4, 7, 0.0).n_dst[-1 + w.n_layers]      # the first rows of batch 0's copy
+    rows = b.no_model_gathered(model, n_rows // 2)
+    assert few < n_rows // 2 and (rows[:few] == 3.0).all() and (rows[few:] == 1.0).all()
+
+
 def test_cache_invalidate_and_set_staleness():
     b = nb()
     import dataclasses
