@@ -16,7 +16,7 @@ namespace no {
 // Per-hop device arrays of a sampled block. Scalars live in `counts` of the owning handle.
 struct HopBuffers {
     int32_t fanout = 0;
-    int32_t n_dst_cap = 0, n_src_cap = 0, nnz_cap = 0;
+    int32_t n_dst_cap = 0, n_src_cap = 0, nnz_cap = 0;      // (past V by n_seeds_cap: seeds that are not different vertices)
     bool has_csc = false;
     const int32_t* d_dst = nullptr;     // alias: seeds copy, previous hop's src_global, or compute list
     const int32_t* d_n_dst = nullptr;   // alias into counts

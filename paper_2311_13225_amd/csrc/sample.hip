@@ -922,9 +922,12 @@ int32_t blocks_create_impl(no_graph_s* g, int32_t n_seeds_cap, const int32_t* fa
     int64_t max_pad = 1, max_src = 1;
     for (int32_t h = 0; h < n_layers; ++h) {
         HopBuffers& H = b->hop[h];
-        int64_t nnz_cap = dst_cap * fanouts[h];
-        int64_t src_cap = dst_cap + nnz_cap;
-        if (src_cap > g->n_vertices) src_cap = g->n_vertices;
+        // Different vertices are V at most, but seeds that are not different ones (several outside [0, V), all read as vertex 0) keep
+        // their places among the sources of every hop. (Where 32 bits number no more slots than those of V destinations there is no
+        // such room.)
+        if (dst_cap > g->n_vertices && dst_cap * (fanouts[h] + 1) >= (1ll << 31) - 1) dst_cap = g->n_vertices;
+        const int64_t nnz_cap = dst_cap * fanouts[h];
+        const int64_t src_cap = std::min(dst_cap + nnz_cap, g->n_vertices + n_seeds_cap);
         NO_REQUIRE(nnz_cap + dst_cap < (1ll << 31) - 1, NO_ERR_OVERFLOW, "blocks: hop %d capacity exceeds int32", h);
         H.fanout = fanouts[h];
         H.n_dst_cap = (int32_t)dst_cap;
@@ -1048,6 +1051,13 @@ extern "C" int32_t no_blocks_view(no_blocks_t blocks, int32_t hop, no_block_view
     NO_REQUIRE(blocks && out, NO_ERR_INVALID_ARG, "no_blocks_view: NULL argument");
     NO_REQUIRE(hop >= 0 && hop < blocks->n_layers, NO_ERR_INVALID_ARG, "no_blocks_view: hop out of range");
     fill_block_view(blocks, hop, out);
+    // the capacities for unique seeds (the arrays have room for others: blocks_create_impl)
+    const int32_t V = (int32_t)blocks->n_vertices;
+    if (out->n_dst_cap > V) {
+        out->nnz_cap = V * blocks->hop[hop].fanout;
+        out->n_dst_cap = V;
+    }
+    out->n_src_cap = std::min(out->n_src_cap, V);
     return NO_OK;
 }
 

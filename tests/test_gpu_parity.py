@@ -1171,6 +1171,50 @@ def test_out_of_range_seed_is_flagged_not_followed():
         assert ei.value.code == -2
 
 
+@pytest.mark.parametrize("arch", ["sage", "gcn_sym"])
+def test_seeds_that_are_not_different_vertices_stay_inside_the_arrays(arch):
+    """Seeds outside [0, V) are all read as vertex 0, so that a batch may list more sources than the graph has vertices. Every array has
+    room for them: the blocks agree with themselves, the step is flagged, and the next good batch is what it always is."""
+    b = nb()
+    V, batch, fanouts, dims = 1000, 1000, (10, 10, 5), [24, 32, 32, 8]
+    src, dst, og, gg = make_graph(V, 30_000, 3, 32)
+    order = np.random.default_rng(3).permutation(V).astype(np.int32)
+    bad = order.copy()
+    bad[::2] = V + 5
+    blocks = b.no_blocks_create(gg, batch, fanouts)
+    b.no_sample_blocks(gg, dev(bad), 1, 0, None, blocks)
+    sizes = np.zeros((len(fanouts), 4), np.int32)
+    assert b.lib().no_blocks_sizes(blocks.h, None, sizes.ctypes.data_as(b.C.POINTER(b.C.c_int32))) == -2
+    assert sizes[:, 1].max() > V
+    for h in range(len(fanouts)):
+        a = b.block_arrays(blocks, h, sizes)
+        new = a["src_global"][sizes[h, 0]:]
+        assert len(np.unique(new)) == len(new) and new.min() >= 0 and new.max() < V
+        assert np.array_equal(a["nbr_global"], a["src_global"][a["indices"]])
+        if h < len(fanouts) - 1:
+            e = a["csc_eid"]
+            assert np.array_equal(np.sort(e), np.arange(len(e))) and (np.diff(a["indices"][e]) >= 0).all()
+    good = order[:300]
+    b.no_sample_blocks(gg, dev(good), 1, 1, None, blocks)
+    compare_blocks(b, blocks, ora.sample_blocks(og, good, fanouts, 1, 1))
+
+    feat, lab, train = dev(si.features(V, dims[0], 3)), dev(si.labels(V, dims[-1], 3)), dev(order)
+    grads = []
+    for batches in ((bad, good), (good,)):
+        gc = b.no_select_hot(gg, train, 100, fanouts, 1, 0.3, 0, dims[1], 3)
+        model = b.no_model_create(gg, dims, batch, fanouts)
+        b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
+        for l in range(3):
+            for t, a in zip(b.no_model_params(model, l + 1), si.init_weights(dims, 3)[l]):
+                t.copy_(dev(a))
+        for ids in batches:
+            st = b.no_train_step(model, gg, feat, lab, dev(ids), gc, 5, 3, 0.0)
+            assert st.bad_seed == int(ids is bad)
+            b.no_cache_invalidate(gc)
+        grads.append([t.clone() for l in range(3) for t in b.no_model_grads(model, l + 1)])
+    assert all(torch.equal(x, y) for x, y in zip(*grads))
+
+
 def test_step_statistics_account_for_every_vertex_of_v1():
     """The statistics block of a step: hits, hot misses and cold vertices add up to |V^1|; bytes gathered are the
     bottom hop's distinct source rows and the reused layer-1 rows (Section 4.2, Stage 3 moves exactly these)."""
