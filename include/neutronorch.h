@@ -147,7 +147,7 @@ int32_t no_blocks_destroy(no_blocks_t blocks);
 
 /* Pre-sampling hotness: the train ids, in the given order, are cut into batches of `batch`;
  * for presample_epochs epochs every batch is sampled for hops 0..n_layers-2 (Philox domain 1,
- * stream seed + epoch*n_batches + b) and each vertex of the resulting V^1 counts once. The hot
+ * stream seed + epoch*n_batches + b) and each vertex of the resulting V^1 counts once (a train id may be repeated). The hot
  * set is the floor(hot_fraction * V) most frequent vertices, ties by ascending id; slot = rank.
  * Creates an empty cache [n_hot, emb_dim] fp32 (versions -1). Synchronises the stream. A train id outside [0, V)
  * gives NO_ERR_OUT_OF_RANGE (it is never followed), an expired scan wait NO_ERR_TIMEOUT; no cache is returned then. */

@@ -12,14 +12,17 @@
 
 namespace no {
 
-// n_vertices > 0: the ids come straight from the caller; one outside [0, V) is not counted and raises *bad_flag
-__global__ void count_members_kernel(const int32_t* ids, const int32_t* d_n, int32_t n_fixed, int32_t* freq,
+// The vertices of V^1 of one batch, each counted once. The first n_seeds ids are the batch's own, which the caller may have repeated:
+// last[v] is the stamp of the last batch that held v (a vertex further down the list stands there once). n_vertices > 0: the
+// ids come straight from the caller; one outside [0, V) is not counted and raises *bad_flag.
+__global__ void count_members_kernel(const int32_t* ids, const int32_t* d_n, int32_t n_seeds, int32_t* last, int32_t stamp, int32_t* freq,
                                      int32_t n_vertices, int32_t* bad_flag) {
-    int32_t n = d_n ? *d_n : n_fixed;
-    int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int32_t n = d_n ? *d_n : n_seeds;
+    const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const int32_t v = ids[i];
     if (n_vertices > 0 && (uint32_t)v >= (uint32_t)n_vertices) { *bad_flag = 1; return; }
+    if (i < n_seeds && atomicExch(&last[v], stamp) == stamp) return;
     atomicAdd(&freq[v], 1);       // integer count: order independent
 }
 
@@ -260,22 +263,22 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
         }
     } else {
         if (n_layers >= 2) NO_CHECK(blocks_create_impl(g, batch, h_fanouts, n_layers - 1, false, &b));
-        for (int32_t p = 0; p < presample_epochs; ++p)
-            for (int64_t bi = 0; bi < nb; ++bi) {
-                const int64_t lo = bi * batch;
-                const int32_t n = (int32_t)((lo + batch <= n_train) ? batch : (n_train - lo));
-                if (n_layers >= 2) {
-                    NO_CHECK(sample_blocks_impl(g, d_train_ids + lo, n, seed + (uint64_t)p * (uint64_t)nb + (uint64_t)bi, 1u,
-                                                n_layers - 1, nullptr, 0, b, st));
-                    const HopBuffers& H = b->hop[n_layers - 2];
-                    hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(H.n_src_cap, 256)), dim3(256), 0, st,
-                                       (const int32_t*)H.src_global.p, (const int32_t*)(b->counts.p + 4 * (n_layers - 2) + 1), 0,
-                                       c->freq.p, 0, (int32_t*)nullptr);
-                } else {
-                    hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st,
-                                       d_train_ids + lo, (const int32_t*)nullptr, n, c->freq.p, (int32_t)V, bad_flag.p);
-                }
+        int32_t* last = c->slot_of_vertex.p;      // (filled after the ranking)
+        for (int64_t job = 0; job < max_count; ++job) {
+            const int64_t lo = job % nb * batch;
+            const int32_t n = (int32_t)std::min<int64_t>(batch, n_train - lo);
+            if (n_layers >= 2) {
+                NO_CHECK(sample_blocks_impl(g, d_train_ids + lo, n, seed + (uint64_t)job, 1u, n_layers - 1, nullptr, 0, b, st));
+                const HopBuffers& H = b->hop[n_layers - 2];
+                hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(H.n_src_cap, 256)), dim3(256), 0, st,
+                                   (const int32_t*)H.src_global.p, (const int32_t*)(b->counts.p + 4 * (n_layers - 2) + 1), n, last,
+                                   (int32_t)job, c->freq.p, 0, (int32_t*)nullptr);
+            } else {
+                hipLaunchKernelGGL(count_members_kernel, dim3((unsigned)ceil_div(n, 256)), dim3(256), 0, st, d_train_ids + lo,
+                                   (const int32_t*)nullptr, n, last, (int32_t)job, c->freq.p, (int32_t)V, bad_flag.p);
             }
+        }
+        NO_CHECK(fill_i32(last, -1, V, st));
     }
     NO_CHECK(launch_status("presample"));
 

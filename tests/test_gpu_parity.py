@@ -264,6 +264,27 @@ def test_select_hot_batch_counts_and_sizes(V, E, n_train, batch, fanouts, bits):
     assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
 
 
+@pytest.mark.parametrize("fanouts", [(10, 5), (6,)])
+@pytest.mark.parametrize("batch", [100, 9_000])       # batches by bitmap; one large batch, by the training sampler
+def test_select_hot_counts_a_repeated_train_id_once_a_batch(fanouts, batch):
+    """Against the oracle's counts batch by batch, of the ids without repetition (a draw depends on the vertex, not on its place)."""
+    b = nb()
+    V, epochs = 10_000, 2
+    src, dst, og, gg = make_graph(V, 100_000, 3, 32)
+    train = si.train_split(V, 1.0, 3)[:9_000].copy()
+    train[1::50] = train[::50]                            # next to each other
+    train[8_999], train[7] = train[8_901], train[8_999]   # far apart, and in two batches
+    n_batches = -(-len(train) // batch)
+    freq = np.zeros(V, np.int64)
+    for job in range(epochs * n_batches):
+        ids = train[job % n_batches * batch:][:batch]
+        ids = ids[np.sort(np.unique(ids, return_index=True)[1])]
+        freq += ora.presample_counts(og, ids, len(ids), fanouts, 1, 9 + job)
+    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, fanouts, epochs, 0.25, 1, 4, 9), V)
+    assert np.array_equal(view["freq"].cpu().numpy().astype(np.int64), freq)
+    assert np.array_equal(view["hot_ids"].cpu().numpy(), np.lexsort((np.arange(V), -freq))[:V // 4])
+
+
 def test_sample_blocks_with_cache_lookup():
     b = nb()
     w = si.WORKLOADS["tiny"]
