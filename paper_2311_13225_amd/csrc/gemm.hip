@@ -627,22 +627,31 @@ static int32_t launch_small_nn(const GemmNNArgs& a, bool b_transposed, hipStream
     return launch_status("gemm_nn_small");
 }
 
+static int64_t nn_tiles(const GemmNNArgs& a) { return ceil_div(a.M_cap, 64) * ceil_div(a.N, 64) * (a.accumulate ? 1 : a.n_problems); }
+
+template <bool B_KC>
+static int32_t launch_tiled_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+    NO_LAUNCH_TIMED((gemm_nn_kernel<B_KC, 64, 64, 1, 2, 3>), dim3(xcd_padded(nn_tiles(a))), dim3(256), st, ev0, ev1, a);
+    return launch_status("gemm_nn");
+}
+
 int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
-    const int64_t tiles = ceil_div(a.M_cap, 64) * ceil_div(a.N, 64);
-    if (tiles <= 128) return launch_small_nn(a, false, st, ev0, ev1);
-    NO_LAUNCH_TIMED((gemm_nn_kernel<false, 64, 64, 1, 2, 3>), dim3(xcd_padded(tiles)), dim3(256), st, ev0, ev1, a);
-    return launch_status("gemm_nn");
+    if (nn_tiles(a) <= 128) return launch_small_nn(a, false, st, ev0, ev1);
+    return launch_tiled_nn<false>(a, st, ev0, ev1);
 }
 
 int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
     GemmNNArgs a = args;
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
-    if (!input_grad_takes_planes(a.M_cap, a.K[0], a.N, a.n_problems)) return launch_small_nn(a, true, st, nullptr, nullptr);
+    if (nn_tiles(a) <= 128) return launch_small_nn(a, true, st, nullptr, nullptr);
+    // The fp32 instruction where the cut rows would be shorter than a unit, and where the planes do not fit (a layer wider than it has
+    // rows; 1000 rows, 1792 x 1792, whole backward pass: 313 us on the kernel for small products, 284 on the tiled one).
+    if (!input_grad_takes_planes(a.M_cap, a.K[0], a.N, a.n_problems)) return launch_tiled_nn<true>(a, st, nullptr, nullptr);
     if (!a.cut_B[0]) {
         const bool one = a.B[1] == a.B[0];
         const size_t each = cut_weights_elements(a.N, a.K[0], true);
-        if (!a.cut_scratch || (one ? 1 : 2) * each * 2 > a.cut_scratch_bytes) return launch_small_nn(a, true, st, nullptr, nullptr);
+        if (!a.cut_scratch || (one ? 1 : 2) * each * 2 > a.cut_scratch_bytes) return launch_tiled_nn<true>(a, st, nullptr, nullptr);
         uint16_t* planes = (uint16_t*)a.cut_scratch;
         NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], true, planes, st));
         a.cut_B[0] = planes;

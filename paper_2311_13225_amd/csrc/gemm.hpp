@@ -15,8 +15,7 @@ struct GemmNNArgs {
     const int32_t* a_rows[2];             // per problem: row m of the operand is row a_rows[m] of A (NULL: row m)
     const float* B[2]; int64_t ldb[2]; int b_align[2];
     int32_t K[2];
-    // large input gradients take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch (where
-    // there is no room for them, the kernel for small products takes over)
+    // large input gradients take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch
     const uint16_t* cut_B[2];
     void* cut_scratch; size_t cut_scratch_bytes;
     float* C[2]; int64_t ldc[2];

@@ -41,8 +41,10 @@ struct LayerWorkspace {
     float* gz = nullptr;             // [n_dst_cap, d_out] masked output gradient
     float* gmean = nullptr;          // [n_dst_cap, d_in]  gradient of the mean, pre-divided by the row length
     float* x_dst_f32 = nullptr;      // [n_dst_cap, d_in]  fp32 copy of bf16 destination rows
-    float* partials = nullptr;       // [2, splits, d_in + 1, d_out]; before that, planes of the weights
-    size_t partials_bytes = 0;
+    float* partials = nullptr;       // [2, splits, d_in + 1, d_out]
+    // Planes of the layer's weights (cut_weights) stand in the place of the two above, which are free until the weight gradients.
+    uint16_t* planes() const { return (uint16_t*)x_dst_f32; }
+    size_t planes_bytes = 0;
     int32_t splits = 1;
     size_t bytes = 0;
 };

@@ -593,9 +593,8 @@ LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_
     w.gz = (float*)(base + off);        off += align256((size_t)n_dst_cap * d_out * 4);
     w.gmean = (float*)(base + off);     off += align256((size_t)n_dst_cap * d_in * 4);
     w.x_dst_f32 = (float*)(base + off); off += align256((size_t)n_dst_cap * d_in * 4);
-    w.partials = (float*)(base + off);
-    w.partials_bytes = align256((size_t)2 * w.splits * (d_in + 1) * d_out * 4);
-    off += w.partials_bytes;
+    w.partials = (float*)(base + off);  off += align256((size_t)2 * w.splits * (d_in + 1) * d_out * 4);
+    w.planes_bytes = (size_t)(base + off - (char*)w.x_dst_f32);
     w.bytes = off;
     return w;
 }
@@ -713,11 +712,11 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     uint16_t* own_planes[2];
     if (!gz_in && (relu || grad_rows)) {
         // The weights of a large input gradient are cut beside the masking (a launch of their own: 3 us of the 80 of a layer of 3.4 K
-        // rows, 256 x 256), into the partials' place, which is free until this layer's weight gradients.
+        // rows, 256 x 256).
         CutJobs cut;
         const size_t plane = cut_weights_elements(d_in, d_out, true);
-        if (grad_x_src && !cut_bwd && input_grad_takes_planes(n_cap, d_out, d_in, 2) && (gcn ? 1 : 2) * plane * 2 <= w.partials_bytes) {
-            own_planes[0] = (uint16_t*)w.partials;
+        if (grad_x_src && !cut_bwd && input_grad_takes_planes(n_cap, d_out, d_in, 2) && (gcn ? 1 : 2) * plane * 2 <= w.planes_bytes) {
+            own_planes[0] = w.planes();
             own_planes[1] = own_planes[0] + plane;
             cut.add(w_self, d_in, d_out, own_planes[0]);
             if (!gcn) cut.add(w_neigh, d_in, d_out, own_planes[1]);
@@ -727,11 +726,6 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         hipLaunchKernelGGL(mask_rows_kernel, dim3(own + cut.blocks()), dim3(256), 0, st, grad_h, grad_rows, h, blk.d_n_dst, n_cap, d_out,
                            relu, w.gz, own, cut);
         gz = w.gz;
-    }
-    const float* x_dst = (const float*)x_src;
-    if (dt == NO_BF16 && !gcn && !bf) {
-        NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, n_cap, d_in, w.x_dst_f32, st));
-        x_dst = w.x_dst_f32;
     }
     if (prof && prep_stage >= 0) prof->end();
     if (grad_x_src) {
@@ -759,14 +753,19 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         a.n_problems = 2; a.accumulate = 0;
         a.cut_B[0] = cut_bwd ? cut_bwd[0] : nullptr;
         a.cut_B[1] = cut_bwd ? cut_bwd[gcn ? 0 : 1] : nullptr;
-        a.cut_scratch = w.partials;       // (free until this layer's weight gradients)
-        a.cut_scratch_bytes = w.partials_bytes;
+        a.cut_scratch = w.planes();
+        a.cut_scratch_bytes = w.planes_bytes;
         a.d_M = blk.d_n_dst; a.M_cap = n_cap; a.N = d_in;
         NO_CHECK(gemm_nn_input_grad(a, st));
         NO_CHECK(transpose_aggregate(w.gmean, d_in, blk.d_csc_indptr, blk.d_csc_dst, blk.d_n_src, blk.n_src_cap,
                                      blk.d_n_dst, grad_x_src, st, below ? below->h : nullptr, below ? below->out_rows : nullptr,
                                      below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr));
         if (prof && dx_stage >= 0) prof->end();
+    }
+    const float* x_dst = (const float*)x_src;
+    if (dt == NO_BF16 && !gcn && !bf) {
+        NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, n_cap, d_in, w.x_dst_f32, st));
+        x_dst = w.x_dst_f32;
     }
     // weight gradients x_dst^T gz, mean^T gz and the bias gradient (column sums of gz, carried by a virtual
     // column of ones in the first product), split over rows and summed in split order

@@ -350,7 +350,7 @@ def layer_case(V, E, F, d_out, fanouts, B, seed, bf16=False, edges=None, seeds=N
 @pytest.mark.parametrize("F,d_out,relu,bf16", [(64, 64, True, False), (602, 256, True, False), (100, 47, False, False),
                                                (33, 5, True, False), (256, 130, True, False), (128, 256, True, True),
                                                (6, 3, False, True), (40, 200, True, False), (70, 41, False, False),
-                                               (256, 41, False, False), (200, 50, True, False)])
+                                               (256, 41, False, False), (200, 50, True, False), (256, 256, True, True)])
 def test_sage_layer_forward_backward(F, d_out, relu, bf16):
     check_layer_forward_backward(layer_case(4000, 60_000, F, d_out, (7, 6), 300, 11, bf16), F, d_out, relu, bf16)
 
@@ -358,7 +358,8 @@ def test_sage_layer_forward_backward(F, d_out, relu, bf16):
 @pytest.mark.parametrize("n,cap,F,d_out", [
     (0, 5000, 64, 64), (1, 5000, 8, 256), (31, 5000, 9, 100), (33, 9000, 33, 48), (63, 5000, 128, 128),      # fewer rows than a step or a tile
     (257, 5000, 129, 65), (1000, 30_000, 100, 256), (5001, 30_000, 66, 7),                                   # remainders of every tile size
-    (4097, 4097, 127, 129), (9000, 9000, 3, 130), (20_100, 30_000, 130, 172)])                              # large tiles; a layer of 3 columns
+    (4097, 4097, 127, 129), (9000, 9000, 3, 130), (20_100, 30_000, 130, 172),                               # large tiles; a layer of 3 columns
+    (2500, 2500, 1800, 1792), (700, 700, 1800, 1790), (20, 70, 9000, 9), (5001, 9000, 66, 5)])                                # few slices: planes in the rows' place too; no planes
 def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     """Weight and input gradients against exact sums. Bound: every term of a sum of K products may be off by the rounding of
     one fp32 product and every addition by that of its partial sum, together below (K + 8) 2^-24 sum |a b|."""
@@ -450,22 +451,20 @@ def test_sage_layer_gradient_products_that_end_just_inside_the_range():
         assert np.count_nonzero(ref) == 2 and np.array_equal(got.cpu().numpy(), ref.astype(np.float32))
 
 
-def test_sage_layer_gradients_of_a_diverged_run_keep_their_pace():
-    """NaN in every operand: the gradients are NaN, and the call stays within a few times of one with ordinary numbers (outputs
-    summed one by one took 54 times as long; measured: 3 times)."""
+def layer_backward_us(n, F, d_out, fill=None):
+    """(time of one backward call of a layer over n rows, its outputs); operands from N(0, 1), or all of them `fill`."""
     b = nb()
-    n, F, d_out = 3400, 256, 256
     g = torch.Generator(device="cuda")
     g.manual_seed(3)
-    rnd = lambda *s: torch.randn(s, generator=g, device="cuda")
-    x, gh, w = rnd(n, F), rnd(n, d_out), rnd(F, d_out)
+    rnd = lambda *s: torch.randn(s, generator=g, device="cuda") if fill is None else torch.full(s, fill, device="cuda")
+    x, gh, w_self, w_neigh = rnd(n, F), rnd(n, d_out), rnd(F, d_out), rnd(F, d_out)
     d_n, ptr = dev(np.array([n], np.int32)), torch.arange(n + 1, dtype=torch.int32, device="cuda")
     blk = b.block_view_from_tensors(d_n, d_n, ptr, ptr[:n].clone(), n, n, ptr, ptr[:n].clone())
     ws = torch.empty(b.no_sage_layer_ws_bytes(n, n, F, d_out), dtype=torch.uint8, device="cuda")
     outs = [torch.empty(s, device="cuda") for s in ((F, d_out), (F, d_out), (d_out,), (n, F))]
 
     def call_us():
-        call = lambda: b.no_sage_layer_bwd(blk, x, x, gh, gh, w, w, False, *outs, ws)
+        call = lambda: b.no_sage_layer_bwd(blk, x, x, gh, gh, w_self, w_neigh, False, *outs, ws)
         call()
         t0, t1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         t0.record()
@@ -475,13 +474,27 @@ def test_sage_layer_gradients_of_a_diverged_run_keep_their_pace():
         torch.cuda.synchronize()
         return t0.elapsed_time(t1) / 20 * 1e3
 
-    ordinary = min(call_us() for _ in range(3))
-    for t in (x, gh, w):
-        t.fill_(float("nan"))
-    diverged = min(call_us() for _ in range(3))
+    return min(call_us() for _ in range(3)), outs
+
+
+def test_sage_layer_gradients_of_a_diverged_run_keep_their_pace():
+    """NaN in every operand: the gradients are NaN, and the call stays within a few times of one with ordinary numbers (outputs
+    summed one by one took 54 times as long; measured: 3 times)."""
+    ordinary = layer_backward_us(3400, 256, 256)[0]
+    diverged, outs = layer_backward_us(3400, 256, 256, float("nan"))
     assert all(torch.isnan(t).all() for t in outs)
     print("ordinary %.1f us, all NaN %.1f us" % (ordinary, diverged))
     assert diverged < 10 * ordinary
+
+
+@pytest.mark.parametrize("n,F,d_out,other,at_most", [(60_000, 1792, 1792, 1024, 4.4), (60_000, 256, 4, 8, 1.25)])
+def test_sage_layer_gradients_of_wide_and_narrow_layers_keep_their_pace(n, F, d_out, other, at_most):
+    """Against the same layer with F = d_out = other, or d_out = other columns. Layers so wide that the weight gradients use few row
+    slices (products: 3.06 times the other's; measured: 3.1 times the time, 5.7 with the input gradient on the kernel for small
+    products), and ones with fewer columns than are cut together (half the products; measured: 1.07 times the time, 1.46)."""
+    ours, others = layer_backward_us(n, F, d_out)[0], layer_backward_us(n, other if F == d_out else F, other)[0]
+    print("%d columns %.1f us, %d columns %.1f us" % (d_out, ours, other, others))
+    assert ours < at_most * others
 
 
 @pytest.mark.parametrize("bf16", [False, True])
