@@ -359,7 +359,8 @@ def test_sage_layer_forward_backward(F, d_out, relu, bf16):
     (0, 5000, 64, 64), (1, 5000, 8, 256), (31, 5000, 9, 100), (33, 9000, 33, 48), (63, 5000, 128, 128),      # fewer rows than a step or a tile
     (257, 5000, 129, 65), (1000, 30_000, 100, 256), (5001, 30_000, 66, 7),                                   # remainders of every tile size
     (4097, 4097, 127, 129), (9000, 9000, 3, 130), (20_100, 30_000, 130, 172),                               # large tiles; a layer of 3 columns
-    (2500, 2500, 1800, 1792), (700, 700, 1800, 1790), (20, 70, 9000, 9), (5001, 9000, 66, 5)])                                # few slices: planes in the rows' place too; no planes
+    (2500, 2500, 1800, 1792), (700, 700, 1800, 1790), (20, 70, 9000, 9), (5001, 9000, 66, 5),                                 # few slices: planes in the rows' place too; no planes
+    (20_100, 30_000, 130, 32), (20_100, 30_000, 32, 130), (20_100, 30_000, 130, 33), (9000, 30_000, 2, 1)])                   # narrow: small tiles at every number of rows
 def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     """Weight and input gradients against exact sums. Bound: every term of a sum of K products may be off by the rounding of
     one fp32 product and every addition by that of its partial sum, together below (K + 8) 2^-24 sum |a b|."""
