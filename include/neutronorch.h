@@ -13,6 +13,9 @@
  *     enqueued on it; calls return without synchronising unless a host out-parameter is
  *     documented to need it. Data-dependent sizes live in device scalars; kernels are
  *     launched at capacity bounds and exit early.
+ *   - Device memory that handles and calls have given up is kept for the next ones: at most 8 GiB per device, and
+ *     only while a handle exists. Destroying the last one gives everything back, and so does an allocation of the
+ *     library's that fails. A program whose other allocators need that memory destroys its handles first.
  *   - Handles are not thread-safe. Same inputs => bit-identical outputs (no float atomics).
  *   - Vertex ids are int32. Edge (src -> dst) makes src an in-neighbour of dst (Eq. 1).
  *   - Matrices are row-major; weights are [d_in, d_out].

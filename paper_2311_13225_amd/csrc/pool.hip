@@ -2,8 +2,8 @@
 // giving memory back to the driver takes 250 us a block, and the driver clears every block before it hands it out again (some
 // 50 GB/s), so that a program which builds graphs or selects hot sets in a loop soon waits for the clearing (measured: the
 // 4.7 ms build of a 124 M edge graph at 51 ms a call, 2.5 GB given back by each).
-// Bounds: at most POOL_BYTES per device are kept, the longest-unused blocks go first; everything kept is given back when an
-// allocation fails and when the last handle of the library is destroyed. A block enters the pool only after its device has
+// Bounds: at most POOL_BYTES per device are kept, the longest-unused blocks go first, and only while a handle of the library
+// exists; everything kept is given back when an allocation fails and when the last handle is destroyed. A block enters the pool only after its device has
 // finished all work (as the driver's own free does), so it may be handed to any thread and any stream.
 #include "common.hpp"
 
@@ -113,10 +113,14 @@ void device_free(void* p) {
     std::vector<Block> back;
     {
         std::lock_guard<std::mutex> l(g_mutex);
-        b.age = ++g_clock;
-        g_kept.emplace(b.bytes, b);
+        if (g_handles == 0) {      // (the temporaries of a call that failed to make the first handle)
+            back.push_back(b);
+        } else {
+            b.age = ++g_clock;
+            g_kept.emplace(b.bytes, b);
+            g_kept_bytes[b.dev] += b.bytes;
+        }
         size_t& kept = g_kept_bytes[b.dev];
-        kept += b.bytes;
         while (kept > POOL_BYTES) {
             auto oldest = g_kept.end();
             for (auto it = g_kept.begin(); it != g_kept.end(); ++it)

@@ -112,6 +112,29 @@ def test_graphs_built_and_destroyed_by_several_threads():
     assert not wrong
 
 
+def test_memory_is_kept_only_while_a_handle_exists():
+    """Neither the temporaries of a build that fails nor the memory of the last graph stay with the library."""
+    import gc
+    b = nb()
+    gc.collect()
+    src, dst = (np.random.default_rng(i).integers(0, 1000, 20_000_000, dtype=np.int32) for i in range(2))
+    bad = src.copy()
+    bad[5] = -1
+
+    def fail(n):
+        with pytest.raises(b.NoError):
+            b.no_build_csr(bad[:n], dst[:n], 1000, 32)
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    free = fail(100)
+    assert free - fail(len(bad)) < 64 << 20              # (its temporaries: 16 bytes an edge)
+    gg = b.no_build_csr(src, dst, 1000, 32)
+    assert free - torch.cuda.mem_get_info()[0] >= 4 * len(src)
+    gg.close()
+    assert free - torch.cuda.mem_get_info()[0] < 64 << 20
+
+
 def test_build_csr_from_device_and_rejects_bad_ids():
     src, dst = si.rmat_edges(500, 5000, 2)
     og = ora.build_csr(src, dst, 500)
