@@ -372,11 +372,11 @@ int32_t no_model_destroy(no_model_t m);
  * every step records an event pair around each stage and synchronises the stream at its end to
  * accumulate the elapsed times (so it is for measurement passes, not for throughput runs).
  * Stages that are a single kernel launch: NO_STAGE_GATHER, NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1,
- * NO_STAGE_GEMM_DW_L1, NO_STAGE_SAMPLE_ROWS_BOTTOM. While enabled, the step's stream also waits for the blocks' side
- * stream (local indices, transposes, id-map wipe) before the end of NO_STAGE_SAMPLE, so that stage is all of the
- * sampling work of the step. */
+ * NO_STAGE_GEMM_DW_L1 (which carries the upper layers' products), NO_STAGE_SAMPLE_ROWS_BOTTOM. While enabled, the side tasks
+ * of the sampling (local indices, transposes, id-map wipe), which otherwise ride on later launches, are finished before the
+ * end of NO_STAGE_SAMPLE, so that stage is all of the sampling work of the step. */
 enum {
-    NO_STAGE_SAMPLE = 0,      /* all hops: sampling, relabel, hot lookup, and (joined) local indices + transposes */
+    NO_STAGE_SAMPLE = 0,      /* all hops: sampling, relabel, hot lookup, local indices, transposes */
     NO_STAGE_GATHER = 1,      /* feature rows of the bottom hop's sources */
     NO_STAGE_AGG_L1 = 2,      /* layer-1 mean aggregation kernel */
     NO_STAGE_GEMM_FWD_L1 = 3, /* layer-1 dense update kernel */

@@ -1,5 +1,5 @@
-// The fp32 products on the fp32 matrix instruction (forward products, and small ones of either kind) and the reduction of the split
-// weight-gradient products. Large gradient products: gemm_cut.hip.
+// The fp32 products on the fp32 matrix instruction (forward products, and input gradients that are not cut) and the reduction of the
+// split weight-gradient products. Other gradient products: gemm_cut.hip.
 #include "gemm_tile.hpp"
 
 namespace no {
@@ -128,11 +128,11 @@ __global__ void __launch_bounds__(256) gemm_nn_small_kernel(GemmNNArgs g) {
     }
 }
 
-// ------------------------------------------------------------------------------------------ NN, forward
+// ------------------------------------------------------------------------------------------ NN, tiled
 
-// LDS-tiled forward products. Block tile 64 x 64 x 32, 256 threads = 2 x 2 wavefronts, each owning a 32 x 32 sub-tile as
-// v_mfma_f32_32x32x2_f32 accumulators. They stay on the fp32 instruction and sum every output element in one fixed order,
-// because the ReLU decisions of a step hang on the last bits of these sums.
+// LDS-tiled products: forward, and the input gradients that are not cut. Block tile 64 x 64 x 32, 256 threads = 2 x 2 wavefronts, each
+// owning a 32 x 32 sub-tile as v_mfma_f32_32x32x2_f32 accumulators. Forward products stay on the fp32 instruction and sum every
+// output element in one fixed order, because the ReLU decisions of a step hang on the last bits of these sums.
 //
 // Operand tiles sit in LDS in one of two layouts, chosen by how the operand lies in memory:
 //   KC (reduction index contiguous in memory): T[x][k], pitch 36 floats; a lane fetches the four
@@ -650,10 +650,10 @@ int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
     if (!input_grad_takes_planes(a.M_cap, a.K[0], a.N, a.n_problems)) return launch_tiled_nn<true>(a, st, nullptr, nullptr);
     if (!a.cut_B[0]) {
         const bool one = a.B[1] == a.B[0];
-        const size_t each = cut_weights_elements(a.N, a.K[0], true);
+        const size_t each = cut_weights_elements(a.N, a.K[0]);
         if (!a.cut_scratch || (one ? 1 : 2) * each * 2 > a.cut_scratch_bytes) return launch_tiled_nn<true>(a, st, nullptr, nullptr);
         uint16_t* planes = (uint16_t*)a.cut_scratch;
-        NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], true, planes, st));
+        NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], planes, st));
         a.cut_B[0] = planes;
         a.cut_B[1] = one ? planes : planes + each;
     }

@@ -1,5 +1,5 @@
 // fp32 matrix products for the dense UPDATE of Eq. 2 and its gradients, on the gfx950 matrix
-// cores (gemm_cut.hip; gemm.hip for small ones). Two shapes:
+// cores (gemm_cut.hip: gradients; gemm.hip: forward products and small gradients). Two shapes:
 //   NN: C[M,N] = sum_p A_p[M,K_p] * B_p[K_p,N] (+ bias, ReLU, optional 1/len row scale); M is a
 //       device scalar (rows past it are skipped); B may be given transposed; the rows of A_p may be
 //       picked out of a larger table by an index (gather fused into the operand load).
@@ -11,9 +11,9 @@
 namespace no {
 
 struct GemmNNArgs {
-    const float* A[2]; int64_t lda[2]; int a_align[2];
+    const float* A[2]; int64_t lda[2];
     const int32_t* a_rows[2];             // per problem: row m of the operand is row a_rows[m] of A (NULL: row m)
-    const float* B[2]; int64_t ldb[2]; int b_align[2];
+    const float* B[2]; int64_t ldb[2];
     int32_t K[2];
     // large input gradients take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch
     const uint16_t* cut_B[2];
@@ -34,8 +34,8 @@ struct GemmNNArgs {
 };
 
 struct GemmTNArgs {
-    const float* A[2]; int64_t lda[2]; int a_align[2];   // [R, Kp] row-major; two problems share G
-    const float* G; int64_t ldg; int g_align;            // [R, N]
+    const float* A[2]; int64_t lda[2];                    // [R, Kp] row-major; two problems share G
+    const float* G; int64_t ldg;                         // [R, N]
     float* P;                                            // partials [2][splits][Kp+1][N]; row Kp of product 0 = column sums of G
     int32_t Kp, N;
     const int32_t* d_R; int32_t R_cap; int32_t splits;   // splits: the most row slices (the partials' layout is sized for it)
@@ -64,26 +64,25 @@ struct GemmBf16NNArgs {
     const float* bias; int32_t relu;
     const int32_t* c_rows; float* c_keep; const int32_t* c_keep_rows;   // as in GemmNNArgs
 };
-// Weights cut for the large gradient products (gemm_cut.hip): planes of one matrix [K][N], reduction index padded to 32.
-__host__ __device__ inline int32_t cut_pad(int32_t K) { return (K + 31) / 32 * 32; }
-inline size_t cut_weights_elements(int32_t K, int32_t N, bool transposed) {
-    return (size_t)3 * (transposed ? (size_t)cut_pad(N) * K : (size_t)cut_pad(K) * N);
-}
+// Weights cut for the large gradient products (gemm_cut.hip): planes of the transpose of one matrix [K][N], the reduction index (over
+// the N columns) padded to 32.
+__host__ __device__ inline int32_t cut_pad(int32_t N) { return (N + 31) / 32 * 32; }
+inline size_t cut_weights_elements(int32_t K, int32_t N) { return (size_t)3 * cut_pad(N) * K; }
 // w1 may be NULL; the second matrix's planes follow the first's (cut_weights_elements apart)
-int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st);
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, uint16_t* out, hipStream_t st);
 // Whether an input gradient of M_cap x N (reduction over K columns) reads planes: more output tiles than compute units for the
 // kernel for small products to keep busy by splitting the reduction.
 inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
-// Matrices cut (transposed) by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
+// Matrices cut by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
 // blocks [end_block[j-1], end_block[j]) of them.
 struct CutJobs {
     const float* w[2 * NO_MAX_LAYERS]; uint16_t* out[2 * NO_MAX_LAYERS]; int32_t K[2 * NO_MAX_LAYERS], N[2 * NO_MAX_LAYERS];
     uint32_t end_block[2 * NO_MAX_LAYERS]; int32_t n = 0;
     void add(const float* matrix, int32_t rows, int32_t cols, uint16_t* planes) {
         w[n] = matrix; out[n] = planes; K[n] = rows; N[n] = cols;
-        end_block[n] = blocks() + (uint32_t)ceil_div((int64_t)cut_weights_elements(rows, cols, true) / 24, 256);
+        end_block[n] = blocks() + (uint32_t)ceil_div((int64_t)cut_weights_elements(rows, cols) / 24, 256);
         ++n;
     }
     uint32_t blocks() const { return n ? end_block[n - 1] : 0u; }
@@ -130,11 +129,5 @@ int32_t gemm_nn_input_grad(const GemmNNArgs& a, hipStream_t st);
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
 int32_t reduce_grads(const ReduceArgs* jobs, int32_t n_jobs, hipStream_t st, const StatsJob* stats_job = nullptr);
-
-inline int ptr_align(const void* p, int64_t ld) {
-    if ((((uintptr_t)p) & 15) == 0 && (ld & 3) == 0) return 4;
-    if ((((uintptr_t)p) & 7) == 0 && (ld & 1) == 0) return 2;
-    return 1;
-}
 
 }  // namespace no

@@ -50,19 +50,17 @@ __device__ constexpr CutTerm CUT_TERM[CUT_TERMS] = {{2, 0, 0}, {0, 2, 0}, {1, 1,
 
 // ------------------------------------------------------------------------------------------ weights
 
-// Both matrices of a layer ([K][N] fp32, row-major) cut into planes: out[matrix][plane][K/8][N][8] with the reduction index
-// fastest, zeros from K to the next multiple of 32. transposed: the operand is W^T, so the reduction runs over the columns:
-// out[matrix][plane][N/8][K][8].
+// The transposes of both matrices of a layer ([K][N] fp32, row-major) cut into planes: out[matrix][plane][N/8][K][8], eight indices of the
+// reduction (over the columns) together, zeros from N to the next multiple of 32.
 __global__ void __launch_bounds__(256) cut_weights_kernel(const float* __restrict__ w0, const float* __restrict__ w1, int32_t K, int32_t N,
-                                                          int32_t transposed, uint16_t* __restrict__ out, int64_t matrix_stride) {
+                                                          uint16_t* __restrict__ out, int64_t matrix_stride) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < matrix_stride / 24) cut_weights_unit(blockIdx.y ? w1 : w0, K, N, transposed != 0, out + blockIdx.y * matrix_stride, i);
+    if (i < matrix_stride / 24) cut_weights_unit(blockIdx.y ? w1 : w0, K, N, out + blockIdx.y * matrix_stride, i);
 }
 
-int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool transposed, uint16_t* out, hipStream_t st) {
-    const int64_t stride = (int64_t)cut_weights_elements(K, N, transposed), units = stride / 24;
-    hipLaunchKernelGGL(cut_weights_kernel, dim3((unsigned)ceil_div(units, 256), w1 ? 2u : 1u), dim3(256), 0, st, w0, w1, K, N,
-                       transposed ? 1 : 0, out, stride);
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, uint16_t* out, hipStream_t st) {
+    const int64_t stride = (int64_t)cut_weights_elements(K, N), units = stride / 24;
+    hipLaunchKernelGGL(cut_weights_kernel, dim3((unsigned)ceil_div(units, 256), w1 ? 2u : 1u), dim3(256), 0, st, w0, w1, K, N, out, stride);
     return launch_status("cut_weights");
 }
 

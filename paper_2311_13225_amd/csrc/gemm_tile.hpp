@@ -57,16 +57,15 @@ __device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
     p[2] = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
-// One unit of a matrix's planes (see cut_weights; i < cut_weights_elements / 24): eight reduction indices of one column.
-__device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int32_t N, bool transposed, uint16_t* out, int64_t i) {
-    const int32_t R = transposed ? N : K, X = transposed ? K : N;       // reduction indices, columns of the operand
-    const int64_t plane = (int64_t)cut_pad(R) * X;
-    const int32_t rb = (int32_t)(i / X), x = (int32_t)(i - (int64_t)rb * X);
+// One unit of a matrix's planes (see cut_weights; i < cut_weights_elements / 24): eight reduction indices of one row of the matrix.
+__device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int32_t N, uint16_t* out, int64_t i) {
+    const int64_t plane = (int64_t)cut_pad(N) * K;
+    const int32_t rb = (int32_t)(i / K), x = (int32_t)(i - (int64_t)rb * K);
     float f[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int32_t r = rb * 8 + j;
-        f[j] = r < R ? (transposed ? w[(int64_t)x * N + r] : w[(int64_t)r * N + x]) : 0.f;
+        f[j] = r < N ? w[(int64_t)x * N + r] : 0.f;
     }
     uint4 p[3];
     cut8(f, p);
@@ -80,7 +79,7 @@ __device__ __forceinline__ void run_cut_jobs(const CutJobs& cut, uint32_t block)
     while (block >= cut.end_block[j]) ++j;
     if (j > 0) block -= cut.end_block[j - 1];
     const int64_t i = (int64_t)block * 256 + threadIdx.x;
-    if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], true, cut.out[j], i);
+    if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], cut.out[j], i);
 }
 
 // Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.

@@ -631,8 +631,8 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                                 blk.n_dst_cap, mean, st, mode, agg_table ? blk.d_src_global : nullptr, hits, e0, e1,
                                 arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr, side_of));
         GemmNNArgs a{};
-        a.A[0] = mean; a.lda[0] = d_in; a.a_align[0] = ptr_align(mean, d_in);
-        a.B[0] = w_self; a.ldb[0] = d_out; a.b_align[0] = ptr_align(w_self, d_out);
+        a.A[0] = mean; a.lda[0] = d_in;
+        a.B[0] = w_self; a.ldb[0] = d_out;
         a.K[0] = d_in;
         a.C[0] = h; a.ldc[0] = d_out;
         a.n_problems = 1; a.accumulate = 1;
@@ -676,11 +676,11 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         x_dst = w.x_dst_f32;
     }
     GemmNNArgs a{};
-    a.A[0] = x_dst; a.lda[0] = d_in; a.a_align[0] = ptr_align(x_dst, d_in);
+    a.A[0] = x_dst; a.lda[0] = d_in;
     a.a_rows[0] = direct_self ? blk.d_src_global : nullptr;
-    a.A[1] = mean;  a.lda[1] = d_in; a.a_align[1] = ptr_align(mean, d_in);
-    a.B[0] = w_self;  a.ldb[0] = d_out; a.b_align[0] = ptr_align(w_self, d_out);
-    a.B[1] = w_neigh; a.ldb[1] = d_out; a.b_align[1] = ptr_align(w_neigh, d_out);
+    a.A[1] = mean;  a.lda[1] = d_in;
+    a.B[0] = w_self;  a.ldb[0] = d_out;
+    a.B[1] = w_neigh; a.ldb[1] = d_out;
     a.K[0] = a.K[1] = d_in;
     a.C[0] = h; a.ldc[0] = d_out;
     a.n_problems = 2; a.accumulate = 1;
@@ -714,7 +714,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         // The weights of a large input gradient are cut beside the masking (a launch of their own: 3 us of the 80 of a layer of 3.4 K
         // rows, 256 x 256).
         CutJobs cut;
-        const size_t plane = cut_weights_elements(d_in, d_out, true);
+        const size_t plane = cut_weights_elements(d_in, d_out);
         if (grad_x_src && !cut_bwd && input_grad_takes_planes(n_cap, d_out, d_in, 2) && (gcn ? 1 : 2) * plane * 2 <= w.planes_bytes) {
             own_planes[0] = w.planes();
             own_planes[1] = own_planes[0] + plane;
@@ -733,9 +733,9 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         // gz W_self^T -> rows [0, n_dst) of grad_x; (gz W_neigh^T) / len(row) -> gmean; then the transpose adds
         if (prof && dx_stage >= 0) prof->begin(dx_stage);
         GemmNNArgs a{};
-        a.A[0] = a.A[1] = gz; a.lda[0] = a.lda[1] = d_out; a.a_align[0] = a.a_align[1] = ptr_align(gz, d_out);
-        a.B[0] = w_self;  a.ldb[0] = d_out; a.b_align[0] = ptr_align(w_self, d_out);
-        a.B[1] = w_neigh; a.ldb[1] = d_out; a.b_align[1] = ptr_align(w_neigh, d_out);
+        a.A[0] = a.A[1] = gz; a.lda[0] = a.lda[1] = d_out;
+        a.B[0] = w_self;  a.ldb[0] = d_out;
+        a.B[1] = w_neigh; a.ldb[1] = d_out;
         a.K[0] = a.K[1] = d_out;
         a.C[0] = grad_x_src; a.ldc[0] = d_in;
         a.C[1] = w.gmean;    a.ldc[1] = d_in;
@@ -744,7 +744,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
             // one matrix: gz W^T / (len + 1) is both the destination's own share (rows [0, n_dst) of grad_x) and
             // what the transpose spreads over the sampled sources
             // (sum: no factor; symmetric normalisation: (len + 1)^-1/2 here, the source's own factor after the transpose)
-            a.B[1] = w_self; a.b_align[1] = a.b_align[0];
+            a.B[1] = w_self;
             a.row_scale_indptr[0] = blk.d_indptr;
             a.row_scale_plus = 1;
             a.row_scale_rsqrt = arch == NO_ARCH_GCN_SYM ? 1 : 0;
@@ -770,10 +770,10 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     // weight gradients x_dst^T gz, mean^T gz and the bias gradient (column sums of gz, carried by a virtual
     // column of ones in the first product), split over rows and summed in split order
     GemmTNArgs t{};
-    t.A[0] = x_dst; t.lda[0] = d_in; t.a_align[0] = ptr_align(x_dst, d_in);
-    t.A[1] = mean;  t.lda[1] = d_in; t.a_align[1] = ptr_align(mean, d_in);
-    if (gcn) { t.A[0] = mean; t.a_align[0] = t.a_align[1]; t.n_problems = 1; }
-    t.G = gz; t.ldg = d_out; t.g_align = ptr_align(gz, d_out);
+    t.A[0] = x_dst; t.lda[0] = d_in;
+    t.A[1] = mean;  t.lda[1] = d_in;
+    if (gcn) { t.A[0] = mean; t.n_problems = 1; }
+    t.G = gz; t.ldg = d_out;
     t.P = w.partials; t.Kp = d_in; t.N = d_out;
     t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits;
     // Batches that fill a fraction of the capacity use fewer slices than the capacity-sized bound: a slice keeps at least

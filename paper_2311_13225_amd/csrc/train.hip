@@ -243,11 +243,11 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
         NO_CHECK(m->wt1.alloc((size_t)2 * m->dims[1] * m->wt1_kpad));
     }
     size_t n_planes = 0;
-    for (int32_t l = 1; l < L; ++l) n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1], true);
+    for (int32_t l = 1; l < L; ++l) n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1]);
     NO_CHECK(m->planes.alloc(n_planes));
     uint16_t* at = m->planes.p;
     for (int32_t l = 1; l < L; ++l)
-        for (int q = 0; q < 2; ++q, at += cut_weights_elements(m->dims[l], m->dims[l + 1], true)) m->cut_bwd[l][q] = at;
+        for (int q = 0; q < 2; ++q, at += cut_weights_elements(m->dims[l], m->dims[l + 1])) m->cut_bwd[l][q] = at;
     size_t ws_bytes = 0;
     for (int32_t l = 1; l <= L; ++l) {
         const HopBuffers& H = m->blocks->hop[L - l];
