@@ -641,13 +641,19 @@ static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) 
     return (uint32_t)((g.N + T - 1) / T) * tn_row_tiles(g, T) * (uint32_t)g.n_problems;
 }
 
+// Those of them that hold products (a tile for the column sums alone is little work, and every product of Kp = T columns has one).
+static __host__ __device__ inline uint32_t tn_product_tiles(const GemmTNArgs& g, int T) {
+    return (uint32_t)((g.N + T - 1) / T) * (uint32_t)((g.Kp + T - 1) / T) * (uint32_t)g.n_problems;
+}
+
 // A product with a side this short fills a quarter of a larger tile and is cut no less often in small ones.
 static __host__ __device__ inline bool tn_narrow(const GemmTNArgs& g) { return g.N <= 32 || g.Kp <= 32; }
 
-// A job takes the larger tiles (fewer cuts per product) where they make blocks for most compute units, a function of the batch's row
-// count (112 blocks, 3.4 K rows: 21.8 us in large tiles, 15.9 in small ones; 176 blocks, 5.5 K rows: 23.1 and 23.6; 256 blocks, 25 K rows:
-// 34.5 and 44.7), unless it is narrow (backward pass of a layer of 60 K rows, us: 256 x 2 192 in large tiles, 164 in small ones; 256 x 16 152 and
-// 143; 3 x 256 121 and 84); its share of the grid is sized for either.
+// A job takes the larger tiles (fewer cuts per product) where they make blocks with products for most compute units, a function of the
+// batch's row count (backward pass of a layer, us, in large tiles / in small ones: 56 blocks, 3.4 K rows, 128 x 256: 47 / 39; 80 blocks, 5 K
+// rows, 128 x 256: 50 / 42; 112 blocks, 3.4 K rows, 256 x 256: 52 / 45; 128 blocks, 8 K rows: 128 x 256 57 / 55, 256 x 128 61 / 63; 160 blocks:
+// 5 K rows, 256 x 256 60 / 61, 10 K rows, 128 x 256 69 / 63; 256 blocks, 16 K rows: 85 / 86; 8 K rows, 256 x 256: 78 / 82), unless it is narrow (60 K
+// rows: 256 x 2 192 / 164; 256 x 16 152 / 143; 3 x 256 121 / 84); its share of the grid is sized for either.
 __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
     int job = 0;
@@ -658,7 +664,7 @@ __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
     if (R > g.R_cap) R = g.R_cap;
     const int used = tn_used_splits(R, g.splits, g.rows_per_split);      // (the reduction reads the first `used` partials only)
     const uint32_t id = blockIdx.x - first;
-    const bool large = !tn_narrow(g) && tn_tiles(g, 128) * used >= TN_LARGE_BLOCKS;
+    const bool large = !tn_narrow(g) && tn_product_tiles(g, 128) * used >= TN_LARGE_BLOCKS;
     if (g.A16) {
         if (large) cut_tn_tile<128, true>(g, id, R, used, smem);
         else cut_tn_tile<64, true>(g, id, R, used, smem);
@@ -676,7 +682,7 @@ int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st,
         if (a.Kp <= 0 || a.N <= 0) continue;
         // (small tiles are only taken while there are few large ones, or by a narrow job)
         const uint64_t small = (uint64_t)tn_tiles(a, 64), large = (uint64_t)tn_tiles(a, 128);
-        const uint64_t most_small = tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / large);
+        const uint64_t most_small = tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / tn_product_tiles(a, 128));
         blocks += std::max(small * most_small, large * (uint64_t)a.splits);
         if (a.A16) blocks = (uint64_t)ceil_div((int64_t)blocks, N_XCD) * N_XCD;
         NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");

@@ -511,14 +511,22 @@ def test_sage_layer_gradients_of_a_diverged_run_keep_their_pace():
     assert diverged < 10 * ordinary
 
 
-@pytest.mark.parametrize("n,F,d_out,other,at_most", [(60_000, 1792, 1792, 1024, 4.4), (60_000, 256, 4, 8, 1.25)])
+@pytest.mark.parametrize("n,F,d_out,other,at_most", [(60_000, 1792, 1792, 1024, 4.4), (60_000, 256, 4, 8, 1.33)])
 def test_sage_layer_gradients_of_wide_and_narrow_layers_keep_their_pace(n, F, d_out, other, at_most):
     """Against the same layer with F = d_out = other, or d_out = other columns. Layers so wide that the weight gradients use few row
     slices (products: 3.06 times the other's; measured: 3.1 times the time, 5.7 with the input gradient on the kernel for small
-    products), and ones with fewer columns than are cut together (half the products; measured: 1.07 times the time, 1.46)."""
+    products), and ones with fewer columns than are cut together (half the products; measured: 1.07 to 1.19 times the time, 1.46)."""
     ours, others = layer_backward_us(n, F, d_out)[0], layer_backward_us(n, other if F == d_out else F, other)[0]
     print("%d columns %.1f us, %d columns %.1f us" % (d_out, ours, other, others))
     assert ours < at_most * others
+
+
+def test_sage_layer_gradients_of_whole_tiles_keep_their_pace():
+    """128 columns, a whole tile, leave the row of column sums a tile of its own, which is not work enough to choose the tiles by:
+    they took 1.21 times as long as 127."""
+    whole, less = layer_backward_us(5000, 128, 256)[0], layer_backward_us(5000, 127, 256)[0]
+    print("128 columns %.1f us, 127 columns %.1f us" % (whole, less))
+    assert whole < 1.1 * less
 
 
 @pytest.mark.parametrize("bf16", [False, True])
