@@ -714,7 +714,7 @@ __global__ void __launch_bounds__(256) reduce_grads_kernel(ReduceLaunch launch, 
     if (a.d_R) {
         int32_t R = *a.d_R;
         if (R > a.R_cap) R = a.R_cap;
-        splits = tn_used_splits(R, a.splits, a.rows_per_split);
+        splits = tn_used_splits(R, a.splits, a.rows_per_split, a.few_splits);
     }
     const int64_t per = (int64_t)(Kp + 1) * N;
     const int64_t i = (int64_t)(blockIdx.x - first) * blockDim.x + threadIdx.x;

@@ -41,14 +41,21 @@ struct GemmTNArgs {
     const int32_t* d_R; int32_t R_cap; int32_t splits;   // splits: the most row slices (the partials' layout is sized for it)
     int32_t n_problems = 2;                              // 1: only A[0]
     const uint16_t* A16 = nullptr;                       // products with bf16 operands: the first one's rows in place of A[0]
-    int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer
+    int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer ...
+    int32_t few_splits = 0;                              // ... though these many, if they keep TN_FEWEST_ROWS rows each
 };
 
+constexpr int32_t TN_FEWEST_ROWS = 64;
+
 // The number of row slices a split product over R rows really uses: the capacity-sized bound `splits`, cut down so that a
-// slice keeps about rows_per_split rows (a function of R alone, so the summation order is the same in every run).
-__host__ __device__ inline int32_t tn_used_splits(int32_t R, int32_t splits, int32_t rows_per_split) {
+// slice keeps about rows_per_split rows, but few_splits of them where those keep TN_FEWEST_ROWS each (a function of R and the shape alone, so
+// the summation order is the same in every run).
+__host__ __device__ inline int32_t tn_used_splits(int32_t R, int32_t splits, int32_t rows_per_split, int32_t few_splits) {
     if (rows_per_split <= 0) return splits;
     int32_t s = (R + rows_per_split - 1) / rows_per_split;
+    int32_t fill = (R + TN_FEWEST_ROWS - 1) / TN_FEWEST_ROWS;
+    if (fill > few_splits) fill = few_splits;
+    if (s < fill) s = fill;
     if (s < 1) s = 1;
     return s < splits ? s : splits;
 }
@@ -109,7 +116,7 @@ struct ReduceArgs {
     float* g_self; float* g_neigh; float* g_bias;
     float lr; float* w_self; float* w_neigh; float* w_bias;
     int32_t n_problems;                                  // 2, or 1: only g_self and g_bias
-    const int32_t* d_R = nullptr; int32_t R_cap = 0; int32_t rows_per_split = 0;   // as in the product: the slices it used
+    const int32_t* d_R = nullptr; int32_t R_cap = 0; int32_t rows_per_split = 0, few_splits = 0;   // as in the product: the slices it used
     // bf16 copies of the two matrices ([N][Kpad], weights_to_bf16_t's layout), rewritten with the updated values (or NULL)
     uint16_t* wt_self = nullptr; uint16_t* wt_neigh = nullptr; int32_t Kpad = 0;
 };

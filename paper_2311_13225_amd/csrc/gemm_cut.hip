@@ -298,7 +298,9 @@ static void launch_cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, h
 
 int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     // Few rows: 32-row blocks (twice as many; measured at 3.4 K / 5.5 K rows x 256 columns: 12.9 / 15.8 us against 15.2 / 18.9 with 64-row
-    // blocks, at 25 K rows 37 against 31). Narrow outputs: all four wavefronts below each other.
+    // blocks, at 25 K rows 37 against 31), by the capacity, which the host knows when it launches: a batch that fills a small part of a larger
+    // one pays for it (backward pass of a layer in a capacity of 19 K / 21 K rows, us: 3.4 K rows, 100 x 256 39.1 / 41.5, 256 x 256 50.6 / 50.3;
+    // 5.5 K rows 48.0 / 49.2, 67.6 / 68.8; 12 K rows 68.3 / 70.3, 99.6 / 98.6). Narrow outputs: all four wavefronts below each other.
     if (a.N <= 64) launch_cut_nn<1, 2, 1, 2>(a, st, ev0, ev1);
     else if (a.M_cap <= 20000) launch_cut_nn<1, 1, 4, 2>(a, st, ev0, ev1);
     else launch_cut_nn<2, 1, 4, 2>(a, st, ev0, ev1);
@@ -662,7 +664,7 @@ __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
     const GemmTNArgs& g = launch.job[job];
     int R = *g.d_R;
     if (R > g.R_cap) R = g.R_cap;
-    const int used = tn_used_splits(R, g.splits, g.rows_per_split);      // (the reduction reads the first `used` partials only)
+    const int used = tn_used_splits(R, g.splits, g.rows_per_split, g.few_splits);      // (the reduction reads the first `used` partials only)
     const uint32_t id = blockIdx.x - first;
     const bool large = !tn_narrow(g) && tn_product_tiles(g, 128) * used >= TN_LARGE_BLOCKS;
     if (g.A16) {
