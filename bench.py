@@ -346,20 +346,25 @@ def main():
     if bf16_products:
         # Layer 1 on a bf16 table: bf16 operands on the matrix cores. At 16x the fp32 matrix rate these two launches are
         # bound by their operands' bytes: bf16 rows + fp32 mean in, fp32 rows out (and the refreshed cache rows); for the
-        # weight gradients bf16 rows + fp32 mean + fp32 output gradient in, the partial tiles out (the launch, and so its time,
-        # carries the upper layers' fp32 weight gradients too, whose bytes and flops are not counted). Their matrix-core
-        # share is reported beside (flops over the bf16 peak).
+        # weight gradients bf16 rows + fp32 mean + fp32 output gradient in, the partial tiles out, and for the layers above,
+        # which the same launch carries, fp32 rows + mean + output gradient in and their partial tiles out. Their matrix-core
+        # share is reported beside (flops over the bf16 peak; the layers above take six bf16 products per fp32 one).
         FWD = "gemm_bf16_nn_kernel(l1 fwd)"
         n_refresh = mean([s_.n_refresh for s_ in stats]) if L >= 2 else 0.0
         H1 = w.dims[1]
         fwd_bytes = n_dst_bottom * (F * 2 + F * 4) + n_dst_bottom * H1 * 4 + n_refresh * H1 * 4
-        used_splits = min(64.0, max(1.0, n_dst_bottom / 256.0))
-        dw_bytes = n_dst_bottom * (F * 2 + F * 4 + H1 * 4) + used_splits * 2 * (F + 1) * H1 * 4
+        few_splits = lambda d_in, d_out: 256 // (-(-d_in // 64) * -(-d_out // 64) * 2)
+        used_splits = lambda rows, d_in, d_out: min(64.0, max(1.0, rows / 256.0, min(rows / 64.0, few_splits(d_in, d_out))))
+        partials = lambda rows, d_in, d_out: used_splits(rows, d_in, d_out) * 2 * (d_in + 1) * d_out * 4
+        dw_bytes = n_dst_bottom * (F * 2 + F * 4 + H1 * 4) + partials(n_dst_bottom, F, H1) + sum(
+            hop("n_dst", L - l) * (2 * w.dims[l - 1] + w.dims[l]) * 4 + partials(hop("n_dst", L - l), w.dims[l - 1], w.dims[l])
+            for l in range(2, L + 1))
         l1_flops = 2.0 * n_dst_bottom * 2 * F * H1
+        dw_bf16_flops = l1_flops + 6 * (gemm_dw_flops - gemm_fwd_flops)
         kern[FWD] = ("hbm", fwd_bytes / 1e9 / (ms["gemm_fwd_l1"] / 1e3), HBM_PEAK_GBPS, "GB/s", ms["gemm_fwd_l1"])
         kern[DW] = ("hbm", dw_bytes / 1e9 / (ms["gemm_dw_l1"] / 1e3), HBM_PEAK_GBPS, "GB/s", ms["gemm_dw_l1"])
         mfma_note = {FWD: round(l1_flops / 1e12 / (ms["gemm_fwd_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4),
-                     DW: round(l1_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4)}
+                     DW: round(dw_bf16_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4)}
     else:
         kern[FWD] = ("mfma", gemm_fwd_flops / 1e12 / (ms["gemm_fwd_l1"] / 1e3), MFMA_F32_PEAK_TFLOPS, "TFLOP/s", ms["gemm_fwd_l1"])
         # (six bf16 products per fp32 one)

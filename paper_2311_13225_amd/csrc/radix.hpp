@@ -6,7 +6,7 @@
 // ballot, stable), puts them in digit order in LDS and stores runs of equal digits contiguously.
 // Bound by memory: a pass has to read and write 8 bytes a pair and reads the keys once more for the counts. Stored straight
 // from the registers (no order in LDS, 16-pair runs at 4096-pair tiles) a pass took 3.4-4.2 ms on 124 M pairs; like this
-// 0.47-0.51 ms for the scatter (3.9 to 4.2 TB/s of the 4.6 a large copy reaches; 0.75 with the tiles dealt to the dies in turn) and
+// 0.47-0.51 ms for the scatter (3.9 to 4.2 TB/s of the 4.75 a large copy reaches; 0.75 with the tiles dealt to the dies in turn) and
 // 0.13 ms for the counts.
 #pragma once
 #include "primitives.hpp"

@@ -47,8 +47,9 @@ __device__ __forceinline__ void run_side_tasks(const NoSideTasks&) {}
 
 constexpr int SIDE_THREADS = 256;
 constexpr int SIDE_SCAN_ITEMS = 8, SIDE_SCAN_TILE = SIDE_THREADS * SIDE_SCAN_ITEMS;
-// Up to this many sources a scan block adds up all counts before its tile by itself (at most 8 round trips of eight 16-byte
-// loads a thread, 4 us for the last block); above, a launch of tile sums goes first.
+// Up to this many sources (by capacity: the hop's chain of tasks is laid down before any count is known) a scan block adds up
+// all counts before its tile by itself (at most 8 round trips of eight 16-byte loads a thread, 4 us for the last block); above, a
+// launch of tile sums goes first.
 constexpr int32_t SIDE_SCAN_ONE_LAUNCH = 65536;
 
 __device__ __forceinline__ int32_t sum4(const int4& v) { return (v.x + v.y) + (v.z + v.w); }
