@@ -61,7 +61,6 @@ struct no_blocks_s {
     no_cache_s* stamped_cache = nullptr;     // the cache whose versions the last split stamped (NULL: none)
     uint64_t stamped_uid = 0;                // ... its identity and the state of its contents when they were stamped
     uint64_t stamped_contents = 0;
-    bool scan_two_pass = false;              // the edge compaction of the next sampling call: two launches instead of one
     no::DevBuf<int32_t> compute_inv;         // [|V^1|]: index in the compute list of position i of V^1, -1 if served from the cache
     bool last_used_cache = false;
     // Side tasks (side.hpp) of the last call not launched yet: the next one of each hop (-1: none), the wipe of the id map

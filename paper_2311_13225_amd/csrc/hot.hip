@@ -88,14 +88,15 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(const RowT
             const int32_t i = i0 + (int32_t)threadIdx.x / G;
             const bool row_ok = i < n_dst;
             int32_t v = 0;
-            int64_t begin = 0, d = 0;
+            int64_t begin = 0;
+            uint32_t d = 0;
             if (row_ok) {
                 v = list[i];
                 begin = (int64_t)rowptr[v];
-                d = (int64_t)rowptr[v + 1] - begin;
+                d = (uint32_t)((int64_t)rowptr[v + 1] - begin);
             }
-            const int64_t pos = draw_position<G>(row_ok, v, d, k, j, key0, key1, c3);
-            const bool on = row_ok && j < k && (int64_t)j < d;
+            const uint32_t pos = draw_position<G>(row_ok, v, d, k, j, key0, key1, c3);
+            const bool on = row_ok && j < k && (uint32_t)j < d;
             visit(on, on ? col[begin + pos] : 0, keep);
         }
         __syncthreads();

@@ -58,7 +58,8 @@ __global__ void __launch_bounds__(256) sample_rows_kernel(const RowT* __restrict
     const int32_t j = (int32_t)(threadIdx.x % G);
     const bool row_ok = i < n_dst;
     int32_t v = 0;
-    int64_t begin = 0, d = 0;
+    int64_t begin = 0;
+    uint32_t d = 0;
     if (row_ok) {
         v = dst[i];
         if (insert_dst && (uint32_t)v >= (uint32_t)n_vertices) {
@@ -67,15 +68,15 @@ __global__ void __launch_bounds__(256) sample_rows_kernel(const RowT* __restrict
             *bad_id_flag = flag_value;
         }
         begin = (int64_t)rowptr[v];
-        d = (int64_t)rowptr[v + 1] - begin;
+        d = (uint32_t)((int64_t)rowptr[v + 1] - begin);
         if (j == 0) {
             src_global[i] = v;
             if (insert_dst) map[v] = i;       // a plain store and the atomicMin below commute: i is the smaller value
             if (seeds_copy) seeds_copy[i] = v;
         }
     }
-    const int64_t pos = draw_position<G>(row_ok, v, d, k, j, key0, key1, c3);
-    const int32_t cnt = d < (int64_t)k ? (int32_t)d : k;
+    const uint32_t pos = draw_position<G>(row_ok, v, d, k, j, key0, key1, c3);
+    const int32_t cnt = d < (uint32_t)k ? (int32_t)d : k;
     if (row_ok && j < k) {
         const int32_t q = i * k + j;
         if (j < cnt) {
@@ -197,31 +198,75 @@ __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __
     }
 }
 
-// One-launch form of the two kernels above (tile sums, then assignment): a single-pass scan. A block publishes its
-// tile's sum in a status word, adds up the words of the tiles before it until it meets one that already holds an
-// inclusive prefix, publishes its own inclusive prefix and assigns. (Workgroups are handed out in index order, per
+// One-launch form of the two kernels above (tile sums, then assignment), for scans of few tiles: a block publishes its
+// tile's sum in a status word, adds up the words of the tiles before it and assigns. (Workgroups are handed out in index order, per
 // die in turn: an earlier tile is done, running, or the next to start on its die, and a waiting block never holds
-// the slot an earlier tile needs.) A word packs both 31-bit counts and a 2-bit state, so it is written and read by one
+// the slot an earlier tile needs.) A word packs both 31-bit counts and a mark, so it is written and read by one
 // 64-bit access at device scope and needs no fence; the words are emptied by the sampling launch before. The wait on
 // an earlier tile is bounded: on expiry the block stores the call's id in `fail_flag` and goes on (wrong output, no hang;
 // the host reports NO_ERR_TIMEOUT wherever it next reads the blocks' counts).
-constexpr unsigned long long SCAN_SUM = 1ull, SCAN_PREFIX = 2ull;
-__device__ __forceinline__ unsigned long long scan_pack(int64_t v, unsigned long long state) {
-    return ((unsigned long long)(v & 0x7fffffffll)) | ((unsigned long long)((v >> 32) & 0x7fffffffll) << 31) | (state << 62);
+// ONE_LAUNCH_TILES: the one-launch form saves a launch (2.3 us and a second read of the slots) and pays for the wait, and for the atomics
+// in which the tiles count themselves, one after another on one address, 10 ns each. Measured, one launch / two,
+// us of sampling: two hops of 3 and 16 tiles 18.1 / 21.3; three hops of 15, 165 and 1005 tiles 87 (each tile a release, the walk back in
+// windows of 64), 80 (neither) / 75; 74 with the first hop alone in one launch.
+constexpr uint32_t ONE_LAUNCH_TILES = 32;
+constexpr unsigned long long SCAN_SUM = 1ull;
+__device__ __forceinline__ unsigned long long scan_pack(int64_t v) {
+    return ((unsigned long long)(v & 0x7fffffffll)) | ((unsigned long long)((v >> 32) & 0x7fffffffll) << 31) | (SCAN_SUM << 62);
 }
 __device__ __forceinline__ int64_t scan_unpack(unsigned long long w) {
     return (int64_t)(w & 0x7fffffffull) | ((int64_t)((w >> 31) & 0x7fffffffull) << 32);
 }
 
+struct ScanWait { unsigned long long* status; int32_t* fail_flag; int32_t flag_value, spin_limit, withhold_first; };
+
+// The sum of the tiles before `tile` (tile < ONE_LAUNCH_TILES), to all threads of the block; publishes this tile's word.
+__device__ __forceinline__ int64_t scan_look_back(const ScanWait& w, uint32_t tile, int64_t total, int64_t* prefix_sh) {
+    if (threadIdx.x < 64) {
+        const uint32_t lane = threadIdx.x;
+        // (withhold_first: test aid; tile 0 keeps its word back, so the tile after it must give up its wait)
+        if (lane == 0 && !(w.withhold_first && tile == 0))
+            __hip_atomic_store(&w.status[tile], scan_pack(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        unsigned long long word = 0ull;
+        if (lane < tile) {
+            int spins = 0;
+            while ((word = __hip_atomic_load(&w.status[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {
+                if (++spins > w.spin_limit) {
+                    __hip_atomic_store(w.fail_flag, w.flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        int64_t v = scan_unpack(word);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+        if (lane == 0) *prefix_sh = v;
+    }
+    __syncthreads();
+    return *prefix_sh;
+}
+
+// Whether this block is the last of n_tiles to come here (the answer is for thread 0; every block calls once, all its threads). What the
+// blocks stored with store_shared before is then in memory, and load_shared reads it: no release, which would write the
+// die's L2 back once a tile.
+__device__ __forceinline__ bool last_tile(unsigned long long* done, uint32_t n_tiles) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    return threadIdx.x == 0 && __hip_atomic_fetch_add(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_tiles - 1;
+}
+// Accesses past the dies' own caches, for words that the clean-up after an expired wait may write again from another die.
+__device__ __forceinline__ void store_shared(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+__device__ __forceinline__ int32_t load_shared(const int32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __restrict__ nbr_pad, int32_t* map,
                                                              const int32_t* d_n_dst, int32_t k, uint64_t k_magic,
-                                                             unsigned long long* status, int32_t* __restrict__ indptr,
+                                                             ScanWait wait, int32_t* __restrict__ indptr,
                                                              int32_t* __restrict__ nbr, int32_t* __restrict__ edge_row,
                                                              int32_t* __restrict__ src_global,
                                                              int32_t* counts /* [0]=n_dst (in), [1]=n_src, [2]=nnz */,
-                                                             int32_t* csc_cnt, int32_t n_zero, int32_t* fail_flag,
-                                                             int32_t flag_value, int32_t spin_limit, int32_t withhold_first,
-                                                             unsigned int* done, SideTasks side) {
+                                                             int32_t* csc_cnt, int32_t n_zero, unsigned long long* done,
+                                                             SideTasks side) {
     if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     __shared__ int64_t smem[ETHREADS / 64 + 1];
     __shared__ int64_t prefix_sh;
@@ -248,71 +293,29 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
     }
     int64_t total;
     int64_t run = block_exclusive_scan<int64_t, ETHREADS>(s, &total, smem);
-    if (threadIdx.x < 64) {
-        // wavefront 0 looks back 64 tiles at a time: lane l reads the word of tile (first - l)
-        const int lane = (int)threadIdx.x;
-        int64_t prefix = 0;
-        if (blockIdx.x > 0) {
-            if (lane == 0)
-                __hip_atomic_store(&status[blockIdx.x], scan_pack(total, SCAN_SUM), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t first = (int64_t)blockIdx.x - 1;      // nearest tile not yet added
-            int spins = 0;
-            while (first >= 0) {
-                const int64_t j = first - lane;
-                unsigned long long w = SCAN_PREFIX << 62;                      // lanes past tile 0: an empty prefix
-                if (j >= 0) w = __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned long long state = w >> 62;
-                const unsigned long long is_prefix = __ballot(state == SCAN_PREFIX), is_empty = __ballot(state == 0ull);
-                // usable lanes: those before the first empty word; the walk ends at the first prefix among them
-                const int n_ok = is_empty ? __builtin_ctzll(is_empty) : 64;
-                const int p_at = is_prefix ? __builtin_ctzll(is_prefix) : 64;
-                const int take = p_at < n_ok ? p_at + 1 : n_ok;               // lanes [0, take) are added
-                int64_t v = lane < take ? scan_unpack(w) : 0;
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-                prefix += v;
-                first -= take;
-                if (p_at < n_ok) break;                                       // reached an inclusive prefix
-                if (take == 0) {
-                    if (++spins > spin_limit) {
-                        if (lane == 0) __hip_atomic_store(fail_flag, flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-            }
-        }
-        if (lane == 0) {
-            // (withhold_first: test aid; tile 0 keeps its word back, so the tile after it must give up its wait)
-            if (!(withhold_first && blockIdx.x == 0))
-            __hip_atomic_store(&status[blockIdx.x], scan_pack(prefix + total, SCAN_PREFIX), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            prefix_sh = prefix;
-            if (base + ETILE >= n_pad) {      // the last tile holds the totals
-                const int64_t all = prefix + total;
-                const int32_t nnz = (int32_t)(all & 0xffffffffll), n_new = (int32_t)(all >> 32);
-                indptr[n_dst] = nnz;
-                counts[1] = n_dst + n_new;
-                counts[2] = nnz;
-            }
-        }
+    const int64_t prefix = scan_look_back(wait, blockIdx.x, total, &prefix_sh);
+    run += prefix;
+    if (threadIdx.x == 0 && base + ETILE >= n_pad) {      // the last tile holds the totals
+        const int64_t all = prefix + total;
+        const int32_t nnz = (int32_t)(all & 0xffffffffll), n_new = (int32_t)(all >> 32);
+        store_shared(&indptr[n_dst], nnz);
+        store_shared(&counts[1], n_dst + n_new);
+        store_shared(&counts[2], nnz);
     }
-    __syncthreads();
-    run += prefix_sh;
 #pragma unroll
     for (int t = 0; t < EITEMS; ++t) {
         const int64_t q = q0 + t;
         if (q < n_pad) {
             const int32_t e = (int32_t)(run & 0xffffffffll);
             const int32_t row = k == 1 ? (int32_t)q : (int32_t)__umul64hi((uint64_t)q, k_magic);   // q / k, exact
-            if (q - (int64_t)row * k == 0) indptr[row] = e;
+            if (q - (int64_t)row * k == 0) store_shared(&indptr[row], e);
             if (f[t] & 1) {
                 nbr[e] = u[t];
                 edge_row[e] = row;
                 if (f[t] >> 32) {
                     const int32_t local = n_dst + (int32_t)(run >> 32);
                     src_global[local] = u[t];
-                    map[u[t]] = local;     // only the first occurrence writes; later readers never match n_dst + q
+                    store_shared(&map[u[t]], local);     // only the first occurrence writes; later readers never match n_dst + q
                 }
             }
             run += f[t];
@@ -321,20 +324,16 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
     // A wait that expired leaves wrong prefixes behind, and kernels after this one would follow them out of their
     // arrays. The tile that finishes last therefore checks the flag and, if it is raised, turns the hop into a
     // consistent empty block: no edges, no new sources, and no entry of this hop left in the id map.
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int n_tiles = (unsigned int)((n_pad + ETILE - 1) / ETILE);
-        const bool last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n_tiles - 1;
-        cleanup_sh = last && __hip_atomic_load(fail_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == flag_value;
-    }
+    const bool last = last_tile(done, (uint32_t)((n_pad + ETILE - 1) / ETILE));
+    if (threadIdx.x == 0) cleanup_sh = last && load_shared(wait.fail_flag) == wait.flag_value;
     __syncthreads();
     if (cleanup_sh) {
         for (int64_t q = threadIdx.x; q < n_pad; q += ETHREADS) {
             const int32_t v = nbr_pad[q];
-            if (v >= 0 && map[v] >= n_dst) map[v] = EMPTY;      // (entries below n_dst belong to the destinations)
+            if (v >= 0 && load_shared(&map[v]) >= n_dst) store_shared(&map[v], EMPTY);      // (entries below n_dst belong to the destinations)
         }
-        for (int32_t r = (int32_t)threadIdx.x; r <= n_dst; r += ETHREADS) indptr[r] = 0;
-        if (threadIdx.x == 0) { counts[1] = n_dst; counts[2] = 0; }
+        for (int32_t r = (int32_t)threadIdx.x; r <= n_dst; r += ETHREADS) store_shared(&indptr[r], 0);
+        if (threadIdx.x == 0) { store_shared(&counts[1], n_dst); store_shared(&counts[2], 0); }
     }
 }
 
@@ -488,7 +487,8 @@ __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* _
 // the split re-keys that map, so every tile block waits, before its map writes, until a counter says that all index
 // blocks with work have read (they come first in index order and take two round trips, the probe takes four: the
 // wait is there for correctness, not because it is ever long).
-__global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, const int32_t* d_n_v1, unsigned long long* status,
+constexpr int IDX_ITEMS = 4;      // edges a thread: a quarter of the blocks that count themselves in one word, 10 ns apart
+__global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, const int32_t* d_n_v1, ScanWait wait,
                                                             uint32_t idx_blocks, const int32_t* d_nnz,
                                                             const int32_t* __restrict__ nbr, int32_t* map,
                                                             int32_t* __restrict__ indices, int32_t* csc_cnt, int32_t* csc_pos,
@@ -497,26 +497,31 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
                                                             int32_t* hit_pos, int32_t* hit_slot,
                                                             int32_t* extra /* n_compute, n_hit, -, -, n_refresh */,
                                                             int32_t* version, int32_t stamp, int32_t* refresh_old,
-                                                            int32_t* fail_flag, int32_t flag_value, int32_t spin_limit,
-                                                            int32_t withhold_first, unsigned int* done, int32_t csc_len,
+                                                            unsigned long long* done, int32_t csc_len,
                                                             int32_t* above_nnz, int32_t* above_indptr,
                                                             const int32_t* above_n_dst, SideTasks side) {
     if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (blockIdx.x < idx_blocks) {
-        const int64_t e = (int64_t)blockIdx.x * ETHREADS + threadIdx.x;
         const int32_t nnz = *d_nnz;
-        if ((int64_t)blockIdx.x * ETHREADS >= nnz) return;      // (whole block: no work, no signal)
-        if (e < nnz) {
-            const int32_t local = map[nbr[e]];
-            indices[e] = local;
+        const int64_t e0 = (int64_t)blockIdx.x * (ETHREADS * IDX_ITEMS) + threadIdx.x;
+        if (e0 - threadIdx.x >= nnz) return;      // (whole block: no work, no signal)
+        int32_t local[IDX_ITEMS];
+#pragma unroll
+        for (int t = 0; t < IDX_ITEMS; ++t) local[t] = e0 + t * ETHREADS < nnz ? map[nbr[e0 + t * ETHREADS]] : 0;
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // every map read of the block has returned
+        __syncthreads();
+        if (threadIdx.x == 0) __hip_atomic_fetch_add(idx_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int t = 0; t < IDX_ITEMS; ++t) {
+            const int64_t e = e0 + t * ETHREADS;
+            if (e >= nnz) continue;
+            indices[e] = local[t];
             // (the range check only matters after an expired wait, when the split may have re-keyed the map already)
-            if (csc_cnt && (uint32_t)local < (uint32_t)csc_len) {      // integer count: order independent
-                const int32_t pos = atomicAdd(&csc_cnt[local], 1);
+            if (csc_cnt && (uint32_t)local[t] < (uint32_t)csc_len) {      // integer count: order independent
+                const int32_t pos = atomicAdd(&csc_cnt[local[t]], 1);
                 if (csc_pos) csc_pos[e] = pos;
             }
         }
-        __syncthreads();      // every map read of the block has returned (its value went into a store)
-        if (threadIdx.x == 0) __hip_atomic_fetch_add(idx_done, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
         return;
     }
     const uint32_t tile = blockIdx.x - idx_blocks;
@@ -544,63 +549,24 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
     }
     int64_t total;
     int64_t run = block_exclusive_scan<int64_t, ETHREADS>(s, &total, smem);
-    if (threadIdx.x < 64) {
-        const int lane = (int)threadIdx.x;
-        int64_t prefix = 0;
-        if (tile > 0) {
-            if (lane == 0)
-                __hip_atomic_store(&status[tile], scan_pack(total, SCAN_SUM), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            int64_t first = (int64_t)tile - 1;
-            int spins = 0;
-            while (first >= 0) {
-                const int64_t j = first - lane;
-                unsigned long long w = SCAN_PREFIX << 62;
-                if (j >= 0) w = __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                const unsigned long long state = w >> 62;
-                const unsigned long long is_prefix = __ballot(state == SCAN_PREFIX), is_empty = __ballot(state == 0ull);
-                const int n_ok = is_empty ? __builtin_ctzll(is_empty) : 64;
-                const int p_at = is_prefix ? __builtin_ctzll(is_prefix) : 64;
-                const int take = p_at < n_ok ? p_at + 1 : n_ok;
-                int64_t val = lane < take ? scan_unpack(w) : 0;
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) val += __shfl_xor(val, o, 64);
-                prefix += val;
-                first -= take;
-                if (p_at < n_ok) break;
-                if (take == 0) {
-                    if (++spins > spin_limit) {
-                        if (lane == 0) __hip_atomic_store(fail_flag, flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        break;
-                    }
-                    __builtin_amdgcn_s_sleep(1);
-                }
-            }
-        }
-        if (lane == 0) {
-            if (!(withhold_first && tile == 0))
-            __hip_atomic_store(&status[tile], scan_pack(prefix + total, SCAN_PREFIX), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            prefix_sh = prefix;
-            if (base + ETILE >= n) {      // the last tile holds the totals
-                const int64_t all = prefix + total;
-                const int32_t n_compute = (int32_t)(all & 0xffffffffll);
-                extra[0] = n_compute;
-                extra[1] = (int32_t)n - n_compute;
-                extra[4] = (int32_t)(all >> 32);
-            }
-        }
-    }
+    const int64_t prefix = scan_look_back(wait, tile, total, &prefix_sh);
     if (threadIdx.x == 0) {
-        const int32_t nnz = *d_nnz;
-        const unsigned int expected = (unsigned int)((nnz + ETHREADS - 1) / ETHREADS);
+        if (base + ETILE >= n) {      // the last tile holds the totals
+            const int64_t all = prefix + total;
+            const int32_t n_compute = (int32_t)(all & 0xffffffffll);
+            store_shared(&extra[0], n_compute);
+            store_shared(&extra[1], (int32_t)n - n_compute);
+            store_shared(&extra[4], (int32_t)(all >> 32));
+        }
+        const unsigned int expected = (unsigned int)(((int64_t)*d_nnz + ETHREADS * IDX_ITEMS - 1) / (ETHREADS * IDX_ITEMS));
         int spins = 0;
-        while (__hip_atomic_load(idx_done, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_AGENT) < expected) {
-            if (++spins > spin_limit) { __hip_atomic_store(fail_flag, flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); break; }
+        while (__hip_atomic_load(idx_done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < expected) {
+            if (++spins > wait.spin_limit) { store_shared(wait.fail_flag, wait.flag_value); break; }
             __builtin_amdgcn_s_sleep(1);
         }
     }
     __syncthreads();
-    run = (run & 0xffffffffll) + (prefix_sh & 0xffffffffll);
+    run = (run & 0xffffffffll) + (prefix & 0xffffffffll);
 #pragma unroll
     for (int t = 0; t < EITEMS; ++t) {
         const int64_t i = i0 + t;
@@ -616,13 +582,13 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
                     version[rslot] = stamp;
                 }
                 compute_list[run] = v[t];
-                map[v[t]] = (int32_t)run;
+                store_shared(&map[v[t]], (int32_t)run);
             } else {
                 const int64_t p = i - run;
                 hit_pos[p] = (int32_t)i;
                 compute_inv[i] = -1;
                 hit_slot[p] = slot[t];
-                map[v[t]] = EMPTY;
+                store_shared(&map[v[t]], EMPTY);
             }
             run += c;
         }
@@ -631,18 +597,14 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
     // their readers) cannot be trusted. The tile that finishes last then leaves a consistent state that no later
     // kernel can follow out of its arrays: nothing to compute, nothing reused, no edges in the hop above, and no
     // entry of V^1 left in the id map. (Versions already stamped stay stamped: the caller is told to invalidate.)
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        const unsigned int n_tiles = (unsigned int)((n + ETILE - 1) / ETILE);
-        const bool last = __hip_atomic_fetch_add(done, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == n_tiles - 1;
-        cleanup_sh = last && __hip_atomic_load(fail_flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == flag_value;
-    }
+    const bool last = last_tile(done, (uint32_t)((n + ETILE - 1) / ETILE));
+    if (threadIdx.x == 0) cleanup_sh = last && load_shared(wait.fail_flag) == wait.flag_value;
     __syncthreads();
     if (cleanup_sh) {
-        for (int64_t i = threadIdx.x; i < n; i += ETHREADS) map[probe.v1[i]] = EMPTY;
+        for (int64_t i = threadIdx.x; i < n; i += ETHREADS) store_shared(&map[probe.v1[i]], EMPTY);
         const int32_t nd = *above_n_dst;
         for (int32_t r = (int32_t)threadIdx.x; r <= nd; r += ETHREADS) above_indptr[r] = 0;
-        if (threadIdx.x == 0) { extra[0] = 0; extra[1] = 0; extra[4] = 0; *above_nnz = 0; }
+        if (threadIdx.x == 0) { store_shared(&extra[0], 0); store_shared(&extra[1], 0); store_shared(&extra[4], 0); *above_nnz = 0; }
     }
 }
 
@@ -661,6 +623,9 @@ __global__ void unstamp_kernel(const int32_t* __restrict__ refresh_slot, const i
 // ---------------------------------------------------------------------------- host side
 
 static inline int64_t edge_tiles(int64_t n_pad_cap) { int64_t t = ceil_div(n_pad_cap, ETILE); return t < 1 ? 1 : t; }
+// words of one scan: a word a tile (status words, or the sums of the two-launch form), then the counter of finished tiles
+static inline int64_t scan_words(int64_t n_pad_cap) { return edge_tiles(n_pad_cap) + 1; }
+static inline bool scan_one_launch(int64_t n_pad_cap) { return edge_tiles(n_pad_cap) <= ONE_LAUNCH_TILES; }
 // does this hop count the edges that leave each source (for its transpose, or for the symmetric normalisation)?
 static inline bool counts_sources(const no_blocks_s* b, const HopBuffers& H) { return H.has_csc || b->count_sources; }
 
@@ -746,6 +711,11 @@ int32_t blocks_finish(no_blocks_s* b, hipStream_t st) {
     return launch_status("side tasks");
 }
 
+static ScanWait scan_wait(no_blocks_s* b, unsigned long long* status) {
+    const ScanWaitDebug dbg = scan_wait_debug();
+    return ScanWait{status, b->counts.p + 4 * b->n_layers + 6, b->call_id, dbg.spin_limit, dbg.withhold_first_tile};
+}
+
 template <typename RowT>
 static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b, int32_t h, const int32_t* d_dst,
                           const int32_t* d_n_dst_in, int32_t n_fixed, bool insert_dst, uint32_t key0, uint32_t key1,
@@ -768,7 +738,7 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
                        rowptr, col, d_dst, d_n_dst_in, n_fixed, H.n_dst_cap, k, key0, key1, c3, H.nbr_pad.p,               \
                        H.src_global.p, b->map.p, insert_dst ? 1 : 0, seeds_copy, cnt, (int32_t)b->n_vertices,               \
                        b->counts.p + 4 * b->n_layers + 5, b->call_id, (unsigned long long*)b->ws.p,                          \
-                       (int32_t)edge_tiles(H.nnz_cap) + 1 + extra_status, zero_extra, side)
+                       (int32_t)scan_words(H.nnz_cap) + extra_status, zero_extra, side)
     if (k <= 8) { NO_LAUNCH_SAMPLE(8); }
     else if (k <= 16) { NO_LAUNCH_SAMPLE(16); }
     else if (k <= 32) { NO_LAUNCH_SAMPLE(32); }
@@ -776,14 +746,9 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
 #undef NO_LAUNCH_SAMPLE
     const unsigned tiles = (unsigned)edge_tiles(H.nnz_cap);
     const uint64_t k_magic = k > 1 ? (~0ull / (uint64_t)k) + 1ull : 0ull;     // ceil(2^64 / k)
-    // One launch where the sampling has the chip to itself or nearly so; two where it runs beside another batch's
-    // products (sampling ahead): there the single-pass blocks, which wait on their predecessors while holding a slot,
-    // measured slower than two short launches.
-    const bool two_pass = b->scan_two_pass;
-    const ScanWaitDebug dbg = scan_wait_debug();
     const int32_t n_zero = counts_sources(b, H) ? H.n_src_cap + 1 : 0;
     side_take(b, tiles, &side);
-    if (two_pass) {
+    if (!scan_one_launch(H.nnz_cap)) {
         hipLaunchKernelGGL(edge_tile_sums_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, H.nbr_pad.p,
                            (const int32_t*)b->map.p, (const int32_t*)cnt, k, tile_sums, H.csc_cnt.p, n_zero, side);
         side_take(b, tiles, &side);
@@ -792,20 +757,11 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
                            H.edge_row.p, H.src_global.p, cnt, side);
     } else {
         hipLaunchKernelGGL(edge_scan_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p,
-                           b->map.p, (const int32_t*)cnt, k, k_magic, (unsigned long long*)b->ws.p, H.indptr.p, H.nbr_global.p,
-                           H.edge_row.p, H.src_global.p, cnt, H.csc_cnt.p, n_zero, b->counts.p + 4 * b->n_layers + 6, b->call_id,
-                           dbg.spin_limit, dbg.withhold_first_tile, (unsigned int*)((unsigned long long*)b->ws.p + tiles), side);
+                           b->map.p, (const int32_t*)cnt, k, k_magic, scan_wait(b, (unsigned long long*)b->ws.p), H.indptr.p, H.nbr_global.p,
+                           H.edge_row.p, H.src_global.p, cnt, H.csc_cnt.p, n_zero, (unsigned long long*)b->ws.p + tiles, side);
     }
     b->side_next[h] = SIDE_INDICES;
     return launch_status("sample_hop");
-}
-
-// One launch for the V^1 split where the sampling has the chip to itself, two launches where it runs beside another
-// batch's products, as for the edge compaction and for the same reason (measured on a V^1 of five tiles: sampling alone
-// 72 -> 68 us in one launch, but 2 % fewer steps per second when sampling ahead).
-static bool v1_one_launch(const no_blocks_s* b, unsigned tiles) {
-    (void)tiles;
-    return !b->scan_two_pass;
 }
 
 int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seeds, uint64_t stream_key, uint32_t domain,
@@ -837,20 +793,18 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
             const unsigned tiles = (unsigned)edge_tiles(P.n_src_cap);
             const unsigned idx_blocks = (unsigned)ceil_div(P.nnz_cap, ETHREADS);
             int64_t* tile_sums = (int64_t*)b->ws.p;
-            if (v1_one_launch(b, tiles)) {
-                const ScanWaitDebug dbg = scan_wait_debug();
-                // (status words and the counter behind them: emptied by the sampling launch of hop L-2, past its own)
-                // (word edge_tiles(P.nnz_cap) is the completion counter of hop L-2's edge scan)
-                unsigned long long* v1_status = (unsigned long long*)b->ws.p + edge_tiles(P.nnz_cap) + 1;
+            if (scan_one_launch(P.n_src_cap)) {
+                // (its words, and behind them the counter of index blocks: emptied by the sampling launch of hop L-2, past its own)
+                unsigned long long* v1_status = (unsigned long long*)b->ws.p + scan_words(P.nnz_cap);
+                const unsigned idx_blocks = (unsigned)ceil_div(P.nnz_cap, ETHREADS * IDX_ITEMS);
                 side_take(b, idx_blocks + tiles, &side);
-                hipLaunchKernelGGL(v1_split_kernel, dim3(side.first_block + side.side_blocks()), dim3(ETHREADS), 0, st, probe, d_n, v1_status,
-                                   idx_blocks, (const int32_t*)(b->counts.p + 4 * (h - 1) + 2), (const int32_t*)P.nbr_global.p,
+                hipLaunchKernelGGL(v1_split_kernel, dim3(side.first_block + side.side_blocks()), dim3(ETHREADS), 0, st, probe, d_n,
+                                   scan_wait(b, v1_status), idx_blocks, (const int32_t*)(b->counts.p + 4 * (h - 1) + 2), (const int32_t*)P.nbr_global.p,
                                    b->map.p, P.indices.p, counts_sources(b, P) ? P.csc_cnt.p : nullptr,
-                                   P.has_csc ? P.csc_dst.p : nullptr, (unsigned int*)(v1_status + tiles),
+                                   P.has_csc ? P.csc_dst.p : nullptr, (unsigned int*)(v1_status + scan_words(P.n_src_cap)),
                                    b->compute_list.p, b->compute_pos.p, b->compute_inv.p, b->refresh_slot.p, b->hit_pos.p,
                                    b->hit_slot.p, extra, stamp_refresh ? cache->version.p : nullptr, (int32_t)step,
-                                   b->refresh_old.p, b->counts.p + 4 * b->n_layers + 6, b->call_id, dbg.spin_limit,
-                                   dbg.withhold_first_tile, (unsigned int*)(v1_status + tiles + 1), P.n_src_cap + 1,
+                                   b->refresh_old.p, v1_status + tiles, P.n_src_cap + 1,
                                    b->counts.p + 4 * (h - 1) + 2, P.indptr.p, (const int32_t*)(b->counts.p + 4 * (h - 1)), side);
             } else {
             side_take(b, tiles + idx_blocks, &side);
@@ -873,8 +827,8 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
         }
         int32_t* zero_extra = h == 0 && !use_cache ? extra : nullptr;
         // the hop above the bottom one also empties the status words of the V^1 split that follows it
-        const int32_t extra_status = (use_cache && h == L - 2 && v1_one_launch(b, (unsigned)edge_tiles(b->hop[h].n_src_cap)))
-                                         ? (int32_t)edge_tiles(b->hop[h].n_src_cap) + 2 : 0;
+        const int32_t extra_status = (use_cache && h == L - 2 && scan_one_launch(b->hop[h].n_src_cap))
+                                         ? (int32_t)scan_words(b->hop[h].n_src_cap) + 1 : 0;
         if (g->rowptr_bits == 64)
             NO_CHECK(sample_hop<int64_t>(g->rowptr64.p, g->col.p, b, h, d_dst, d_n, n_seeds, h == 0, key0, key1, domain, st,
                                          zero_extra, extra_status));
@@ -958,7 +912,7 @@ int32_t blocks_create_impl(no_graph_s* g, int32_t n_seeds_cap, const int32_t* fa
     NO_CHECK(b->map.alloc((size_t)g->n_vertices));
     NO_CHECK(fill_i32(b->map.p, EMPTY, g->n_vertices, nullptr));
     const int64_t max_items = max_pad > max_src ? max_pad : max_src;
-    NO_CHECK(b->ws.alloc((size_t)(2 * edge_tiles(max_items + 1) + 8) * sizeof(int64_t)));      // two sets of status words and their counters
+    NO_CHECK(b->ws.alloc((size_t)(2 * scan_words(max_items + 1) + 8) * sizeof(int64_t)));      // the words of two scans, and a counter
     if (n_layers >= 2) {
         size_t v1_cap = (size_t)b->hop[n_layers - 2].n_src_cap;
         NO_CHECK(b->compute_list.alloc(v1_cap));

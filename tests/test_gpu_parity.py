@@ -330,6 +330,30 @@ def test_sample_blocks_with_cache_lookup():
     assert total_hits > 0
 
 
+@pytest.mark.parametrize("V,batch", [
+    (40_000, 1024),       # 31 tiles of slots, 32 of V^1 (32768 sources at most): both scans in one launch
+    (40_000, 1025),       # 32 and 33: the split of V^1 in two launches
+    (31_668, 1100),       # 34 and 32: the compaction in two
+    (40_000, 1100)])      # 34 and 35: both in two
+def test_sample_blocks_scans_in_one_launch_and_in_two(V, batch):
+    b = nb()
+    fanouts = (31, 3)
+    src, dst, og, gg = make_graph(V, 40 * V, 3, 32)
+    train = si.train_split(V, 0.65, 3)
+    oc = ora.select_hot(og, train[:4096], 1024, fanouts, 1, 0.2, 2, 8, 0)
+    gc = b.no_select_hot(gg, dev(train[:4096]), 1024, fanouts, 1, 0.2, 2, 8, 0)
+    ver = np.random.default_rng(1).integers(-1, 6, oc.n_hot).astype(np.int32)
+    oc.version[:] = ver
+    b.no_cache_view(gc, V)["version"].copy_(dev(ver))
+    blocks = b.no_blocks_create(gg, batch, fanouts)
+    for step, n in [(5, batch), (6, batch - 37), (7, 1)]:
+        seeds = train[:n].copy()
+        print("V %d, %d of %d seeds" % (V, n, batch), flush=True)
+        for with_cache in (True, False):
+            b.no_sample_blocks(gg, dev(seeds), 0, step, gc if with_cache else None, blocks)
+            compare_blocks(b, blocks, ora.sample_blocks(og, seeds, fanouts, 0, step, oc if with_cache else None), with_cache=with_cache)
+
+
 # --------------------------------------------------------------------------------------- gather
 
 @pytest.mark.parametrize("dim,dtype", [(64, "f32"), (602, "f32"), (100, "f32"), (7, "f32"), (256, "f32"),
