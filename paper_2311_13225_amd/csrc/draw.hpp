@@ -75,4 +75,27 @@ __device__ __forceinline__ uint32_t draw_position(bool row_ok, int32_t v, uint32
     return shuffle ? pos : (uint32_t)j;
 }
 
+// All slots of a row by one thread (k <= K): positions of a draw of k of the row's d > k entries. The steps in order: step j
+// finds in its own position, and in its partner's, what the latest step that had that position for a partner put there. (That is always
+// one of the first k positions: a byte.)
+template <int K>
+__device__ __forceinline__ void draw_row(int32_t v, uint32_t d, int32_t k, uint32_t key0, uint32_t key1, uint32_t c3, uint32_t (&pos)[K]) {
+    uint32_t r[K], put[K / 4];
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if (j < k) {
+            r[j] = swap_partner(philox_random64(key0, key1, (uint32_t)v, 0u, (uint32_t)j, c3), d, (uint32_t)j);
+            uint32_t mine = (uint32_t)j, p = r[j];
+#pragma unroll
+            for (int t = 0; t < j; ++t) {
+                const uint32_t pt = (put[t / 4] >> (8 * (t & 3))) & 0xffu;
+                mine = r[t] == (uint32_t)j ? pt : mine;
+                p = r[t] == r[j] ? pt : p;
+            }
+            pos[j] = p;
+            put[j / 4] = (j & 3) == 0 ? mine : put[j / 4] | mine << (8 * (j & 3));
+        }
+    }
+}
+
 }  // namespace no

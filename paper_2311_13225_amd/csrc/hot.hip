@@ -3,6 +3,7 @@
 // the hot set is the top floor(fraction * V) by (count descending, id ascending).
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 #include <unordered_set>
 #include "primitives.hpp"
 #include "draw.hpp"
@@ -27,30 +28,175 @@ __global__ void count_members_kernel(const int32_t* ids, const int32_t* d_n, int
 }
 
 // One workgroup pre-samples one whole batch, all hops in one launch: V^1 is only wanted as a set, so a vertex is a bit of the
-// batch's bitmap (workgroup-scope atomics: they end in the L2 of the die the workgroup runs on) and the order in which the
-// lanes meet it does not matter; the draws themselves depend on nothing but (stream, vertex, slot, hop). Hops above the last
-// also append every vertex they meet for the first time to the batch's list, the destinations of the next hop.
-// Batches are independent, so as many workgroups run as there are batches in a group (train ids job % n_batches).
-// Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
-// unit. Measured (2.4 M vertices, 124 M edges, 1523 batches of 1024 seeds, fanouts 15 and 10): no_select_hot 117 ms with the
-// batches one after another through the training sampler, 4.3 ms like this; a group of 508 batches takes 1.26 ms and moves 3.7 GB (64-byte
-// sectors of column entries, bitmap lines in and out).
+// batch's bitmap and the order in which the lanes meet it does not matter; the draws themselves depend on nothing but (stream, vertex,
+// slot, hop). Hops above the last also append every vertex they meet for the first time to the batch's list, the destinations of
+// the next hop. Batches are independent (train ids job % n_batches): workgroups take them in turn.
+//
+// The bitmap stands in LDS, in up to PRESAMPLE_RANGES parts of PRESAMPLE_RANGE vertices one after the other: a vertex of a later part
+// waits in the `later` list while the first part is filled (4 bytes written and read in order; as a bit of a bitmap in memory it
+// was a 64-byte sector read and written at random, and those were 60 % of the 52 M L2 misses of 508 batches). A thread draws whole
+// rows, whose column entries it requests together.
+// Measured (2.4 M vertices, 124 M edges, 1523 batches of 1024 seeds, fanouts 15 and 10), the pre-sampling alone: 3774 us with
+// the bitmaps in memory, 1665 like this (278 us a batch and compute unit); it reads 47 G random sectors a second of the 54 G that independent
+// 4-byte reads from 1 GB reach here.
 constexpr int PRESAMPLE_THREADS = 1024;
+constexpr int PRESAMPLE_RANGE = 152 * 1024 * 8;      // vertices; 152 of the 160 KB of a compute unit
+constexpr int PRESAMPLE_RANGES = 4;
+constexpr int PRESAMPLE_WORKERS = 256;               // workgroups of a launch: one a compute unit
+constexpr int64_t PRESAMPLE_LIST_WORDS = 2ll << 28;  // and what their lists may take together (2 GiB; above, batches are few and large)
 struct PresampleHops { int32_t fanout[NO_MAX_LAYERS]; int32_t n; };
+// The batches of one launch: train ids, streams, and the vertices' range.
+struct PresampleJobs {
+    const int32_t* train; int64_t n_train; int32_t batch; int64_t n_batches, first_job; int32_t n_jobs; uint64_t seed; PresampleHops hops;
+    int32_t n_vertices; int32_t* bad_flag;
+};
+
+template <int K, typename RowT>
+__global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_lds_kernel(PresampleJobs in, const RowT* __restrict__ rowptr,
+                                                                          const int32_t* __restrict__ col, uint32_t* __restrict__ bitmaps,
+                                                                          int64_t words, int32_t range, int32_t n_ranges, int32_t* lists,
+                                                                          int64_t list_cap, int32_t* laters, int64_t later_cap) {
+    extern __shared__ __attribute__((aligned(16))) uint32_t bits[];      // the current part's bitmap
+    __shared__ int32_t n_list, n_later;
+    int32_t* list = lists + (int64_t)blockIdx.x * list_cap;
+    int32_t* later = laters + (int64_t)blockIdx.x * later_cap;
+    const int lane = lane_id(), tid = (int)threadIdx.x;
+    const int32_t range_words = range / 32;
+    auto clear = [&] {
+        for (int32_t w = tid; w < range_words / 4; w += PRESAMPLE_THREADS) reinterpret_cast<uint4*>(bits)[w] = make_uint4(0u, 0u, 0u, 0u);
+        __syncthreads();
+    };
+    // the list's first n entries that lie in the part from `lo` on
+    auto mark_list = [&](int32_t n, int32_t lo) {
+        for (int32_t i = tid; i < n; i += PRESAMPLE_THREADS) {
+            const uint32_t at = (uint32_t)(list[i] - lo);
+            if (at < (uint32_t)range) atomicOr(&bits[at >> 5], 1u << (at & 31));
+        }
+        __syncthreads();
+    };
+    auto append = [&](bool on, int32_t u, int32_t* to, int32_t* count) {      // (every lane of the wavefront; one counter access for it)
+        const uint64_t m = __ballot(on);
+        int32_t at = 0;
+        if (m && lane == 0) at = atomicAdd(count, __popcll(m));
+        at = __builtin_amdgcn_readfirstlane(at);
+        if (on) to[at + __popcll(m & ((1ull << lane) - 1ull))] = u;
+    };
+    // a vertex of the part from `lo` on: marked, and where it was not marked before and `keep`, it joins the list
+    auto visit = [&](bool on, int32_t u, int32_t lo, bool keep) {
+        const uint32_t at = (uint32_t)(u - lo), bit = 1u << (at & 31);
+        if (!keep) {
+            if (on) atomicOr(&bits[at >> 5], bit);
+            return;
+        }
+        const bool fresh = on && !(atomicOr(&bits[at >> 5], bit) & bit);
+        append(fresh, u, list, &n_list);
+    };
+    for (int32_t b = (int32_t)blockIdx.x; b < in.n_jobs; b += (int32_t)gridDim.x) {
+        const int64_t job = in.first_job + b, first = (job % in.n_batches) * in.batch;
+        const int32_t n_seeds = (int32_t)min((int64_t)in.batch, in.n_train - first);
+        uint32_t* out = bitmaps + (int64_t)b * words;
+        const uint64_t key = in.seed + (uint64_t)job;
+        const uint32_t key0 = (uint32_t)key, key1 = (uint32_t)(key >> 32);
+        __syncthreads();                              // (the batch before is done with the counters)
+        if (tid == 0) n_list = 0;
+        for (int32_t stage = 0; stage <= in.hops.n; ++stage) {      // the seeds, then the hops
+            const bool keep = stage < in.hops.n;
+            if (tid == 0) n_later = 0;
+            if (stage == 0 || n_ranges > 1) clear(); else __syncthreads();
+            const int32_t n_before = n_list;
+            if (n_ranges > 1) mark_list(n_before, 0);
+            __syncthreads();                          // (everybody has read the count before it grows)
+            if (stage == 0) {
+                for (int32_t i0 = 0; i0 < n_seeds; i0 += PRESAMPLE_THREADS) {
+                    const int32_t i = i0 + tid;
+                    const int32_t v = i < n_seeds ? in.train[first + i] : 0;
+                    const bool ok = i < n_seeds && (uint32_t)v < (uint32_t)in.n_vertices;
+                    if (i < n_seeds && !ok) *in.bad_flag = 1;       // never followed; the caller gets an error and no cache
+                    visit(ok && v < range, v, 0, true);
+                    if (n_ranges > 1) append(ok && v >= range, v, later, &n_later);
+                }
+            } else {
+                const int32_t h = stage - 1, k = in.hops.fanout[h];
+                const uint32_t c3 = (1u << 8) | (uint32_t)h;
+                for (int32_t i0 = 0; i0 < n_before; i0 += PRESAMPLE_THREADS) {
+                    const int32_t i = i0 + tid;
+                    int64_t begin = 0;
+                    uint32_t d = 0;
+                    int32_t v = 0;
+                    if (i < n_before) {
+                        v = list[i];
+                        begin = (int64_t)rowptr[v];
+                        d = (uint32_t)((int64_t)rowptr[v + 1] - begin);
+                    }
+                    uint32_t pos[K];
+#pragma unroll
+                    for (int j = 0; j < K; ++j) pos[j] = (uint32_t)j;
+                    if (d > (uint32_t)k) draw_row<K>(v, d, k, key0, key1, c3, pos);
+                    const int32_t n = (int32_t)min(d, (uint32_t)k);
+                    int32_t n_out = 0;
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {      // (the vertex in the place of its position)
+                        pos[j] = j < n ? (uint32_t)col[begin + pos[j]] : ~0u;
+                        if (K > 16 && j % 8 == 7) __builtin_amdgcn_sched_barrier(0);      // (not all the addresses at a time: they spill)
+                    }
+#pragma unroll
+                    for (int j = 0; j < K; ++j) {
+                        if (j < k) visit(pos[j] < (uint32_t)range, (int32_t)pos[j], 0, keep);
+                        n_out += (int32_t)pos[j] >= range ? 1 : 0;
+                    }
+                    if (n_ranges > 1) {
+                        int32_t at = wave_inclusive_scan(n_out);
+                        const int32_t all = __builtin_amdgcn_readlane(at, 63);
+                        int32_t base = 0;
+                        if (all && lane == 0) base = atomicAdd(&n_later, all);
+                        at += __builtin_amdgcn_readfirstlane(base) - n_out;
+#pragma unroll
+                        for (int j = 0; j < K; ++j)
+                            if ((int32_t)pos[j] >= range) later[at++] = (int32_t)pos[j];
+                    }
+                }
+            }
+            __syncthreads();
+            for (int32_t r = 0; r < n_ranges; ++r) {
+                const int32_t lo = r * range;
+                if (r > 0) {
+                    clear();
+                    mark_list(n_before, lo);
+                    const int32_t n = n_later;
+                    for (int32_t i0 = 0; i0 < n; i0 += PRESAMPLE_THREADS) {
+                        const int32_t i = i0 + tid;
+                        const int32_t u = i < n ? later[i] : -1;
+                        visit(i < n && u >= lo && u - lo < range, u, lo, keep);
+                    }
+                    __syncthreads();
+                }
+                if (!keep) {
+                    const int32_t n4 = (int32_t)min((int64_t)range_words, words - lo / 32) / 4;
+                    uint4* to = reinterpret_cast<uint4*>(out + lo / 32);
+                    for (int32_t w = tid; w < n4; w += PRESAMPLE_THREADS) to[w] = reinterpret_cast<const uint4*>(bits)[w];
+                    __syncthreads();
+                }
+            }
+        }
+    }
+}
+
+// The same with the bitmaps in memory, for more vertices than PRESAMPLE_RANGES parts hold and for wider fanouts: workgroup-scope atomics
+// (they end in the L2 of the die the workgroup runs on), a group of G lanes to a row, so that many workgroups share a compute
+// unit. Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
+// unit. (In place of batches one after another through the training sampler: 117 -> 4.3 ms on the graph above.)
 template <int G, typename RowT>
-__global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(const RowT* __restrict__ rowptr, const int32_t* __restrict__ col,
-                                                                      const int32_t* __restrict__ train, int64_t n_train,
-                                                                      int32_t batch, int64_t n_batches, int64_t first_job,
-                                                                      uint64_t seed, PresampleHops hops, int32_t n_vertices,
-                                                                      uint32_t* bitmaps, int64_t words, int32_t* lists,
-                                                                      int64_t list_cap, int32_t* bad_flag) {
+__global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(PresampleJobs in, const RowT* __restrict__ rowptr,
+                                                                      const int32_t* __restrict__ col, uint32_t* bitmaps, int64_t words,
+                                                                      int32_t* lists, int64_t list_cap) {
     __shared__ int32_t n_list;
-    const int64_t job = first_job + blockIdx.x;
-    const int64_t lo = (job % n_batches) * batch;
-    const int32_t n_seeds = (int32_t)min((int64_t)batch, n_train - lo);
+    const int64_t job = in.first_job + blockIdx.x;
+    const int64_t lo = (job % in.n_batches) * in.batch;
+    const int32_t n_seeds = (int32_t)min((int64_t)in.batch, in.n_train - lo);
+    const PresampleHops& hops = in.hops;
     uint32_t* bm = bitmaps + (int64_t)blockIdx.x * words;
     int32_t* list = lists + (int64_t)blockIdx.x * list_cap;
-    const uint64_t key = seed + (uint64_t)job;
+    const uint64_t key = in.seed + (uint64_t)job;
     const uint32_t key0 = (uint32_t)key, key1 = (uint32_t)(key >> 32);
     const int lane = lane_id();
     // marks u; where it was not marked before and `keep`, it joins the list (one counter access per wavefront)
@@ -71,9 +217,9 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(const RowT
     __syncthreads();
     for (int32_t i0 = 0; i0 < n_seeds; i0 += PRESAMPLE_THREADS) {
         const int32_t i = i0 + (int32_t)threadIdx.x;
-        int32_t v = i < n_seeds ? train[lo + i] : 0;
-        const bool ok = i < n_seeds && (uint32_t)v < (uint32_t)n_vertices;
-        if (i < n_seeds && !ok) *bad_flag = 1;       // never followed; the caller gets an error and no cache
+        int32_t v = i < n_seeds ? in.train[lo + i] : 0;
+        const bool ok = i < n_seeds && (uint32_t)v < (uint32_t)in.n_vertices;
+        if (i < n_seeds && !ok) *in.bad_flag = 1;       // never followed; the caller gets an error and no cache
         visit(ok, v, true);
     }
     __syncthreads();
@@ -103,39 +249,51 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(const RowT
     }
 }
 
-// freq[v] += number of bitmaps that hold v. A thread owns one word (32 vertices) of up to COUNT_MAPS bitmaps and adds them
-// up in bit planes: eighteen operations on a word count 32 vertices at once, and a vertex costs one atomic per COUNT_MAPS batches
-// instead of one per batch.
-constexpr int COUNT_PLANES = 9, COUNT_MAPS = (1 << COUNT_PLANES) - 1;
-__global__ void __launch_bounds__(256) count_bitmaps_kernel(const uint32_t* __restrict__ bitmaps, int64_t words, int32_t n_maps,
-                                                            int64_t n_vertices, int32_t* freq) {
-    const int64_t w = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (w >= words) return;
-    const int32_t first = (int32_t)blockIdx.y * COUNT_MAPS, last = min(n_maps, first + COUNT_MAPS);
-    uint32_t plane[COUNT_PLANES] = {0};
-    auto add = [&](uint32_t c) {
+// freq[v] += number of bitmaps that hold v. A block owns 64 words (2048 vertices); its wavefronts deal the bitmaps out among them, a
+// thread one word of each, and add them up in bit planes: fourteen operations on a word count 32 vertices at once. The
+// wavefronts' counts meet in LDS, and no other block has these vertices, so nothing is added atomically in memory (one
+// atomic a vertex and 511 bitmaps: 105 us for 508 bitmaps of 2.4 M vertices, against 50 like this).
+constexpr int COUNT_PLANES = 7, COUNT_MAPS = (1 << COUNT_PLANES) - 1, COUNT_WAVES = 8, COUNT_FLIGHT = 16;
+__global__ void __launch_bounds__(64 * COUNT_WAVES) count_bitmaps_kernel(const uint32_t* __restrict__ bitmaps, int64_t words, int32_t n_maps,
+                                                                         int64_t n_vertices, int32_t* freq) {
+    __shared__ int32_t sums[64 * 33];
+    const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
+    const int64_t w0 = (int64_t)blockIdx.x * 64, w = w0 + lane;
+    for (int i = (int)threadIdx.x; i < 64 * 33; i += 64 * COUNT_WAVES) sums[i] = 0;
+    __syncthreads();
+    for (int32_t first = wave * COUNT_MAPS; w < words && first < n_maps; first += COUNT_WAVES * COUNT_MAPS) {
+        const int32_t last = min(n_maps, first + COUNT_MAPS);
+        uint32_t plane[COUNT_PLANES] = {0};
+        auto add = [&](uint32_t c) {
 #pragma unroll
-        for (int p = 0; p < COUNT_PLANES; ++p) {
-            const uint32_t carry = plane[p] & c;
-            plane[p] ^= c;
-            c = carry;
+            for (int p = 0; p < COUNT_PLANES; ++p) {
+                const uint32_t carry = plane[p] & c;
+                plane[p] ^= c;
+                c = carry;
+            }
+        };
+        int32_t m = first;
+        for (; m + COUNT_FLIGHT <= last; m += COUNT_FLIGHT) {
+            uint32_t x[COUNT_FLIGHT];
+#pragma unroll
+            for (int q = 0; q < COUNT_FLIGHT; ++q) x[q] = bitmaps[(int64_t)(m + q) * words + w];
+#pragma unroll
+            for (int q = 0; q < COUNT_FLIGHT; ++q) add(x[q]);
         }
-    };
-    int32_t m = first;
-    for (; m + 8 <= last; m += 8) {
-        uint32_t x[8];
+        for (; m < last; ++m) add(bitmaps[(int64_t)m * words + w]);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) x[q] = bitmaps[(int64_t)(m + q) * words + w];
+        for (int b = 0; b < 32; ++b) {
+            int32_t n = 0;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) add(x[q]);
+            for (int p = 0; p < COUNT_PLANES; ++p) n |= (int32_t)((plane[p] >> b) & 1u) << p;
+            if (n) atomicAdd(&sums[lane * 33 + b], n);
+        }
     }
-    for (; m < last; ++m) add(bitmaps[(int64_t)m * words + w]);
-#pragma unroll
-    for (int b = 0; b < 32; ++b) {
-        int32_t n = 0;
-#pragma unroll
-        for (int p = 0; p < COUNT_PLANES; ++p) n |= (int32_t)((plane[p] >> b) & 1u) << p;
-        if (n && w * 32 + b < n_vertices) atomicAdd(&freq[w * 32 + b], n);      // integer count: order independent
+    __syncthreads();
+    for (int i = (int)threadIdx.x; i < 2048; i += 64 * COUNT_WAVES) {
+        const int64_t v = w0 * 32 + i;
+        const int32_t n = sums[(i >> 5) * 33 + (i & 31)];
+        if (n && v < n_vertices) freq[v] += n;
     }
 }
 
@@ -218,48 +376,68 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
     struct FGuard { DevBuf<int32_t>* f[2]; ~FGuard() { ReleaseScope scope; f[0]->release(); f[1]->release(); } } fguard{{&bad_flag, &arena}};
     NO_CHECK(bad_flag.alloc(1));
     NO_CHECK(fill_i32(bad_flag.p, 0, 1, st));
-    // slots a batch draws at most, and destinations of its last pre-sampled hop at most
-    int64_t slots = 0, dst_cap = batch;
+    // slots a batch draws at most (in all, and in one stage: the seeds, a hop), and destinations of its last pre-sampled hop at most
+    int64_t slots = 0, last_slots = batch, dst_cap = batch;
     int32_t widest = 1;
     for (int32_t h = 0; h + 1 < n_layers; ++h) {
         slots += dst_cap * h_fanouts[h];
+        last_slots = std::max(last_slots, dst_cap * h_fanouts[h]);
         if (h + 2 < n_layers) dst_cap = std::min<int64_t>(V, dst_cap * (h_fanouts[h] + 1));
         widest = std::max(widest, h_fanouts[h]);
     }
     const bool by_group = n_layers >= 2 && presample_by_group(max_count, slots);
     // A group is as many batches as fit 192 MiB (larger device allocations take the runtime some 250 us to give back), more
     // where that would make more than 16 groups; groups are of equal size.
-    const int64_t words = ceil_div(V, 32), per_batch = words + dst_cap;       // (32-bit words)
-    int64_t group = 0, arena_words = 0;
+    // Bitmaps in LDS: lists and waiting vertices are per workgroup, and a group is a whole number of batches for each of them where it
+    // takes several.
+    const int64_t n_ranges = ceil_div(V, PRESAMPLE_RANGE);
+    const int32_t range = (int32_t)(ceil_div(ceil_div(V, n_ranges), 128) * 128);
+    const int64_t later_cap = n_ranges > 1 ? last_slots : 0;
+    const bool in_lds = by_group && n_ranges <= PRESAMPLE_RANGES && widest <= 32 && std::min<int64_t>(max_count, PRESAMPLE_WORKERS) * (dst_cap + later_cap) <= PRESAMPLE_LIST_WORDS;
+    const int64_t words = ceil_div(V, 128) * 4, per_batch = words + (in_lds ? 0 : dst_cap);       // (32-bit words)
+    int64_t group = 0, arena_words = 0, workers = 0;
     if (by_group) {
         const int64_t room = std::max<int64_t>(192ll << 18, std::min<int64_t>(4ll << 28, max_count * per_batch / 16));
         group = std::max<int64_t>(1, std::min<int64_t>(max_count, room / per_batch));
         group = ceil_div(max_count, ceil_div(max_count, group));
-        arena_words = group * per_batch;
+        if (in_lds) {
+            workers = std::min<int64_t>(group, PRESAMPLE_WORKERS);
+            group = ceil_div(group, workers) * workers;
+        }
+        arena_words = group * per_batch + workers * (dst_cap + later_cap);
     }
     const int64_t sort_words = c->n_hot > 0 ? 6 * V + (int64_t)(radix_ws_bytes(V) + 15) / 4 : 0;
     NO_CHECK(arena.alloc((size_t)std::max(arena_words, sort_words)));
     if (by_group) {
         uint32_t* bitmaps = (uint32_t*)arena.p;
         int32_t* lists = arena.p + group * words;
-        PresampleHops hops{};
-        hops.n = n_layers - 1;
-        for (int32_t h = 0; h < hops.n; ++h) hops.fanout[h] = h_fanouts[h];
+        int32_t* laters = lists + workers * dst_cap;
+        PresampleJobs in{d_train_ids, n_train, batch, nb, 0, 0, seed, {}, (int32_t)V, bad_flag.p};
+        in.hops.n = n_layers - 1;
+        for (int32_t h = 0; h < in.hops.n; ++h) in.hops.fanout[h] = h_fanouts[h];
+        const size_t lds = (size_t)range / 8;
         for (int64_t job = 0; job < max_count; job += group) {
             const int32_t n = (int32_t)std::min<int64_t>(group, max_count - job);
-            NO_CHECK(fill_i32((int32_t*)bitmaps, 0, n * words, st));
-#define NO_LAUNCH_PRESAMPLE(G, RowT, rp)                                                                                        \
-    hipLaunchKernelGGL((presample_kernel<G, RowT>), dim3((unsigned)n), dim3(PRESAMPLE_THREADS), 0, st, rp, g->col.p, d_train_ids, n_train, \
-                       batch, nb, job, seed, hops, (int32_t)V, bitmaps, words, lists, dst_cap, bad_flag.p)
-#define NO_LAUNCH_PRESAMPLE_G(G) \
-    do { if (g->rowptr_bits == 64) NO_LAUNCH_PRESAMPLE(G, int64_t, g->rowptr64.p); else NO_LAUNCH_PRESAMPLE(G, int32_t, g->rowptr32.p); } while (0)
-            if (widest <= 8) NO_LAUNCH_PRESAMPLE_G(8);
-            else if (widest <= 16) NO_LAUNCH_PRESAMPLE_G(16);
-            else if (widest <= 32) NO_LAUNCH_PRESAMPLE_G(32);
-            else NO_LAUNCH_PRESAMPLE_G(64);
-#undef NO_LAUNCH_PRESAMPLE_G
-#undef NO_LAUNCH_PRESAMPLE
-            hipLaunchKernelGGL(count_bitmaps_kernel, dim3((unsigned)ceil_div(words, 256), (unsigned)ceil_div(n, COUNT_MAPS)), dim3(256), 0, st,
+            in.first_job = job;
+            in.n_jobs = n;
+            auto launch = [&](auto rp) -> int32_t {
+                using RowT = std::remove_const_t<std::remove_pointer_t<decltype(rp)>>;
+                if (in_lds) {
+                    auto kernel = widest <= 16 ? presample_lds_kernel<16, RowT> : presample_lds_kernel<32, RowT>;
+                    NO_HIP_CHECK(hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+                    hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(n, workers)), dim3(PRESAMPLE_THREADS), lds, st, in, rp, g->col.p,
+                                       bitmaps, words, range, (int32_t)n_ranges, lists, dst_cap, laters, later_cap);
+                    return NO_OK;
+                }
+                NO_CHECK(fill_i32((int32_t*)bitmaps, 0, n * words, st));
+                auto kernel = widest <= 8 ? presample_kernel<8, RowT> : widest <= 16 ? presample_kernel<16, RowT>
+                            : widest <= 32 ? presample_kernel<32, RowT> : presample_kernel<64, RowT>;
+                hipLaunchKernelGGL(kernel, dim3((unsigned)n), dim3(PRESAMPLE_THREADS), 0, st, in, rp, g->col.p, bitmaps, words, lists, dst_cap);
+                return NO_OK;
+            };
+            if (g->rowptr_bits == 64) NO_CHECK(launch((const int64_t*)g->rowptr64.p));
+            else NO_CHECK(launch((const int32_t*)g->rowptr32.p));
+            hipLaunchKernelGGL(count_bitmaps_kernel, dim3((unsigned)ceil_div(words, 64)), dim3(64 * COUNT_WAVES), 0, st,
                                (const uint32_t*)bitmaps, words, n, V, c->freq.p);
         }
     } else {

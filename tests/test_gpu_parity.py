@@ -287,6 +287,31 @@ def test_select_hot_batch_counts_and_sizes(V, E, n_train, batch, fanouts, bits):
     assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
 
 
+@pytest.mark.parametrize("V,fanouts,batch", [
+    (1_245_184, (16, 4, 2), 256),      # the most vertices that one bitmap in LDS holds; a thread draws 16 slots at most
+    (1_245_185, (17, 3, 2), 256),      # two parts, and 17 slots
+    (2_500_000, (32, 2), 4),           # three parts, 32 slots, more batches than workgroups
+    (4_980_736, (5, 16, 2), 256),      # four full parts
+    (4_980_737, (5, 5, 2), 256),       # one vertex too many: bitmaps in memory
+    (1_300_000, (33, 2), 256)])        # one slot too many: bitmaps in memory
+def test_select_hot_bitmaps_in_parts(V, fanouts, batch):
+    b = nb()
+    rng = np.random.default_rng(V)
+    E = 3_000_000                      # most vertices have a few neighbours, some thousands have far more than a draw takes
+    dst = np.where(rng.random(E) < 0.5, rng.integers(0, 5000, E) * (V // 5000), rng.integers(0, V, E)).astype(np.int32)
+    src = np.where(rng.random(E) < 0.5, rng.integers(0, 5000, E) * (V // 5000) + V // 5000 - 1, rng.integers(0, V, E)).astype(np.int32)
+    og, gg = ora.build_csr(src, dst, V), b.no_build_csr(dev(src), dev(dst), V, 32)
+    train = np.concatenate([rng.choice(5000, 900, replace=False) * (V // 5000), [0, 1, V - 1, V - 2]])
+    train = np.unique(train).astype(np.int32)
+    rng.shuffle(train)
+    print("V %d, %d train ids" % (V, len(train)), flush=True)
+    oc = ora.select_hot(og, train, batch, fanouts, 2, 0.01, 1, 4, 5)
+    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, fanouts, 2, 0.01, 1, 4, 5), V)
+    assert oc.freq.max() > 1 and (oc.freq > 0).sum() > 5000
+    assert np.array_equal(view["freq"].cpu().numpy().astype(np.int64), oc.freq)
+    assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
+
+
 @pytest.mark.parametrize("fanouts", [(10, 5), (6,)])
 @pytest.mark.parametrize("batch", [100, 9_000])       # batches by bitmap; one large batch, by the training sampler
 def test_select_hot_counts_a_repeated_train_id_once_a_batch(fanouts, batch):
