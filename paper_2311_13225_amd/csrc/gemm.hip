@@ -1,5 +1,5 @@
-// The fp32 products on the fp32 matrix instruction (forward products, and input gradients that are not cut) and the reduction of the
-// split weight-gradient products. Other gradient products: gemm_cut.hip.
+// The fp32 products on the fp32 matrix instruction (forward products and input gradients that are not cut) and the reduction of the
+// split weight-gradient products. On the bf16 matrix cores: gemm_fwd.hip (large forward products), gemm_cut.hip (gradients).
 #include "gemm_tile.hpp"
 
 namespace no {
@@ -131,8 +131,7 @@ __global__ void __launch_bounds__(256) gemm_nn_small_kernel(GemmNNArgs g) {
 // ------------------------------------------------------------------------------------------ NN, tiled
 
 // LDS-tiled products: forward, and the input gradients that are not cut. Block tile 64 x 64 x 32, 256 threads = 2 x 2 wavefronts, each
-// owning a 32 x 32 sub-tile as v_mfma_f32_32x32x2_f32 accumulators. Forward products stay on the fp32 instruction and sum every
-// output element in one fixed order, because the ReLU decisions of a step hang on the last bits of these sums.
+// owning a 32 x 32 sub-tile as v_mfma_f32_32x32x2_f32 accumulators. Every output element is summed in one fixed order.
 //
 // Operand tiles sit in LDS in one of two layouts, chosen by how the operand lies in memory:
 //   KC (reduction index contiguous in memory): T[x][k], pitch 36 floats; a lane fetches the four
@@ -619,6 +618,7 @@ __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
 }
 
 int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);      // gemm_cut.hip
+int32_t cut_fwd(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);     // gemm_fwd.hip
 
 static int32_t launch_small_nn(const GemmNNArgs& a, bool b_transposed, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     dim3 grid((unsigned)ceil_div(a.N, 32), (unsigned)ceil_div(a.M_cap, 32), (unsigned)(a.accumulate ? 1 : a.n_problems));
@@ -638,6 +638,20 @@ static int32_t launch_tiled_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t e
 int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
     if (nn_tiles(a) <= 128) return launch_small_nn(a, false, st, ev0, ev1);
+    if (a.cut_B[0]) return cut_fwd(a, st, ev0, ev1);
+    // The weights are cut by a launch of their own (3 to 5 us), here or at the start of a step: worth it from some 8 K rows x 256 columns on (3.4 K
+    // rows, 2 x 256 x 256: 17.4 us on the fp32 instruction, 15.8 + 2.8; 13 K: 47.5, 31 + 4.6; the step of a large bf16 table, whose second layer has
+    // 3.4 K rows: 224 us with the fp32 instruction, 230).
+    const bool two = a.n_problems > 1;
+    const size_t each = cut_weights_elements(a.K[0], a.N, true);
+    if (forward_takes_planes(a.M_cap, a.K[0], a.N) && (!two || a.K[1] == a.K[0]) && a.cut_scratch && (two ? 2 : 1) * each * 2 <= a.cut_scratch_bytes) {
+        GemmNNArgs c = a;
+        uint16_t* planes = (uint16_t*)a.cut_scratch;
+        NO_CHECK(cut_weights(a.B[0], two ? a.B[1] : nullptr, a.K[0], a.N, true, planes, st));
+        c.cut_B[0] = planes;
+        c.cut_B[1] = planes + each;
+        return cut_fwd(c, st, ev0, ev1);
+    }
     return launch_tiled_nn<false>(a, st, ev0, ev1);
 }
 
@@ -653,7 +667,7 @@ int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
         const size_t each = cut_weights_elements(a.N, a.K[0]);
         if (!a.cut_scratch || (one ? 1 : 2) * each * 2 > a.cut_scratch_bytes) return launch_tiled_nn<true>(a, st, nullptr, nullptr);
         uint16_t* planes = (uint16_t*)a.cut_scratch;
-        NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], planes, st));
+        NO_CHECK(cut_weights(a.B[0], one ? nullptr : a.B[1], a.N, a.K[0], false, planes, st));
         a.cut_B[0] = planes;
         a.cut_B[1] = one ? planes : planes + each;
     }

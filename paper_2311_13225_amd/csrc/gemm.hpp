@@ -15,7 +15,7 @@ struct GemmNNArgs {
     const int32_t* a_rows[2];             // per problem: row m of the operand is row a_rows[m] of A (NULL: row m)
     const float* B[2]; int64_t ldb[2];
     int32_t K[2];
-    // large input gradients take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch
+    // large products take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch
     const uint16_t* cut_B[2];
     void* cut_scratch; size_t cut_scratch_bytes;
     float* C[2]; int64_t ldc[2];
@@ -74,26 +74,34 @@ struct GemmBf16NNArgs {
 // Weights cut for the large gradient products (gemm_cut.hip): planes of the transpose of one matrix [K][N], the reduction index (over
 // the N columns) padded to 32.
 __host__ __device__ inline int32_t cut_pad(int32_t N) { return (N + 31) / 32 * 32; }
-inline size_t cut_weights_elements(int32_t K, int32_t N) { return (size_t)3 * cut_pad(N) * K; }
-// w1 may be NULL; the second matrix's planes follow the first's (cut_weights_elements apart)
-int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, uint16_t* out, hipStream_t st);
+__host__ __device__ inline size_t cut_weights_elements(int32_t K, int32_t N, bool forward = false) {
+    return forward ? (size_t)3 * cut_pad(K) * N : (size_t)3 * cut_pad(N) * K;
+}
+// w1 may be NULL; the second matrix's planes follow the first's (cut_weights_elements apart). forward: planes of the matrix itself, for a
+// forward product (gemm_fwd.hip), the reduction over its K rows.
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool forward, uint16_t* out, hipStream_t st);
 // Whether an input gradient of M_cap x N (reduction over K columns) reads planes: more output tiles than compute units for the
 // kernel for small products to keep busy by splitting the reduction.
 inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
+// Whether a forward product of about `rows` rows does (gemm_nn_forward says why the line lies there).
+inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N) { return ceil_div(rows, 64) * ceil_div(N, 64) >= 512 && K >= 8; }
 // Matrices cut by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
 // blocks [end_block[j-1], end_block[j]) of them.
 struct CutJobs {
-    const float* w[2 * NO_MAX_LAYERS]; uint16_t* out[2 * NO_MAX_LAYERS]; int32_t K[2 * NO_MAX_LAYERS], N[2 * NO_MAX_LAYERS];
-    uint32_t end_block[2 * NO_MAX_LAYERS]; int32_t n = 0;
-    void add(const float* matrix, int32_t rows, int32_t cols, uint16_t* planes) {
+    static constexpr int MOST = 2 * NO_MAX_LAYERS;
+    const float* w[MOST]; uint16_t* out[MOST]; int32_t K[MOST], N[MOST];
+    uint32_t end_block[MOST]; int32_t n = 0; uint32_t forward = 0;      // (bit j: matrix j in the forward layout)
+    void add(const float* matrix, int32_t rows, int32_t cols, uint16_t* planes, bool fwd = false) {
         w[n] = matrix; out[n] = planes; K[n] = rows; N[n] = cols;
-        end_block[n] = blocks() + (uint32_t)ceil_div((int64_t)cut_weights_elements(rows, cols) / 24, 256);
+        forward |= fwd ? 1u << n : 0u;
+        end_block[n] = blocks() + (uint32_t)ceil_div((int64_t)cut_weights_elements(rows, cols, fwd) / 24, 256);
         ++n;
     }
     uint32_t blocks() const { return n ? end_block[n - 1] : 0u; }
 };
+int32_t cut_all(const CutJobs& cut, hipStream_t st);      // in a launch of their own
 inline int32_t bf16_kpad(int32_t K) { return (K + 15) / 16 * 16; }
 int32_t weights_to_bf16_t(const float* w, int32_t K, int32_t N, int32_t Kpad, uint16_t* out, hipStream_t st);
 int32_t gemm_bf16_nn(const GemmBf16NNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);

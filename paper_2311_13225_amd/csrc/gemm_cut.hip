@@ -21,7 +21,7 @@
 // once per step (or call), into the order in which the matrix cores take them; rows once per 128 output columns.
 // Measured, fp32 instruction -> this: input gradient of 60 K x 256 rows by two 256 x 256 matrices 176 -> 108 us, 5.5 K rows 21 -> 16;
 // weight gradients of 25 K rows, 2 x 100 x 256: 47 -> 35 us, of 60 K rows, 2 x 256 x 256: 194 -> 130.
-// (Forward products stay on the fp32 instruction: see gemm.hip.)
+// (Forward products: gemm_fwd.hip.)
 #include <algorithm>
 
 #include "gemm_tile.hpp"
@@ -43,25 +43,28 @@ __device__ __forceinline__ bool finite(float v) { return fabsf(v) < INFINITY; }
 // z stays 0 while every value that was added is finite, and is NaN from then on (one instruction a value, no lane mask)
 __device__ __forceinline__ void note_not_finite(float& z, float v) { z = fmaf(v, 0.f, z); }
 
-// The partial products of one pair of fragments, smallest first, and the accumulator each goes to.
-constexpr int CUT_TERMS = 6;
-struct CutTerm { int a, b, acc; };
-__device__ constexpr CutTerm CUT_TERM[CUT_TERMS] = {{2, 0, 0}, {0, 2, 0}, {1, 1, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
-
 // ------------------------------------------------------------------------------------------ weights
 
 // The transposes of both matrices of a layer ([K][N] fp32, row-major) cut into planes: out[matrix][plane][N/8][K][8], eight indices of the
-// reduction (over the columns) together, zeros from N to the next multiple of 32.
+// reduction (over the columns) together, zeros from N to the next multiple of 32. forward: the matrices themselves, out[..][K/8][N][8].
 __global__ void __launch_bounds__(256) cut_weights_kernel(const float* __restrict__ w0, const float* __restrict__ w1, int32_t K, int32_t N,
-                                                          uint16_t* __restrict__ out, int64_t matrix_stride) {
+                                                          int32_t forward, uint16_t* __restrict__ out, int64_t matrix_stride) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i < matrix_stride / 24) cut_weights_unit(blockIdx.y ? w1 : w0, K, N, out + blockIdx.y * matrix_stride, i);
+    if (i < matrix_stride / 24) cut_weights_unit(blockIdx.y ? w1 : w0, K, N, forward != 0, out + blockIdx.y * matrix_stride, i);
 }
 
-int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, uint16_t* out, hipStream_t st) {
-    const int64_t stride = (int64_t)cut_weights_elements(K, N), units = stride / 24;
-    hipLaunchKernelGGL(cut_weights_kernel, dim3((unsigned)ceil_div(units, 256), w1 ? 2u : 1u), dim3(256), 0, st, w0, w1, K, N, out, stride);
+int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool forward, uint16_t* out, hipStream_t st) {
+    const int64_t stride = (int64_t)cut_weights_elements(K, N, forward), units = stride / 24;
+    hipLaunchKernelGGL(cut_weights_kernel, dim3((unsigned)ceil_div(units, 256), w1 ? 2u : 1u), dim3(256), 0, st, w0, w1, K, N, forward ? 1 : 0, out, stride);
     return launch_status("cut_weights");
+}
+
+__global__ void __launch_bounds__(256) cut_all_kernel(CutJobs cut) { run_cut_jobs(cut, blockIdx.x); }
+
+int32_t cut_all(const CutJobs& cut, hipStream_t st) {
+    if (cut.n == 0) return NO_OK;
+    hipLaunchKernelGGL(cut_all_kernel, dim3(cut.blocks()), dim3(256), 0, st, cut);
+    return launch_status("cut_all");
 }
 
 // ------------------------------------------------------------------------------------------ NN

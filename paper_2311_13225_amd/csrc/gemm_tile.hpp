@@ -38,6 +38,11 @@ __device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
 // (An operand from 2^104 or a sum from 2^79 on leaves it at the top: gemm_cut.hip sums those outputs on the fp32 instruction.)
 constexpr float CUT_SCALE = 16777216.f, CUT_UNSCALE = 1.f / (CUT_SCALE * CUT_SCALE);
 
+// The partial products of one pair of fragments, smallest first, and the accumulator each goes to.
+constexpr int CUT_TERMS = 6;
+struct CutTerm { int a, b, acc; };
+__device__ constexpr CutTerm CUT_TERM[CUT_TERMS] = {{2, 0, 0}, {0, 2, 0}, {1, 1, 0}, {1, 0, 0}, {0, 1, 0}, {0, 0, 1}};
+
 // Eight values, each cut into three bf16 values (gemm_cut.hip): the three planes (packed in pairs)
 __device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
     uint32_t h[4], m[4], l[4];
@@ -57,15 +62,17 @@ __device__ __forceinline__ void cut8(const float (&f)[8], uint4 (&p)[3]) {
     p[2] = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
-// One unit of a matrix's planes (see cut_weights; i < cut_weights_elements / 24): eight reduction indices of one row of the matrix.
-__device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int32_t N, uint16_t* out, int64_t i) {
-    const int64_t plane = (int64_t)cut_pad(N) * K;
-    const int32_t rb = (int32_t)(i / K), x = (int32_t)(i - (int64_t)rb * K);
+// One unit of a matrix's planes (see cut_weights; i < cut_weights_elements / 24): eight reduction indices of one row of the matrix, or
+// (forward) of one column.
+__device__ __forceinline__ void cut_weights_unit(const float* w, int32_t K, int32_t N, bool forward, uint16_t* out, int64_t i) {
+    const int32_t X = forward ? N : K, R = forward ? K : N;      // the product reduces over R
+    const int64_t plane = (int64_t)cut_pad(R) * X;
+    const int32_t rb = (int32_t)(i / X), x = (int32_t)(i - (int64_t)rb * X);
     float f[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int32_t r = rb * 8 + j;
-        f[j] = r < N ? w[(int64_t)x * N + r] : 0.f;
+        f[j] = r < R ? (forward ? w[(int64_t)r * N + x] : w[(int64_t)x * N + r]) : 0.f;
     }
     uint4 p[3];
     cut8(f, p);
@@ -79,7 +86,8 @@ __device__ __forceinline__ void run_cut_jobs(const CutJobs& cut, uint32_t block)
     while (block >= cut.end_block[j]) ++j;
     if (j > 0) block -= cut.end_block[j - 1];
     const int64_t i = (int64_t)block * 256 + threadIdx.x;
-    if (i < (int64_t)cut_pad(cut.N[j]) / 8 * cut.K[j]) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], cut.out[j], i);
+    const bool forward = cut.forward >> j & 1;
+    if (i < (int64_t)cut_weights_elements(cut.K[j], cut.N[j], forward) / 24) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], forward, cut.out[j], i);
 }
 
 // Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.

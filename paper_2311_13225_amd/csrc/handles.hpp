@@ -94,6 +94,7 @@ struct RefreshState {
     size_t snap_n = 0;                     // floats in a snapshot
     int32_t snap_arch = 0;
     no::DevBuf<float> mean;                // [n_hot, feat_dim]
+    no::DevBuf<uint16_t> planes;           // the snapshot's matrices cut for the product
     no::DevBuf<char> x0;                   // bf16 tables only: the hot vertices' own rows
     no::DevBuf<float> x_f32;               // bf16 tables only: the same rows in fp32
     hipStream_t stream = nullptr;          // default priority, non-blocking
@@ -105,7 +106,7 @@ struct RefreshState {
         if (ev_snap) { (void)hipEventDestroy(ev_snap); ev_snap = nullptr; }
         if (ev_done) { (void)hipEventDestroy(ev_done); ev_done = nullptr; }
         if (blocks) { blocks->release(); delete blocks; blocks = nullptr; }
-        emb_pending.release(); version_pending.release(); snap.release(); snap_cur.release(); mean.release(); x0.release(); x_f32.release();
+        emb_pending.release(); version_pending.release(); snap.release(); snap_cur.release(); mean.release(); planes.release(); x0.release(); x_f32.release();
         pending = false;
     }
 };

@@ -45,6 +45,9 @@ struct LayerWorkspace {
     // Planes of the layer's weights (cut_weights) stand in the place of the two above, which are free until the weight gradients.
     uint16_t* planes() const { return (uint16_t*)x_dst_f32; }
     size_t planes_bytes = 0;
+    // ... and of its forward product in the place of the two first, which nothing uses before the backward pass
+    void* fwd_planes = nullptr;
+    size_t fwd_planes_bytes = 0;
     int32_t splits = 1;
     size_t bytes = 0;
 };
@@ -119,7 +122,8 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof = nullptr, int agg_stage = -1,
                      int gemm_stage = -1, const void* agg_table = nullptr, int32_t arch = NO_ARCH_SAGE_MEAN, const Layer1Reuse* reuse = nullptr, bool aggregate_done = false,
                      const SourceWeights* weights = nullptr, const PaddedSlots* padded = nullptr,
-                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr);
+                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr);
+// cut_fwd: the layer's two matrices cut for the forward product, by the caller; without them the product may cut them itself
 // cut_bwd: the layer's two matrices cut for the input gradient (kept by a model, rewritten by the reduction); without them the
 // product cuts them itself
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,

@@ -27,6 +27,7 @@ static int32_t refresh_create(no_cache_s* c, no_graph_s* g, no_dtype dt, int32_t
     NO_CHECK(r->snap.alloc(r->snap_n));
     NO_CHECK(r->snap_cur.alloc(r->snap_n));
     NO_CHECK(r->mean.alloc((size_t)c->n_hot * feat_dim));
+    NO_CHECK(r->planes.alloc(2 * cut_weights_elements(feat_dim, c->emb_dim, true)));
     if (dt == NO_BF16) {
         NO_CHECK(r->x0.alloc((size_t)c->n_hot * feat_dim * 2));
         NO_CHECK(r->x_f32.alloc((size_t)c->n_hot * feat_dim));
@@ -87,6 +88,8 @@ extern "C" int32_t no_refresh_hot_begin(no_cache_t c, no_graph_t g, const void* 
     view.d_indices = view.d_nbr_global;        // aggregate straight from the table through the global ids
     LayerWorkspace w;
     w.x_dst_f32 = bf16 ? r->x_f32.p : nullptr;
+    w.fwd_planes = r->planes.p;
+    w.fwd_planes_bytes = r->planes.n * 2;
     const PaddedSlots slots{r->blocks->hop[0].nbr_pad.p, r->blocks->hop[0].fanout};
     SourceWeights sw;
     if (arch == NO_ARCH_GCN_SYM) { sw.cnt = r->blocks->hop[0].csc_cnt.p; sw.local = r->blocks->hop[0].indices.p; }

@@ -595,6 +595,8 @@ LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_
     w.x_dst_f32 = (float*)(base + off); off += align256((size_t)n_dst_cap * d_in * 4);
     w.partials = (float*)(base + off);  off += align256((size_t)2 * w.splits * (d_in + 1) * d_out * 4);
     w.planes_bytes = (size_t)(base + off - (char*)w.x_dst_f32);
+    w.fwd_planes = w.gz;
+    w.fwd_planes_bytes = (size_t)((char*)w.x_dst_f32 - (char*)w.gz);
     w.bytes = off;
     return w;
 }
@@ -606,7 +608,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof, int agg_stage, int gemm_stage,
                      const void* agg_table, int32_t arch, const Layer1Reuse* reuse,
                      bool aggregate_done, const SourceWeights* weights, const PaddedSlots* padded,
-                     const Bf16Products* bf, no_blocks_s* side_of) {
+                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd) {
     // aggregate_done: `mean` (and the reused rows of H^1) were already written by an earlier launch of the same
     // aggregation (a batch prepared ahead); only the product runs
     // reuse: the output rows are scattered into H^1, recomputed hot rows also refresh the cache, and the reused
@@ -639,6 +641,9 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap; a.N = d_out;
         a.bias = bias; a.relu = relu;
         scatter(a);
+        a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
+        a.cut_scratch = w.fwd_planes;
+        a.cut_scratch_bytes = w.fwd_planes_bytes;
         e0 = e1 = nullptr;
         if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
         return gemm_nn_forward(a, st, e0, e1);
@@ -687,6 +692,10 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap; a.N = d_out;
     a.bias = bias; a.relu = relu;
     scatter(a);
+    a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
+    a.cut_B[1] = cut_fwd ? cut_fwd[1] : nullptr;
+    a.cut_scratch = w.fwd_planes;
+    a.cut_scratch_bytes = w.fwd_planes_bytes;
     e0 = e1 = nullptr;
     if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
     return gemm_nn_forward(a, st, e0, e1);

@@ -99,9 +99,10 @@ struct no_model_s {
     // they may not match them: weights_dirty, raised by no_model_params, through which a caller writes, and by a change of form)
     no::DevBuf<uint16_t> wt1;
     int32_t wt1_kpad = 0;
-    // the matrices of the layers above layer 1 cut for their input gradients (cut_weights): made again in every step, by
-    // extra blocks of the loss launch, so that no copy of them outlives a step
+    // the matrices cut for the large forward products, at the start of every step, and those of the layers above layer 1 for their input
+    // gradients, by extra blocks of the loss launch (cut_weights): made again in every step, so that no copy of them outlives one
     no::DevBuf<uint16_t> planes;
+    uint16_t* cut_fwd[NO_MAX_LAYERS][2] = {{nullptr}};      // (NULL: no large product)
     uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
     bool weights_dirty = true;
     no::DevBuf<float> mean[NO_MAX_LAYERS];           // layer l (index l-1): [n_dst_cap, d_{l-1}]
@@ -243,11 +244,19 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
         NO_CHECK(m->wt1.alloc((size_t)2 * m->dims[1] * m->wt1_kpad));
     }
     size_t n_planes = 0;
-    for (int32_t l = 1; l < L; ++l) n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1]);
+    for (int32_t l = 0; l < L; ++l)
+        n_planes += 2 * cut_weights_elements(m->dims[l], m->dims[l + 1], true) + (l > 0 ? 2 * cut_weights_elements(m->dims[l], m->dims[l + 1]) : 0);
     NO_CHECK(m->planes.alloc(n_planes));
     uint16_t* at = m->planes.p;
-    for (int32_t l = 1; l < L; ++l)
-        for (int q = 0; q < 2; ++q, at += cut_weights_elements(m->dims[l], m->dims[l + 1])) m->cut_bwd[l][q] = at;
+    for (int32_t l = 0; l < L; ++l)
+        for (int q = 0; q < 2; ++q) {
+            // (a batch fills 15 to 45 % of a hop's capacity)
+            if (forward_takes_planes((int64_t)m->blocks->hop[L - 1 - l].n_dst_cap * 2 / 5, m->dims[l], m->dims[l + 1])) m->cut_fwd[l][q] = at;
+            at += cut_weights_elements(m->dims[l], m->dims[l + 1], true);
+            if (l == 0) continue;
+            m->cut_bwd[l][q] = at;
+            at += cut_weights_elements(m->dims[l], m->dims[l + 1]);
+        }
     size_t ws_bytes = 0;
     for (int32_t l = 1; l <= L; ++l) {
         const HopBuffers& H = m->blocks->hop[L - l];
@@ -370,6 +379,19 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         NO_REQUIRE(step + 1 < (1ll << 31), NO_ERR_INVALID_ARG, "no_train_step_ahead: step out of range");
         NO_CHECK(ensure_lookahead(m, g));
     }
+    // bf16 table: layer 1's products take bf16 operands (features as stored; mean, weights, output gradient rounded)
+    const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
+    // The weights of the step's large forward products, cut. Ahead of the wait for a batch prepared on the other stream, which leaves the
+    // stream idle for some 10 us: the launch runs there.
+    {
+        CutJobs cut;
+        for (int32_t l = 0; l < L; ++l) {
+            if (!m->cut_fwd[l][0] || (l == 0 && bf16_products)) continue;
+            cut.add(m->params.p + m->off_w_self[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][0], true);
+            if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][1], true);
+        }
+        NO_CHECK(cut_all(cut, st));
+    }
     // a batch sampled ahead by the previous call is used if it is exactly this one; anything else is dropped
     // (a cache is the same cache only with the same identity and an unchanged generation: a refresh commit, an
     //  invalidate or a new bound since the split make the prepared batch another batch than a step would sample now)
@@ -414,8 +436,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     sg.table = arch_is_gcn(m->arch) ? nullptr : d_features;    // GCN-style layers read every row inside the aggregation
     sg.row_bytes = row_bytes;
     sg.out = m->x0.p;
-    // bf16 table: layer 1's products take bf16 operands (features as stored; mean, weights, output gradient rounded)
-    const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
     uint16_t* wt_self = m->wt1.p;
     uint16_t* wt_neigh = m->wt1.p ? m->wt1.p + (size_t)m->dims[1] * m->wt1_kpad : nullptr;
     if (bf16_products && m->weights_dirty) {
@@ -532,6 +552,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             reuse.hits.d_n = extra + 1; reuse.hits.n_cap = blk.n_dst_cap; reuse.hits.dst = m->h[0].p; reuse.hits.dim = d_out;
         }
         LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out);
+        w.fwd_planes_bytes = 0;      // (the step has cut the weights that are to be cut)
         // symmetric normalisation: the column sums of the block's adjacency are the per-source edge counts of the hop
         // (written with the local indices); the fused layer-1 aggregate reads global ids,
         // so it also takes the local index of every entry
@@ -556,11 +577,11 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                   m->params.p + m->off_bias[0], d_out, l < L ? 1 : 0, m->mean[0].p, h_out, w, st, &prof,
                                   NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
-                                  bf16_products ? &bfp : nullptr, B));
+                                  bf16_products ? &bfp : nullptr, B, m->cut_fwd[0][0] ? m->cut_fwd[0] : nullptr));
         } else
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,
-                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B));
+                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->cut_fwd[l - 1][0] ? m->cut_fwd[l - 1] : nullptr));
         if (l == L && L >= 2) prof.end();
         if (l == 1 && d_next_seeds) {
             if (next_uses_cache && L >= 2 && m->arch == NO_ARCH_SAGE_MEAN) NO_HIP_CHECK(hipEventRecord(m->ev_l1_done, st));

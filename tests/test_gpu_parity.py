@@ -457,6 +457,58 @@ def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     assert torch.isnan(gx[n:]).all()
 
 
+def forward_layer(b, n, cap, x, w_self, w_neigh, bias, relu):
+    """One layer whose row v samples itself: the mean is x, h = act(x (W_self + W_neigh) + bias)."""
+    F, d_out = w_self.shape
+    i32 = lambda a: dev(np.asarray(a, np.int32))
+    blk = b.block_view_from_tensors(i32([n]), i32([n]), i32(np.minimum(np.arange(cap + 1), n)), i32(np.arange(cap)), cap, cap)
+    ws = torch.empty(b.no_sage_layer_ws_bytes(cap, cap, F, d_out), dtype=torch.uint8, device="cuda")
+    mean, h = torch.empty((cap, F), device="cuda"), torch.full((cap, d_out), -7.0, device="cuda")
+    b.no_sage_layer_fwd(blk, dev(x), dev(w_self), dev(w_neigh), dev(bias), relu, mean, h, ws)
+    return h
+
+
+@pytest.mark.parametrize("n,cap,F,d_out", [
+    (1, 8192, 256, 256), (63, 8192, 8, 256), (65, 9000, 9, 250),                # fewer rows than a tile; the shortest reductions
+    (4096, 8192, 31, 256), (4097, 8192, 33, 256), (8200, 8200, 40, 129),       # the last row of small tiles in one round, the first beyond
+    (8193, 8193, 64, 193), (32_800, 32_800, 70, 47), (16_500, 16_500, 602, 130),   # remainders of both tile sizes and of the steps
+    (8191, 8191, 64, 129), (9000, 9000, 7, 256), (8192, 8192, 3000, 256)])     # fp32 instruction: one row too few, too few columns; planes of a layer as wide as it has rows
+def test_sage_layer_forward_products_at_tile_edges(n, cap, F, d_out):
+    """Against exact sums. Bound as for the gradients: (K + 8) 2^-24 sum |a b| (the bias among the terms)."""
+    b = nb()
+    rng = np.random.default_rng(n + F)
+    f32 = lambda *s: rng.standard_normal(s).astype(np.float32)
+    x, w_self, w_neigh, bias = f32(cap, F), f32(F, d_out), f32(F, d_out), f32(d_out)
+    for relu in (False, True):
+        h = forward_layer(b, n, cap, x, w_self, w_neigh, bias, relu).cpu().numpy()
+        x64 = x[:n].astype(np.float64)
+        ref = x64 @ w_self.astype(np.float64) + x64 @ w_neigh.astype(np.float64) + bias
+        mag = np.abs(x64) @ (np.abs(w_self).astype(np.float64) + np.abs(w_neigh)) + np.abs(bias)
+        assert (np.abs(h[:n] - (np.maximum(ref, 0.0) if relu else ref)) <= (2 * F + 9) * 2.0 ** -24 * mag).all()
+        assert (h[n:] == -7.0).all()
+
+
+def test_sage_layer_forward_products_of_infinities_and_the_largest_numbers():
+    """Infinite and NaN operands, and one near the end of the range, give what sums of fp32 products give, and nothing else changes."""
+    b = nb()
+    rng = np.random.default_rng(6)
+    n, F, d_out = 9000, 100, 256
+    f32 = lambda *s: (rng.standard_normal(s) * 1e-3).astype(np.float32)
+    x, w_self, w_neigh, bias = f32(n, F), f32(F, d_out), f32(F, d_out), f32(d_out)
+    x[5, 3], x[70, 0], x[200, 99], x[8999, 50] = np.inf, -np.inf, np.nan, 3.4e38
+    w_self[7, 9], w_neigh[40, 200] = np.inf, 3.4e38
+    h = forward_layer(b, n, n, x, w_self, w_neigh, bias, False).cpu().numpy()
+    x64 = x.astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        ref = x64 @ w_self.astype(np.float64) + x64 @ w_neigh.astype(np.float64) + bias
+        mag = np.abs(x64) @ (np.abs(w_self).astype(np.float64) + np.abs(w_neigh)) + np.abs(bias)
+    big = np.isfinite(ref) & (mag > 3e38)                      # (fp32 sums may overflow on the way there)
+    assert np.array_equal(np.isnan(h), np.isnan(ref))
+    assert np.array_equal(np.isinf(h) & ~big, np.isinf(ref)) and (np.sign(h)[np.isinf(ref)] == np.sign(ref)[np.isinf(ref)]).all()
+    ok = np.isfinite(ref) & ~big
+    assert ok.sum() > 0.9 * ref.size and (np.abs(h[ok] - ref[ok]) <= (2 * F + 9) * 2.0 ** -24 * mag[ok]).all()
+
+
 def test_sage_layer_gradient_products_of_infinities_and_the_largest_numbers():
     """An infinite gradient gives infinite products (NaN where infinities of both signs meet, and there only), one near the end of
     the fp32 range finite ones, as sums of fp32 products do."""
