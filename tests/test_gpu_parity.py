@@ -149,6 +149,21 @@ def test_build_csr_from_device_and_rejects_bad_ids():
         nb().no_build_csr(src, dst, 500, 48)
 
 
+@pytest.mark.parametrize("V,dedup", [(1, False), (3, True), (512, False), (513, True), (8192, False), (8193, True), (1 << 18, False),
+                                     ((1 << 18) + 1, True), (1 << 22, False), ((1 << 22) + 1, False)])
+def test_build_csr_digits_within_and_across_the_ids(V, dedup):
+    # 2 * 9, 2 * 13 and 2 * 22 bits are the most for 2, 3 and 5 passes: a digit across both ids, or none, on each side of these
+    print("case", V, dedup, flush=True)
+    rng = np.random.default_rng(V)
+    E = 40_001
+    src, dst = (rng.choice(np.concatenate([rng.integers(0, V, 300), V - 1 - rng.integers(0, min(V, 300), 300)]), E).astype(np.int32)
+                for _ in range(2))
+    og = ora.build_csr(src, dst, V, dedup=dedup)
+    rowptr, col = nb().no_graph_view(nb().no_build_csr(dev(src), dev(dst), V, 32, dedup=dedup))[3:]
+    assert np.array_equal(rowptr.cpu().numpy().astype(np.int64), og.rowptr)
+    assert np.array_equal(col.cpu().numpy()[:len(og.col)], og.col)
+
+
 @pytest.mark.parametrize("symmetrise,dedup,ids64,on_device", [(True, False, False, False), (False, True, False, True),
                                                               (True, True, True, False), (False, False, True, True)])
 def test_build_csr_flags(symmetrise, dedup, ids64, on_device):
