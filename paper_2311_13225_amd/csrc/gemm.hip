@@ -639,9 +639,11 @@ int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hip
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
     if (nn_tiles(a) <= 128) return launch_small_nn(a, false, st, ev0, ev1);
     if (a.cut_B[0]) return cut_fwd(a, st, ev0, ev1);
-    // The weights are cut by a launch of their own (3 to 5 us), here or at the start of a step: worth it from some 8 K rows x 256 columns on (3.4 K
-    // rows, 2 x 256 x 256: 17.4 us on the fp32 instruction, 15.8 + 2.8; 13 K: 47.5, 31 + 4.6; the step of a large bf16 table, whose second layer has
-    // 3.4 K rows: 224 us with the fp32 instruction, 230).
+    // The weights are cut by a launch of their own (3 to 5 us), here or at the start of a step; what the planes save grows with the tiles and,
+    // more slowly, with the reduction. Measured, a layer forward and backward, two products with 256 columns, us on the fp32 instruction / with
+    // planes: 9 K rows, K = 16 43.6 / 48.1, 128 65.2 / 66.9; 20 K rows, K = 32 58.1 / 58.8, 64 74.5 / 75.1, 100 89.8 / 88.2; 40 K rows, K = 16
+    // 89.4 / 85.5; 90 K rows, K = 47 266 / 248; the product alone at 13 K rows, K = 256 47.5 / 31 + 4.6. Below 512 tiles few blocks are
+    // left to hide the cut (3.4 K rows, K = 256: 17.4 / 15.8 + 2.8; a step whose second layer that is 224 / 230).
     const bool two = a.n_problems > 1;
     const size_t each = cut_weights_elements(a.K[0], a.N, true);
     if (forward_takes_planes(a.M_cap, a.K[0], a.N) && (!two || a.K[1] == a.K[0]) && a.cut_scratch && (two ? 2 : 1) * each * 2 <= a.cut_scratch_bytes) {

@@ -86,7 +86,10 @@ inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
 // Whether a forward product of about `rows` rows does (gemm_nn_forward says why the line lies there).
-inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N) { return ceil_div(rows, 64) * ceil_div(N, 64) >= 512 && K >= 8; }
+inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N) {
+    const int64_t tiles = ceil_div(rows, 64) * ceil_div(N, 64);
+    return K >= 8 && tiles >= 512 && tiles * (K + 50) >= 150000;
+}
 // Matrices cut by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
 // blocks [end_block[j-1], end_block[j]) of them.
 struct CutJobs {

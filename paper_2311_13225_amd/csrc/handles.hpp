@@ -63,6 +63,7 @@ struct no_blocks_s {
     uint64_t stamped_contents = 0;
     no::DevBuf<int32_t> compute_inv;         // [|V^1|]: index in the compute list of position i of V^1, -1 if served from the cache
     bool last_used_cache = false;
+    bool scan_two_pass = false;              // the scans of the next sampling call: always two launches
     // Side tasks (side.hpp) of the last call not launched yet: the next one of each hop (-1: none), the wipe of the id map
     // after hop wipe_hop, and the copy of that hop's destination rows.
     int32_t side_next[NO_MAX_LAYERS];

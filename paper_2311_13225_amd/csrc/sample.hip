@@ -205,11 +205,14 @@ __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __
 // 64-bit access at device scope and needs no fence; the words are emptied by the sampling launch before. The wait on
 // an earlier tile is bounded: on expiry the block stores the call's id in `fail_flag` and goes on (wrong output, no hang;
 // the host reports NO_ERR_TIMEOUT wherever it next reads the blocks' counts).
-// ONE_LAUNCH_TILES: the one-launch form saves a launch (2.3 us and a second read of the slots) and pays for the wait, and for the atomics
-// in which the tiles count themselves, one after another on one address, 10 ns each. Measured, one launch / two,
-// us of sampling: two hops of 3 and 16 tiles 18.1 / 21.3; three hops of 15, 165 and 1005 tiles 87 (each tile a release, the walk back in
-// windows of 64), 80 (neither) / 75; 74 with the first hop alone in one launch.
-constexpr uint32_t ONE_LAUNCH_TILES = 32;
+// ONE_LAUNCH_TILES, where the sampling has the chip to itself: the one-launch form saves a launch (2.3 us and a second read of the
+// slots) and pays for the wait and for the count of finished tiles, each a release (a write-back of the die's L2), one after another,
+// 10 to 20 ns each. Measured, one launch / two, us of a whole step: scans of 4 and 52 tiles and a split of 5 104.3 / 108.5; of 5, 47 and
+// 411 tiles and a split of 48 174.7 / 179.4; sampling alone, scans of 15, 165 and 1005 tiles 87 (walk back in windows of 64) / 75,
+// 74 with the first two in one launch. With stores past the L2 in place of the releases the first of these took 107.8.
+// Beside a step's products the releases write back what those have in the L2: 210.3 us a step / 209.2, so there it is always two.
+constexpr uint32_t ONE_LAUNCH_TILES = 256;
+static_assert(ONE_LAUNCH_TILES <= ETHREADS, "a thread a word");
 constexpr unsigned long long SCAN_SUM = 1ull;
 __device__ __forceinline__ unsigned long long scan_pack(int64_t v) {
     return ((unsigned long long)(v & 0x7fffffffll)) | ((unsigned long long)((v >> 32) & 0x7fffffffll) << 31) | (SCAN_SUM << 62);
@@ -220,40 +223,38 @@ __device__ __forceinline__ int64_t scan_unpack(unsigned long long w) {
 
 struct ScanWait { unsigned long long* status; int32_t* fail_flag; int32_t flag_value, spin_limit, withhold_first; };
 
-// The sum of the tiles before `tile` (tile < ONE_LAUNCH_TILES), to all threads of the block; publishes this tile's word.
-__device__ __forceinline__ int64_t scan_look_back(const ScanWait& w, uint32_t tile, int64_t total, int64_t* prefix_sh) {
-    if (threadIdx.x < 64) {
-        const uint32_t lane = threadIdx.x;
-        // (withhold_first: test aid; tile 0 keeps its word back, so the tile after it must give up its wait)
-        if (lane == 0 && !(w.withhold_first && tile == 0))
-            __hip_atomic_store(&w.status[tile], scan_pack(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned long long word = 0ull;
-        if (lane < tile) {
-            int spins = 0;
-            while ((word = __hip_atomic_load(&w.status[lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {
-                if (++spins > w.spin_limit) {
-                    __hip_atomic_store(w.fail_flag, w.flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    break;
-                }
-                __builtin_amdgcn_s_sleep(1);
+// The sum of the tiles before `tile` (tile < ONE_LAUNCH_TILES, a thread a word), to all threads of the block; publishes this tile's word.
+__device__ __forceinline__ int64_t scan_look_back(const ScanWait& w, uint32_t tile, int64_t total, int64_t* prefix_sh /* [ETHREADS / 64] */) {
+    // (withhold_first: test aid; tile 0 keeps its word back, so the tile after it must give up its wait)
+    if (threadIdx.x == 0 && !(w.withhold_first && tile == 0))
+        __hip_atomic_store(&w.status[tile], scan_pack(total), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned long long word = 0ull;
+    if (threadIdx.x < tile) {
+        int spins = 0;
+        while ((word = __hip_atomic_load(&w.status[threadIdx.x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0ull) {
+            if (++spins > w.spin_limit) {
+                __hip_atomic_store(w.fail_flag, w.flag_value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                break;
             }
+            __builtin_amdgcn_s_sleep(1);
         }
-        int64_t v = scan_unpack(word);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-        if (lane == 0) *prefix_sh = v;
     }
+    int64_t v = scan_unpack(word);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+    if ((threadIdx.x & 63) == 0) prefix_sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    return *prefix_sh;
+    v = 0;
+#pragma unroll
+    for (int i = 0; i < ETHREADS / 64; ++i) v += prefix_sh[i];
+    return v;
 }
 
 // Whether this block is the last of n_tiles to come here (the answer is for thread 0; every block calls once, all its threads). What the
-// blocks stored with store_shared before is then in memory, and load_shared reads it: no release, which would write the
-// die's L2 back once a tile.
+// blocks stored before is then in memory, and load_shared reads it.
 __device__ __forceinline__ bool last_tile(unsigned long long* done, uint32_t n_tiles) {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    return threadIdx.x == 0 && __hip_atomic_fetch_add(done, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_tiles - 1;
+    return threadIdx.x == 0 && __hip_atomic_fetch_add(done, 1ull, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == n_tiles - 1;
 }
 // Accesses past the dies' own caches, for words that the clean-up after an expired wait may write again from another die.
 __device__ __forceinline__ void store_shared(int32_t* p, int32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -269,7 +270,7 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
                                                              SideTasks side) {
     if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     __shared__ int64_t smem[ETHREADS / 64 + 1];
-    __shared__ int64_t prefix_sh;
+    __shared__ int64_t prefix_sh[ETHREADS / 64];
     __shared__ int cleanup_sh;
     for (int64_t t = (int64_t)blockIdx.x * ETHREADS + threadIdx.x; t < n_zero; t += (int64_t)side.first_block * ETHREADS) csc_cnt[t] = 0;
     const int32_t n_dst = *d_n_dst;
@@ -293,14 +294,14 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
     }
     int64_t total;
     int64_t run = block_exclusive_scan<int64_t, ETHREADS>(s, &total, smem);
-    const int64_t prefix = scan_look_back(wait, blockIdx.x, total, &prefix_sh);
+    const int64_t prefix = scan_look_back(wait, blockIdx.x, total, prefix_sh);
     run += prefix;
     if (threadIdx.x == 0 && base + ETILE >= n_pad) {      // the last tile holds the totals
         const int64_t all = prefix + total;
         const int32_t nnz = (int32_t)(all & 0xffffffffll), n_new = (int32_t)(all >> 32);
-        store_shared(&indptr[n_dst], nnz);
-        store_shared(&counts[1], n_dst + n_new);
-        store_shared(&counts[2], nnz);
+        indptr[n_dst] = nnz;
+        counts[1] = n_dst + n_new;
+        counts[2] = nnz;
     }
 #pragma unroll
     for (int t = 0; t < EITEMS; ++t) {
@@ -308,14 +309,14 @@ __global__ void __launch_bounds__(ETHREADS) edge_scan_kernel(const int32_t* __re
         if (q < n_pad) {
             const int32_t e = (int32_t)(run & 0xffffffffll);
             const int32_t row = k == 1 ? (int32_t)q : (int32_t)__umul64hi((uint64_t)q, k_magic);   // q / k, exact
-            if (q - (int64_t)row * k == 0) store_shared(&indptr[row], e);
+            if (q - (int64_t)row * k == 0) indptr[row] = e;
             if (f[t] & 1) {
                 nbr[e] = u[t];
                 edge_row[e] = row;
                 if (f[t] >> 32) {
                     const int32_t local = n_dst + (int32_t)(run >> 32);
                     src_global[local] = u[t];
-                    store_shared(&map[u[t]], local);     // only the first occurrence writes; later readers never match n_dst + q
+                    map[u[t]] = local;     // only the first occurrence writes; later readers never match n_dst + q
                 }
             }
             run += f[t];
@@ -511,22 +512,23 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");      // every map read of the block has returned
         __syncthreads();
         if (threadIdx.x == 0) __hip_atomic_fetch_add(idx_done, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        // (the range check only matters after an expired wait, when the split may have re-keyed the map already)
+        int32_t pos[IDX_ITEMS];
+        if (csc_cnt)
 #pragma unroll
-        for (int t = 0; t < IDX_ITEMS; ++t) {
-            const int64_t e = e0 + t * ETHREADS;
-            if (e >= nnz) continue;
-            indices[e] = local[t];
-            // (the range check only matters after an expired wait, when the split may have re-keyed the map already)
-            if (csc_cnt && (uint32_t)local[t] < (uint32_t)csc_len) {      // integer count: order independent
-                const int32_t pos = atomicAdd(&csc_cnt[local[t]], 1);
-                if (csc_pos) csc_pos[e] = pos;
+            for (int t = 0; t < IDX_ITEMS; ++t)              // integer count: order independent
+                if (e0 + t * ETHREADS < nnz && (uint32_t)local[t] < (uint32_t)csc_len) pos[t] = atomicAdd(&csc_cnt[local[t]], 1);
+#pragma unroll
+        for (int t = 0; t < IDX_ITEMS; ++t)
+            if (e0 + t * ETHREADS < nnz) {
+                indices[e0 + t * ETHREADS] = local[t];
+                if (csc_pos && (uint32_t)local[t] < (uint32_t)csc_len) csc_pos[e0 + t * ETHREADS] = pos[t];
             }
-        }
         return;
     }
     const uint32_t tile = blockIdx.x - idx_blocks;
     __shared__ int64_t smem[ETHREADS / 64 + 1];
-    __shared__ int64_t prefix_sh;
+    __shared__ int64_t prefix_sh[ETHREADS / 64];
     __shared__ int cleanup_sh;
     const int64_t n = *d_n_v1;
     const int64_t base = (int64_t)tile * ETILE;
@@ -549,14 +551,14 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
     }
     int64_t total;
     int64_t run = block_exclusive_scan<int64_t, ETHREADS>(s, &total, smem);
-    const int64_t prefix = scan_look_back(wait, tile, total, &prefix_sh);
+    const int64_t prefix = scan_look_back(wait, tile, total, prefix_sh);
     if (threadIdx.x == 0) {
         if (base + ETILE >= n) {      // the last tile holds the totals
             const int64_t all = prefix + total;
             const int32_t n_compute = (int32_t)(all & 0xffffffffll);
-            store_shared(&extra[0], n_compute);
-            store_shared(&extra[1], (int32_t)n - n_compute);
-            store_shared(&extra[4], (int32_t)(all >> 32));
+            extra[0] = n_compute;
+            extra[1] = (int32_t)n - n_compute;
+            extra[4] = (int32_t)(all >> 32);
         }
         const unsigned int expected = (unsigned int)(((int64_t)*d_nnz + ETHREADS * IDX_ITEMS - 1) / (ETHREADS * IDX_ITEMS));
         int spins = 0;
@@ -582,13 +584,13 @@ __global__ void __launch_bounds__(ETHREADS) v1_split_kernel(CacheProbe probe, co
                     version[rslot] = stamp;
                 }
                 compute_list[run] = v[t];
-                store_shared(&map[v[t]], (int32_t)run);
+                map[v[t]] = (int32_t)run;
             } else {
                 const int64_t p = i - run;
                 hit_pos[p] = (int32_t)i;
                 compute_inv[i] = -1;
                 hit_slot[p] = slot[t];
-                store_shared(&map[v[t]], EMPTY);
+                map[v[t]] = EMPTY;
             }
             run += c;
         }
@@ -625,7 +627,7 @@ __global__ void unstamp_kernel(const int32_t* __restrict__ refresh_slot, const i
 static inline int64_t edge_tiles(int64_t n_pad_cap) { int64_t t = ceil_div(n_pad_cap, ETILE); return t < 1 ? 1 : t; }
 // words of one scan: a word a tile (status words, or the sums of the two-launch form), then the counter of finished tiles
 static inline int64_t scan_words(int64_t n_pad_cap) { return edge_tiles(n_pad_cap) + 1; }
-static inline bool scan_one_launch(int64_t n_pad_cap) { return edge_tiles(n_pad_cap) <= ONE_LAUNCH_TILES; }
+static inline bool scan_one_launch(const no_blocks_s* b, int64_t n_pad_cap) { return !b->scan_two_pass && edge_tiles(n_pad_cap) <= ONE_LAUNCH_TILES; }
 // does this hop count the edges that leave each source (for its transpose, or for the symmetric normalisation)?
 static inline bool counts_sources(const no_blocks_s* b, const HopBuffers& H) { return H.has_csc || b->count_sources; }
 
@@ -748,7 +750,7 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
     const uint64_t k_magic = k > 1 ? (~0ull / (uint64_t)k) + 1ull : 0ull;     // ceil(2^64 / k)
     const int32_t n_zero = counts_sources(b, H) ? H.n_src_cap + 1 : 0;
     side_take(b, tiles, &side);
-    if (!scan_one_launch(H.nnz_cap)) {
+    if (!scan_one_launch(b, H.nnz_cap)) {
         hipLaunchKernelGGL(edge_tile_sums_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, H.nbr_pad.p,
                            (const int32_t*)b->map.p, (const int32_t*)cnt, k, tile_sums, H.csc_cnt.p, n_zero, side);
         side_take(b, tiles, &side);
@@ -793,7 +795,7 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
             const unsigned tiles = (unsigned)edge_tiles(P.n_src_cap);
             const unsigned idx_blocks = (unsigned)ceil_div(P.nnz_cap, ETHREADS);
             int64_t* tile_sums = (int64_t*)b->ws.p;
-            if (scan_one_launch(P.n_src_cap)) {
+            if (scan_one_launch(b, P.n_src_cap)) {
                 // (its words, and behind them the counter of index blocks: emptied by the sampling launch of hop L-2, past its own)
                 unsigned long long* v1_status = (unsigned long long*)b->ws.p + scan_words(P.nnz_cap);
                 const unsigned idx_blocks = (unsigned)ceil_div(P.nnz_cap, ETHREADS * IDX_ITEMS);
@@ -827,7 +829,7 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
         }
         int32_t* zero_extra = h == 0 && !use_cache ? extra : nullptr;
         // the hop above the bottom one also empties the status words of the V^1 split that follows it
-        const int32_t extra_status = (use_cache && h == L - 2 && scan_one_launch(b->hop[h].n_src_cap))
+        const int32_t extra_status = (use_cache && h == L - 2 && scan_one_launch(b, b->hop[h].n_src_cap))
                                          ? (int32_t)scan_words(b->hop[h].n_src_cap) + 1 : 0;
         if (g->rowptr_bits == 64)
             NO_CHECK(sample_hop<int64_t>(g->rowptr64.p, g->col.p, b, h, d_dst, d_n, n_seeds, h == 0, key0, key1, domain, st,

@@ -447,6 +447,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     if (!presampled) prof.kernel_pair(NO_STAGE_SAMPLE_ROWS_BOTTOM, &sev0, &sev1);
     prof.begin(NO_STAGE_SAMPLE);
     if (!presampled) {
+        B->scan_two_pass = false;
         B->time_ev0 = sev0; B->time_ev1 = sev1; B->time_hop = sev0 ? L - 1 : -1;
         NO_CHECK(sample_blocks_impl(g, d_seeds, n_seeds, seed + (uint64_t)step, 0u, L, cache, step, B, st, false, &sg, true));
         // measurement passes count the side tasks (local indices, transposes, map wipe, copied rows) with the sampling
@@ -472,6 +473,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         NO_HIP_CHECK(hipStreamWaitEvent(m->sample_stream, m->ev_can_sample, 0));
         SideGather sg2 = sg;
         sg2.out = m->x0_alt.p;
+        m->blocks_alt->scan_two_pass = true;      // this sampling shares the chip with the step's products
         NO_CHECK(sample_blocks_impl(g, d_next_seeds, n_next_seeds, seed + (uint64_t)(step + 1), 0u, L, cache, step + 1,
                                     m->blocks_alt, m->sample_stream, false, &sg2, true));
         // (the aggregation, if there will be one, takes side tasks along; its event replaces this one)

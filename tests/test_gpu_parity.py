@@ -371,14 +371,14 @@ def test_sample_blocks_with_cache_lookup():
 
 
 @pytest.mark.parametrize("V,batch", [
-    (40_000, 1024),       # 31 tiles of slots, 32 of V^1 (32768 sources at most): both scans in one launch
-    (40_000, 1025),       # 32 and 33: the split of V^1 in two launches
-    (31_668, 1100),       # 34 and 32: the compaction in two
-    (40_000, 1100)])      # 34 and 35: both in two
+    (262_144, 8192),      # 248 tiles of slots, 256 of V^1 (as many as there are vertices): both scans in one launch
+    (300_000, 8200),      # 249 and 257: the split of V^1 in two launches
+    (260_000, 8457),      # 257 and 254: the compaction in two
+    (300_000, 8457)])     # 257 and 265: both in two
 def test_sample_blocks_scans_in_one_launch_and_in_two(V, batch):
     b = nb()
     fanouts = (31, 3)
-    src, dst, og, gg = make_graph(V, 40 * V, 3, 32)
+    src, dst, og, gg = make_graph(V, 8 * V, 3, 32)
     train = si.train_split(V, 0.65, 3)
     oc = ora.select_hot(og, train[:4096], 1024, fanouts, 1, 0.2, 2, 8, 0)
     gc = b.no_select_hot(gg, dev(train[:4096]), 1024, fanouts, 1, 0.2, 2, 8, 0)
@@ -484,10 +484,11 @@ def forward_layer(b, n, cap, x, w_self, w_neigh, bias, relu):
 
 
 @pytest.mark.parametrize("n,cap,F,d_out", [
-    (1, 8192, 256, 256), (63, 8192, 8, 256), (65, 9000, 9, 250),                # fewer rows than a tile; the shortest reductions
-    (4096, 8192, 31, 256), (4097, 8192, 33, 256), (8200, 8200, 40, 129),       # the last row of small tiles in one round, the first beyond
-    (8193, 8193, 64, 193), (32_800, 32_800, 70, 47), (16_500, 16_500, 602, 130),   # remainders of both tile sizes and of the steps
-    (8191, 8191, 64, 129), (9000, 9000, 7, 256), (8192, 8192, 3000, 256)])     # fp32 instruction: one row too few, too few columns; planes of a layer as wide as it has rows
+    (1, 9000, 256, 256), (63, 42_000, 8, 256), (65, 41_000, 9, 250),             # fewer rows than a tile; the shortest reductions
+    (4096, 30_000, 31, 256), (4097, 30_000, 33, 256), (8200, 36_000, 40, 129),  # the last row of small tiles in one round, the first beyond
+    (8193, 22_000, 64, 193), (32_800, 81_000, 70, 47), (16_500, 16_500, 602, 130),   # remainders of both tile sizes and of the steps
+    (9600, 9600, 200, 256), (9536, 9536, 200, 256), (42_000, 42_000, 7, 256),   # the least work for planes, a row of tiles less; too few columns
+    (8192, 8192, 3000, 256)])                                                    # planes of a layer as wide as it has rows
 def test_sage_layer_forward_products_at_tile_edges(n, cap, F, d_out):
     """Against exact sums. Bound as for the gradients: (K + 8) 2^-24 sum |a b| (the bias among the terms)."""
     b = nb()
@@ -507,7 +508,7 @@ def test_sage_layer_forward_products_of_infinities_and_the_largest_numbers():
     """Infinite and NaN operands, and one near the end of the range, give what sums of fp32 products give, and nothing else changes."""
     b = nb()
     rng = np.random.default_rng(6)
-    n, F, d_out = 9000, 100, 256
+    n, F, d_out = 17_000, 100, 256
     f32 = lambda *s: (rng.standard_normal(s) * 1e-3).astype(np.float32)
     x, w_self, w_neigh, bias = f32(n, F), f32(F, d_out), f32(F, d_out), f32(d_out)
     x[5, 3], x[70, 0], x[200, 99], x[8999, 50] = np.inf, -np.inf, np.nan, 3.4e38
