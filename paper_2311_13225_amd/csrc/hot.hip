@@ -249,51 +249,78 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(PresampleJ
     }
 }
 
-// freq[v] += number of bitmaps that hold v. A block owns 64 words (2048 vertices); its wavefronts deal the bitmaps out among them, a
-// thread one word of each, and add them up in bit planes: fourteen operations on a word count 32 vertices at once. The
-// wavefronts' counts meet in LDS, and no other block has these vertices, so nothing is added atomically in memory (one
-// atomic a vertex and 511 bitmaps: 105 us for 508 bitmaps of 2.4 M vertices, against 50 like this).
-constexpr int COUNT_PLANES = 7, COUNT_MAPS = (1 << COUNT_PLANES) - 1, COUNT_WAVES = 8, COUNT_FLIGHT = 16;
-__global__ void __launch_bounds__(64 * COUNT_WAVES) count_bitmaps_kernel(const uint32_t* __restrict__ bitmaps, int64_t words, int32_t n_maps,
+// freq[v] += number of bitmaps that hold v. A thread adds one word of the bitmaps up in bit planes, two operations a plane for 32
+// vertices at once, and takes the planes apart at the end. Where the bitmaps are long a wavefront owns 64 words of all of them, and a
+// vertex that any of them holds costs one atomic: bound by the bitmaps' bytes (89 of 27.75 M vertices, 309 MB: 89 us).
+// SHARED: where that leaves the chip idle, the eight wavefronts of a block share 64 words and deal the bitmaps out evenly; their counts meet in
+// LDS, and no other block has these vertices. Every wavefront takes planes apart, however few its bitmaps are, and the block goes
+// through all its counts: long bitmaps, and few of them, are the other form's. How few depends on how many atomics that one needs (`large`:
+// batches such as are drawn in LDS; most counts are not zero). Measured, us, one wavefront / shared, bitmaps of large batches: 8 of 10 K
+// vertices 16 / 6; 12 of 2.4 M 11 / 16, 60 24 / 19, 400 82 / 36; 400 of 3.7 M 85 / 54. Of small ones: 100 of 2.4 M 13 / 16, 250
+// 24 / 21; 400 of 3.7 M 32 / 50. 89 of 27.75 M: 89 / 250.
+constexpr int COUNT_FLIGHT = 16;
+constexpr int count_planes(bool shared) { return shared ? 7 : 9; }
+constexpr int count_waves(bool shared) { return shared ? 8 : 4; }      // (long bitmaps: small blocks, dealt more evenly)
+static inline bool count_shared(int64_t words, int64_t n_maps, bool large) {
+    return words < (large ? 64 * 2560 : 64 * 1536) && n_maps >= words / (large ? 3000 : 800);
+}
+template <bool SHARED>
+__global__ void __launch_bounds__(64 * count_waves(SHARED), 8) count_bitmaps_kernel(const uint32_t* __restrict__ bitmaps, int64_t words, int32_t n_maps,
                                                                          int64_t n_vertices, int32_t* freq) {
-    __shared__ int32_t sums[64 * 33];
+    constexpr int WAVES = count_waves(SHARED), PLANES = count_planes(SHARED), MAPS = (1 << PLANES) - 1;
+    __shared__ int32_t sums[SHARED ? 64 * 33 : 1];
     const int lane = lane_id(), wave = (int)(threadIdx.x >> 6);
-    const int64_t w0 = (int64_t)blockIdx.x * 64, w = w0 + lane;
-    for (int i = (int)threadIdx.x; i < 64 * 33; i += 64 * COUNT_WAVES) sums[i] = 0;
-    __syncthreads();
-    for (int32_t first = wave * COUNT_MAPS; w < words && first < n_maps; first += COUNT_WAVES * COUNT_MAPS) {
-        const int32_t last = min(n_maps, first + COUNT_MAPS);
-        uint32_t plane[COUNT_PLANES] = {0};
+    const int64_t w0 = ((int64_t)blockIdx.x * (SHARED ? 1 : WAVES) + (SHARED ? 0 : wave)) * 64, w = w0 + lane;
+    if constexpr (SHARED) {
+        for (int i = (int)threadIdx.x; i < 64 * 33; i += 64 * WAVES) sums[i] = 0;
+        __syncthreads();
+    }
+    const int32_t share = SHARED ? (n_maps + WAVES - 1) / WAVES : n_maps;
+    const int32_t begin = SHARED ? wave * share : 0, end = min(n_maps, begin + share);
+    for (int32_t first = begin; w < words && first < end; first += MAPS) {
+        const int32_t last = min(end, first + MAPS);
+        uint32_t plane[PLANES] = {0};
         auto add = [&](uint32_t c) {
 #pragma unroll
-            for (int p = 0; p < COUNT_PLANES; ++p) {
+            for (int p = 0; p < PLANES; ++p) {
                 const uint32_t carry = plane[p] & c;
                 plane[p] ^= c;
                 c = carry;
             }
         };
         int32_t m = first;
+        uint32_t x[COUNT_FLIGHT];
         for (; m + COUNT_FLIGHT <= last; m += COUNT_FLIGHT) {
-            uint32_t x[COUNT_FLIGHT];
 #pragma unroll
             for (int q = 0; q < COUNT_FLIGHT; ++q) x[q] = bitmaps[(int64_t)(m + q) * words + w];
 #pragma unroll
             for (int q = 0; q < COUNT_FLIGHT; ++q) add(x[q]);
         }
-        for (; m < last; ++m) add(bitmaps[(int64_t)m * words + w]);
+        if (m < last) {      // the rest together too (past the last bitmap: that one again, not added)
+#pragma unroll
+            for (int q = 0; q < COUNT_FLIGHT; ++q) x[q] = bitmaps[(int64_t)min(m + q, last - 1) * words + w];
+#pragma unroll
+            for (int q = 0; q < COUNT_FLIGHT; ++q) add(m + q < last ? x[q] : 0u);
+        }
 #pragma unroll
         for (int b = 0; b < 32; ++b) {
             int32_t n = 0;
 #pragma unroll
-            for (int p = 0; p < COUNT_PLANES; ++p) n |= (int32_t)((plane[p] >> b) & 1u) << p;
-            if (n) atomicAdd(&sums[lane * 33 + b], n);
+            for (int p = 0; p < PLANES; ++p) n |= (int32_t)((plane[p] >> b) & 1u) << p;
+            if constexpr (SHARED) {
+                if (n) atomicAdd(&sums[lane * 33 + b], n);
+            } else {
+                if (n && w * 32 + b < n_vertices) atomicAdd(&freq[w * 32 + b], n);
+            }
         }
     }
-    __syncthreads();
-    for (int i = (int)threadIdx.x; i < 2048; i += 64 * COUNT_WAVES) {
-        const int64_t v = w0 * 32 + i;
-        const int32_t n = sums[(i >> 5) * 33 + (i & 31)];
-        if (n && v < n_vertices) freq[v] += n;
+    if constexpr (SHARED) {
+        __syncthreads();
+        for (int i = (int)threadIdx.x; i < 2048; i += 64 * WAVES) {
+            const int64_t v = w0 * 32 + i;
+            const int32_t n = sums[(i >> 5) * 33 + (i & 31)];
+            if (n && v < n_vertices) freq[v] += n;
+        }
     }
 }
 
@@ -437,8 +464,12 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
             };
             if (g->rowptr_bits == 64) NO_CHECK(launch((const int64_t*)g->rowptr64.p));
             else NO_CHECK(launch((const int32_t*)g->rowptr32.p));
-            hipLaunchKernelGGL(count_bitmaps_kernel, dim3((unsigned)ceil_div(words, 64)), dim3(64 * COUNT_WAVES), 0, st,
-                               (const uint32_t*)bitmaps, words, n, V, c->freq.p);
+            if (count_shared(words, n, in_lds))
+                hipLaunchKernelGGL(count_bitmaps_kernel<true>, dim3((unsigned)ceil_div(words, 64)), dim3(64 * count_waves(true)), 0, st,
+                                   (const uint32_t*)bitmaps, words, n, V, c->freq.p);
+            else
+                hipLaunchKernelGGL(count_bitmaps_kernel<false>, dim3((unsigned)ceil_div(words, 64 * count_waves(false))), dim3(64 * count_waves(false)), 0,
+                                   st, (const uint32_t*)bitmaps, words, n, V, c->freq.p);
         }
     } else {
         if (n_layers >= 2) NO_CHECK(blocks_create_impl(g, batch, h_fanouts, n_layers - 1, false, &b));

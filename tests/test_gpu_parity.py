@@ -327,6 +327,31 @@ def test_select_hot_bitmaps_in_parts(V, fanouts, batch):
     assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
 
 
+@pytest.mark.parametrize("V,batch,n_batches", [
+    (130, 2, 17),                      # two bitmaps and a bit for each wavefront that shares them
+    (10_000, 3, 2),                    # fewer bitmaps than wavefronts
+    (10_000, 1, 2100),                 # 263 for each: three rounds of what seven planes hold
+    (3_145_600, 4, 121), (3_145_600, 4, 122),      # small batches: too few to share, just enough
+    (3_145_729, 4, 130),               # too long to share
+    (3_200_000, 1, 8320),              # 520 in a launch: more than nine planes hold
+    (4_980_736, 8192, 51), (4_980_736, 8192, 52)])      # large batches: too few, just enough
+def test_select_hot_counts_of_few_and_many_bitmaps(V, batch, n_batches):
+    """Every vertex has one in-neighbour, so a batch's V^1 is its seeds and theirs; one seed is in nine batches of ten or more."""
+    b = nb()
+    rng = np.random.default_rng(V + n_batches)
+    parent = rng.integers(0, V, V).astype(np.int32)
+    train = np.where(rng.random(batch * n_batches) < 0.9, V // 3, rng.integers(0, V, batch * n_batches)).astype(np.int32)
+    print("V %d, %d batches of %d" % (V, n_batches, batch), flush=True)
+    job = np.repeat(np.arange(n_batches, dtype=np.int64), batch)
+    met = np.unique(np.concatenate([job * V + train, job * V + parent[train]]))
+    freq = np.bincount(met % V, minlength=V)
+    gg = b.no_build_csr(dev(parent), dev(np.arange(V, dtype=np.int32)), V, 32)
+    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, (2, 1), 1, 0.01, 1, 4, 5), V)
+    assert freq.max() > 0.8 * n_batches
+    assert np.array_equal(view["freq"].cpu().numpy().astype(np.int64), freq)
+    assert np.array_equal(view["hot_ids"].cpu().numpy(), np.lexsort((np.arange(V), -freq))[:V // 100])
+
+
 @pytest.mark.parametrize("fanouts", [(10, 5), (6,)])
 @pytest.mark.parametrize("batch", [100, 9_000])       # batches by bitmap; one large batch, by the training sampler
 def test_select_hot_counts_a_repeated_train_id_once_a_batch(fanouts, batch):
