@@ -184,9 +184,10 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_lds_kernel(Presam
 // The same with the bitmaps in memory, for more vertices than PRESAMPLE_RANGES parts hold and for wider fanouts: workgroup-scope atomics
 // (they end in the L2 of the die the workgroup runs on), a group of G lanes to a row, so that many workgroups share a compute
 // unit. Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
-// unit. (In place of batches one after another through the training sampler: 117 -> 4.3 ms on the graph above.)
+// unit (two workgroups, which is what the bound on the registers is for: with 106 scalar ones there was room for one, and 260 batches of 256 seeds,
+// fanouts 40, 20 and 5, took 812 us; like this 600). In place of batches one after another through the training sampler: 117 -> 4.3 ms on the graph above.
 template <int G, typename RowT>
-__global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_kernel(PresampleJobs in, const RowT* __restrict__ rowptr,
+__global__ void __launch_bounds__(PRESAMPLE_THREADS, 8) presample_kernel(PresampleJobs in, const RowT* __restrict__ rowptr,
                                                                       const int32_t* __restrict__ col, uint32_t* bitmaps, int64_t words,
                                                                       int32_t* lists, int64_t list_cap) {
     __shared__ int32_t n_list;
