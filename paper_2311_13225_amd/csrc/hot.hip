@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_lds_kernel(Presam
     }
 }
 
-// The same with the bitmaps in memory, for more vertices than PRESAMPLE_RANGES parts hold and for wider fanouts: workgroup-scope atomics
+// The same with the bitmaps in memory, for more vertices than PRESAMPLE_RANGES parts hold, for wider fanouts and for small batches: workgroup-scope atomics
 // (they end in the L2 of the die the workgroup runs on), a group of G lanes to a row, so that many workgroups share a compute
 // unit. Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
 // unit (two workgroups, which is what the bound on the registers is for: with 106 scalar ones there was room for one, and 260 batches of 256 seeds,
@@ -349,11 +349,23 @@ void cache_unregister(no_cache_s* c) { std::lock_guard<std::mutex> l(g_cache_mut
 bool cache_is_live(no_cache_s* c) { std::lock_guard<std::mutex> l(g_cache_mutex); return g_live_caches.count(c) != 0; }
 }  // namespace no
 
+// Whether a batch keeps a workgroup busy while its bitmap stands in LDS. Every stage empties the bitmap's parts and goes through the list for each, and a
+// thread draws the slots of its row one after the other, which few rows leave without cover: batches of few seeds, in memory, share a
+// compute unit and take a group of lanes to a row. Measured, time of a call in memory over that in LDS: one part, fanouts 10 and 5,
+// 64 seeds 0.93, 256 1.18; 15, 10 and 5, 16 seeds 0.88, 64 1.27; 25 and 10, 64 seeds 0.69, 256 1.01, 1024 1.46. Four parts, 10 and 5, 256
+// seeds 0.90, 1024 1.15; 15, 10 and 5, 64 seeds 0.89, 256 1.32; 25 and 10, 256 seeds 0.82, 1024 1.09.
+static bool presample_fills_workgroup(int32_t batch, int64_t slots_per_batch, int32_t widest, int64_t n_ranges) {
+    if (batch >= 256) return n_ranges <= 2 || slots_per_batch >= (widest <= 16 ? 10000 : 40000);
+    return widest <= 16 ? batch >= 32 * n_ranges && slots_per_batch >= 1250 * n_ranges : batch >= 32 && slots_per_batch >= 12000 + 6000 * n_ranges;
+}
+
 // Whether whole batches are pre-sampled by one workgroup each, a group of them per launch, or one after the other with the
 // training sampler, every hop spread over the chip. A batch takes the sampler a dozen launches (about 80 us) however small it
-// is, and a workgroup about 2 us per 1024 slots, 512 of them at a time: few but very large batches stay with the sampler.
-static bool presample_by_group(int64_t n_batches, int64_t slots_per_batch) {
-    const double rounds = (double)((n_batches + 511) / 512);
+// is, and a workgroup about 2 us per 1024 slots, as many of them at a time as the chip holds (bitmaps in LDS: one a compute unit): few but very
+// large batches stay with the sampler. Measured, sampler / workgroups, us a call on 2.4 M vertices, fanouts 15, 10 and 5: 4 batches of 4096
+// 387 / 542, 16 1111 / 679; 6 of 60,000 1385 / 5114; fanouts 10 and 5, 4 of 4096 229 / 174, 6 of 60,000 481 / 790, 20 1248 / 814.
+static bool presample_by_group(int64_t n_batches, int64_t slots_per_batch, int64_t at_a_time) {
+    const double rounds = (double)ceil_div(n_batches, at_a_time);
     return rounds * (20.0 + 2.0 * (double)slots_per_batch / 1024.0) < 80.0 * (double)n_batches;
 }
 
@@ -413,7 +425,6 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
         if (h + 2 < n_layers) dst_cap = std::min<int64_t>(V, dst_cap * (h_fanouts[h] + 1));
         widest = std::max(widest, h_fanouts[h]);
     }
-    const bool by_group = n_layers >= 2 && presample_by_group(max_count, slots);
     // A group is as many batches as fit 192 MiB (larger device allocations take the runtime some 250 us to give back), more
     // where that would make more than 16 groups; groups are of equal size.
     // Bitmaps in LDS: lists and waiting vertices are per workgroup, and a group is a whole number of batches for each of them where it
@@ -421,7 +432,10 @@ extern "C" int32_t no_select_hot(no_graph_t g, const int32_t* d_train_ids, int64
     const int64_t n_ranges = ceil_div(V, PRESAMPLE_RANGE);
     const int32_t range = (int32_t)(ceil_div(ceil_div(V, n_ranges), 128) * 128);
     const int64_t later_cap = n_ranges > 1 ? last_slots : 0;
-    const bool in_lds = by_group && n_ranges <= PRESAMPLE_RANGES && widest <= 32 && std::min<int64_t>(max_count, PRESAMPLE_WORKERS) * (dst_cap + later_cap) <= PRESAMPLE_LIST_WORDS;
+    const bool fits_lds = n_ranges <= PRESAMPLE_RANGES && widest <= 32 && presample_fills_workgroup(batch, slots, widest, n_ranges) &&
+                          std::min<int64_t>(max_count, PRESAMPLE_WORKERS) * (dst_cap + later_cap) <= PRESAMPLE_LIST_WORDS;
+    const bool by_group = n_layers >= 2 && presample_by_group(max_count, slots, (fits_lds ? 1 : 2) * PRESAMPLE_WORKERS);
+    const bool in_lds = by_group && fits_lds;
     const int64_t words = ceil_div(V, 128) * 4, per_batch = words + (in_lds ? 0 : dst_cap);       // (32-bit words)
     int64_t group = 0, arena_words = 0, workers = 0;
     if (by_group) {

@@ -305,11 +305,27 @@ def test_select_hot_batch_counts_and_sizes(V, E, n_train, batch, fanouts, bits):
 @pytest.mark.parametrize("V,fanouts,batch", [
     (1_245_184, (16, 4, 2), 256),      # the most vertices that one bitmap in LDS holds; a thread draws 16 slots at most
     (1_245_185, (17, 3, 2), 256),      # two parts, and 17 slots
-    (2_500_000, (32, 2), 4),           # three parts, 32 slots, more batches than workgroups
+    (2_500_000, (32, 2), 4),           # room for three parts, but few seeds a batch: bitmaps in memory, more batches than compute units
     (4_980_736, (5, 16, 2), 256),      # four full parts
     (4_980_737, (5, 5, 2), 256),       # one vertex too many: bitmaps in memory
     (1_300_000, (33, 2), 256)])        # one slot too many: bitmaps in memory
 def test_select_hot_bitmaps_in_parts(V, fanouts, batch):
+    check_hot_against_oracle(V, fanouts, batch, 2)
+
+
+@pytest.mark.parametrize("V,fanouts,batch,epochs", [
+    (2_500_000, (32, 3, 2), 256, 1),   # three parts, 32 slots: just too few of them for LDS
+    (2_500_000, (32, 4, 2), 256, 1),   # enough
+    (2_500_000, (32, 4, 2), 256, 70),  # more batches than workgroups
+    (1_245_184, (16, 4, 2), 31, 1), (1_245_184, (16, 4, 2), 32, 1),            # one part: the least seeds a batch
+    (1_245_184, (5, 5, 2), 35, 1), (1_245_184, (5, 5, 2), 36, 1),              # and slots
+    (1_245_185, (7, 2, 2), 108, 1), (1_245_185, (7, 2, 2), 109, 1),            # two parts
+    (1_245_185, (17, 16, 2), 78, 1), (1_245_185, (17, 16, 2), 79, 1)])         # and wide rows
+def test_select_hot_bitmaps_in_lds_and_in_memory(V, fanouts, batch, epochs):
+    check_hot_against_oracle(V, fanouts, batch, epochs)
+
+
+def check_hot_against_oracle(V, fanouts, batch, epochs):
     b = nb()
     rng = np.random.default_rng(V)
     E = 3_000_000                      # most vertices have a few neighbours, some thousands have far more than a draw takes
@@ -320,8 +336,8 @@ def test_select_hot_bitmaps_in_parts(V, fanouts, batch):
     train = np.unique(train).astype(np.int32)
     rng.shuffle(train)
     print("V %d, %d train ids" % (V, len(train)), flush=True)
-    oc = ora.select_hot(og, train, batch, fanouts, 2, 0.01, 1, 4, 5)
-    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, fanouts, 2, 0.01, 1, 4, 5), V)
+    oc = ora.select_hot(og, train, batch, fanouts, epochs, 0.01, 1, 4, 5)
+    view = b.no_cache_view(b.no_select_hot(gg, dev(train), batch, fanouts, epochs, 0.01, 1, 4, 5), V)
     assert oc.freq.max() > 1 and (oc.freq > 0).sum() > 5000
     assert np.array_equal(view["freq"].cpu().numpy().astype(np.int64), oc.freq)
     assert np.array_equal(view["hot_ids"].cpu().numpy(), oc.hot_ids)
