@@ -6,10 +6,11 @@
 // One hop is four kernels over a fixed-stride ("padded") edge array, slot q = row * fanout + j:
 //   1. sample_rows   a sub-wave group of G lanes (G = 8/16/32/64 >= fanout) serves one destination;
 //                    lane j draws slot j with Philox4x32-10 keyed by (stream; vertex, slot, domain,
-//                    hop), the group resolves the partial Fisher-Yates swap chain with cross-lane
-//                    shuffles, and every sampled id does atomicMin(map[id], n_dst + q): the first
+//                    hop), the group hands the partial Fisher-Yates swap chain from lane to lane
+//                    by DPP, and every sampled id does atomicMin(map[id], n_dst + q): the first
 //                    occurrence of an id in (row, slot) order wins, whatever the execution order;
-//   2. edge_tile_sums  per 1024-slot tile: number of sampled edges and of first occurrences;
+//   2. edge_tile_sums  per 1024-slot tile: number of sampled edges and of first occurrences
+//                    (many tiles: tile_offsets adds them up);
 //   3. edge_assign   tile prefix + block scan: compact edge ids, row pointers, new local ids in
 //                    first-occurrence order, map[id] = local id;
 //   4. edge_indices  indices[e] = map[id]; counts per source for the transpose.
@@ -30,7 +31,7 @@ namespace no {
 
 // Tiles of the slot scans: 1024 slots (four per thread). Measured on three hops of 15 K / 34 K / 122 K slots: sampling
 // stage 232 / 190 / 173 / 171 / 179 us at 4096 / 2048 / 1024 / 512 / 256 slots per tile (a thread's dependent loads and
-// its scattered stores are the latency of the kernel; more tiles only lengthen the look-back by one poll per 64).
+// its scattered stores are the latency of the kernel; more tiles are more sums for every block to add up).
 constexpr int ETHREADS = 256, EITEMS = 4, ETILE = ETHREADS * EITEMS;
 
 // ---------------------------------------------------------------------------- 1. sampling
@@ -133,9 +134,51 @@ __global__ void __launch_bounds__(ETHREADS) edge_tile_sums_kernel(int32_t* __res
     if (threadIdx.x == 0) tile_sums[blockIdx.x] = s;
 }
 
+// The sum of the first n tiles, to all threads of the block: added up here, or read where tile_offsets_kernel has done it.
+__device__ __forceinline__ int64_t tiles_before(const int64_t* __restrict__ tile_sums, int64_t n, int32_t summed, int64_t* smem) {
+    if (summed) return tile_sums[n];
+    int64_t s = 0;
+    for (int64_t t = threadIdx.x; t < n; t += ETHREADS) s += tile_sums[t];
+    return block_sum<int64_t, ETHREADS>(s, smem);
+}
+
+// Sums of the tiles before each of them in place of their own, and behind them the sum of all, by one block. Without it every block adds up all tiles
+// before its own, which grows with their square. Measured, without / with: bulk refresh of 14 K tiles 1.17 / 1.14 ms, of 81 K 6.79 / 5.43, of
+// 271 K 32.4 / 17.4, of 1.08 M 313 / 30.8; sampling with room for 23 K tiles, of which a batch fills a part, 489 / 502 us.
+constexpr int64_t OFFSETS_TILES = 24576;
+__global__ void __launch_bounds__(1024) tile_offsets_kernel(const int32_t* d_n, int32_t k, int64_t* sums) {
+    constexpr int PER = 8;
+    __shared__ int64_t smem[1024 / 64 + 1];
+    const int64_t n_tiles = ((int64_t)*d_n * k + ETILE - 1) / ETILE;
+    int64_t v[PER], next[PER], carry = 0;
+    auto request = [&](int64_t base) {
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t t = base + (int64_t)threadIdx.x * PER + i;
+            next[i] = t < n_tiles ? sums[t] : 0;
+        }
+    };
+    request(0);
+    for (int64_t base = 0; base < n_tiles; base += 1024 * PER) {
+        int64_t s = 0, total;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) s += v[i] = next[i];
+        request(base + 1024 * PER);
+        int64_t run = carry + block_exclusive_scan<int64_t, 1024>(s, &total, smem);
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int64_t t = base + (int64_t)threadIdx.x * PER + i;
+            if (t < n_tiles) sums[t] = run;
+            run += v[i];
+        }
+        carry += total;
+    }
+    if (threadIdx.x == 0) sums[n_tiles] = carry;
+}
+
 __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __restrict__ nbr_pad, int32_t* map,
                                                                const int32_t* d_n_dst, int32_t k, uint64_t k_magic,
-                                                               const int64_t* __restrict__ tile_sums,
+                                                               const int64_t* __restrict__ tile_sums, int32_t summed,
                                                                int32_t* __restrict__ indptr, int32_t* __restrict__ nbr,
                                                                int32_t* __restrict__ edge_row, int32_t* __restrict__ src_global,
                                                                int32_t* counts /* [0]=n_dst (in), [1]=n_src, [2]=nnz */,
@@ -146,9 +189,7 @@ __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __
     const int64_t n_pad = (int64_t)n_dst * k;
     const int64_t n_tiles = (n_pad + ETILE - 1) / ETILE;
     if (blockIdx.x == 0) {
-        int64_t s = 0;
-        for (int64_t t = threadIdx.x; t < n_tiles; t += ETHREADS) s += tile_sums[t];
-        s = block_sum<int64_t, ETHREADS>(s, smem);
+        const int64_t s = tiles_before(tile_sums, n_tiles, summed, smem);
         if (threadIdx.x == 0) {
             const int32_t nnz = (int32_t)(s & 0xffffffffll), n_new = (int32_t)(s >> 32);
             indptr[n_dst] = nnz;
@@ -158,12 +199,7 @@ __global__ void __launch_bounds__(ETHREADS) edge_assign_kernel(const int32_t* __
     }
     const int64_t base = (int64_t)blockIdx.x * ETILE;
     if (base >= n_pad) return;
-    int64_t tile_off = 0;
-    {
-        int64_t s = 0;
-        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += ETHREADS) s += tile_sums[t];
-        tile_off = block_sum<int64_t, ETHREADS>(s, smem);
-    }
+    const int64_t tile_off = tiles_before(tile_sums, blockIdx.x, summed, smem);
     const int64_t q0 = base + (int64_t)threadIdx.x * EITEMS;
     int64_t f[EITEMS];
     int32_t u[EITEMS];
@@ -408,7 +444,7 @@ __global__ void __launch_bounds__(ETHREADS) v1_tile_sums_kernel(CacheProbe probe
 __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* __restrict__ v1, const int32_t* __restrict__ probe_slot,
                                                                 const int32_t* __restrict__ probe_ver,
                                                                 const int32_t* d_n_v1,
-                                                                const int64_t* __restrict__ tile_sums, int32_t* map,
+                                                                const int64_t* __restrict__ tile_sums, int32_t summed, int32_t* map,
                                                                 int32_t* compute_list, int32_t* compute_pos, int32_t* compute_inv,
                                                                 int32_t* refresh_slot, int32_t* hit_pos,
                                                                 int32_t* hit_slot, int32_t* extra /* n_compute, n_hit, -, -, n_refresh */,
@@ -421,9 +457,7 @@ __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* _
     const int64_t n = *d_n_v1;
     const int64_t n_tiles = (n + ETILE - 1) / ETILE;
     if (blockIdx.x == 0) {
-        int64_t s = 0;
-        for (int64_t t = threadIdx.x; t < n_tiles; t += ETHREADS) s += tile_sums[t];
-        s = block_sum<int64_t, ETHREADS>(s, smem);
+        const int64_t s = tiles_before(tile_sums, n_tiles, summed, smem);
         if (threadIdx.x == 0) {
             const int32_t n_compute = (int32_t)(s & 0xffffffffll);
             extra[0] = n_compute;
@@ -433,12 +467,7 @@ __global__ void __launch_bounds__(ETHREADS) v1_partition_kernel(const int32_t* _
     }
     const int64_t base = (int64_t)blockIdx.x * ETILE;
     if (base >= n) return;
-    int64_t tile_off = 0;
-    {
-        int64_t s = 0;
-        for (int64_t t = threadIdx.x; t < (int64_t)blockIdx.x; t += ETHREADS) s += tile_sums[t] & 0xffffffffll;
-        tile_off = block_sum<int64_t, ETHREADS>(s, smem);
-    }
+    const int64_t tile_off = tiles_before(tile_sums, blockIdx.x, summed, smem) & 0xffffffffll;
     const int64_t i0 = base + (int64_t)threadIdx.x * EITEMS;
     int32_t c[EITEMS], slot[EITEMS], vv[EITEMS], pv[EITEMS];
     int64_t s = 0;
@@ -627,6 +656,12 @@ __global__ void unstamp_kernel(const int32_t* __restrict__ refresh_slot, const i
 static inline int64_t edge_tiles(int64_t n_pad_cap) { int64_t t = ceil_div(n_pad_cap, ETILE); return t < 1 ? 1 : t; }
 // words of one scan: a word a tile (status words, or the sums of the two-launch form), then the counter of finished tiles
 static inline int64_t scan_words(int64_t n_pad_cap) { return edge_tiles(n_pad_cap) + 1; }
+// scans with room for more than OFFSETS_TILES tiles have their sums added up by a launch between the two
+static inline int32_t scan_summed(int64_t n_pad_cap, const int32_t* d_n, int32_t k, int64_t* tile_sums, hipStream_t st) {
+    if (edge_tiles(n_pad_cap) <= OFFSETS_TILES) return 0;
+    hipLaunchKernelGGL(tile_offsets_kernel, dim3(1), dim3(1024), 0, st, d_n, k, tile_sums);
+    return 1;
+}
 static inline bool scan_one_launch(const no_blocks_s* b, int64_t n_pad_cap) { return !b->scan_two_pass && edge_tiles(n_pad_cap) <= ONE_LAUNCH_TILES; }
 // does this hop count the edges that leave each source (for its transpose, or for the symmetric normalisation)?
 static inline bool counts_sources(const no_blocks_s* b, const HopBuffers& H) { return H.has_csc || b->count_sources; }
@@ -753,9 +788,10 @@ static int32_t sample_hop(const RowT* rowptr, const int32_t* col, no_blocks_s* b
     if (!scan_one_launch(b, H.nnz_cap)) {
         hipLaunchKernelGGL(edge_tile_sums_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, H.nbr_pad.p,
                            (const int32_t*)b->map.p, (const int32_t*)cnt, k, tile_sums, H.csc_cnt.p, n_zero, side);
+        const int32_t summed = scan_summed(H.nnz_cap, cnt, k, tile_sums, st);
         side_take(b, tiles, &side);
         hipLaunchKernelGGL(edge_assign_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p,
-                           b->map.p, (const int32_t*)cnt, k, k_magic, (const int64_t*)tile_sums, H.indptr.p, H.nbr_global.p,
+                           b->map.p, (const int32_t*)cnt, k, k_magic, (const int64_t*)tile_sums, summed, H.indptr.p, H.nbr_global.p,
                            H.edge_row.p, H.src_global.p, cnt, side);
     } else {
         hipLaunchKernelGGL(edge_scan_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, (const int32_t*)H.nbr_pad.p,
@@ -814,9 +850,10 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
                                b->probe_slot.p, b->probe_ver.p, tiles, (const int32_t*)(b->counts.p + 4 * (h - 1) + 2),
                                (const int32_t*)P.nbr_global.p, (const int32_t*)b->map.p, P.indices.p,
                                counts_sources(b, P) ? P.csc_cnt.p : nullptr, P.has_csc ? P.csc_dst.p : nullptr, side);
+            const int32_t summed = scan_summed(P.n_src_cap, d_n, 1, tile_sums, st);
             side_take(b, tiles, &side);
             hipLaunchKernelGGL(v1_partition_kernel, dim3(tiles + side.side_blocks()), dim3(ETHREADS), 0, st, d_dst,
-                               (const int32_t*)b->probe_slot.p, (const int32_t*)b->probe_ver.p, d_n, (const int64_t*)tile_sums, b->map.p, b->compute_list.p, b->compute_pos.p, b->compute_inv.p, b->refresh_slot.p, b->hit_pos.p,
+                               (const int32_t*)b->probe_slot.p, (const int32_t*)b->probe_ver.p, d_n, (const int64_t*)tile_sums, summed, b->map.p, b->compute_list.p, b->compute_pos.p, b->compute_inv.p, b->refresh_slot.p, b->hit_pos.p,
                                b->hit_slot.p, extra, stamp_refresh ? cache->version.p : nullptr, (int32_t)step,
                                b->refresh_old.p, side);
             }

@@ -435,6 +435,30 @@ def test_sample_blocks_scans_in_one_launch_and_in_two(V, batch):
             compare_blocks(b, blocks, ora.sample_blocks(og, seeds, fanouts, 0, step, oc if with_cache else None), with_cache=with_cache)
 
 
+@pytest.mark.parametrize("V,E,batch,fanouts", [
+    (600_000, 3_000_000, 400_000, (64,)),             # 25,000 tiles of slots: their sums by a launch of their own
+    (26_000_000, 4_000_000, 450_000, (64, 2))])       # and room for as many of V^1
+def test_sample_blocks_scans_of_very_many_tiles(V, E, batch, fanouts):
+    b = nb()
+    rng = np.random.default_rng(E)
+    src, dst = (rng.integers(0, V, E).astype(np.int32) for _ in range(2))
+    dst[:E // 4] = rng.integers(0, 2000, E // 4)      # (some rows of more entries than a draw takes)
+    og, gg = ora.build_csr(src, dst, V), b.no_build_csr(dev(src), dev(dst), V, 32)
+    seeds = np.concatenate([np.arange(2000, dtype=np.int32), 2000 + rng.permutation(V - 2000)[:batch - 2000].astype(np.int32)])
+    assert batch * 64 > 24_576 * 1024 and (len(fanouts) == 1 or min(batch * 65, V + batch) > 24_576 * 1024)
+    oc = gc = None
+    if len(fanouts) > 1:
+        args = (1024, fanouts, 1, 0.02, 2, 8, 0)
+        oc, gc = ora.select_hot(og, seeds[:4096], *args), b.no_select_hot(gg, dev(seeds[:4096]), *args)
+        oc.version[:] = np.random.default_rng(1).integers(-1, 6, oc.n_hot)
+        b.no_cache_view(gc, V)["version"].copy_(dev(oc.version.astype(np.int32)))
+    blocks = b.no_blocks_create(gg, batch, fanouts)
+    for step, n in [(5, batch), (6, 3)]:
+        print("V %d, %d of %d seeds" % (V, n, batch), flush=True)
+        b.no_sample_blocks(gg, dev(seeds[:n]), 0, step, gc, blocks)
+        compare_blocks(b, blocks, ora.sample_blocks(og, seeds[:n], fanouts, 0, step, oc), with_cache=oc is not None)
+
+
 # --------------------------------------------------------------------------------------- gather
 
 @pytest.mark.parametrize("dim,dtype", [(64, "f32"), (602, "f32"), (100, "f32"), (7, "f32"), (256, "f32"),
