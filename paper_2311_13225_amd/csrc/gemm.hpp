@@ -85,10 +85,12 @@ int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool
 inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
-// Whether a forward product of about `rows` rows does (gemm_nn_forward says why the line lies there).
-inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N) {
+// Whether a forward product of about `rows` rows does (gemm_nn_forward says why the lines lie there).
+inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N, int32_t n_problems) {
     const int64_t tiles = ceil_div(rows, 64) * ceil_div(N, 64);
-    return K >= 8 && tiles >= 512 && tiles * (K + 50) >= 150000;
+    if (K < 8 || N == 64 || tiles < 512 || tiles * (K + 50) < 150000) return false;
+    const bool half_empty = N % 128 > 0 && N % 128 <= 64;      // (the last column tile, of 128)
+    return n_problems > 1 || (tiles * (K + 150) >= 325000 && (K >= 128 || !half_empty));
 }
 // Matrices cut by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
 // blocks [end_block[j-1], end_block[j]) of them.

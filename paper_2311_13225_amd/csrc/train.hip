@@ -102,7 +102,7 @@ struct no_model_s {
     // the matrices cut for the large forward products, at the start of every step, and those of the layers above layer 1 for their input
     // gradients, by extra blocks of the loss launch (cut_weights): made again in every step, so that no copy of them outlives one
     no::DevBuf<uint16_t> planes;
-    uint16_t* cut_fwd[NO_MAX_LAYERS][2] = {{nullptr}};      // (NULL: no large product)
+    uint16_t* cut_fwd[NO_MAX_LAYERS][2] = {{nullptr}};      // (NULL: no large product, in any form of the layer)
     uint16_t* cut_bwd[NO_MAX_LAYERS][2] = {{nullptr}};
     bool weights_dirty = true;
     no::DevBuf<float> mean[NO_MAX_LAYERS];           // layer l (index l-1): [n_dst_cap, d_{l-1}]
@@ -115,6 +115,25 @@ struct no_model_s {
     no::DevBuf<no_step_stats> stats;
     bool last_used_cache = false;
     int32_t arch = NO_ARCH_SAGE_MEAN;
+    // rows that layer l + 1's products have in about every step (a batch fills 15 to 45 % of the capacity of the hops below the seeds; the
+    // seeds' own products are small)
+    int64_t rows_about(int32_t l) const { return (int64_t)blocks->hop[n_layers - 1 - l].n_dst_cap * 2 / 5; }
+    bool bf16_products(int32_t l) const { return l == 0 && feat_dtype == NO_BF16 && arch == NO_ARCH_SAGE_MEAN; }
+    // Where the steps cut layer l + 1's matrices for its forward product (NULL: they do not). The launch that cuts is on the step's path, and sparse
+    // batches fill less of their room the larger they are, so the product has to be a long one; one of a column count that is no
+    // multiple of 64, which the fp32 instruction reads one by one, need not be as long. Once layer 1's is cut, the upper layers' ride with it.
+    // Measured, us a step without / with planes. 800 K vertices, three hops, batches of 400, 1000, 2000 and 4096: 100 features, 256 columns 169 / 175,
+    // 242 / 244, 350 / 352, 514 / 499; 200 columns 169 / 174, 244 / 239, 347 / 336; 256 features, 128 columns 161 / 166, 216 / 219, 300 / 291; 32
+    // features, 128 columns, 1000 154 / 165. 233 K vertices, two hops, batches of 1500 and 3000: 602 features, 256 columns 233 / 227, 347 / 307; 300
+    // features 178 / 178, 252 / 232. One product: 602 features, batches of 1024 174 / 177, of 2048 247 / 239; three hops, batches
+    // of 2048, 100 features 352 / 360, 256 features, 200 columns 462 / 448, of 4096, 256 columns 625 / 602.
+    uint16_t* const* planes_of(int32_t l) const {
+        const bool one = no::arch_is_gcn(arch);
+        if (!cut_fwd[l][0] || bf16_products(l) || !no::forward_takes_planes(rows_about(l), dims[l], dims[l + 1], one ? 1 : 2)) return nullptr;
+        const int64_t work = no::ceil_div(rows_about(l), 64) * no::ceil_div(dims[l + 1], 64) * dims[l];
+        const int64_t least = (dims[l + 1] % 64 ? 400000 : 600000) / (dims[l] >= 300 ? 2 : 1) * (one ? 2 : 1);
+        return work >= least || (l > 0 && planes_of(0)) ? cut_fwd[l] : nullptr;
+    }
     // sampling ahead (Section 4.2, Stage 1): a second set of blocks and destination rows filled on a stream of its
     // own while the current batch trains; created by the first call that asks for it
     no_blocks_s* blocks_alt = nullptr;
@@ -250,8 +269,7 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
     uint16_t* at = m->planes.p;
     for (int32_t l = 0; l < L; ++l)
         for (int q = 0; q < 2; ++q) {
-            // (a batch fills 15 to 45 % of a hop's capacity)
-            if (forward_takes_planes((int64_t)m->blocks->hop[L - 1 - l].n_dst_cap * 2 / 5, m->dims[l], m->dims[l + 1])) m->cut_fwd[l][q] = at;
+            if (forward_takes_planes(m->rows_about(l), m->dims[l], m->dims[l + 1], 2)) m->cut_fwd[l][q] = at;
             at += cut_weights_elements(m->dims[l], m->dims[l + 1], true);
             if (l == 0) continue;
             m->cut_bwd[l][q] = at;
@@ -380,13 +398,13 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         NO_CHECK(ensure_lookahead(m, g));
     }
     // bf16 table: layer 1's products take bf16 operands (features as stored; mean, weights, output gradient rounded)
-    const bool bf16_products = m->feat_dtype == NO_BF16 && m->arch == NO_ARCH_SAGE_MEAN;
+    const bool bf16_products = m->bf16_products(0);
     // The weights of the step's large forward products, cut. Ahead of the wait for a batch prepared on the other stream, which leaves the
     // stream idle for some 10 us: the launch runs there.
     {
         CutJobs cut;
         for (int32_t l = 0; l < L; ++l) {
-            if (!m->cut_fwd[l][0] || (l == 0 && bf16_products)) continue;
+            if (!m->planes_of(l)) continue;
             cut.add(m->params.p + m->off_w_self[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][0], true);
             if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][1], true);
         }
@@ -579,11 +597,11 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                   m->params.p + m->off_bias[0], d_out, l < L ? 1 : 0, m->mean[0].p, h_out, w, st, &prof,
                                   NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
-                                  bf16_products ? &bfp : nullptr, B, m->cut_fwd[0][0] ? m->cut_fwd[0] : nullptr));
+                                  bf16_products ? &bfp : nullptr, B, m->planes_of(0)));
         } else
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,
-                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->cut_fwd[l - 1][0] ? m->cut_fwd[l - 1] : nullptr));
+                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->planes_of(l - 1)));
         if (l == L && L >= 2) prof.end();
         if (l == 1 && d_next_seeds) {
             if (next_uses_cache && L >= 2 && m->arch == NO_ARCH_SAGE_MEAN) NO_HIP_CHECK(hipEventRecord(m->ev_l1_done, st));

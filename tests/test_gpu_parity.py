@@ -414,11 +414,14 @@ def test_sample_blocks_with_cache_lookup():
 @pytest.mark.parametrize("V,batch", [
     (262_144, 8192),      # 248 tiles of slots, 256 of V^1 (as many as there are vertices): both scans in one launch
     (300_000, 8200),      # 249 and 257: the split of V^1 in two launches
-    (260_000, 8457),      # 257 and 254: the compaction in two
+    (250_000, 8457),      # 257 and 253: the compaction in two
     (300_000, 8457)])     # 257 and 265: both in two
 def test_sample_blocks_scans_in_one_launch_and_in_two(V, batch):
     b = nb()
     fanouts = (31, 3)
+    slots, v1 = batch * 31, min(batch * 32, V + batch)      # (room for: a batch of different seeds may have as many)
+    expected = {(262_144, 8192): (1, 1), (300_000, 8200): (1, 2), (250_000, 8457): (2, 1), (300_000, 8457): (2, 2)}[V, batch]
+    assert tuple(1 if -(-n // 1024) <= 256 else 2 for n in (slots, v1)) == expected
     src, dst, og, gg = make_graph(V, 8 * V, 3, 32)
     train = si.train_split(V, 0.65, 3)
     oc = ora.select_hot(og, train[:4096], 1024, fanouts, 1, 0.2, 2, 8, 0)
@@ -548,6 +551,17 @@ def forward_layer(b, n, cap, x, w_self, w_neigh, bias, relu):
     return h
 
 
+def forward_error(h, ref):
+    return np.linalg.norm(h - ref) / np.linalg.norm(ref)
+
+
+def forward_error_bound(K):
+    """Relative 2-norm error of sums of K products on pieces. A chain of 6 K / 16 additions rounds each to 2^-24 of a partial sum at most: taken as
+    independent, below 2^-24 sqrt(6 K / 16) / 2, and two roundings for the bias and the output. (A product without one of the six partial products
+    is off by 1.2e-6 and more: the middle pieces are about 2^-9 / sqrt(3) of their operands, 1.3e-6 together; the small ones 2^-17.)"""
+    return 2.0 ** -24 * (1.0 + np.sqrt(6 * K / 16) / 2)
+
+
 @pytest.mark.parametrize("n,cap,F,d_out", [
     (1, 9000, 256, 256), (63, 42_000, 8, 256), (65, 41_000, 9, 250),             # fewer rows than a tile; the shortest reductions
     (4096, 30_000, 31, 256), (4097, 30_000, 33, 256), (8200, 36_000, 40, 129),  # the last row of small tiles in one round, the first beyond
@@ -567,6 +581,33 @@ def test_sage_layer_forward_products_at_tile_edges(n, cap, F, d_out):
         mag = np.abs(x64) @ (np.abs(w_self).astype(np.float64) + np.abs(w_neigh)) + np.abs(bias)
         assert (np.abs(h[:n] - (np.maximum(ref, 0.0) if relu else ref)) <= (2 * F + 9) * 2.0 ** -24 * mag).all()
         assert (h[n:] == -7.0).all()
+        if not relu:
+            assert forward_error(h[:n], ref) <= forward_error_bound(2 * F)
+
+
+@pytest.mark.parametrize("n,cap,F,d_out", [
+    (1, 12_000, 400, 256), (65, 12_000, 410, 250),                       # fewer rows than a tile, a tile and a row
+    (17_300, 17_301, 150, 256), (17_200, 17_200, 149, 256),              # about the least work for planes with one product
+    (29_000, 29_000, 128, 129), (90_000, 90_000, 127, 129),              # a column tile that is half empty: the least reduction, one less
+    (16_500, 22_000, 602, 130), (8_193, 33_000, 333, 100), (20_000, 20_000, 300, 64)])
+def test_gcn_layer_forward_products_at_tile_edges(n, cap, F, d_out):
+    """One matrix. Rows that sample nothing: the aggregate is the row itself. Bounds as above."""
+    b = nb()
+    rng = np.random.default_rng(n + F)
+    x, w, bias = (rng.standard_normal(sh).astype(np.float32) for sh in ((cap, F), (F, d_out), d_out))
+    i32 = lambda a: dev(np.asarray(a, np.int32))
+    blk = b.block_view_from_tensors(i32([n]), i32([n]), i32(np.zeros(cap + 1)), i32(np.zeros(1)), cap, cap)
+    ws = torch.empty(b.no_sage_layer_ws_bytes(cap, cap, F, d_out), dtype=torch.uint8, device="cuda")
+    agg, h = torch.empty((cap, F), device="cuda"), torch.full((cap, d_out), -7.0, device="cuda")
+    ref = x[:n].astype(np.float64) @ w + bias
+    mag = np.abs(x[:n]).astype(np.float64) @ np.abs(w) + np.abs(bias)
+    for _ in range(2):                                                   # (a second call finds the first one's planes in the workspace)
+        print("one product", n, cap, F, d_out, flush=True)
+        b.no_gcn_layer_fwd(blk, dev(x), dev(w), dev(bias), False, agg, h, ws)
+        got = h.cpu().numpy()
+        assert (np.abs(got[:n] - ref) <= (F + 9) * 2.0 ** -24 * mag).all() and (got[n:] == -7.0).all()
+        assert forward_error(got[:n], ref) <= forward_error_bound(F)
+        w, ref = -w, 2.0 * bias.astype(np.float64) - ref
 
 
 def test_sage_layer_forward_products_of_infinities_and_the_largest_numbers():
@@ -1154,6 +1195,45 @@ def test_refresh_hot_rows_match_oracle(bf16):
     assert np.array_equal(view["version"].cpu().numpy(), ver2)
     assert_close(view["emb"].cpu().numpy(), emb2, "refreshed rows, second round")
     assert not np.array_equal(emb, emb2)
+
+
+@pytest.mark.parametrize("form", ["sage", "gcn", "gcn_sum", "gcn_sym"])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_refresh_of_many_hot_rows(form, bf16):
+    """Enough rows for the product on planes (36,002 and, twice in a row, with other weights; 70 features are no whole step), and the forms with
+    one matrix."""
+    b = nb()
+    V, F, D, fan = 40_003, 70, 250, (5, 4)
+    src, dst, og, gg = make_graph(V, 300_000, 4, 32)
+    feat = si.features(V, F, 4, "bf16" if bf16 else "f32")
+    oc = ora.select_hot(og, si.train_split(V, 0.65, 4), 512, fan, 1, 0.9, 3, D, 4)
+    gc = b.no_select_hot(gg, dev(si.train_split(V, 0.65, 4)), 512, fan, 1, 0.9, 3, D, 4)
+    gcn = form != "sage"
+    if gcn:
+        b.no_cache_set_layer_form(gc, b.ARCH_OF_NAME[form])
+    tfeat = dev(feat.view(np.int16) if bf16 else feat)
+    for version in (6, 9):
+        print(form, bf16, version, flush=True)
+        (w_self, w_neigh, bias), = si.init_weights([F, D], version)
+        b.no_refresh_hot_begin(gc, gg, tfeat, dev(w_self), None if gcn else dev(w_neigh), dev(bias), fan[-1], version, 99)
+        b.no_refresh_hot_commit(gc)
+        emb, ver = ora.refresh_hot(og, feat, oc, (w_self, bias) if gcn else (w_self, w_neigh, bias), fan[-1], version, 99, feat_is_bf16=bf16,
+                                   norm=ora.gcn_norm_of(form) if gcn else "mean")
+        view = b.no_cache_view(gc, V)
+        assert np.array_equal(view["version"].cpu().numpy(), ver)
+        got = view["emb"].cpu().numpy()
+        assert_close(got, emb, "refreshed rows")
+        # (the aggregate, of up to five rows, is rounded to fp32 before the product)
+        assert forward_error(got, emb) <= forward_error_bound(F if gcn else 2 * F) + 2.0 ** -23
+
+
+@pytest.mark.parametrize("ahead", [False, True])
+@pytest.mark.parametrize("arch", ["sage", "gcn", "gcn_sym"])
+def test_train_steps_with_forward_products_on_planes(arch, ahead):
+    import dataclasses
+    w = dataclasses.replace(si.WORKLOADS["tiny"], n_vertices=100_000, n_edges=600_000, batch=8000, fanouts=(10, 5), feat_dim=300, hidden=250,
+                            staleness=2, hot_fraction=0.2)
+    assert run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=ahead) > 0
 
 
 def test_superbatch_schedule_with_bulk_refresh():
