@@ -366,14 +366,8 @@ def main():
         mfma_note = {FWD: round(l1_flops / 1e12 / (ms["gemm_fwd_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4),
                      DW: round(dw_bf16_flops / 1e12 / (ms["gemm_dw_l1"] / 1e3) / MFMA_BF16_PEAK_TFLOPS, 4)}
     else:
-        # (the library decides by two fifths of the rows there is room for)
-        rows_room = w.batch
-        for f in w.fanouts[:-1]:
-            rows_room = min(rows_room * (f + 1), w.n_vertices)
-        rows_about = rows_room * 2 // 5
         # (on planes, and always for the weight gradients: six bf16 products per fp32 one)
-        tiles = -(-rows_about // 64) * -(-w.dims[1] // 64)
-        planes = tiles >= 512 and tiles * (F + 50) >= 150000
+        planes = b.no_model_forward_planes(model, 1)
         if planes:
             FWD = "cut_fwd_kernel(l1 fwd)"
         kern[FWD] = ("mfma", gemm_fwd_flops / 1e12 / (ms["gemm_fwd_l1"] / 1e3), MFMA_BF16_PEAK_TFLOPS / 6 if planes else MFMA_F32_PEAK_TFLOPS,

@@ -305,6 +305,9 @@ int32_t no_model_grads(no_model_t m, int32_t layer, float** d_gw_self, float** d
 /* Activations of the last step: d_h fp32 [rows, dims[layer]] (layer 1 with a cache: all of V^1),
  * d_mean fp32 [n_dst, dims[layer-1]]. */
 int32_t no_model_activations(no_model_t m, int32_t layer, const float** d_h, const float** d_mean);
+/* *planes = 1 if the model's steps multiply this layer's forward product on the bf16 matrix cores, every fp32 operand in three exact bf16
+ * pieces (six bf16 products per fp32 one), else 0 (the fp32 instruction; bf16 operands in layer 1 on a bf16 table). */
+int32_t no_model_forward_planes(no_model_t m, int32_t layer, int32_t* planes);
 int32_t no_model_blocks(no_model_t m, no_blocks_t* blocks);   /* blocks of the last step (owned by m) */
 /* Gathered feature rows of the last step: the rows of the bottom hop's destinations [n_dst, F] (the
  * neighbour rows are read from the table by the fused layer-1 aggregation and are not materialised). */
@@ -374,7 +377,8 @@ int32_t no_model_destroy(no_model_t m);
  * Stages that are a single kernel launch: NO_STAGE_GATHER, NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1,
  * NO_STAGE_GEMM_DW_L1 (which carries the upper layers' products), NO_STAGE_SAMPLE_ROWS_BOTTOM. While enabled, the side tasks
  * of the sampling (local indices, transposes, id-map wipe), which otherwise ride on later launches, are finished before the
- * end of NO_STAGE_SAMPLE, so that stage is all of the sampling work of the step. */
+ * end of NO_STAGE_SAMPLE, so that stage is all of the sampling work of the step. NO_STAGE_GEMM_FWD_L1 also counts the launch that
+ * cuts a step's weights for its large forward products, the upper layers' among them. */
 enum {
     NO_STAGE_SAMPLE = 0,      /* all hops: sampling, relabel, hot lookup, local indices, transposes */
     NO_STAGE_GATHER = 1,      /* feature rows of the bottom hop's sources */

@@ -106,7 +106,7 @@ struct CutJobs {
     }
     uint32_t blocks() const { return n ? end_block[n - 1] : 0u; }
 };
-int32_t cut_all(const CutJobs& cut, hipStream_t st);      // in a launch of their own
+int32_t cut_all(const CutJobs& cut, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);      // in a launch of their own
 inline int32_t bf16_kpad(int32_t K) { return (K + 15) / 16 * 16; }
 int32_t weights_to_bf16_t(const float* w, int32_t K, int32_t N, int32_t Kpad, uint16_t* out, hipStream_t st);
 int32_t gemm_bf16_nn(const GemmBf16NNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);

@@ -61,9 +61,9 @@ int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool
 
 __global__ void __launch_bounds__(256) cut_all_kernel(CutJobs cut) { run_cut_jobs(cut, blockIdx.x); }
 
-int32_t cut_all(const CutJobs& cut, hipStream_t st) {
+int32_t cut_all(const CutJobs& cut, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (cut.n == 0) return NO_OK;
-    hipLaunchKernelGGL(cut_all_kernel, dim3(cut.blocks()), dim3(256), 0, st, cut);
+    NO_LAUNCH_TIMED(cut_all_kernel, dim3(cut.blocks()), dim3(256), st, ev0, ev1, cut);
     return launch_status("cut_all");
 }
 

@@ -333,6 +333,13 @@ extern "C" int32_t no_model_grads(no_model_t m, int32_t layer, float** d_gw_self
     return NO_OK;
 }
 
+extern "C" int32_t no_model_forward_planes(no_model_t m, int32_t layer, int32_t* planes) {
+    clear_error();
+    NO_REQUIRE(m && planes && layer >= 1 && layer <= m->n_layers, NO_ERR_INVALID_ARG, "no_model_forward_planes: bad argument");
+    *planes = m->planes_of(layer - 1) ? 1 : 0;
+    return NO_OK;
+}
+
 extern "C" int32_t no_model_activations(no_model_t m, int32_t layer, const float** d_h, const float** d_mean) {
     clear_error();
     NO_CHECK(check_layer_index(m, layer, "no_model_activations"));
@@ -399,6 +406,9 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     }
     // bf16 table: layer 1's products take bf16 operands (features as stored; mean, weights, output gradient rounded)
     const bool bf16_products = m->bf16_products(0);
+    StageProfiler& prof = m->prof;
+    prof.st = st;
+    prof.n = 0;
     // The weights of the step's large forward products, cut. Ahead of the wait for a batch prepared on the other stream, which leaves the
     // stream idle for some 10 us: the launch runs there.
     {
@@ -408,7 +418,9 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             cut.add(m->params.p + m->off_w_self[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][0], true);
             if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][1], true);
         }
-        NO_CHECK(cut_all(cut, st));
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        if (cut.n) prof.kernel_pair(NO_STAGE_GEMM_FWD_L1, &ev0, &ev1);
+        NO_CHECK(cut_all(cut, st, ev0, ev1));
     }
     // a batch sampled ahead by the previous call is used if it is exactly this one; anything else is dropped
     // (a cache is the same cache only with the same identity and an unchanged generation: a refresh commit, an
@@ -439,10 +451,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     }
     no_blocks_s* B = m->blocks;
     no_step_stats* stats = d_stats ? d_stats : m->stats.p;
-
-    StageProfiler& prof = m->prof;
-    prof.st = st;
-    prof.n = 0;
 
     // Sample. Only the destination rows of the bottom hop are gathered densely (layer 1's weight gradient reads them;
     // the forward product reads the table rows itself); that copy is one of the sampling call's side tasks and goes with

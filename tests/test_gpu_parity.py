@@ -1231,8 +1231,15 @@ def test_refresh_of_many_hot_rows(form, bf16):
 @pytest.mark.parametrize("arch", ["sage", "gcn", "gcn_sym"])
 def test_train_steps_with_forward_products_on_planes(arch, ahead):
     import dataclasses
+    b = nb()
     w = dataclasses.replace(si.WORKLOADS["tiny"], n_vertices=100_000, n_edges=600_000, batch=8000, fanouts=(10, 5), feat_dim=300, hidden=250,
                             staleness=2, hot_fraction=0.2)
+    src, dst, og, gg = make_graph(w.n_vertices, w.n_edges, w.seed, 32)
+    model = b.no_model_create(gg, w.dims, w.batch, w.fanouts)
+    b.no_model_set_arch(model, b.ARCH_OF_NAME[arch] if arch != "sage" else b.NO_ARCH_SAGE_MEAN)
+    assert b.no_model_forward_planes(model, 1) and not b.no_model_forward_planes(model, 2)
+    with pytest.raises(b.NoError):
+        b.no_model_forward_planes(model, 3)
     assert run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=ahead) > 0
 
 
