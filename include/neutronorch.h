@@ -215,6 +215,9 @@ int32_t no_gather_features(const void* d_table, no_dtype dt, int64_t n_rows, int
  * GraphSAGE-mean layer (Eq. 1 with AGGREGATE = average, Eq. 2 with a dense UPDATE)
  * ---------------------------------------------------------------------------------------- */
 
+/* Workspace of one layer call, forward or backward. A call may write all of it (the forward pass of a large fp32 layer keeps its weights, cut for
+ * the matrix cores, there), and nothing in it has to survive a call: calls in stream order may share one, calls that overlap in
+ * time, on different streams or in graphs replayed beside each other, need one each. */
 size_t no_sage_layer_ws_bytes(int32_t n_dst_cap, int32_t n_src_cap, int32_t d_in, int32_t d_out);
 
 /* Forward: d_mean[v,:] = average of d_x_src[indices[e],:] over row v (zeros for an empty row);
