@@ -185,7 +185,7 @@ __global__ void __launch_bounds__(PRESAMPLE_THREADS) presample_lds_kernel(Presam
 // (they end in the L2 of the die the workgroup runs on), a group of G lanes to a row, so that many workgroups share a compute
 // unit. Bound by the latency of the dependent reads list -> row pointers -> column entry -> bitmap, hidden by 32 waves per compute
 // unit (two workgroups, which is what the bound on the registers is for: with 106 scalar ones there was room for one, and 260 batches of 256 seeds,
-// fanouts 40, 20 and 5, took 812 us; like this 600). In place of batches one after another through the training sampler: 117 -> 4.3 ms on the graph above.
+// fanouts 40, 20 and 5, took 806 us; like this 597). In place of batches one after another through the training sampler: 117 -> 4.3 ms on the graph above.
 template <int G, typename RowT>
 __global__ void __launch_bounds__(PRESAMPLE_THREADS, 8) presample_kernel(PresampleJobs in, const RowT* __restrict__ rowptr,
                                                                       const int32_t* __restrict__ col, uint32_t* bitmaps, int64_t words,
