@@ -639,26 +639,6 @@ int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hip
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
     if (nn_tiles(a) <= 128) return launch_small_nn(a, false, st, ev0, ev1);
     if (a.cut_B[0]) return cut_fwd(a, st, ev0, ev1);
-    // The weights are cut by a launch of their own (3 to 5 us), here or at the start of a step; what the planes save grows with the tiles and,
-    // more slowly, with the reduction. Measured, a layer forward and backward, two products with 256 columns, us on the fp32 instruction / with
-    // planes: 9 K rows, K = 16 43.6 / 48.1, 128 65.2 / 66.9; 20 K rows, K = 32 58.1 / 58.8, 64 74.5 / 75.1, 100 89.8 / 88.2; 40 K rows, K = 16
-    // 89.4 / 85.5; 90 K rows, K = 47 266 / 248; the product alone at 13 K rows, K = 256 47.5 / 31 + 4.6. Below 512 tiles few blocks are
-    // left to hide the cut (3.4 K rows, K = 256: 17.4 / 15.8 + 2.8; a step whose second layer that is 224 / 230).
-    // One product has half of the work to save from: 12 K rows, 256 columns, K = 256 32 / 37, 602 60.3 / 59.9; 20 K rows, 256 columns, K = 100 30.3 / 31.2,
-    // 256 44.9 / 43.3; 128 columns, K = 256 34 / 38; 90 K rows, 200 columns, K = 8 45 / 38.5; 30 K rows, 100 columns, K = 200 44.5 / 38.9; and more of
-    // it in a column tile that is half empty: 90 K rows, 172 columns, K = 32 41 / 47, 200 117 / 109; 47 columns, K = 100 45 / 48, 256 76 / 74. 64 columns
-    // are one whole tile, for which rows are cut as often as for 128 (two products, 90 K rows, K = 100 54.5 / 58, 602 214 / 242; 47 columns, which the
-    // fp32 instruction reads one by one, 62.7 / 59 and 263 / 239).
-    const bool two = a.n_problems > 1;
-    const size_t each = cut_weights_elements(a.K[0], a.N, true);
-    if (forward_takes_planes(a.M_cap, a.K[0], a.N, a.n_problems) && (!two || a.K[1] == a.K[0]) && a.cut_scratch && (two ? 2 : 1) * each * 2 <= a.cut_scratch_bytes) {
-        GemmNNArgs c = a;
-        uint16_t* planes = (uint16_t*)a.cut_scratch;
-        NO_CHECK(cut_weights(a.B[0], two ? a.B[1] : nullptr, a.K[0], a.N, true, planes, st));
-        c.cut_B[0] = planes;
-        c.cut_B[1] = planes + each;
-        return cut_fwd(c, st, ev0, ev1);
-    }
     return launch_tiled_nn<false>(a, st, ev0, ev1);
 }
 

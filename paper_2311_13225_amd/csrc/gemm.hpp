@@ -15,7 +15,7 @@ struct GemmNNArgs {
     const int32_t* a_rows[2];             // per problem: row m of the operand is row a_rows[m] of A (NULL: row m)
     const float* B[2]; int64_t ldb[2];
     int32_t K[2];
-    // large products take the B operands as bf16 planes (cut_weights): made by the caller, or here in cut_scratch
+    // large products take the B operands as bf16 planes (cut_weights): made by the caller, or, for an input gradient, here in cut_scratch
     const uint16_t* cut_B[2];
     void* cut_scratch; size_t cut_scratch_bytes;
     float* C[2]; int64_t ldc[2];
@@ -85,12 +85,32 @@ int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool
 inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
-// Whether a forward product of about `rows` rows does (gemm_nn_forward says why the lines lie there).
+// Whether a forward product of about `rows` rows in a step or a bulk refresh does: from where it wins by enough to show in a step. Measured, two
+// products / one, with a launch for the weights, us on the fp32 instruction / on planes: 256 columns, 9 K rows, K = 128 65.2 / 66.9; 20 K rows, K = 64 74.5 / 75.1, 100
+// 89.8 / 88.2; 90 K rows, K = 47 266 / 248; one product, 12 K rows, K = 256 32 / 37, 602 60.3 / 59.9; 20 K rows, K = 100 30.3 / 31.2, 256 44.9 / 43.3; 90 K rows, 172 columns,
+// K = 32 41 / 47, 200 117 / 109. (The step of the sparse graph, batch 1024, 307 us with both hidden layers on planes, 310 without.)
 inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N, int32_t n_problems) {
     const int64_t tiles = ceil_div(rows, 64) * ceil_div(N, 64);
     if (K < 8 || N == 64 || tiles < 512 || tiles * (K + 50) < 150000) return false;
     const bool half_empty = N % 128 > 0 && N % 128 <= 64;      // (the last column tile, of 128)
     return n_problems > 1 || (tiles * (K + 150) >= 325000 && (K >= 128 || !half_empty));
+}
+// Whether the forward product of a layer call does. Its weights are cut by extra blocks of the aggregation in front of it. Measured, aggregation
+// and product, two products / one, time on planes over that on the fp32 instruction: 256 columns, 3.4 K rows, K = 256 1.10 / 1.15, 602 1.02 / 1.07; 5 K rows,
+// 100 1.02 / 1.05, 256 0.91 / 1.02, 602 0.82 / 0.89; 9 K rows, 64 1.05 / 1.18, 100 1.00 / 1.09, 256 0.90 / 1.01; 13 K rows, 32 0.95 / 1.03, 64 0.89 / 0.95, 100 0.83 /
+// 0.87, 256 0.77 / 0.85; 20 K rows, 32 1.00 / 1.04, 64 0.94 / 0.99, 100 0.92 / 0.93; 40 K rows, 16 0.81 / 0.91. 128 columns, 5 K rows, 602 1.00 / 1.05; 9 K rows, 100 1.03 /
+// 1.04, 256 0.91 / 1.02, 602 0.82 / 0.90; 20 K rows, 100 1.03 / 1.13, 256 0.91 / 1.00; 40 K rows, 100 0.94 / 0.97. 64 columns are one whole tile, for which rows are cut
+// as often as for 128: 13 K rows, 602 1.02 / 1.04, 20 K rows, 100 1.08 / 1.10, 256 0.95 / 1.05, 602 0.89 / 0.96. Columns that are no multiple of 64 the fp32
+// instruction reads one by one: 172 columns, K = 256, 3.4 K rows 0.80 / 0.97, 7 K 0.78 / 0.91; 100 columns, 5 K rows 0.81 / 0.97, 9 K 0.79 / 0.92; 47 columns, 9 K rows
+// 0.88 / 1.01, 40 K 0.84 / 0.96, K = 100 0.96 / 1.08 and 0.94 / 1.08; 100 columns, K = 32, 20 K rows 1.20 / 1.34, 40 K 0.99 / 1.06, 90 K 0.89 / 0.95;
+// one product, 90 K rows, 200 columns, K = 8 0.86, 172, K = 32 1.15.
+inline bool layer_takes_planes(int64_t rows, int32_t K, int32_t N, int32_t n_problems) {
+    const int64_t tiles = ceil_div(rows, 64) * ceil_div(N, 64);
+    const bool whole = N % 64 == 0, wide = N > 64, half_empty = N % 128 > 0 && N % 128 <= 64;      // (the last column tile, of 128)
+    if (K < 8) return false;
+    if (n_problems > 1)
+        return (K >= 200 && tiles >= (whole ? 300 : 140)) || (K >= 64 && tiles >= (N > 128 ? 700 : 1200) && wide) || (tiles >= (K >= 16 ? 2000 : 2600) && N != 64);
+    return wide && (K >= 128 || !half_empty) && ((K >= (whole ? 400 : 200) && tiles >= 300) || (K >= 64 && tiles >= (N > 128 ? 800 : 1200)) || tiles >= 2400);
 }
 // Matrices cut by extra blocks of another launch of blocks of 256 threads: matrix j, [K][N], takes the
 // blocks [end_block[j-1], end_block[j]) of them.

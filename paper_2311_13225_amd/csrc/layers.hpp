@@ -105,6 +105,7 @@ struct BelowLayer { const float* h = nullptr; const int32_t* out_rows = nullptr;
 int32_t layer_splits(int32_t n_dst_cap, int32_t d_in, int32_t d_out);
 LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out);
 
+// cut: matrices that extra blocks of the launch cut
 // side_of: the launch takes along the side tasks that this sampling call left (side_take)
 // agg_mode other than AGG_NEIGH_MEAN: the destination's own row (row r of x_src, or row self_idx[r]) joins the
 // aggregate (Eq. 1 over N_in(v) U {v})
@@ -112,7 +113,7 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
                        const int32_t* d_n_dst, int32_t n_dst_cap, float* mean, hipStream_t st,
                        int32_t agg_mode = AGG_NEIGH_MEAN, const int32_t* self_idx = nullptr, const RowCopyJob* copy = nullptr,
                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr,
-                       const PaddedSlots* padded = nullptr, no_blocks_s* side_of = nullptr);
+                       const PaddedSlots* padded = nullptr, no_blocks_s* side_of = nullptr, const CutJobs* cut = nullptr);
 int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_t* csc_indptr, const int32_t* csc_dst,
                             const int32_t* d_n_src, int32_t n_src_cap, const int32_t* d_n_dst, float* grad_x,
                             hipStream_t st, const float* mask_h = nullptr, const int32_t* out_rows = nullptr,
@@ -122,8 +123,9 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof = nullptr, int agg_stage = -1,
                      int gemm_stage = -1, const void* agg_table = nullptr, int32_t arch = NO_ARCH_SAGE_MEAN, const Layer1Reuse* reuse = nullptr, bool aggregate_done = false,
                      const SourceWeights* weights = nullptr, const PaddedSlots* padded = nullptr,
-                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr);
-// cut_fwd: the layer's two matrices cut for the forward product, by the caller; without them the product may cut them itself
+                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false);
+// cut_fwd: where the layer's matrices are cut for the forward product, beside the aggregation unless cut_done; without it a product that
+// takes planes has them cut into the workspace
 // cut_bwd: the layer's two matrices cut for the input gradient (kept by a model, rewritten by the reduction); without them the
 // product cuts them itself
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,

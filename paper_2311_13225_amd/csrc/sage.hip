@@ -6,7 +6,7 @@
 #include "layers.hpp"
 #include "handles.hpp"
 #include "gemm_tile.hpp"
-#include "side.hpp"
+#include "riders.hpp"
 
 #include <stdlib.h>
 #include <mutex>
@@ -289,7 +289,8 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
                            int32_t n_cap, const int32_t* d_n_init, float* out, int64_t ld_out, int32_t dim, hipStream_t st,
                            const int32_t* self_idx = nullptr, int32_t agg_mode = AGG_NEIGH_MEAN, const float* mask_h = nullptr,
                            const int32_t* out_rows = nullptr, float* masked_out = nullptr, const RowCopyJob* copy = nullptr,
-                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr, no_blocks_s* side_of = nullptr) {
+                           hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr, no_blocks_s* side_of = nullptr,
+                           const CutJobs* cut = nullptr) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -321,13 +322,11 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
         launch_as(weighted, std::false_type{}, side, grid);
     };
     if constexpr (MEAN) {
-        SideTasks side;
-        if (side_of) side_take(side_of, own, &side);
-        if (side.n > 0) {
-            if (sw.cnt) launch(std::true_type{}, side, own + side.side_blocks());
-            else launch(std::false_type{}, side, own + side.side_blocks());
-            return;
-        }
+        launch_with_riders(cut, side_of, own, [&](const auto& side, uint32_t grid) {
+            if (sw.cnt) launch(std::true_type{}, side, grid);
+            else launch(std::false_type{}, side, grid);
+        });
+        return;
     }
     NoSideTasks none;
     none.first_block = own;
@@ -415,7 +414,7 @@ __global__ void __launch_bounds__(256) padded_rows_kernel(RowCopyJob job, const 
 template <typename T, int VEC>
 static void launch_padded(const T* src, int64_t ld_src, const int32_t* pad, int32_t k, const int32_t* d_n, int32_t n_cap,
                           float* out, int64_t ld_out, int32_t dim, hipStream_t st, const int32_t* self_idx, int32_t agg_mode,
-                          const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1, no_blocks_s* side_of) {
+                          const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1, no_blocks_s* side_of, const CutJobs* cut) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -440,30 +439,23 @@ static void launch_padded(const T* src, int64_t ld_src, const int32_t* pad, int3
     };
     using Few = std::integral_constant<int, 8>;
     using Many = std::integral_constant<int, 16>;
-    SideTasks side;
-    if (side_of) side_take(side_of, own, &side);
-    NoSideTasks none;
-    none.first_block = own;
-    if (side.n > 0) {
-        if (k <= 8) launch(Few{}, side, own + side.side_blocks());
-        else launch(Many{}, side, own + side.side_blocks());
-    } else {
-        if (k <= 8) launch(Few{}, none, own);
-        else launch(Many{}, none, own);
-    }
+    launch_with_riders(cut, side_of, own, [&](const auto& side, uint32_t grid) {
+        if (k <= 8) launch(Few{}, side, grid);
+        else launch(Many{}, side, grid);
+    });
 }
 
 int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_t* indptr, const int32_t* indices,
                        const int32_t* d_n_dst, int32_t n_dst_cap, float* mean, hipStream_t st, int32_t agg_mode,
                        const int32_t* self_idx, const RowCopyJob* copy, hipEvent_t ev0, hipEvent_t ev1,
-                       const SourceWeights* weights, const PaddedSlots* padded, no_blocks_s* side_of) {
+                       const SourceWeights* weights, const PaddedSlots* padded, no_blocks_s* side_of, const CutJobs* cut) {
     if (n_dst_cap <= 0) return NO_OK;
     if (padded && padded->pad && !(weights && weights->cnt)) {
         // the rows are addressed through the sampler's slot array (global ids): two memory round trips fewer per item
         const int32_t* pad = padded->pad;
         const int32_t k = padded->k;
 #define NO_PAD_FWD(T, V, ptr) \
-    launch_padded<T, V>(ptr, dim, pad, k, d_n_dst, n_dst_cap, mean, dim, dim, st, self_idx, agg_mode, copy, ev0, ev1, side_of)
+    launch_padded<T, V>(ptr, dim, pad, k, d_n_dst, n_dst_cap, mean, dim, dim, st, self_idx, agg_mode, copy, ev0, ev1, side_of, cut)
         if (dt == NO_F32) {
             const float* x = (const float*)x_src;
             const bool a16 = (((uintptr_t)x | (uintptr_t)mean) & 15) == 0, a8 = (((uintptr_t)x | (uintptr_t)mean) & 7) == 0;
@@ -481,7 +473,7 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
     }
 #define NO_SEG_FWD(T, V, ptr) \
     launch_segment<T, V, true>(ptr, dim, indptr, indices, d_n_dst, n_dst_cap, nullptr, mean, dim, dim, st, self_idx, agg_mode, \
-                               nullptr, nullptr, nullptr, copy, ev0, ev1, weights, side_of)
+                               nullptr, nullptr, nullptr, copy, ev0, ev1, weights, side_of, cut)
     if (dt == NO_F32) {
         const float* x = (const float*)x_src;
         const bool a16 = (((uintptr_t)x | (uintptr_t)mean) & 15) == 0, a8 = (((uintptr_t)x | (uintptr_t)mean) & 7) == 0;
@@ -608,7 +600,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof, int agg_stage, int gemm_stage,
                      const void* agg_table, int32_t arch, const Layer1Reuse* reuse,
                      bool aggregate_done, const SourceWeights* weights, const PaddedSlots* padded,
-                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd) {
+                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd, bool cut_done) {
     // aggregate_done: `mean` (and the reused rows of H^1) were already written by an earlier launch of the same
     // aggregation (a batch prepared ahead); only the product runs
     // reuse: the output rows are scattered into H^1, recomputed hot rows also refresh the cache, and the reused
@@ -619,7 +611,22 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.c_rows = reuse->compute_pos;
         a.c_keep = reuse->emb; a.c_keep_rows = reuse->refresh_slot; a.c_keep_stamp = reuse->version; a.stamp = reuse->step;      // version == NULL: stamped by the split already
     };
-    if (arch_is_gcn(arch)) {
+    // The weights of a product on planes are cut beside the aggregation, which does not read them.
+    const bool gcn = arch_is_gcn(arch);
+    CutJobs cut;
+    uint16_t* own_planes[2];
+    const size_t each = cut_weights_elements(d_in, d_out, true);
+    auto takes_planes = agg_table ? forward_takes_planes : layer_takes_planes;
+    if (!cut_fwd && !bf && takes_planes(blk.n_dst_cap, d_in, d_out, gcn ? 1 : 2) && (gcn ? 1 : 2) * each * 2 <= w.fwd_planes_bytes) {
+        own_planes[0] = (uint16_t*)w.fwd_planes;
+        own_planes[1] = own_planes[0] + each;
+        cut_fwd = own_planes;
+    }
+    if (cut_fwd && !cut_done) {
+        cut.add(w_self, d_in, d_out, cut_fwd[0], true);
+        if (!gcn) cut.add(w_neigh, d_in, d_out, cut_fwd[1], true);
+    }
+    if (gcn) {
         // Eq. 1 over N_in(v) U {v} (the destination's own row joins the aggregate: average, sum, or symmetric
         // normalisation with per-source weights), Eq. 2 with one matrix
         hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -631,7 +638,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         }
         NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
                                 blk.n_dst_cap, mean, st, mode, agg_table ? blk.d_src_global : nullptr, hits, e0, e1,
-                                arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr, side_of));
+                                arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr, side_of, &cut));
         GemmNNArgs a{};
         a.A[0] = mean; a.lda[0] = d_in;
         a.B[0] = w_self; a.ldb[0] = d_out;
@@ -642,8 +649,6 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.bias = bias; a.relu = relu;
         scatter(a);
         a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
-        a.cut_scratch = w.fwd_planes;
-        a.cut_scratch_bytes = w.fwd_planes_bytes;
         e0 = e1 = nullptr;
         if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
         return gemm_nn_forward(a, st, e0, e1);
@@ -658,7 +663,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     if (!aggregate_done)
         NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
                                 blk.n_dst_cap, mean, st, AGG_NEIGH_MEAN, nullptr, hits, e0, e1, nullptr,
-                                agg_table ? padded : nullptr, side_of));
+                                agg_table ? padded : nullptr, side_of, &cut));
     if (bf) {
         // bf16 operands on the matrix cores: the destinations' rows straight from the table (bf16 as stored), the mean
         // rounded on load, the weights from their bf16 copies
@@ -694,8 +699,6 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     scatter(a);
     a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
     a.cut_B[1] = cut_fwd ? cut_fwd[1] : nullptr;
-    a.cut_scratch = w.fwd_planes;
-    a.cut_scratch_bytes = w.fwd_planes_bytes;
     e0 = e1 = nullptr;
     if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
     return gemm_nn_forward(a, st, e0, e1);

@@ -119,8 +119,9 @@ struct no_model_s {
     // seeds' own products are small)
     int64_t rows_about(int32_t l) const { return (int64_t)blocks->hop[n_layers - 1 - l].n_dst_cap * 2 / 5; }
     bool bf16_products(int32_t l) const { return l == 0 && feat_dtype == NO_BF16 && arch == NO_ARCH_SAGE_MEAN; }
-    // Where the steps cut layer l + 1's matrices for its forward product (NULL: they do not). The launch that cuts is on the step's path, and sparse
-    // batches fill less of their room the larger they are, so the product has to be a long one; one of a column count that is no
+    // Where the steps cut layer l + 1's matrices for its forward product (NULL: they do not). Beside that layer's aggregation; layer 1's of a batch
+    // prepared ahead by a launch on the step's path, and sparse batches fill less of their room the larger they are, so the product has to be a
+    // long one; one of a column count that is no
     // multiple of 64, which the fp32 instruction reads one by one, need not be as long. Once layer 1's is cut, the upper layers' ride with it.
     // Measured, us a step without / with planes. 800 K vertices, three hops, batches of 400, 1000, 2000 and 4096: 100 features, 256 columns 169 / 175,
     // 242 / 244, 350 / 352, 514 / 499; 200 columns 169 / 174, 244 / 239, 347 / 336; 256 features, 128 columns 161 / 166, 216 / 219, 300 / 291; 32
@@ -409,19 +410,6 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     StageProfiler& prof = m->prof;
     prof.st = st;
     prof.n = 0;
-    // The weights of the step's large forward products, cut. Ahead of the wait for a batch prepared on the other stream, which leaves the
-    // stream idle for some 10 us: the launch runs there.
-    {
-        CutJobs cut;
-        for (int32_t l = 0; l < L; ++l) {
-            if (!m->planes_of(l)) continue;
-            cut.add(m->params.p + m->off_w_self[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][0], true);
-            if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], m->dims[l], m->dims[l + 1], m->cut_fwd[l][1], true);
-        }
-        hipEvent_t ev0 = nullptr, ev1 = nullptr;
-        if (cut.n) prof.kernel_pair(NO_STAGE_GEMM_FWD_L1, &ev0, &ev1);
-        NO_CHECK(cut_all(cut, st, ev0, ev1));
-    }
     // a batch sampled ahead by the previous call is used if it is exactly this one; anything else is dropped
     // (a cache is the same cache only with the same identity and an unchanged generation: a refresh commit, an
     //  invalidate or a new bound since the split make the prepared batch another batch than a step would sample now)
@@ -429,6 +417,17 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                             m->ahead_n == n_seeds && m->ahead_cache == cache && m->ahead_features == d_features &&
                             (!cache || (cache->uid == m->ahead_cache_uid && cache->generation == m->ahead_cache_generation));
     bool aggregated = false;
+    // Layer 1's weights, cut, where no aggregation of this call takes that along. Ahead of the wait for the batch prepared on the other
+    // stream, which leaves this one idle for some 10 us: the launch runs there.
+    const bool cut_first = presampled && m->ahead_aggregated && m->planes_of(0);
+    if (cut_first) {
+        CutJobs cut;
+        cut.add(m->params.p + m->off_w_self[0], m->dims[0], m->dims[1], m->cut_fwd[0][0], true);
+        if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[0], m->dims[0], m->dims[1], m->cut_fwd[0][1], true);
+        hipEvent_t ev0 = nullptr, ev1 = nullptr;
+        prof.kernel_pair(NO_STAGE_GEMM_FWD_L1, &ev0, &ev1);
+        NO_CHECK(cut_all(cut, st, ev0, ev1));
+    }
     if (m->ahead_valid) {
         // (ev_sampled is recorded after everything the sampling stream did for that batch, the aggregation included)
         NO_HIP_CHECK(hipStreamWaitEvent(st, m->ev_sampled, 0));
@@ -580,7 +579,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             reuse.hits.d_n = extra + 1; reuse.hits.n_cap = blk.n_dst_cap; reuse.hits.dst = m->h[0].p; reuse.hits.dim = d_out;
         }
         LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out);
-        w.fwd_planes_bytes = 0;      // (the step has cut the weights that are to be cut)
+        w.fwd_planes_bytes = 0;      // (planes_of says which weights are cut)
         // symmetric normalisation: the column sums of the block's adjacency are the per-source edge counts of the hop
         // (written with the local indices); the fused layer-1 aggregate reads global ids,
         // so it also takes the local index of every entry
@@ -605,7 +604,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                   m->params.p + m->off_bias[0], d_out, l < L ? 1 : 0, m->mean[0].p, h_out, w, st, &prof,
                                   NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
-                                  bf16_products ? &bfp : nullptr, B, m->planes_of(0)));
+                                  bf16_products ? &bfp : nullptr, B, m->planes_of(0), cut_first));
         } else
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,

@@ -610,6 +610,13 @@ def test_gcn_layer_forward_products_at_tile_edges(n, cap, F, d_out):
         w, ref = -w, 2.0 * bias.astype(np.float64) - ref
 
 
+@pytest.mark.parametrize("n,cap,F,d_out", [(4750, 4801, 200, 256), (4700, 4736, 200, 256), (2900, 2945, 201, 190), (11_140, 11_140, 64, 250), (1, 4801, 300, 256),
+                                           (31_990, 32_000, 16, 256), (41_500, 41_600, 8, 250), (42_000, 42_000, 100, 128)])
+def test_sage_layer_forward_products_from_the_fewest_tiles_on(n, cap, F, d_out):
+    """Sizes about which a layer call takes its product to planes, whose weights the aggregation's launch cuts. Bounds as above."""
+    test_sage_layer_forward_products_at_tile_edges(n, cap, F, d_out)
+
+
 def test_sage_layer_forward_products_of_infinities_and_the_largest_numbers():
     """Infinite and NaN operands, and one near the end of the range, give what sums of fp32 products give, and nothing else changes."""
     b = nb()
@@ -1241,6 +1248,17 @@ def test_train_steps_with_forward_products_on_planes(arch, ahead):
     with pytest.raises(b.NoError):
         b.no_model_forward_planes(model, 3)
     assert run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=ahead) > 0
+
+
+def test_train_step_with_the_weights_of_two_layers_cut_beside_their_aggregations():
+    import dataclasses
+    b = nb()
+    w = dataclasses.replace(si.WORKLOADS["tiny"], n_vertices=100_000, n_edges=600_000, batch=2500, fanouts=(10, 5, 5), feat_dim=300, hidden=252,
+                            staleness=2, hot_fraction=0.2)
+    src, dst, og, gg = make_graph(w.n_vertices, w.n_edges, w.seed, 32)
+    model = b.no_model_create(gg, w.dims, w.batch, w.fanouts)
+    assert [b.no_model_forward_planes(model, layer) for layer in (1, 2, 3)] == [True, True, False]
+    assert run_steps(w, 2, use_cache=True, lr=0.02) > 0
 
 
 def test_superbatch_schedule_with_bulk_refresh():
