@@ -126,6 +126,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false);
 // cut_fwd: where the layer's matrices are cut for the forward product, beside the aggregation unless cut_done; without it a product that
 // takes planes has them cut into the workspace
+// input_products_done: both products of the input gradient are made already (head.hip)
 // cut_bwd: the layer's two matrices cut for the input gradient (kept by a model, rewritten by the reduction); without them the
 // product cuts them itself
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,
@@ -138,7 +139,27 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
                       const StatsJob* stats_job = nullptr, const float* gz_in = nullptr,
                       const BelowLayer* below = nullptr, GradJobs* pending = nullptr, bool defer = false,
                       const SourceWeights* weights = nullptr, const Bf16Products* bf = nullptr,
-                      uint16_t* const* cut_bwd = nullptr);
+                      uint16_t* const* cut_bwd = nullptr, bool input_products_done = false);
+// The last layer of a step over its n seeds and the loss (head.hip): everything from the rows of the layer below to the two input
+// gradients that the transposed sum reads. w_neigh == NULL: one matrix (GCN-style average or sum).
+constexpr int32_t HEAD_MOST_COLUMNS = 256, HEAD_MOST_CLASSES = 256;
+struct HeadArgs {
+    const float* x; const int32_t* indptr; const int32_t* idx;            // rows of the layer below [n_src, d], the seeds' block
+    const float* w_self; const float* w_neigh; const float* bias;
+    const int32_t* labels; const int32_t* seeds;
+    int32_t n, d, C, agg_mode;
+    float* mean; float* logits; float* grad; float* row_loss;
+    float* grad_self; float* grad_mean;                                  // [n, d]: of the seeds' own rows, of what the transpose spreads
+    int32_t* bad_label_flag; int32_t flag_value;
+    uint32_t row_blocks; int32_t parts;                                  // (set by the launch)
+};
+// Which last layers take it. Rows are read in units of four columns and stand in LDS, the logits too; the symmetric normalisation
+// has weights of its own for every source.
+inline bool head_takes(int32_t arch, int32_t d, int32_t C, int32_t n_src_cap) {
+    return arch != NO_ARCH_GCN_SYM && d % 4 == 0 && d <= HEAD_MOST_COLUMNS && C >= 4 && C <= HEAD_MOST_CLASSES &&
+           (int64_t)n_src_cap * d * 4 < (1ll << 32);
+}
+int32_t head_forward_backward(const HeadArgs& a, const CutJobs& cut, no_blocks_s* side_of, hipStream_t st);
 int32_t gather_rows(const void* d_table, int32_t row_bytes, int64_t table_stride, const int32_t* d_ids,
                     const int32_t* d_n, int32_t n_cap, void* d_out, int64_t out_stride, hipStream_t st);
 

@@ -711,7 +711,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
                       int reduce_stage, int dx_stage, const int32_t* grad_rows, float lr, float* w_self_rw,
                       float* w_neigh_rw, float* bias_rw, int32_t arch, const StatsJob* stats_job, const float* gz_in,
                       const BelowLayer* below, GradJobs* pending, bool defer, const SourceWeights* weights,
-                      const Bf16Products* bf, uint16_t* const* cut_bwd) {
+                      const Bf16Products* bf, uint16_t* const* cut_bwd, bool input_products_done) {
     const bool gcn = arch_is_gcn(arch);
     if (arch == NO_ARCH_GCN_SYM && grad_x_src && !(weights && weights->cnt)) {
         set_error("GCN-style layer with symmetric normalisation: the block has no per-source edge counts");
@@ -768,7 +768,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         a.cut_scratch = w.planes();
         a.cut_scratch_bytes = w.planes_bytes;
         a.d_M = blk.d_n_dst; a.M_cap = n_cap; a.N = d_in;
-        NO_CHECK(gemm_nn_input_grad(a, st));
+        if (!input_products_done) NO_CHECK(gemm_nn_input_grad(a, st));
         NO_CHECK(transpose_aggregate(w.gmean, d_in, blk.d_csc_indptr, blk.d_csc_dst, blk.d_n_src, blk.n_src_cap,
                                      blk.d_n_dst, grad_x_src, st, below ? below->h : nullptr, below ? below->out_rows : nullptr,
                                      below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr));

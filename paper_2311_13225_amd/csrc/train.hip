@@ -559,6 +559,8 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     }
 
     // forward
+    const int32_t C = m->dims[L];
+    const bool head = L >= 2 && head_takes(m->arch, m->dims[L - 1], C, B->hop[0].n_src_cap);      // the last layer goes with the loss
     no_block_view view[NO_MAX_LAYERS];
     for (int32_t h = 0; h < L; ++h) fill_block_view(B, h, &view[h]);
     for (int32_t l = 1; l <= L; ++l) {
@@ -605,7 +607,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                   NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
                                   bf16_products ? &bfp : nullptr, B, m->planes_of(0), cut_first));
-        } else
+        } else if (l < L || !head)
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,
                               nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->planes_of(l - 1)));
@@ -623,19 +625,33 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         }
     }
 
-    // loss on the seeds
-    const int32_t C = m->dims[L];
+    // loss on the seeds (with it the weights that the input gradients below take as planes are cut)
     prof.begin(NO_STAGE_LOSS);
     CutJobs cut;
-    for (int32_t l = 1; l < L; ++l) {
+    for (int32_t l = 1; l < (head ? L - 1 : L); ++l) {
         const int32_t K = m->dims[l], N = m->dims[l + 1];
         if (!input_grad_takes_planes(view[L - 1 - l].n_dst_cap, N, K, 2)) continue;
         cut.add(m->params.p + m->off_w_self[l], K, N, m->cut_bwd[l][0]);
         if (!arch_is_gcn(m->arch)) cut.add(m->params.p + m->off_w_neigh[l], K, N, m->cut_bwd[l][1]);
     }
-    hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)ceil_div(n_seeds, 4) + cut.blocks()), dim3(256), 0, st,
-                       (const float*)m->h[L - 1].p, d_labels, (const int32_t*)B->seeds.p, n_seeds, C, m->gh[L - 1].p, m->row_loss.p,
-                       B->counts.p + 4 * L + 7, B->call_id, cut);
+    if (head) {
+        HeadArgs a{};
+        a.x = m->h[L - 2].p; a.indptr = view[0].d_indptr; a.idx = view[0].d_indices;
+        a.w_self = m->params.p + m->off_w_self[L - 1]; a.bias = m->params.p + m->off_bias[L - 1];
+        a.w_neigh = arch_is_gcn(m->arch) ? nullptr : m->params.p + m->off_w_neigh[L - 1];
+        a.labels = d_labels; a.seeds = B->seeds.p;
+        a.n = n_seeds; a.d = m->dims[L - 1]; a.C = C;
+        a.agg_mode = m->arch == NO_ARCH_GCN ? AGG_SELF_MEAN : m->arch == NO_ARCH_GCN_SUM ? AGG_SELF_SUM : AGG_NEIGH_MEAN;
+        a.mean = m->mean[L - 1].p; a.logits = m->h[L - 1].p; a.grad = m->gh[L - 1].p; a.row_loss = m->row_loss.p;
+        a.grad_self = m->gh[L - 2].p;
+        a.grad_mean = carve_workspace(m->ws.p + m->ws_off[L - 1], view[0].n_dst_cap, a.d, C).gmean;
+        a.bad_label_flag = B->counts.p + 4 * L + 7; a.flag_value = B->call_id;
+        NO_CHECK(head_forward_backward(a, cut, B, st));
+    } else {
+        hipLaunchKernelGGL(softmax_xent_kernel, dim3((unsigned)ceil_div(n_seeds, 4) + cut.blocks()), dim3(256), 0, st,
+                           (const float*)m->h[L - 1].p, d_labels, (const int32_t*)B->seeds.p, n_seeds, C, m->gh[L - 1].p, m->row_loss.p,
+                           B->counts.p + 4 * L + 7, B->call_id, cut);
+    }
     prof.end();
     // (mean loss and block sizes are written by an extra block of the step's last kernel, the layer-1 reduction)
     StatsJob stats_job;
@@ -693,7 +709,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                l == 1 ? &prof : nullptr, NO_STAGE_BWD_L1_PREP, NO_STAGE_GEMM_DW_L1, NO_STAGE_BWD_L1_REDUCE,
                                -1, grad_rows, lr, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                                m->params.p + m->off_bias[l - 1], m->arch, l == 1 ? &stats_job : nullptr, gz_in,
-                               l >= 2 ? &below : nullptr, &pending, l >= 2, &sw, (bf16_products && l == 1) ? &bfp : nullptr, l >= 2 ? m->cut_bwd[l - 1] : nullptr));
+                               l >= 2 ? &below : nullptr, &pending, l >= 2, &sw, (bf16_products && l == 1) ? &bfp : nullptr, l >= 2 ? m->cut_bwd[l - 1] : nullptr, l == L && head));
     }
 
     // (the SGD step ran inside each layer's gradient reduction, after every kernel that read the weights;

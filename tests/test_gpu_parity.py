@@ -1261,6 +1261,18 @@ def test_train_step_with_the_weights_of_two_layers_cut_beside_their_aggregations
     assert run_steps(w, 2, use_cache=True, lr=0.02) > 0
 
 
+@pytest.mark.parametrize("arch,batch,fanouts,hidden,classes", [
+    ("sage", 1, (10, 5), 64, 16), ("sage", 15, (64, 2), 4, 4), ("gcn", 16, (17, 3), 8, 5), ("sage", 17, (3, 16, 2), 12, 15),    # a block's rows, short rows of few units
+    ("sage", 300, (33, 3), 256, 64), ("gcn_sum", 33, (9, 3), 60, 65), ("gcn", 129, (15, 3), 128, 17), ("sage", 100, (1, 2), 252, 47),    # column groups and 16s of classes
+    ("sage", 257, (7, 3), 100, 128), ("gcn", 260, (7, 3), 256, 129), ("sage", 65, (8, 4), 200, 192), ("sage", 65, (8, 4), 132, 193), ("gcn_sum", 40, (25, 3), 256, 256),
+    ("sage", 4100, (4, 2), 64, 20),                                                                                   # more row blocks than compute units
+    ("sage", 40, (8, 4), 260, 20), ("sage", 40, (8, 4), 66, 20), ("gcn", 40, (8, 4), 64, 3), ("sage", 40, (8, 4), 64, 257), ("gcn_sym", 40, (8, 4), 64, 20)])   # not in one launch
+def test_train_steps_at_the_edges_of_the_last_layers_launch(arch, batch, fanouts, hidden, classes):
+    import dataclasses
+    w = dataclasses.replace(si.WORKLOADS["tiny"], batch=batch, fanouts=fanouts, hidden=hidden, n_classes=classes, feat_dim=20, staleness=2, hot_fraction=0.2)
+    run_steps(w, 2, use_cache=True, lr=0.02, arch=arch)
+
+
 def test_superbatch_schedule_with_bulk_refresh():
     """n = 3 batches per super-batch, bound 2n - 1 = 5: every step against the oracle walking the same schedule;
     from the second super-batch on every hot vertex of V^1 is served from the cache."""
