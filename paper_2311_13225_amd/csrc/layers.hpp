@@ -67,6 +67,10 @@ enum { AGG_NEIGH_MEAN = 0,   // average of the sampled row (GraphSAGE-mean; the 
 
 inline bool arch_is_gcn(int32_t arch) { return arch == NO_ARCH_GCN || arch == NO_ARCH_GCN_SUM || arch == NO_ARCH_GCN_SYM; }
 
+inline int32_t aggregate_mode(int32_t arch) {
+    return arch == NO_ARCH_GCN_SUM ? AGG_SELF_SUM : arch == NO_ARCH_GCN_SYM ? AGG_SELF_SYM : arch == NO_ARCH_GCN ? AGG_SELF_MEAN : AGG_NEIGH_MEAN;
+}
+
 // Where the number of block edges that leave each source comes from (symmetric normalisation): counts per local
 // source, or the row pointers of the block's transpose (is_ptr); `local` maps entry p of the aggregated index array
 // to its local source when that array holds other ids (the fused layer-1 aggregate reads global ids).

@@ -630,14 +630,14 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         // Eq. 1 over N_in(v) U {v} (the destination's own row joins the aggregate: average, sum, or symmetric
         // normalisation with per-source weights), Eq. 2 with one matrix
         hipEvent_t e0 = nullptr, e1 = nullptr;
-        if (prof && agg_stage >= 0) prof->kernel_pair(agg_stage, &e0, &e1);
-        const int32_t mode = arch == NO_ARCH_GCN_SUM ? AGG_SELF_SUM : arch == NO_ARCH_GCN_SYM ? AGG_SELF_SYM : AGG_SELF_MEAN;
+        if (prof && agg_stage >= 0 && !aggregate_done) prof->kernel_pair(agg_stage, &e0, &e1);
         if (arch == NO_ARCH_GCN_SYM && !(weights && weights->cnt)) {
             set_error("GCN-style layer with symmetric normalisation: the block has no per-source edge counts");
             return NO_ERR_INVALID_ARG;
         }
-        NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
-                                blk.n_dst_cap, mean, st, mode, agg_table ? blk.d_src_global : nullptr, hits, e0, e1,
+        if (!aggregate_done)
+            NO_CHECK(mean_aggregate(agg_table ? agg_table : x_src, dt, d_in, blk.d_indptr, blk.d_indices, blk.d_n_dst,
+                                blk.n_dst_cap, mean, st, aggregate_mode(arch), agg_table ? blk.d_src_global : nullptr, hits, e0, e1,
                                 arch == NO_ARCH_GCN_SYM ? weights : nullptr, agg_table ? padded : nullptr, side_of, &cut));
         GemmNNArgs a{};
         a.A[0] = mean; a.lda[0] = d_in;

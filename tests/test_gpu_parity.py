@@ -1273,6 +1273,32 @@ def test_train_steps_at_the_edges_of_the_last_layers_launch(arch, batch, fanouts
     run_steps(w, 2, use_cache=True, lr=0.02, arch=arch)
 
 
+@pytest.mark.parametrize("forms", [("gcn", "sage"), ("sage", "gcn"), ("gcn_sym", "gcn_sum")])
+def test_a_batch_prepared_for_one_layer_form_is_not_used_for_another(forms):
+    b = nb()
+    w = si.WORKLOADS["tiny"]
+    _, _, _, gg = make_graph(w.n_vertices, w.n_edges, w.seed, 32)
+    feat, lab = dev(si.features(w.n_vertices, w.feat_dim, w.seed, "f32")), dev(si.labels(w.n_vertices, w.n_classes, w.seed))
+    train = si.train_split(w.n_vertices, 0.65, w.seed)
+    seeds = [dev(si.batch_seeds(train, w.batch, t)) for t in range(2)]
+    code = lambda form: b.NO_ARCH_SAGE_MEAN if form == "sage" else b.ARCH_OF_NAME[form]
+    grads = []
+    for ahead in (True, False):
+        model = b.no_model_create(gg, w.dims, w.batch, w.fanouts)
+        for layer, three in enumerate(si.init_weights(w.dims, w.seed)):
+            for t, a in zip(b.no_model_params(model, layer + 1), three):
+                t.copy_(dev(a))
+        for step, form in enumerate(forms):
+            b.no_model_set_arch(model, code(form))
+            if ahead:
+                b.no_train_step_ahead(model, gg, feat, lab, seeds[step], seeds[1] if step == 0 else None, False, None, step, w.seed, 0.01)
+            else:
+                b.no_train_step(model, gg, feat, lab, seeds[step], None, step, w.seed, 0.01)
+        grads.append([t.cpu().numpy() for layer in (1, 2) for i, t in enumerate(b.no_model_grads(model, layer)) if i != 1 or forms[1] == "sage"])
+    for x, y in zip(*grads):
+        assert np.array_equal(x, y)
+
+
 def test_superbatch_schedule_with_bulk_refresh():
     """n = 3 batches per super-batch, bound 2n - 1 = 5: every step against the oracle walking the same schedule;
     from the second super-batch on every hot vertex of V^1 is served from the cache."""
