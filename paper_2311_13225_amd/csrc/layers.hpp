@@ -127,7 +127,8 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof = nullptr, int agg_stage = -1,
                      int gemm_stage = -1, const void* agg_table = nullptr, int32_t arch = NO_ARCH_SAGE_MEAN, const Layer1Reuse* reuse = nullptr, bool aggregate_done = false,
                      const SourceWeights* weights = nullptr, const PaddedSlots* padded = nullptr,
-                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false);
+                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false, hipEvent_t product_done = nullptr);
+// product_done: recorded behind the product (taken from its launch)
 // cut_fwd: where the layer's matrices are cut for the forward product, beside the aggregation unless cut_done; without it a product that
 // takes planes has them cut into the workspace
 // input_products_done: both products of the input gradient are made already (head.hip)

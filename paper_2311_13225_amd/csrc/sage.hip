@@ -600,7 +600,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof, int agg_stage, int gemm_stage,
                      const void* agg_table, int32_t arch, const Layer1Reuse* reuse,
                      bool aggregate_done, const SourceWeights* weights, const PaddedSlots* padded,
-                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd, bool cut_done) {
+                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd, bool cut_done, hipEvent_t product_done) {
     // aggregate_done: `mean` (and the reused rows of H^1) were already written by an earlier launch of the same
     // aggregation (a batch prepared ahead); only the product runs
     // reuse: the output rows are scattered into H^1, recomputed hot rows also refresh the cache, and the reused
@@ -610,6 +610,16 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         if (!reuse) return;
         a.c_rows = reuse->compute_pos;
         a.c_keep = reuse->emb; a.c_keep_rows = reuse->refresh_slot; a.c_keep_stamp = reuse->version; a.stamp = reuse->step;      // version == NULL: stamped by the split already
+    };
+    auto product = [&](auto launch) -> int32_t {
+        hipEvent_t p0 = nullptr, p1 = nullptr;
+        if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &p0, &p1);
+        if (p0 || !product_done) {
+            NO_CHECK(launch(p0, p1));
+            if (product_done) NO_HIP_CHECK(hipEventRecord(product_done, st));
+            return NO_OK;
+        }
+        return launch(nullptr, product_done);
     };
     // The weights of a product on planes are cut beside the aggregation, which does not read them.
     const bool gcn = arch_is_gcn(arch);
@@ -649,9 +659,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.bias = bias; a.relu = relu;
         scatter(a);
         a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
-        e0 = e1 = nullptr;
-        if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
-        return gemm_nn_forward(a, st, e0, e1);
+        return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_nn_forward(a, st, p0, p1); });
     }
     // agg_table != NULL: the rows to average are rows of that table addressed by blk.d_indices (global ids),
     // while x_src holds only the destination rows (fused gather + aggregate of the bottom layer). An fp32
@@ -676,9 +684,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap;
         a.bias = bias; a.relu = relu;
         if (reuse) { a.c_rows = reuse->compute_pos; a.c_keep = reuse->emb; a.c_keep_rows = reuse->refresh_slot; }
-        e0 = e1 = nullptr;
-        if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
-        return gemm_bf16_nn(a, st, e0, e1);
+        return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_bf16_nn(a, st, p0, p1); });
     }
     const float* x_dst = direct_self ? (const float*)agg_table : (const float*)x_src;
     if (dt == NO_BF16) {
@@ -699,9 +705,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     scatter(a);
     a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
     a.cut_B[1] = cut_fwd ? cut_fwd[1] : nullptr;
-    e0 = e1 = nullptr;
-    if (prof && gemm_stage >= 0) prof->kernel_pair(gemm_stage, &e0, &e1);
-    return gemm_nn_forward(a, st, e0, e1);
+    return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_nn_forward(a, st, p0, p1); });
 }
 
 int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* mean,

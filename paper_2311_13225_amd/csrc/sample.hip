@@ -739,12 +739,17 @@ void side_take(no_blocks_s* b, uint32_t own_blocks, SideTasks* side) {
     }
 }
 
-int32_t blocks_finish(no_blocks_s* b, hipStream_t st) {
+int32_t blocks_finish(no_blocks_s* b, hipStream_t st, hipEvent_t done) {
+    const hipEvent_t none = nullptr;
+    bool recorded = false;
     while (side_pending(b)) {
         SideTasks side;
         side_take(b, 0, &side);
-        hipLaunchKernelGGL(side_tasks_kernel, dim3(side.side_blocks()), dim3(SIDE_THREADS), 0, st, side);
+        const hipEvent_t last = side_pending(b) ? nullptr : done;
+        NO_LAUNCH_TIMED(side_tasks_kernel, dim3(side.side_blocks()), dim3(SIDE_THREADS), st, none, last, side);
+        recorded = last != nullptr;
     }
+    if (done && !recorded) NO_HIP_CHECK(hipEventRecord(done, st));
     return launch_status("side tasks");
 }
 
