@@ -711,12 +711,7 @@ __global__ void __launch_bounds__(256) reduce_grads_kernel(ReduceLaunch launch, 
     while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
     const ReduceArgs& a = launch.job[job];
     const int32_t Kp = a.Kp, N = a.N;
-    int32_t splits = a.splits;
-    if (a.d_R) {
-        int32_t R = *a.d_R;
-        if (R > a.R_cap) R = a.R_cap;
-        splits = tn_used_splits(R, a.splits, a.rows_per_split, a.few_splits);
-    }
+    const int32_t splits = *tn_used_word(a.P, a.splits, Kp, N);
     const int64_t per = (int64_t)(Kp + 1) * N;
     const int64_t i = (int64_t)(blockIdx.x - first) * blockDim.x + threadIdx.x;
     const int q = (int)blockIdx.y;

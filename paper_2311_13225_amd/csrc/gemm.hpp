@@ -41,7 +41,7 @@ struct GemmTNArgs {
     const int32_t* d_R; int32_t R_cap; int32_t splits;   // splits: the most row slices (the partials' layout is sized for it)
     int32_t n_problems = 2;                              // 1: only A[0]
     const uint16_t* A16 = nullptr;                       // products with bf16 operands: the first one's rows in place of A[0]
-    int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer ...
+    int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer (large tiles: tn_plan) ...
     int32_t few_splits = 0;                              // ... though these many, if they keep TN_FEWEST_ROWS rows each
 };
 
@@ -58,6 +58,11 @@ __host__ __device__ inline int32_t tn_used_splits(int32_t R, int32_t splits, int
     if (s < fill) s = fill;
     if (s < 1) s = 1;
     return s < splits ? s : splits;
+}
+
+// Where the product leaves the number of slices it used for the reduction: in the place of the column sums that product 1 does not have.
+__host__ __device__ inline int32_t* tn_used_word(float* P, int32_t splits, int32_t Kp, int32_t N) {
+    return reinterpret_cast<int32_t*>(P + ((int64_t)splits * (Kp + 1) + Kp) * N);
 }
 
 // Products with bf16 operands (a layer fed by a bf16 feature table): see gemm_bf16.hip.
@@ -145,11 +150,10 @@ struct StatsJob {
 // The reduction that follows a split product: sums the partials in split order into the three gradients; with
 // lr != 0 also applies W <- W - lr * g.
 struct ReduceArgs {
-    const float* P; int32_t splits, Kp, N;
+    float* P; int32_t splits, Kp, N;
     float* g_self; float* g_neigh; float* g_bias;
     float lr; float* w_self; float* w_neigh; float* w_bias;
     int32_t n_problems;                                  // 2, or 1: only g_self and g_bias
-    const int32_t* d_R = nullptr; int32_t R_cap = 0; int32_t rows_per_split = 0, few_splits = 0;   // as in the product: the slices it used
     // bf16 copies of the two matrices ([N][Kpad], weights_to_bf16_t's layout), rewritten with the updated values (or NULL)
     uint16_t* wt_self = nullptr; uint16_t* wt_neigh = nullptr; int32_t Kpad = 0;
 };

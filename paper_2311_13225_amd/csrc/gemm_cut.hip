@@ -362,11 +362,6 @@ struct ColumnUnit {
     }
 };
 
-// Row tiles of a product: with the row of column sums, which a bf16 job keeps in a tile of its own.
-static __host__ __device__ inline uint32_t tn_row_tiles(const GemmTNArgs& g, int T) {
-    return g.A16 ? (uint32_t)((g.Kp + T - 1) / T) + 1u : (uint32_t)((g.Kp + 1 + T - 1) / T);
-}
-
 // The jobs of one launch (by value in the kernel arguments): job j owns the linear block ids [end_block[j-1], end_block[j]).
 struct CutTNLaunch { GemmTNArgs job[NO_MAX_LAYERS]; uint32_t end_block[NO_MAX_LAYERS]; int32_t n; };
 
@@ -375,67 +370,28 @@ constexpr int tn_shared_bytes(int T) { return 6 * T * SPITCH * 2 > T * (T + 4) *
 
 // Block `id` of a job: a T x T tile of one product over one slice; 2 x 2 wavefronts. Half of the threads bring a tile of A, the
 // other half one of G, each W = T / 32 columns x eight rows. Column W q + c of a tile stands in LDS row 32 c + q (a
-// wavefront then writes neighbouring rows); the output tile is put back in order on its way through LDS.
+// wavefront then writes neighbouring rows); the output tile is put back in order on its way through LDS. The bias gradient, the column sums of G,
+// is added up by the blocks of product 0's first row tile from the rows that they bring.
+// The tiles of a slice read the same rows, so they get consecutive logical ids, dealt to the dies in chunks (a job starts at a multiple of the
+// dies), and a slice is fetched into one L2 (10 K rows, 2 x 602 x 256: the loads alone 30 -> 18 us, the launch 57.3 -> 55.6).
 // BF16: the operands are taken in bf16 instead (the first as it is stored, the others rounded to nearest-even), so there is one
-// plane and one partial product; the bias gradient stays the fp32 column sum, always by a row tile of its own.
+// plane and one partial product; the bias gradient stays the fp32 column sum.
 template <int T, bool BF16>
 __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, int R, int used, unsigned char* smem) {
     constexpr int W = T / 32, Q = 32, PLANE = T * SPITCH, OPITCH = T + 4, I = T / 64, PLANES = BF16 ? 1 : 3;
     uint16_t* As = reinterpret_cast<uint16_t*>(smem);
     uint16_t* Gs = As + PLANES * PLANE;
-    const uint32_t gx = (uint32_t)((g.N + T - 1) / T), gy = (uint32_t)tn_row_tiles(g, T);
-    int bx, by, prob, split;
-    if (BF16) {
-        // These products are bound by their operands' bytes: the tiles of a slice read the same rows, so they get consecutive
-        // logical ids, dealt to the dies in chunks (the job stands first in its launch), and a slice is fetched into one L2.
-        const uint32_t per = gx * gy * (uint32_t)g.n_problems, total = per * (uint32_t)used, padded = (total + N_XCD - 1) / N_XCD * N_XCD;
-        if (id >= padded) return;
-        const uint32_t lid = id % N_XCD * (padded / N_XCD) + id / N_XCD, rem = lid % per;
-        if (lid >= total) return;
-        split = (int)(lid / per);
-        bx = (int)(rem % gx); by = (int)((rem / gx) % gy); prob = (int)(rem / (gx * gy));
-    } else {
-        // in the order of a plain 3-D grid (column tile fastest, then row tile, then problem x slice)
-        const int bz = (int)(id / (gx * gy));
-        bx = (int)(id % gx); by = (int)((id / gx) % gy);
-        prob = bz / used; split = bz % used;
-        if (prob >= g.n_problems) return;
-    }
+    const uint32_t gx = (uint32_t)((g.N + T - 1) / T), gy = (uint32_t)((g.Kp + T - 1) / T);
+    const uint32_t per = gx * gy * (uint32_t)g.n_problems, total = per * (uint32_t)used, padded = (total + N_XCD - 1) / N_XCD * N_XCD;
+    if (id >= padded) return;
+    const uint32_t lid = id % N_XCD * (padded / N_XCD) + id / N_XCD, rem = lid % per;
+    if (lid >= total) return;
+    const int split = (int)(lid / per), bx = (int)(rem % gx), by = (int)((rem / gx) % gy), prob = (int)(rem / (gx * gy));
     int chunk = (R + used - 1) / used;
     chunk = (chunk + SK - 1) / SK * SK;
     const int r0 = split * chunk, r1 = min(R, r0 + chunk);
     const int m0 = by * T, n0 = bx * T, tid = (int)threadIdx.x;
     float* P = g.P + ((int64_t)prob * g.splits + split) * (int64_t)(g.Kp + 1) * g.N;
-    if (m0 >= g.Kp) {
-        // Kp is a multiple of the tile height: this row tile holds nothing but row Kp, the column sums of G that product
-        // 0 carries (the bias gradient). The sums are taken directly, in a fixed order (row r0 + i by thread group i mod PARTS,
-        // groups combined in order). Product 1 has no such row (the reduction never reads it).
-        if (prob != 0) return;
-        float* red = reinterpret_cast<float*>(smem);         // [PARTS][T]
-        const int c = tid % T, part = tid / T;
-        constexpr int PARTS = 256 / T;
-        float s = 0.f;
-        if (n0 + c < g.N) {
-            int r = r0 + part;
-            for (; r + 7 * PARTS < r1; r += 8 * PARTS) {
-                float v[8];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) v[q] = g.G[(int64_t)(r + q * PARTS) * g.ldg + n0 + c];
-#pragma unroll
-                for (int q = 0; q < 8; ++q) s += v[q];
-            }
-            for (; r < r1; r += PARTS) s += g.G[(int64_t)r * g.ldg + n0 + c];
-        }
-        red[part * T + c] = s;
-        __syncthreads();
-        if (part == 0 && n0 + c < g.N) {
-            float t = red[c];
-#pragma unroll
-            for (int q = 1; q < PARTS; ++q) t += red[q * T + c];
-            P[(int64_t)g.Kp * g.N + n0 + c] = t;
-        }
-        return;
-    }
     const int wave = tid >> 6, wm = wave >> 1, wn = wave & 1, lane = tid & 63, half = lane >> 5, l32 = lane & 31;
     floatx16 acc[BF16 ? 1 : 2][I][I];
 #pragma unroll
@@ -451,8 +407,10 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     const int64_t ld = mine_a ? g.lda[prob] : g.ldg;
     const int q = tid % Q, k8 = (tid % 128) / Q * 8;
     const int col = (mine_a ? m0 : n0) + q * W, lim = mine_a ? g.Kp : g.N;
-    const int ones = !BF16 && mine_a && prob == 0 ? g.Kp - col : -1;        // which of them is the column of ones, if 0 .. W - 1
-    const bool with_ones = !BF16 && prob == 0 && g.Kp < m0 + T;
+    const bool sums = prob == 0 && by == 0;
+    float sum[W];
+#pragma unroll
+    for (int c = 0; c < W; ++c) sum[c] = 0.f;
     // Columns past the operand are never stored, but must be read inside it: a unit that sticks out is read where it ends with
     // the row and shifted.
     const bool edge = m0 + T > g.Kp || n0 + T > g.N;
@@ -477,15 +435,17 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
                 for (int c = 0; c < W; ++c) u.f[j][c] = k8 + j >= lo && k8 + j < hi ? u.f[j][c] : 0.f;
         }
+        if (sums && !mine_a) {
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int c = 0; c < W; ++c) sum[c] += u.f[j][c];
+        }
 #pragma unroll
         for (int c = 0; c < W; ++c) {
             float f[8];
 #pragma unroll
             for (int j = 0; j < 8; ++j) f[j] = u.f[j][c];
-            if (with_ones && ones == c) {
-#pragma unroll
-                for (int j = 0; j < 8; ++j) f[j] = k8 + j >= lo && k8 + j < hi ? 1.f : 0.f;
-            }
             if (BF16) {
                 *reinterpret_cast<uint4*>(S + c * Q * SPITCH) =
                     make_uint4(bf16_pair(f[0], f[1]), bf16_pair(f[2], f[3]), bf16_pair(f[4], f[5]), bf16_pair(f[6], f[7]));
@@ -559,10 +519,19 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
             multiply();
         }
     }
-    // the output tile through LDS, its rows and columns back in order
     float* Cs = reinterpret_cast<float*>(smem);
     float bad = 0.f;
     __syncthreads();
+    if (sums) {      // four groups of rows, in order
+        if (!mine_a) {
+#pragma unroll
+            for (int c = 0; c < W; ++c) Cs[k8 / 8 * T + q * W + c] = sum[c];
+        }
+        __syncthreads();
+        if (tid < T && n0 + tid < g.N) P[(int64_t)g.Kp * g.N + n0 + tid] = ((Cs[tid] + Cs[T + tid]) + Cs[2 * T + tid]) + Cs[3 * T + tid];
+        __syncthreads();
+    }
+    // the output tile through LDS, its rows and columns back in order
 #pragma unroll
     for (int i = 0; i < I; ++i)
 #pragma unroll
@@ -576,12 +545,12 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
             }
     __syncthreads();
     constexpr int C4 = T / 4;
-    const int rows_out = BF16 ? g.Kp : g.Kp + 1, c4 = tid % C4 * 4, n = n0 + c4;
+    const int c4 = tid % C4 * 4, n = n0 + c4;
     const bool vec = (g.N % 4 == 0) && ((reinterpret_cast<uintptr_t>(P) & 15) == 0) && n + 4 <= g.N;
 #pragma unroll 4
     for (int lr = tid / C4; lr < T; lr += 256 / C4) {
         const int row = m0 + lr;
-        if (row >= rows_out || n >= g.N) continue;
+        if (row >= g.Kp || n >= g.N) continue;
         const float4 t = *reinterpret_cast<const float4*>(&Cs[lr * OPITCH + c4]);
         float* dst = P + (int64_t)row * g.N + n;
         if (vec) *reinterpret_cast<float4*>(dst) = t;
@@ -597,11 +566,9 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     // operands at a time, lanes 0-31 the first of them, a column a lane: the one whose LDS row the lane's fragment was).
     auto column = [](int x) { return x % Q * W + x / Q; };
     const float *pa[I], *pg[I];
-    bool one[I];
 #pragma unroll
     for (int i = 0; i < I; ++i) {
         const int m = m0 + column(wm * (T / 2) + i * 32 + l32);
-        one[i] = prob == 0 && m == g.Kp;
         pa[i] = g.A[prob] + min(m, g.Kp - 1);
         pg[i] = g.G + min(n0 + column(wn * (T / 2) + i * 32 + l32), g.N - 1);
 #pragma unroll
@@ -619,7 +586,7 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int i = 0; i < I; ++i) {
                 const float va = pa[i][(int64_t)min(at, r1 - 1) * g.lda[prob]], vb = pg[i][(int64_t)min(at, r1 - 1) * g.ldg];
-                a[u][i] = in ? (one[i] ? 1.f : va) : 0.f;
+                a[u][i] = in ? va : 0.f;
                 b[u][i] = in ? vb : 0.f;
             }
         }
@@ -637,17 +604,12 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int x = column(wm * (T / 2) + i * 32 + acc_row(r, lane)), y = column(wn * (T / 2) + j * 32 + l32);
-                if (m0 + x >= rows_out || n0 + y >= g.N || finite(Cs[x * OPITCH + y])) continue;
+                if (m0 + x >= g.Kp || n0 + y >= g.N || finite(Cs[x * OPITCH + y])) continue;
                 P[(int64_t)(m0 + x) * g.N + n0 + y] = acc[0][i][j][r];
             }
 }
 
 static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) {
-    return (uint32_t)((g.N + T - 1) / T) * tn_row_tiles(g, T) * (uint32_t)g.n_problems;
-}
-
-// Those of them that hold products (a tile for the column sums alone is little work, and every product of Kp = T columns has one).
-static __host__ __device__ inline uint32_t tn_product_tiles(const GemmTNArgs& g, int T) {
     return (uint32_t)((g.N + T - 1) / T) * (uint32_t)((g.Kp + T - 1) / T) * (uint32_t)g.n_problems;
 }
 
@@ -659,17 +621,50 @@ static __host__ __device__ inline bool tn_narrow(const GemmTNArgs& g) { return g
 // rows, 128 x 256: 50 / 42; 112 blocks, 3.4 K rows, 256 x 256: 52 / 45; 128 blocks, 8 K rows: 128 x 256 57 / 55, 256 x 128 61 / 63; 160 blocks:
 // 5 K rows, 256 x 256 60 / 61, 10 K rows, 128 x 256 69 / 63; 256 blocks, 16 K rows: 85 / 86; 8 K rows, 256 x 256: 78 / 82), unless it is narrow (60 K
 // rows: 256 x 2 192 / 164; 256 x 16 152 / 143; 3 x 256 121 / 84); its share of the grid is sized for either.
+
+// The slices of a job in large tiles on fp32 operands. A block alone on a compute unit takes 2.2 us a step of 32 rows, two together 2.6, so that the
+// jobs of a launch are cut, all into slices of as many rows, to fill TN_SLOTS places once: with 256 rows a slice some units had two blocks
+// and others one (sums over 90 K rows, 2 x 256 x 256, 320 blocks: 182 us; 504: 151; 13 K rows, 320: 38.6, 472: 32.0; 10 K rows, 2 x 602 x 256,
+// 400: 54.8; 500: 48.9; 25 K rows, 2 x 100 x 256, 256: 35.9; 448: 31.9). Blocks in small tiles and on bf16 operands are short: four of them count as one.
+// (A function of the row counts and shapes alone, so the order of the sums is the same in every run.)
+constexpr int TN_SLOTS = 512, TN_LEAST_ROWS = 128;
+__device__ __forceinline__ int tn_rows(const GemmTNArgs& g) { return min(*g.d_R, g.R_cap); }
+__device__ __forceinline__ int tn_plan(const CutTNLaunch& launch, int job, int R, bool* large) {
+    const GemmTNArgs& g = launch.job[job];
+    const int plain = tn_used_splits(R, g.splits, g.rows_per_split, g.few_splits);
+    *large = !tn_narrow(g) && tn_tiles(g, 128) * plain >= TN_LARGE_BLOCKS;
+    if (!*large || g.A16) return plain;
+    int others = 0, tiles = 0;
+    float work = 0.f;
+    for (int j = 0; j < launch.n; ++j) {
+        const GemmTNArgs& o = launch.job[j];
+        const int rows = tn_rows(o), s = tn_used_splits(rows, o.splits, o.rows_per_split, o.few_splits), t = (int)tn_tiles(o, 128);
+        const bool lg = !tn_narrow(o) && t * s >= (int)TN_LARGE_BLOCKS;
+        if (lg && !o.A16) {
+            tiles += t;
+            work += (float)t * (float)rows;
+        } else {
+            others += (lg ? t : (int)tn_tiles(o, 64)) * s;
+        }
+    }
+    const int room = max(TN_SLOTS - others / 4, TN_SLOTS / 2);
+    if (2 * tiles > room) return plain;
+    // (a job's last slices, one a tile, may be short ones: room for them)
+    const int rows = max(((int)(work / (float)(room - tiles)) + SK) / SK * SK, TN_LEAST_ROWS);
+    return max(min((R + rows - 1) / rows, g.splits), 1);
+}
+
 __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
     int job = 0;
     uint32_t first = 0;
     while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
     const GemmTNArgs& g = launch.job[job];
-    int R = *g.d_R;
-    if (R > g.R_cap) R = g.R_cap;
-    const int used = tn_used_splits(R, g.splits, g.rows_per_split, g.few_splits);      // (the reduction reads the first `used` partials only)
+    const int R = tn_rows(g);
+    bool large;
+    const int used = tn_plan(launch, job, R, &large);
     const uint32_t id = blockIdx.x - first;
-    const bool large = !tn_narrow(g) && tn_product_tiles(g, 128) * used >= TN_LARGE_BLOCKS;
+    if (id == 0 && threadIdx.x == 0) *tn_used_word(g.P, g.splits, g.Kp, g.N) = used;      // (the reduction reads the first `used` partials only)
     if (g.A16) {
         if (large) cut_tn_tile<128, true>(g, id, R, used, smem);
         else cut_tn_tile<64, true>(g, id, R, used, smem);
@@ -687,9 +682,8 @@ int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st,
         if (a.Kp <= 0 || a.N <= 0) continue;
         // (small tiles are only taken while there are few large ones, or by a narrow job)
         const uint64_t small = (uint64_t)tn_tiles(a, 64), large = (uint64_t)tn_tiles(a, 128);
-        const uint64_t most_small = tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / tn_product_tiles(a, 128));
-        blocks += std::max(small * most_small, large * (uint64_t)a.splits);
-        if (a.A16) blocks = (uint64_t)ceil_div((int64_t)blocks, N_XCD) * N_XCD;
+        const uint64_t most_small = tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / tn_tiles(a, 128));
+        blocks += (uint64_t)ceil_div((int64_t)std::max(small * most_small, large * (uint64_t)a.splits), N_XCD) * N_XCD;
         NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");
         launch.job[launch.n] = a;
         launch.end_block[launch.n] = (uint32_t)blocks;

@@ -107,7 +107,7 @@ struct Layer1Reuse {
 struct BelowLayer { const float* h = nullptr; const int32_t* out_rows = nullptr; float* gz_out = nullptr; };
 
 int32_t layer_splits(int32_t n_dst_cap, int32_t d_in, int32_t d_out);
-LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out);
+LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out, bool in_step = false);
 
 // cut: matrices that extra blocks of the launch cut
 // side_of: the launch takes along the side tasks that this sampling call left (side_take)

@@ -9,6 +9,7 @@
 #include "riders.hpp"
 
 #include <stdlib.h>
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -577,9 +578,14 @@ int32_t layer_splits(int32_t n_dst_cap, int32_t d_in, int32_t d_out) {
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out) {
+// in_step: a step's workspace is its model's own, with room for as many slices as fill the chip with large tiles (tn_plan).
+LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out, bool in_step) {
     LayerWorkspace w;
     w.splits = layer_splits(n_dst_cap, d_in, d_out);
+    if (in_step) {
+        const int64_t fill = 512 / (2 * ceil_div(d_in, 128) * ceil_div(d_out, 128)), by_rows = ceil_div(n_dst_cap, 128);
+        w.splits = (int32_t)std::max<int64_t>(w.splits, std::min<int64_t>(std::min(fill, by_rows), 128));
+    }
     size_t off = 0;
     char* base = (char*)ws;
     w.gz = (float*)(base + off);        off += align256((size_t)n_dst_cap * d_out * 4);
@@ -801,7 +807,6 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     t.rows_per_split = 256;
     t.few_splits = (int32_t)(256 / (ceil_div(d_in, 64) * ceil_div(d_out, 64) * t.n_problems));
     ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
-    r.d_R = t.d_R; r.R_cap = t.R_cap; r.rows_per_split = t.rows_per_split; r.few_splits = t.few_splits;
     if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
     if (pending && defer) {
         // an upper layer inside a step: its product and reduction ride on the bottom layer's launches

@@ -284,7 +284,7 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
         NO_CHECK(m->h[l - 1].alloc((size_t)H.n_dst_cap * m->dims[l]));
         NO_CHECK(m->gh[l - 1].alloc((size_t)H.n_dst_cap * m->dims[l]));
         m->ws_off[l - 1] = ws_bytes;
-        ws_bytes += carve_workspace(nullptr, H.n_dst_cap, m->dims[l - 1], m->dims[l]).bytes;
+        ws_bytes += carve_workspace(nullptr, H.n_dst_cap, m->dims[l - 1], m->dims[l], true).bytes;
     }
     m->ws_bytes = ws_bytes;
     NO_CHECK(m->ws.alloc(ws_bytes));
@@ -596,7 +596,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             reuse.hits.src = cache->emb.p; reuse.hits.src_rows = B->hit_slot.p; reuse.hits.dst_rows = B->hit_pos.p;
             reuse.hits.d_n = extra + 1; reuse.hits.n_cap = blk.n_dst_cap; reuse.hits.dst = m->h[0].p; reuse.hits.dim = d_out;
         }
-        LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out);
+        LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out, true);
         w.fwd_planes_bytes = 0;      // (planes_of says which weights are cut)
         // symmetric normalisation: the column sums of the block's adjacency are the per-source edge counts of the hop
         // (written with the local indices); the fused layer-1 aggregate reads global ids,
@@ -660,7 +660,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         a.agg_mode = aggregate_mode(m->arch);
         a.mean = m->mean[L - 1].p; a.logits = m->h[L - 1].p; a.grad = m->gh[L - 1].p; a.row_loss = m->row_loss.p;
         a.grad_self = m->gh[L - 2].p;
-        a.grad_mean = carve_workspace(m->ws.p + m->ws_off[L - 1], view[0].n_dst_cap, a.d, C).gmean;
+        a.grad_mean = carve_workspace(m->ws.p + m->ws_off[L - 1], view[0].n_dst_cap, a.d, C, true).gmean;
         a.bad_label_flag = B->counts.p + 4 * L + 7; a.flag_value = B->call_id;
         NO_CHECK(head_forward_backward(a, cut, B, st));
     } else {
@@ -707,10 +707,10 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
             const no_block_view& blk_below = view[L - l + 1];
             below.h = m->h[l - 2].p;
             below.out_rows = (l == 2 && used_cache) ? B->compute_inv.p : nullptr;
-            below.gz_out = carve_workspace(m->ws.p + m->ws_off[l - 2], blk_below.n_dst_cap, m->dims[l - 2], m->dims[l - 1]).gz;
+            below.gz_out = carve_workspace(m->ws.p + m->ws_off[l - 2], blk_below.n_dst_cap, m->dims[l - 2], m->dims[l - 1], true).gz;
         }
-        if (l < L) gz_in = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out).gz;
-        LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out);
+        if (l < L) gz_in = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out, true).gz;
+        LayerWorkspace w = carve_workspace(m->ws.p + m->ws_off[l - 1], blk.n_dst_cap, d_in, d_out, true);
         SourceWeights sw;
         if (m->arch == NO_ARCH_GCN_SYM) sw.cnt = B->hop[L - l].csc_cnt.p;
         Bf16Products bfp;
