@@ -617,7 +617,7 @@ __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
     }
 }
 
-int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);      // gemm_cut.hip
+int32_t cut_nn(const GemmNNArgs& a, const GemmTNArgs* job, bool* job_done, hipStream_t st);      // gemm_cut.hip
 int32_t cut_fwd(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1);     // gemm_fwd.hip
 
 static int32_t launch_small_nn(const GemmNNArgs& a, bool b_transposed, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
@@ -642,7 +642,7 @@ int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hip
     return launch_tiled_nn<false>(a, st, ev0, ev1);
 }
 
-int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
+int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st, const GemmTNArgs* job, bool* job_done) {
     GemmNNArgs a = args;
     if (a.M_cap <= 0 || a.N <= 0) return NO_OK;
     if (nn_tiles(a) <= 128) return launch_small_nn(a, true, st, nullptr, nullptr);
@@ -658,14 +658,11 @@ int32_t gemm_nn_input_grad(const GemmNNArgs& args, hipStream_t st) {
         a.cut_B[0] = planes;
         a.cut_B[1] = one ? planes : planes + each;
     }
-    return cut_nn(a, st, nullptr, nullptr);
+    return cut_nn(a, job, job_done, st);
 }
 
 // ------------------------------------------------------------------------------------------ gradient reduction
 
-// Sums the split partial products in split order: g_self = rows [0,Kp) of product 0, g_bias = row Kp of
-// product 0, g_neigh = rows [0,Kp) of product 1. With lr != 0 the parameters take their SGD step in the
-// same pass (W <- W - lr * g), after every kernel that read them.
 __device__ void write_step_stats(const StatsJob& j) {
     __shared__ float sm[256];
     float s = 0.f;
@@ -709,37 +706,7 @@ __global__ void __launch_bounds__(256) reduce_grads_kernel(ReduceLaunch launch, 
     int job = 0;
     uint32_t first = 0;
     while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
-    const ReduceArgs& a = launch.job[job];
-    const int32_t Kp = a.Kp, N = a.N;
-    const int32_t splits = *tn_used_word(a.P, a.splits, Kp, N);
-    const int64_t per = (int64_t)(Kp + 1) * N;
-    const int64_t i = (int64_t)(blockIdx.x - first) * blockDim.x + threadIdx.x;
-    const int q = (int)blockIdx.y;
-    if (i >= per || q >= a.n_problems) return;
-    const bool bias_row = i >= (int64_t)Kp * N;
-    if (q == 1 && bias_row) return;
-    const float* p = a.P + (int64_t)q * a.splits * per + i;
-    // eight partials are requested before the first add; the adds stay in split order
-    float s = 0.f;
-    int32_t k = 0;
-    for (; k + 8 <= splits; k += 8) {
-        float v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(k + j) * per];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s += v[j];
-    }
-    for (; k < splits; ++k) s += p[(int64_t)k * per];
-    float* gout = bias_row ? a.g_bias + (i - (int64_t)Kp * N) : (q == 0 ? a.g_self + i : a.g_neigh + i);
-    *gout = s;
-    float* w = a.w_self ? (bias_row ? a.w_bias + (i - (int64_t)Kp * N) : (q == 0 ? a.w_self + i : a.w_neigh + i)) : nullptr;
-    if (a.lr != 0.f && w) *w -= a.lr * s;
-    if (a.wt_self && w && !bias_row) {
-        // the parameter's bf16 copy for the next step's products (transposed: [N][Kpad]), round-to-nearest-even
-        const uint32_t u = __float_as_uint(*w);
-        const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
-        (q == 0 ? a.wt_self : a.wt_neigh)[(int64_t)n * a.Kpad + k] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-    }
+    reduce_block(launch.job[job], blockIdx.x - first, (int)blockIdx.y);
 }
 
 int32_t reduce_grads(const ReduceArgs* jobs, int32_t n_jobs, hipStream_t st, const StatsJob* stats_job) {
@@ -748,7 +715,7 @@ int32_t reduce_grads(const ReduceArgs* jobs, int32_t n_jobs, hipStream_t st, con
     for (int32_t j = 0; j < n_jobs && launch.n < NO_MAX_LAYERS; ++j) {
         const ReduceArgs& a = jobs[j];
         if (a.Kp <= 0 || a.N <= 0) continue;
-        blocks += (uint64_t)ceil_div((int64_t)(a.Kp + 1) * a.N, 256);
+        blocks += (uint64_t)reduce_blocks(a);
         NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "reduce_grads: too many blocks");
         launch.job[launch.n] = a;
         launch.end_block[launch.n] = (uint32_t)blocks;

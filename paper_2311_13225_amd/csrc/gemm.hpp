@@ -169,7 +169,8 @@ struct GradJobs {
 // ev0 / ev1 (optional): events that take the product kernel's own start and end times
 // forward: one result, the sum of the products; input gradient: independent results, B transposed
 int32_t gemm_nn_forward(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-int32_t gemm_nn_input_grad(const GemmNNArgs& a, hipStream_t st);
+// job: weight gradients that the launch may take along (*job_done: they went with it)
+int32_t gemm_nn_input_grad(const GemmNNArgs& a, hipStream_t st, const GemmTNArgs* job, bool* job_done);
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0 = nullptr,
                          hipEvent_t ev1 = nullptr);
 int32_t reduce_grads(const ReduceArgs* jobs, int32_t n_jobs, hipStream_t st, const StatsJob* stats_job = nullptr);

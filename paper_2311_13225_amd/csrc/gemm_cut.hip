@@ -74,13 +74,16 @@ int32_t cut_all(const CutJobs& cut, hipStream_t st, hipEvent_t ev0, hipEvent_t e
 // straight from their planes (a lane's eight indices are 16 contiguous bytes, the 32 lanes of a fragment 512: L2 reads, one
 // step ahead). What is left at 60 K rows is memory next to the products: without the loads of B the launch takes 81 of 101 us,
 // without either operand's 70.
-template <int MI, int NJ, int WN, int OCC>
-__global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
-    constexpr int WM = 4 / WN, BM = 32 * MI * WM, BN = 32 * NJ * WN, PLANE = BM * SPITCH, COPY = 3 * PLANE;
-    constexpr int UNITS = BM >= 64 ? BM / 64 : 1, CW = 32 * NJ, CPITCH = CW + 4;
-    constexpr int BYTES = 2 * COPY * 2 > 4 * 32 * CPITCH * 4 ? 2 * COPY * 2 : 4 * 32 * CPITCH * 4;
-    __shared__ __attribute__((aligned(16))) unsigned char smem[BYTES];
-    __shared__ float scale_sh[BM];
+template <int MI, int NJ, int WN>
+struct NNTile {
+    static constexpr int BM = 32 * MI * (4 / WN), BN = 32 * NJ * WN, COPY = 3 * BM * SPITCH, CPITCH = 32 * NJ + 4;
+    static constexpr int BYTES = 2 * COPY * 2 > 4 * 32 * CPITCH * 4 ? 2 * COPY * 2 : 4 * 32 * CPITCH * 4;
+};
+template <int MI, int NJ, int WN>
+__device__ __forceinline__ void cut_nn_tile(const GemmNNArgs& g, unsigned char* smem /* [BYTES] */, float* scale_sh /* [BM] */) {
+    using Tile = NNTile<MI, NJ, WN>;
+    constexpr int BM = Tile::BM, BN = Tile::BN, PLANE = BM * SPITCH, COPY = Tile::COPY;
+    constexpr int UNITS = BM >= 64 ? BM / 64 : 1, CW = 32 * NJ, CPITCH = Tile::CPITCH;
     uint16_t* As = reinterpret_cast<uint16_t*>(smem);
     int M = *g.d_M;
     if (M > g.M_cap) M = g.M_cap;
@@ -292,22 +295,11 @@ __global__ void __launch_bounds__(256, OCC) cut_nn_kernel(GemmNNArgs g) {
             }
 }
 
-template <int MI, int NJ, int WN, int OCC>
-static void launch_cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    constexpr int BM = 32 * MI * (4 / WN), BN = 32 * NJ * WN;
-    dim3 grid(xcd_padded(ceil_div(a.N, BN) * ceil_div(a.M_cap, BM) * a.n_problems));
-    NO_LAUNCH_TIMED((cut_nn_kernel<MI, NJ, WN, OCC>), grid, dim3(256), st, ev0, ev1, a);
-}
-
-int32_t cut_nn(const GemmNNArgs& a, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
-    // Few rows: 32-row blocks (twice as many; measured at 3.4 K / 5.5 K rows x 256 columns: 12.9 / 15.8 us against 15.2 / 18.9 with 64-row
-    // blocks, at 25 K rows 37 against 31), by the capacity, which the host knows when it launches: a batch that fills a small part of a larger
-    // one pays for it (backward pass of a layer in a capacity of 19 K / 21 K rows, us: 3.4 K rows, 100 x 256 39.1 / 41.5, 256 x 256 50.6 / 50.3;
-    // 5.5 K rows 48.0 / 49.2, 67.6 / 68.8; 12 K rows 68.3 / 70.3, 99.6 / 98.6). Narrow outputs: all four wavefronts below each other.
-    if (a.N <= 64) launch_cut_nn<1, 2, 1, 2>(a, st, ev0, ev1);
-    else if (a.M_cap <= 20000) launch_cut_nn<1, 1, 4, 2>(a, st, ev0, ev1);
-    else launch_cut_nn<2, 1, 4, 2>(a, st, ev0, ev1);
-    return launch_status("cut_nn");
+template <int MI, int NJ, int WN>
+__global__ void __launch_bounds__(256, 2) cut_nn_kernel(GemmNNArgs g) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NNTile<MI, NJ, WN>::BYTES];
+    __shared__ float scale_sh[NNTile<MI, NJ, WN>::BM];
+    cut_nn_tile<MI, NJ, WN>(g, smem, scale_sh);
 }
 
 // ------------------------------------------------------------------------------------------ TN
@@ -654,16 +646,15 @@ __device__ __forceinline__ int tn_plan(const CutTNLaunch& launch, int job, int R
     return max(min((R + rows - 1) / rows, g.splits), 1);
 }
 
-__global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
+__device__ __forceinline__ void cut_tn_block(const CutTNLaunch& launch, uint32_t block, unsigned char* smem /* [tn_shared_bytes(128)] */) {
     int job = 0;
     uint32_t first = 0;
-    while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
+    while (job + 1 < launch.n && block >= launch.end_block[job]) first = launch.end_block[job++];
     const GemmTNArgs& g = launch.job[job];
     const int R = tn_rows(g);
     bool large;
     const int used = tn_plan(launch, job, R, &large);
-    const uint32_t id = blockIdx.x - first;
+    const uint32_t id = block - first;
     if (id == 0 && threadIdx.x == 0) *tn_used_word(g.P, g.splits, g.Kp, g.N) = used;      // (the reduction reads the first `used` partials only)
     if (g.A16) {
         if (large) cut_tn_tile<128, true>(g, id, R, used, smem);
@@ -672,6 +663,34 @@ __global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
         if (large) cut_tn_tile<128, false>(g, id, R, used, smem);
         else cut_tn_tile<64, false>(g, id, R, used, smem);
     }
+}
+
+__global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
+    cut_tn_block(launch, blockIdx.x, smem);
+}
+
+// Input gradient and weight gradients of a layer call in one launch (nn_blocks: a multiple of the dies): neither waits for the other, and a layer
+// of some thousand rows fills the chip with neither. Only where the weight gradients are in small tiles at every number of rows: beside blocks of
+// large ones, which leave room for two on a compute unit, the input gradient takes longer than before them (3.4 K rows, 256 x 256: 30 us -> 26
+// in small tiles, 24 with room for large ones; steps of 25 K rows 311 -> 321 us).
+template <int MI, int NJ, int WN>
+__global__ void __launch_bounds__(256, 3) cut_grads_kernel(GemmNNArgs g, uint32_t nn_blocks, GemmTNArgs t) {
+    constexpr int NN = NNTile<MI, NJ, WN>::BYTES, TN = tn_shared_bytes(64);
+    __shared__ __attribute__((aligned(16))) unsigned char smem[NN > TN ? NN : TN];
+    __shared__ float scale_sh[NNTile<MI, NJ, WN>::BM];
+    if (blockIdx.x < nn_blocks) {
+        cut_nn_tile<MI, NJ, WN>(g, smem, scale_sh);
+        return;
+    }
+    const int R = tn_rows(t), used = tn_used_splits(R, t.splits, t.rows_per_split, t.few_splits);
+    const uint32_t id = blockIdx.x - nn_blocks;
+    if (id == 0 && threadIdx.x == 0) *tn_used_word(t.P, t.splits, t.Kp, t.N) = used;
+    cut_tn_tile<64, false>(t, id, R, used, smem);
+}
+// Whether a job is in small tiles at every number of rows up to its room (the slices grow with the rows).
+static bool tn_always_small(const GemmTNArgs& t) {
+    return !t.A16 && !tn_narrow(t) && tn_tiles(t, 128) * (uint32_t)tn_used_splits(t.R_cap, t.splits, t.rows_per_split, t.few_splits) < TN_LARGE_BLOCKS;
 }
 
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
@@ -692,6 +711,31 @@ int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st,
     if (launch.n == 0) return NO_OK;
     NO_LAUNCH_TIMED(cut_tn_kernel, dim3((unsigned)blocks), dim3(256), st, ev0, ev1, launch);
     return launch_status("gemm_tn");
+}
+
+template <int MI, int NJ, int WN>
+static int32_t launch_cut_nn(const GemmNNArgs& a, const GemmTNArgs* job, bool* job_done, hipStream_t st) {
+    const unsigned blocks = xcd_padded(ceil_div(a.N, NNTile<MI, NJ, WN>::BN) * ceil_div(a.M_cap, NNTile<MI, NJ, WN>::BM) * a.n_problems);
+    if constexpr (WN > 1) {
+        if (job && tn_always_small(*job)) {
+            const unsigned tn_blocks = xcd_padded((int64_t)tn_tiles(*job, 64) * tn_used_splits(job->R_cap, job->splits, job->rows_per_split, job->few_splits));
+            hipLaunchKernelGGL((cut_grads_kernel<MI, NJ, WN>), dim3(blocks + tn_blocks), dim3(256), 0, st, a, blocks, *job);
+            *job_done = true;
+            return launch_status("cut_grads");
+        }
+    }
+    hipLaunchKernelGGL((cut_nn_kernel<MI, NJ, WN>), dim3(blocks), dim3(256), 0, st, a);
+    return launch_status("cut_nn");
+}
+
+int32_t cut_nn(const GemmNNArgs& a, const GemmTNArgs* job, bool* job_done, hipStream_t st) {
+    // Few rows: 32-row blocks (twice as many; measured at 3.4 K / 5.5 K rows x 256 columns: 12.9 / 15.8 us against 15.2 / 18.9 with 64-row
+    // blocks, at 25 K rows 37 against 31), by the capacity, which the host knows when it launches: a batch that fills a small part of a larger
+    // one pays for it (backward pass of a layer in a capacity of 19 K / 21 K rows, us: 3.4 K rows, 100 x 256 39.1 / 41.5, 256 x 256 50.6 / 50.3;
+    // 5.5 K rows 48.0 / 49.2, 67.6 / 68.8; 12 K rows 68.3 / 70.3, 99.6 / 98.6). Narrow outputs: all four wavefronts below each other.
+    if (a.N <= 64) return launch_cut_nn<1, 2, 1>(a, job, job_done, st);
+    if (a.M_cap <= 20000) return launch_cut_nn<1, 1, 4>(a, job, job_done, st);
+    return launch_cut_nn<2, 1, 4>(a, job, job_done, st);
 }
 
 }  // namespace no

@@ -118,6 +118,42 @@ struct RowUnit {
     }
 };
 
+// A block of 256 threads of the reduction of a layer's split products, q = 0 or 1: sums the split partial products in split order: g_self = rows
+// [0,Kp) of product 0, g_bias = row Kp of product 0, g_neigh = rows [0,Kp) of product 1. With lr != 0 the parameters take their SGD step in the
+// same pass (W <- W - lr * g), after every kernel that read them.
+inline int64_t reduce_blocks(const ReduceArgs& a) { return ceil_div((int64_t)(a.Kp + 1) * a.N, 256); }
+__device__ __forceinline__ void reduce_block(const ReduceArgs& a, uint32_t block, int q) {
+    const int32_t Kp = a.Kp, N = a.N;
+    const int32_t splits = *tn_used_word(a.P, a.splits, Kp, N);
+    const int64_t per = (int64_t)(Kp + 1) * N;
+    const int64_t i = (int64_t)block * 256 + threadIdx.x;
+    if (i >= per || q >= a.n_problems) return;
+    const bool bias_row = i >= (int64_t)Kp * N;
+    if (q == 1 && bias_row) return;
+    const float* p = a.P + (int64_t)q * a.splits * per + i;
+    // eight partials are requested before the first add; the adds stay in split order
+    float s = 0.f;
+    int32_t k = 0;
+    for (; k + 8 <= splits; k += 8) {
+        float v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(k + j) * per];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) s += v[j];
+    }
+    for (; k < splits; ++k) s += p[(int64_t)k * per];
+    float* gout = bias_row ? a.g_bias + (i - (int64_t)Kp * N) : (q == 0 ? a.g_self + i : a.g_neigh + i);
+    *gout = s;
+    float* w = a.w_self ? (bias_row ? a.w_bias + (i - (int64_t)Kp * N) : (q == 0 ? a.w_self + i : a.w_neigh + i)) : nullptr;
+    if (a.lr != 0.f && w) *w -= a.lr * s;
+    if (a.wt_self && w && !bias_row) {
+        // the parameter's bf16 copy for the next step's products (transposed: [N][Kpad]), round-to-nearest-even
+        const uint32_t u = __float_as_uint(*w);
+        const int32_t k = (int32_t)(i / N), n = (int32_t)(i - (int64_t)k * N);
+        (q == 0 ? a.wt_self : a.wt_neigh)[(int64_t)n * a.Kpad + k] = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
+    }
+}
+
 // Workgroups are handed to the 8 accelerator dies (XCDs, each with its own L2) round-robin by linear
 // id. The tiles that share an operand panel (all column tiles of one row tile; all tiles of one
 // reduction slice) get consecutive *logical* ids, and logical ids are dealt out in chunks per XCD, so

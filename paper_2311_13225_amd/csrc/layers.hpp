@@ -118,10 +118,11 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
                        int32_t agg_mode = AGG_NEIGH_MEAN, const int32_t* self_idx = nullptr, const RowCopyJob* copy = nullptr,
                        hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr,
                        const PaddedSlots* padded = nullptr, no_blocks_s* side_of = nullptr, const CutJobs* cut = nullptr);
+// reduce (without masked_out): a layer's weight gradients, whose products are made, reduced by extra blocks of the launch
 int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_t* csc_indptr, const int32_t* csc_dst,
                             const int32_t* d_n_src, int32_t n_src_cap, const int32_t* d_n_dst, float* grad_x,
                             hipStream_t st, const float* mask_h = nullptr, const int32_t* out_rows = nullptr,
-                            float* masked_out = nullptr, const SourceWeights* weights = nullptr);
+                            float* masked_out = nullptr, const SourceWeights* weights = nullptr, const ReduceArgs* reduce = nullptr);
 int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* w_self,
                      const float* w_neigh, const float* bias, int32_t d_out, int32_t relu, float* mean, float* h,
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof = nullptr, int agg_stage = -1,

@@ -291,7 +291,7 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
                            const int32_t* self_idx = nullptr, int32_t agg_mode = AGG_NEIGH_MEAN, const float* mask_h = nullptr,
                            const int32_t* out_rows = nullptr, float* masked_out = nullptr, const RowCopyJob* copy = nullptr,
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr, no_blocks_s* side_of = nullptr,
-                           const CutJobs* cut = nullptr) {
+                           const CutJobs* cut = nullptr, const ReduceArgs* reduce = nullptr) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -327,6 +327,12 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
             if (sw.cnt) launch(std::true_type{}, side, grid);
             else launch(std::false_type{}, side, grid);
         });
+        return;
+    } else if (reduce) {
+        ReduceSide side{own, (uint32_t)reduce_blocks(*reduce), *reduce};
+        const uint32_t grid = own + side.blocks * (uint32_t)reduce->n_problems;
+        if (sw.cnt) launch_as(std::true_type{}, std::false_type{}, side, grid);
+        else launch_as(std::false_type{}, std::false_type{}, side, grid);
         return;
     }
     NoSideTasks none;
@@ -496,13 +502,13 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
 int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_t* csc_indptr, const int32_t* csc_dst,
                             const int32_t* d_n_src, int32_t n_src_cap, const int32_t* d_n_dst, float* grad_x,
                             hipStream_t st, const float* mask_h, const int32_t* out_rows, float* masked_out,
-                            const SourceWeights* weights) {
+                            const SourceWeights* weights, const ReduceArgs* reduce) {
     if (n_src_cap <= 0) return NO_OK;
     const uintptr_t al = (uintptr_t)gmean_scaled | (uintptr_t)grad_x | (uintptr_t)mask_h | (uintptr_t)masked_out;
     const bool a16 = (al & 15) == 0, a8 = (al & 7) == 0;
 #define NO_SEG_BWD(V) \
     launch_segment<float, V, false>(gmean_scaled, dim, csc_indptr, csc_dst, d_n_src, n_src_cap, d_n_dst, grad_x, dim, dim, st, \
-                                    nullptr, AGG_NEIGH_MEAN, mask_h, out_rows, masked_out, nullptr, nullptr, nullptr, weights)
+                                    nullptr, AGG_NEIGH_MEAN, mask_h, out_rows, masked_out, nullptr, nullptr, nullptr, weights, nullptr, nullptr, reduce)
     if (dim % 4 == 0 && a16) NO_SEG_BWD(4);
     else if (dim % 2 == 0 && a8) NO_SEG_BWD(2);
     else NO_SEG_BWD(1);
@@ -750,6 +756,30 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         gz = w.gz;
     }
     if (prof && prep_stage >= 0) prof->end();
+    // weight gradients x_dst^T gz, mean^T gz and the bias gradient (column sums of gz), split over rows and summed in split order
+    const float* x_dst = dt == NO_BF16 && !gcn && !bf ? w.x_dst_f32 : (const float*)x_src;
+    GemmTNArgs t{};
+    t.A[0] = x_dst; t.lda[0] = d_in;
+    t.A[1] = mean;  t.lda[1] = d_in;
+    if (gcn) { t.A[0] = mean; t.n_problems = 1; }
+    t.G = gz; t.ldg = d_out;
+    t.P = w.partials; t.Kp = d_in; t.N = d_out;
+    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits;
+    // Batches that fill a fraction of the capacity use fewer slices than the capacity-sized bound: a slice keeps at least
+    // this many rows. Measured on a batch of 24 K rows (bound: 64 slices): the product takes the same time from 64 down
+    // to 93 slices' worth of rows (256 per slice) and 10 % longer at 384 and above (too few blocks), while the reduction
+    // after it reads fewer partial tiles.
+    // Few rows of a layer with few tiles are cut finer, until there are 256 blocks of small tiles or 64 rows a slice (backward pass, us: 1 K rows,
+    // 100 x 47: 25.5 -> 20.1, 128 x 256: 26.1 -> 24.0; 2 K rows, 64 x 64: 24.0 -> 20.4; 5 K rows: 28.9 -> 26.3).
+    t.rows_per_split = 256;
+    t.few_splits = (int32_t)(256 / (ceil_div(d_in, 64) * ceil_div(d_out, 64) * t.n_problems));
+    ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
+    if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
+    // In a layer call the weight gradients may go with the launch of the input gradient, unless the weights' planes stand where the partials
+    // go or the fp32 rows are still to be made.
+    const bool together = !pending && !(dt == NO_BF16 && !gcn) &&
+                          (gcn ? 1 : 2) * cut_weights_elements(d_in, d_out) * 2 <= (size_t)((char*)w.partials - (char*)w.x_dst_f32);
+    bool tn_done = false;
     if (grad_x_src) {
         // uses the pre-update weights, so it runs before the reduce that may apply the SGD step:
         // gz W_self^T -> rows [0, n_dst) of grad_x; (gz W_neigh^T) / len(row) -> gmean; then the transpose adds
@@ -778,36 +808,13 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         a.cut_scratch = w.planes();
         a.cut_scratch_bytes = w.planes_bytes;
         a.d_M = blk.d_n_dst; a.M_cap = n_cap; a.N = d_in;
-        if (!input_products_done) NO_CHECK(gemm_nn_input_grad(a, st));
+        if (!input_products_done) NO_CHECK(gemm_nn_input_grad(a, st, together ? &t : nullptr, &tn_done));
         NO_CHECK(transpose_aggregate(w.gmean, d_in, blk.d_csc_indptr, blk.d_csc_dst, blk.d_n_src, blk.n_src_cap,
                                      blk.d_n_dst, grad_x_src, st, below ? below->h : nullptr, below ? below->out_rows : nullptr,
-                                     below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr));
+                                     below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr, tn_done ? &r : nullptr));
         if (prof && dx_stage >= 0) prof->end();
     }
-    const float* x_dst = (const float*)x_src;
-    if (dt == NO_BF16 && !gcn && !bf) {
-        NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, n_cap, d_in, w.x_dst_f32, st));
-        x_dst = w.x_dst_f32;
-    }
-    // weight gradients x_dst^T gz, mean^T gz and the bias gradient (column sums of gz, carried by a virtual
-    // column of ones in the first product), split over rows and summed in split order
-    GemmTNArgs t{};
-    t.A[0] = x_dst; t.lda[0] = d_in;
-    t.A[1] = mean;  t.lda[1] = d_in;
-    if (gcn) { t.A[0] = mean; t.n_problems = 1; }
-    t.G = gz; t.ldg = d_out;
-    t.P = w.partials; t.Kp = d_in; t.N = d_out;
-    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits;
-    // Batches that fill a fraction of the capacity use fewer slices than the capacity-sized bound: a slice keeps at least
-    // this many rows. Measured on a batch of 24 K rows (bound: 64 slices): the product takes the same time from 64 down
-    // to 93 slices' worth of rows (256 per slice) and 10 % longer at 384 and above (too few blocks), while the reduction
-    // after it reads fewer partial tiles.
-    // Few rows of a layer with few tiles are cut finer, until there are 256 blocks of small tiles or 64 rows a slice (backward pass, us: 1 K rows,
-    // 100 x 47: 25.5 -> 20.1, 128 x 256: 26.1 -> 24.0; 2 K rows, 64 x 64: 24.0 -> 20.4; 5 K rows: 28.9 -> 26.3).
-    t.rows_per_split = 256;
-    t.few_splits = (int32_t)(256 / (ceil_div(d_in, 64) * ceil_div(d_out, 64) * t.n_problems));
-    ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
-    if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
+    if (dt == NO_BF16 && !gcn && !bf) NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, n_cap, d_in, w.x_dst_f32, st));
     if (pending && defer) {
         // an upper layer inside a step: its product and reduction ride on the bottom layer's launches
         if (pending->n >= NO_MAX_LAYERS) { set_error("sage_backward: too many deferred layers"); return NO_ERR_CAPACITY; }
@@ -824,9 +831,12 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     tj[n_tn++] = t;
     for (int32_t i = 0; pending && i < pending->n && n_jobs < NO_MAX_LAYERS; ++i) { tj[n_tn++] = pending->tn[i]; rj[n_jobs++] = pending->red[i]; }
     if (pending) pending->n = 0;
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
-    NO_CHECK(gemm_tn_partials(tj, n_tn, st, e0, e1));
+    if (tn_done) return launch_status("sage_backward");      // (the reduction went with the transposed sum)
+    {
+        hipEvent_t e0 = nullptr, e1 = nullptr;
+        if (prof && dw_stage >= 0) prof->kernel_pair(dw_stage, &e0, &e1);
+        NO_CHECK(gemm_tn_partials(tj, n_tn, st, e0, e1));
+    }
     if (prof && reduce_stage >= 0) prof->begin(reduce_stage);
     NO_CHECK(reduce_grads(rj, n_jobs, st, stats_job));
     if (prof && reduce_stage >= 0) prof->end();
