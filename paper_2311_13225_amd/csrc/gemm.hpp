@@ -39,6 +39,8 @@ struct GemmTNArgs {
     float* P;                                            // partials [2][splits][Kp+1][N]; row Kp of product 0 = column sums of G
     int32_t Kp, N;
     const int32_t* d_R; int32_t R_cap; int32_t splits;   // splits: the most row slices (the partials' layout is sized for it)
+    int32_t plain_splits = 0;                            // the most slices of rows_per_split rows (splits: of any)
+    int32_t small_up_to = 0;                             // > 0: R is about this, and small tiles may be taken for short launches
     int32_t n_problems = 2;                              // 1: only A[0]
     const uint16_t* A16 = nullptr;                       // products with bf16 operands: the first one's rows in place of A[0]
     int32_t rows_per_split = 0;                          // > 0: only ceil(R / rows_per_split) slices are used when that is fewer (large tiles: tn_plan) ...

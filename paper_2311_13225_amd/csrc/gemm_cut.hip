@@ -400,9 +400,9 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     const int q = tid % Q, k8 = (tid % 128) / Q * 8;
     const int col = (mine_a ? m0 : n0) + q * W, lim = mine_a ? g.Kp : g.N;
     const bool sums = prob == 0 && by == 0;
-    float sum[W];
+    double sum[W];      // (in 64 bits: no less exact than the product with a column of ones that this replaces)
 #pragma unroll
-    for (int c = 0; c < W; ++c) sum[c] = 0.f;
+    for (int c = 0; c < W; ++c) sum[c] = 0.0;
     // Columns past the operand are never stored, but must be read inside it: a unit that sticks out is read where it ends with
     // the row and shifted.
     const bool edge = m0 + T > g.Kp || n0 + T > g.N;
@@ -429,9 +429,9 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
         }
         if (sums && !mine_a) {
 #pragma unroll
-            for (int j = 0; j < 8; ++j)
+            for (int c = 0; c < W; ++c)
 #pragma unroll
-                for (int c = 0; c < W; ++c) sum[c] += u.f[j][c];
+                for (int j = 0; j < 8; ++j) sum[c] += (double)u.f[j][c];
         }
 #pragma unroll
         for (int c = 0; c < W; ++c) {
@@ -517,10 +517,11 @@ __device__ __forceinline__ void cut_tn_tile(const GemmTNArgs& g, uint32_t id, in
     if (sums) {      // four groups of rows, in order
         if (!mine_a) {
 #pragma unroll
-            for (int c = 0; c < W; ++c) Cs[k8 / 8 * T + q * W + c] = sum[c];
+            for (int c = 0; c < W; ++c) reinterpret_cast<double*>(smem)[k8 / 8 * T + q * W + c] = sum[c];
         }
         __syncthreads();
-        if (tid < T && n0 + tid < g.N) P[(int64_t)g.Kp * g.N + n0 + tid] = ((Cs[tid] + Cs[T + tid]) + Cs[2 * T + tid]) + Cs[3 * T + tid];
+        const double* part = reinterpret_cast<const double*>(smem) + tid;
+        if (tid < T && n0 + tid < g.N) P[(int64_t)g.Kp * g.N + n0 + tid] = (float)(((part[0] + part[T]) + part[2 * T]) + part[3 * T]);
         __syncthreads();
     }
     // the output tile through LDS, its rows and columns back in order
@@ -621,16 +622,17 @@ static __host__ __device__ inline bool tn_narrow(const GemmTNArgs& g) { return g
 // (A function of the row counts and shapes alone, so the order of the sums is the same in every run.)
 constexpr int TN_SLOTS = 512, TN_LEAST_ROWS = 128;
 __device__ __forceinline__ int tn_rows(const GemmTNArgs& g) { return min(*g.d_R, g.R_cap); }
+__device__ __forceinline__ int tn_plain_slices(const GemmTNArgs& g, int R) { return tn_used_splits(R, g.plain_splits, g.rows_per_split, g.few_splits); }
 __device__ __forceinline__ int tn_plan(const CutTNLaunch& launch, int job, int R, bool* large) {
     const GemmTNArgs& g = launch.job[job];
-    const int plain = tn_used_splits(R, g.splits, g.rows_per_split, g.few_splits);
+    const int plain = tn_plain_slices(g, R);
     *large = !tn_narrow(g) && tn_tiles(g, 128) * plain >= TN_LARGE_BLOCKS;
     if (!*large || g.A16) return plain;
     int others = 0, tiles = 0;
     float work = 0.f;
     for (int j = 0; j < launch.n; ++j) {
         const GemmTNArgs& o = launch.job[j];
-        const int rows = tn_rows(o), s = tn_used_splits(rows, o.splits, o.rows_per_split, o.few_splits), t = (int)tn_tiles(o, 128);
+        const int rows = tn_rows(o), s = tn_plain_slices(o, rows), t = (int)tn_tiles(o, 128);
         const bool lg = !tn_narrow(o) && t * s >= (int)TN_LARGE_BLOCKS;
         if (lg && !o.A16) {
             tiles += t;
@@ -643,18 +645,39 @@ __device__ __forceinline__ int tn_plan(const CutTNLaunch& launch, int job, int R
     if (2 * tiles > room) return plain;
     // (a job's last slices, one a tile, may be short ones: room for them)
     const int rows = max(((int)(work / (float)(room - tiles)) + SK) / SK * SK, TN_LEAST_ROWS);
-    return max(min((R + rows - 1) / rows, g.splits), 1);
+    return max(min((R + rows - 1) / rows, g.splits), plain);
 }
 
-__device__ __forceinline__ void cut_tn_block(const CutTNLaunch& launch, uint32_t block, unsigned char* smem /* [tn_shared_bytes(128)] */) {
+// All jobs in small tiles, four blocks on a compute unit (31 KB of LDS, 118 registers) in place of two: they hide each other's waits, and fewer slices
+// leave less to reduce. Faster as long as the whole launch is short (us, large and small tiles in one kernel / this: 1 K rows, 2 x 256 x 47
+// 7.8 / 5.6; 3.4 K rows, 2 x 256 x 256 14.1 / 12.2; 5 K rows 20.3 / 15.2; 13 K rows 32.2 / 30.6; 25 K rows, 2 x 100 x 256 31.9 / 30.6; 10 K rows, 2 x 602 x 256
+// 46.7 / 53.4; 40 K rows, 2 x 256 x 256 68.1 / 78.3). Not in steps, where more of the chip is left to the next batch's sampling by fewer blocks
+// (dense GCN-style 151 / 157, sparse 313 / 314).
+__global__ void __launch_bounds__(256, 4) cut_tn_small_kernel(CutTNLaunch launch) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(64)];
     int job = 0;
     uint32_t first = 0;
-    while (job + 1 < launch.n && block >= launch.end_block[job]) first = launch.end_block[job++];
+    while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
+    const GemmTNArgs& g = launch.job[job];
+    const int R = tn_rows(g), used = tn_plain_slices(g, R);
+    const uint32_t id = blockIdx.x - first;
+    if (id == 0 && threadIdx.x == 0) *tn_used_word(g.P, g.splits, g.Kp, g.N) = used;      // (the reduction reads the first `used` partials only)
+    cut_tn_tile<64, false>(g, id, R, used, smem);
+}
+// What a layer call's launch has to do, about, in steps of 32 rows of a large tile, and up to where small tiles win.
+constexpr int64_t TN_SMALL_WORK = 3500, TN_SMALL_WORK_WITH_INPUT_GRADIENT = 5000;
+static int64_t tn_work(const GemmTNArgs& t) { return (int64_t)tn_tiles(t, 128) * t.small_up_to / SK; }
+
+__global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
+    int job = 0;
+    uint32_t first = 0;
+    while (job + 1 < launch.n && blockIdx.x >= launch.end_block[job]) first = launch.end_block[job++];
     const GemmTNArgs& g = launch.job[job];
     const int R = tn_rows(g);
     bool large;
     const int used = tn_plan(launch, job, R, &large);
-    const uint32_t id = block - first;
+    const uint32_t id = blockIdx.x - first;
     if (id == 0 && threadIdx.x == 0) *tn_used_word(g.P, g.splits, g.Kp, g.N) = used;      // (the reduction reads the first `used` partials only)
     if (g.A16) {
         if (large) cut_tn_tile<128, true>(g, id, R, used, smem);
@@ -665,15 +688,11 @@ __device__ __forceinline__ void cut_tn_block(const CutTNLaunch& launch, uint32_t
     }
 }
 
-__global__ void __launch_bounds__(256, 2) cut_tn_kernel(CutTNLaunch launch) {
-    __shared__ __attribute__((aligned(16))) unsigned char smem[tn_shared_bytes(128)];
-    cut_tn_block(launch, blockIdx.x, smem);
-}
-
 // Input gradient and weight gradients of a layer call in one launch (nn_blocks: a multiple of the dies): neither waits for the other, and a layer
-// of some thousand rows fills the chip with neither. Only where the weight gradients are in small tiles at every number of rows: beside blocks of
-// large ones, which leave room for two on a compute unit, the input gradient takes longer than before them (3.4 K rows, 256 x 256: 30 us -> 26
-// in small tiles, 24 with room for large ones; steps of 25 K rows 311 -> 321 us).
+// of some thousand rows fills the chip with neither. In small tiles: beside blocks of large ones, which leave room for two on a compute unit, the
+// input gradient takes longer than before them (3.4 K rows, 256 x 256: 30 us -> 26 in small tiles, 24 with room for large ones; steps of 25 K rows 311 ->
+// 321 us). Forward and backward pass of a layer, us, in two launches / in one: 3.4 K rows, 256 x 256 70.7 / 65.2; 5.2 K 96.2 / 80.3; 10 K 129 / 119; 20 K 211 /
+// 205; 4 K rows, 602 x 64 104 / 88; 12 K 223 / 204; 8 K rows, 602 x 256 213 / 211; 30 K rows, 100 x 256 180 / 170.
 template <int MI, int NJ, int WN>
 __global__ void __launch_bounds__(256, 3) cut_grads_kernel(GemmNNArgs g, uint32_t nn_blocks, GemmTNArgs t) {
     constexpr int NN = NNTile<MI, NJ, WN>::BYTES, TN = tn_shared_bytes(64);
@@ -683,33 +702,37 @@ __global__ void __launch_bounds__(256, 3) cut_grads_kernel(GemmNNArgs g, uint32_
         cut_nn_tile<MI, NJ, WN>(g, smem, scale_sh);
         return;
     }
-    const int R = tn_rows(t), used = tn_used_splits(R, t.splits, t.rows_per_split, t.few_splits);
+    const int R = tn_rows(t), used = tn_plain_slices(t, R);
     const uint32_t id = blockIdx.x - nn_blocks;
     if (id == 0 && threadIdx.x == 0) *tn_used_word(t.P, t.splits, t.Kp, t.N) = used;
     cut_tn_tile<64, false>(t, id, R, used, smem);
 }
-// Whether a job is in small tiles at every number of rows up to its room (the slices grow with the rows).
-static bool tn_always_small(const GemmTNArgs& t) {
-    return !t.A16 && !tn_narrow(t) && tn_tiles(t, 128) * (uint32_t)tn_used_splits(t.R_cap, t.splits, t.rows_per_split, t.few_splits) < TN_LARGE_BLOCKS;
-}
-
 int32_t gemm_tn_partials(const GemmTNArgs* jobs, int32_t n_jobs, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     CutTNLaunch launch{};
     uint64_t blocks = 0;
+    int64_t work = 0;
+    bool all_small = true;
+    for (int32_t j = 0; j < n_jobs; ++j)
+        if (jobs[j].Kp > 0 && jobs[j].N > 0) {
+            work += tn_work(jobs[j]);
+            all_small = all_small && !jobs[j].A16 && jobs[j].small_up_to > 0;
+        }
+    all_small = all_small && work <= TN_SMALL_WORK;
     for (int32_t j = 0; j < n_jobs && launch.n < NO_MAX_LAYERS; ++j) {
         const GemmTNArgs& a = jobs[j];
         if (a.Kp <= 0 || a.N <= 0) continue;
         // (small tiles are only taken while there are few large ones, or by a narrow job)
         const uint64_t small = (uint64_t)tn_tiles(a, 64), large = (uint64_t)tn_tiles(a, 128);
-        const uint64_t most_small = tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / tn_tiles(a, 128));
-        blocks += (uint64_t)ceil_div((int64_t)std::max(small * most_small, large * (uint64_t)a.splits), N_XCD) * N_XCD;
+        const uint64_t most_small = all_small || tn_narrow(a) ? (uint64_t)a.splits : std::min<uint64_t>((uint64_t)a.splits, (TN_LARGE_BLOCKS - 1) / tn_tiles(a, 128));
+        blocks += (uint64_t)ceil_div((int64_t)std::max(small * most_small, all_small ? 0 : large * (uint64_t)a.splits), N_XCD) * N_XCD;
         NO_REQUIRE(blocks < (1ull << 31), NO_ERR_CAPACITY, "gemm_tn: too many blocks");
         launch.job[launch.n] = a;
         launch.end_block[launch.n] = (uint32_t)blocks;
         ++launch.n;
     }
     if (launch.n == 0) return NO_OK;
-    NO_LAUNCH_TIMED(cut_tn_kernel, dim3((unsigned)blocks), dim3(256), st, ev0, ev1, launch);
+    if (all_small) NO_LAUNCH_TIMED(cut_tn_small_kernel, dim3((unsigned)blocks), dim3(256), st, ev0, ev1, launch);
+    else NO_LAUNCH_TIMED(cut_tn_kernel, dim3((unsigned)blocks), dim3(256), st, ev0, ev1, launch);
     return launch_status("gemm_tn");
 }
 
@@ -717,7 +740,7 @@ template <int MI, int NJ, int WN>
 static int32_t launch_cut_nn(const GemmNNArgs& a, const GemmTNArgs* job, bool* job_done, hipStream_t st) {
     const unsigned blocks = xcd_padded(ceil_div(a.N, NNTile<MI, NJ, WN>::BN) * ceil_div(a.M_cap, NNTile<MI, NJ, WN>::BM) * a.n_problems);
     if constexpr (WN > 1) {
-        if (job && tn_always_small(*job)) {
+        if (job && tn_work(*job) <= TN_SMALL_WORK_WITH_INPUT_GRADIENT) {
             const unsigned tn_blocks = xcd_padded((int64_t)tn_tiles(*job, 64) * tn_used_splits(job->R_cap, job->splits, job->rows_per_split, job->few_splits));
             hipLaunchKernelGGL((cut_grads_kernel<MI, NJ, WN>), dim3(blocks + tn_blocks), dim3(256), 0, st, a, blocks, *job);
             *job_done = true;

@@ -764,7 +764,8 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     if (gcn) { t.A[0] = mean; t.n_problems = 1; }
     t.G = gz; t.ldg = d_out;
     t.P = w.partials; t.Kp = d_in; t.N = d_out;
-    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits;
+    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits; t.plain_splits = layer_splits(n_cap, d_in, d_out);
+    t.small_up_to = pending ? 0 : n_cap;      // (a step's batch fills 15 to 45 % of the capacity; a caller's block is its own size)
     // Batches that fill a fraction of the capacity use fewer slices than the capacity-sized bound: a slice keeps at least
     // this many rows. Measured on a batch of 24 K rows (bound: 64 slices): the product takes the same time from 64 down
     // to 93 slices' worth of rows (256 per slice) and 10 % longer at 384 and above (too few blocks), while the reduction
