@@ -121,6 +121,10 @@ __global__ void __launch_bounds__(256) gemm_nn_small_kernel(GemmNNArgs g) {
         float v = ((red[0][r][ln] + red[1][r][ln]) + red[2][r][ln]) + red[3][r][ln] + bias_v[i];
         if (g.relu) v = v > 0.f ? v : 0.f;
         C[(int64_t)crow[i] * ldc + col] = v * scale[i];
+        if (g.positive) {      // (four lanes of the same row; N is a multiple of 4, so they are all here)
+            const uint32_t four = (uint32_t)(__ballot(v > 0.f) >> (ln & ~3)) & 15u;
+            if ((ln & 3) == 0) g.positive[(int64_t)crow[i] * (g.N / 4) + col / 4] = (uint8_t)four;
+        }
         if (krow[i] >= 0) {
             g.c_keep[(int64_t)krow[i] * ldc + col] = v * scale[i];
             if (col == 0 && g.c_keep_stamp) g.c_keep_stamp[krow[i]] = g.stamp;
@@ -600,6 +604,7 @@ __global__ void __launch_bounds__(256, OCC) gemm_nn_kernel(GemmNNArgs g) {
             if (g.relu) v[i] = v[i] > 0.f ? v[i] : 0.f;
             v[i] *= scale[j];
         }
+        if (g.positive) g.positive[(int64_t)crow[j] * (g.N / 4) + col / 4] = positive_of(v[0], v[1], v[2], v[3]);
         float* dst = C + (int64_t)crow[j] * ldc + col;
         float* keep = krow[j] >= 0 ? g.c_keep + (int64_t)krow[j] * ldc + col : nullptr;
         if (vec) {

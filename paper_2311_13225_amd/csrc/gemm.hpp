@@ -31,6 +31,8 @@ struct GemmNNArgs {
     // c_keep_stamp[that row] = stamp: the cache refresh of a recomputed hot vertex.
     const int32_t* c_rows;
     float* c_keep; const int32_t* c_keep_rows; int32_t* c_keep_stamp; int32_t stamp;
+    // which outputs of C[0] are positive, a byte for every four columns of a row (N a multiple of 4), at the output's row; NULL: not asked for
+    uint8_t* positive;
 };
 
 struct GemmTNArgs {
@@ -76,7 +78,7 @@ struct GemmBf16NNArgs {
     float* C; int64_t ldc;
     const int32_t* d_M; int32_t M_cap;
     const float* bias; int32_t relu;
-    const int32_t* c_rows; float* c_keep; const int32_t* c_keep_rows;   // as in GemmNNArgs
+    const int32_t* c_rows; float* c_keep; const int32_t* c_keep_rows; uint8_t* positive;   // as in GemmNNArgs
 };
 // Weights cut for the large gradient products (gemm_cut.hip): planes of the transpose of one matrix [K][N], the reduction index (over
 // the N columns) padded to 32.

@@ -7,7 +7,7 @@
 //   NN: C[M,N] = X[x_rows[m], 0:K] * Ws + round(Mn[m, 0:K]) * Wn + bias (ReLU, scattered rows, cache refresh rows)
 //   TN: P[q][s][0:K, 0:N] = A_q[rows of slice s]^T * round(G[rows of slice s]), A_0 = X (bf16), A_1 = round(Mn);
 //       row K of P[0][s] = column sums of G over the slice in fp32 (the bias gradient takes no rounding)
-#include "gemm.hpp"
+#include "gemm_tile.hpp"
 
 namespace no {
 
@@ -208,6 +208,7 @@ __global__ void __launch_bounds__(256) gemm_bf16_nn_kernel(GemmBf16NNArgs g) {
                 float* dst = g.C + (int64_t)crow_sh[row] * g.ldc + col;
                 const int kr = krow_sh[row];
                 float* keep = kr >= 0 ? g.c_keep + (int64_t)kr * g.ldc + col : nullptr;
+                if (g.positive) g.positive[(int64_t)crow_sh[row] * (g.N / 4) + col / 4] = positive_of(t.x, t.y, t.z, t.w);
                 if (vec) {
                     *reinterpret_cast<float4*>(dst) = t;
                     if (keep) *reinterpret_cast<float4*>(keep) = t;

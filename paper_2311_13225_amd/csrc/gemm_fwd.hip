@@ -224,6 +224,7 @@ __device__ __forceinline__ void cut_fwd_tile(const GemmNNArgs& g, int M, int bx,
             for (int e = 0; e < 4; ++e) v[e] = v[e] > 0.f ? v[e] : 0.f;
         }
         const int kr = krow_sh[lr];
+        if (g.positive) g.positive[(int64_t)crow_sh[lr] * (N / 4) + n / 4] = positive_of(v[0], v[1], v[2], v[3]);
         float* dst = C + (int64_t)crow_sh[lr] * ldc + n;
         float* keep = kr >= 0 ? g.c_keep + (int64_t)kr * ldc + n : nullptr;
         if (vec) {

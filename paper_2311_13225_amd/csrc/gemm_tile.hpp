@@ -90,6 +90,11 @@ __device__ __forceinline__ void run_cut_jobs(const CutJobs& cut, uint32_t block)
     if (i < (int64_t)cut_weights_elements(cut.K[j], cut.N[j], forward) / 24) cut_weights_unit(cut.w[j], cut.K[j], cut.N[j], forward, cut.out[j], i);
 }
 
+// Which of four neighbouring outputs are positive (GemmNNArgs::positive).
+__device__ __forceinline__ uint8_t positive_of(float a, float b, float c, float d) {
+    return (uint8_t)((a > 0.f ? 1 : 0) | (b > 0.f ? 2 : 0) | (c > 0.f ? 4 : 0) | (d > 0.f ? 8 : 0));
+}
+
 // Accumulator element r of lane: row = 8*(r/4) + 4*(lane/32) + r%4, column = lane%32 of the 32x32 tile.
 __device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r >> 2) + 4 * (lane >> 5) + (r & 3); }
 

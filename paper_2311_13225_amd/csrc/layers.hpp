@@ -104,7 +104,8 @@ struct Layer1Reuse {
 // What the layer below needs from a layer's input gradient: masked by its ReLU decision (its output h, one row per
 // source row of this layer) and, when only some rows take a gradient, compacted to them (out_rows[u] = row of gz_out
 // for source row u, -1 = none; NULL = same row). With this the input gradient goes straight to gz_out.
-struct BelowLayer { const float* h = nullptr; const int32_t* out_rows = nullptr; float* gz_out = nullptr; };
+// positive: that decision as the layer's product left it, a byte for every four columns (NULL: read from h)
+struct BelowLayer { const float* h = nullptr; const uint8_t* positive = nullptr; const int32_t* out_rows = nullptr; float* gz_out = nullptr; };
 
 int32_t layer_splits(int32_t n_dst_cap, int32_t d_in, int32_t d_out);
 LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out, bool in_step = false);
@@ -122,13 +123,13 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
 int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_t* csc_indptr, const int32_t* csc_dst,
                             const int32_t* d_n_src, int32_t n_src_cap, const int32_t* d_n_dst, float* grad_x,
                             hipStream_t st, const float* mask_h = nullptr, const int32_t* out_rows = nullptr,
-                            float* masked_out = nullptr, const SourceWeights* weights = nullptr, const ReduceArgs* reduce = nullptr);
+                            float* masked_out = nullptr, const SourceWeights* weights = nullptr, const ReduceArgs* reduce = nullptr, const uint8_t* mask_bits = nullptr);
 int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, int32_t d_in, const float* w_self,
                      const float* w_neigh, const float* bias, int32_t d_out, int32_t relu, float* mean, float* h,
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof = nullptr, int agg_stage = -1,
                      int gemm_stage = -1, const void* agg_table = nullptr, int32_t arch = NO_ARCH_SAGE_MEAN, const Layer1Reuse* reuse = nullptr, bool aggregate_done = false,
                      const SourceWeights* weights = nullptr, const PaddedSlots* padded = nullptr,
-                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false, hipEvent_t product_done = nullptr);
+                     const Bf16Products* bf = nullptr, no_blocks_s* side_of = nullptr, uint16_t* const* cut_fwd = nullptr, bool cut_done = false, hipEvent_t product_done = nullptr, uint8_t* positive = nullptr);
 // product_done: recorded behind the product (taken from its launch)
 // cut_fwd: where the layer's matrices are cut for the forward product, beside the aggregation unless cut_done; without it a product that
 // takes planes has them cut into the workspace

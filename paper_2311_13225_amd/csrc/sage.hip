@@ -103,17 +103,21 @@ __device__ __forceinline__ void accum_unit(float (&acc)[1], const uint16_t& b) {
 // the items of a row are consecutive, which keeps the reads of a source row next to each other in time.
 // Up to eight source rows are loaded before the first add; the adds stay in segment order.
 // MASKED: the result goes to masked_out (backward inside a step), a variant of its own because the registers it holds cost the plain
-// form 3 us of the 84 of a layer's forward and backward pass (3.4 K rows, 256 x 256).
+// form 3 us of the 84 of a layer's forward and backward pass (3.4 K rows, 256 x 256). MASK_BITS: the ReLU decisions from the bytes that the layer
+// below's product left, a sixteenth of its output's size (steps, us: 4096 seeds, 256 columns 675.5 -> 670.8, bf16 209.5 -> 206.3, dense 198.3 -> 197.1).
 // Side: SideTasks where the launch carries some, else NoSideTasks (the tasks' code costs the widest forms 2 to 34 registers).
-template <typename T, int VEC, bool MEAN, bool WEIGHTED, bool MASKED, typename Side>
+enum { MASK_NONE = 0, MASK_H, MASK_BITS };
+template <typename T, int VEC, bool MEAN, bool WEIGHTED, int MASK, typename Side>
 __global__ void __launch_bounds__(256, MEAN ? 1 : WEIGHTED ? 4 : 5) segment_rows_kernel(RowCopyJob job, const T* __restrict__ src, int64_t ld_src,
                                                            const int32_t* __restrict__ seg, const int32_t* __restrict__ idx,
                                                            const int32_t* d_n_rows, int32_t n_rows_cap,
                                                            const int32_t* d_n_init, float* __restrict__ out, int64_t ld_out,
                                                            int32_t units, int32_t g_log2, int32_t n_chunks,
                                                            const int32_t* __restrict__ self_idx, int32_t agg_mode,
-                                                           const float* __restrict__ mask_h, const int32_t* __restrict__ out_rows,
+                                                           const void* __restrict__ mask, const int32_t* __restrict__ out_rows,
                                                            float* __restrict__ masked_out, SourceWeights sw, Side side) {
+    constexpr bool MASKED = MASK != MASK_NONE;
+    using Decision = std::conditional_t<MASK == MASK_BITS, uint8_t, typename RawUnit<float, MASKED ? VEC : 1>::type>;
     if (blockIdx.x >= side.first_block) { run_side_tasks(side); return; }
     if (job.dst && blockIdx.x >= job.first_block) {
         // extra blocks of the launch: dst[dst_rows[i], :] = src[src_rows[i], :], one wavefront per row (rows that are
@@ -151,11 +155,11 @@ __global__ void __launch_bounds__(256, MEAN ? 1 : WEIGHTED ? 4 : 5) segment_rows
         // are asked for before the segment: the kernel is bound by its chain of dependent round trips, which they would make two
         // longer at the end (step of 4096 seeds, 256 columns: 774 -> 752 us; super-batch with most rows served by the cache: 1477 -> 1437).
         int64_t masked_row = row;
-        typename RawUnit<float, MASKED ? VEC : 1>::type decision{};
-        if (MASKED) {
+        Decision decision{};
+        if constexpr (MASKED) {
             if (out_rows) masked_row = out_rows[row];
             if (masked_row < 0) continue;
-            decision = *reinterpret_cast<const decltype(decision)*>(mask_h + row * ld_out + (int64_t)u * VEC);
+            decision = static_cast<const Decision*>(mask)[row * units + u];      // (rows of ld_out = units * VEC columns)
         }
         float acc[VEC];
 #pragma unroll
@@ -272,9 +276,14 @@ __global__ void __launch_bounds__(256, MEAN ? 1 : WEIGHTED ? 4 : 5) segment_rows
 #pragma unroll
             for (int c = 0; c < VEC; ++c) acc[c] *= ws;
         }
-        if (MASKED) {
+        if constexpr (MASKED) {
             float hm[VEC];
-            __builtin_memcpy(hm, &decision, MASKED ? sizeof(hm) : 0);
+            if constexpr (MASK == MASK_H) {
+                __builtin_memcpy(hm, &decision, sizeof(hm));
+            } else {
+#pragma unroll
+                for (int c = 0; c < VEC; ++c) hm[c] = (uint32_t)decision >> c & 1u ? 1.f : 0.f;
+            }
             float* mo = masked_out + masked_row * ld_out + (int64_t)u * VEC;
 #pragma unroll
             for (int c = 0; c < VEC; ++c) mo[c] = hm[c] > 0.f ? acc[c] : 0.f;
@@ -291,7 +300,7 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
                            const int32_t* self_idx = nullptr, int32_t agg_mode = AGG_NEIGH_MEAN, const float* mask_h = nullptr,
                            const int32_t* out_rows = nullptr, float* masked_out = nullptr, const RowCopyJob* copy = nullptr,
                            hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr, const SourceWeights* weights = nullptr, no_blocks_s* side_of = nullptr,
-                           const CutJobs* cut = nullptr, const ReduceArgs* reduce = nullptr) {
+                           const CutJobs* cut = nullptr, const ReduceArgs* reduce = nullptr, const uint8_t* mask_bits = nullptr) {
     const int32_t units = dim / VEC;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
@@ -312,15 +321,19 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
     const uint32_t own = (uint32_t)(blocks + copy_blocks);
     auto launch_as = [&](auto weighted, auto masked, const auto& side, uint32_t grid) {
         using Side = std::decay_t<decltype(side)>;
+        const void* mask = decltype(masked)::value == MASK_BITS ? (const void*)mask_bits : (const void*)mask_h;
         NO_LAUNCH_TIMED((segment_rows_kernel<T, VEC, MEAN, decltype(weighted)::value, decltype(masked)::value, Side>), dim3(grid), dim3(256), st, ev0, ev1, job, src,
-                        ld_src, seg, idx, d_n, n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask_h, out_rows,
+                        ld_src, seg, idx, d_n, n_cap, d_n_init, out, ld_out, units, g_log2, n_chunks, self_idx, agg_mode, mask, out_rows,
                         masked_out, sw, side);
     };
     auto launch = [&](auto weighted, const auto& side, uint32_t grid) {
         if constexpr (!MEAN) {
-            if (masked_out) { launch_as(weighted, std::true_type{}, side, grid); return; }
+            if constexpr (VEC == 4) {
+                if (masked_out && mask_bits) { launch_as(weighted, std::integral_constant<int, MASK_BITS>{}, side, grid); return; }
+            }
+            if (masked_out) { launch_as(weighted, std::integral_constant<int, MASK_H>{}, side, grid); return; }
         }
-        launch_as(weighted, std::false_type{}, side, grid);
+        launch_as(weighted, std::integral_constant<int, MASK_NONE>{}, side, grid);
     };
     if constexpr (MEAN) {
         launch_with_riders(cut, side_of, own, [&](const auto& side, uint32_t grid) {
@@ -331,8 +344,8 @@ static void launch_segment(const T* src, int64_t ld_src, const int32_t* seg, con
     } else if (reduce) {
         ReduceSide side{own, (uint32_t)reduce_blocks(*reduce), *reduce};
         const uint32_t grid = own + side.blocks * (uint32_t)reduce->n_problems;
-        if (sw.cnt) launch_as(std::true_type{}, std::false_type{}, side, grid);
-        else launch_as(std::false_type{}, std::false_type{}, side, grid);
+        if (sw.cnt) launch_as(std::true_type{}, std::integral_constant<int, MASK_NONE>{}, side, grid);
+        else launch_as(std::false_type{}, std::integral_constant<int, MASK_NONE>{}, side, grid);
         return;
     }
     NoSideTasks none;
@@ -502,13 +515,13 @@ int32_t mean_aggregate(const void* x_src, no_dtype dt, int32_t dim, const int32_
 int32_t transpose_aggregate(const float* gmean_scaled, int32_t dim, const int32_t* csc_indptr, const int32_t* csc_dst,
                             const int32_t* d_n_src, int32_t n_src_cap, const int32_t* d_n_dst, float* grad_x,
                             hipStream_t st, const float* mask_h, const int32_t* out_rows, float* masked_out,
-                            const SourceWeights* weights, const ReduceArgs* reduce) {
+                            const SourceWeights* weights, const ReduceArgs* reduce, const uint8_t* mask_bits) {
     if (n_src_cap <= 0) return NO_OK;
     const uintptr_t al = (uintptr_t)gmean_scaled | (uintptr_t)grad_x | (uintptr_t)mask_h | (uintptr_t)masked_out;
     const bool a16 = (al & 15) == 0, a8 = (al & 7) == 0;
 #define NO_SEG_BWD(V) \
     launch_segment<float, V, false>(gmean_scaled, dim, csc_indptr, csc_dst, d_n_src, n_src_cap, d_n_dst, grad_x, dim, dim, st, \
-                                    nullptr, AGG_NEIGH_MEAN, mask_h, out_rows, masked_out, nullptr, nullptr, nullptr, weights, nullptr, nullptr, reduce)
+                                    nullptr, AGG_NEIGH_MEAN, mask_h, out_rows, masked_out, nullptr, nullptr, nullptr, weights, nullptr, nullptr, reduce, mask_bits)
     if (dim % 4 == 0 && a16) NO_SEG_BWD(4);
     else if (dim % 2 == 0 && a8) NO_SEG_BWD(2);
     else NO_SEG_BWD(1);
@@ -612,7 +625,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
                      const LayerWorkspace& w, hipStream_t st, StageProfiler* prof, int agg_stage, int gemm_stage,
                      const void* agg_table, int32_t arch, const Layer1Reuse* reuse,
                      bool aggregate_done, const SourceWeights* weights, const PaddedSlots* padded,
-                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd, bool cut_done, hipEvent_t product_done) {
+                     const Bf16Products* bf, no_blocks_s* side_of, uint16_t* const* cut_fwd, bool cut_done, hipEvent_t product_done, uint8_t* positive) {
     // aggregate_done: `mean` (and the reused rows of H^1) were already written by an earlier launch of the same
     // aggregation (a batch prepared ahead); only the product runs
     // reuse: the output rows are scattered into H^1, recomputed hot rows also refresh the cache, and the reused
@@ -670,6 +683,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap; a.N = d_out;
         a.bias = bias; a.relu = relu;
         scatter(a);
+        a.positive = positive;
         a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
         return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_nn_forward(a, st, p0, p1); });
     }
@@ -696,6 +710,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
         a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap;
         a.bias = bias; a.relu = relu;
         if (reuse) { a.c_rows = reuse->compute_pos; a.c_keep = reuse->emb; a.c_keep_rows = reuse->refresh_slot; }
+        a.positive = positive;
         return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_bf16_nn(a, st, p0, p1); });
     }
     const float* x_dst = direct_self ? (const float*)agg_table : (const float*)x_src;
@@ -715,6 +730,7 @@ int32_t sage_forward(const no_block_view& blk, const void* x_src, no_dtype dt, i
     a.d_M = blk.d_n_dst; a.M_cap = blk.n_dst_cap; a.N = d_out;
     a.bias = bias; a.relu = relu;
     scatter(a);
+    a.positive = positive;
     a.cut_B[0] = cut_fwd ? cut_fwd[0] : nullptr;
     a.cut_B[1] = cut_fwd ? cut_fwd[1] : nullptr;
     return product([&](hipEvent_t p0, hipEvent_t p1) { return gemm_nn_forward(a, st, p0, p1); });
@@ -812,7 +828,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
         if (!input_products_done) NO_CHECK(gemm_nn_input_grad(a, st, together ? &t : nullptr, &tn_done));
         NO_CHECK(transpose_aggregate(w.gmean, d_in, blk.d_csc_indptr, blk.d_csc_dst, blk.d_n_src, blk.n_src_cap,
                                      blk.d_n_dst, grad_x_src, st, below ? below->h : nullptr, below ? below->out_rows : nullptr,
-                                     below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr, tn_done ? &r : nullptr));
+                                     below ? below->gz_out : nullptr, arch == NO_ARCH_GCN_SYM ? weights : nullptr, tn_done ? &r : nullptr, below ? below->positive : nullptr));
         if (prof && dx_stage >= 0) prof->end();
     }
     if (dt == NO_BF16 && !gcn && !bf) NO_CHECK(bf16_rows_to_f32((const uint16_t*)x_src, blk.d_n_dst, n_cap, d_in, w.x_dst_f32, st));

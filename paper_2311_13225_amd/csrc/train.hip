@@ -108,6 +108,7 @@ struct no_model_s {
     no::DevBuf<float> mean[NO_MAX_LAYERS];           // layer l (index l-1): [n_dst_cap, d_{l-1}]
     no::DevBuf<float> h[NO_MAX_LAYERS];              // layer l output [rows, d_l]; h[0] holds all of V^1
     no::DevBuf<float> gh[NO_MAX_LAYERS];             // gradient w.r.t. h[l-1]
+    no::DevBuf<uint8_t> positive[NO_MAX_LAYERS];     // which entries of h[l-1] its product made positive, a byte for four (hidden layers of a multiple of 4)
     no::DevBuf<char> ws;                             // one region per layer (a layer writes the next one's gz while its own is in use)
     size_t ws_bytes = 0;
     size_t ws_off[NO_MAX_LAYERS] = {0};
@@ -175,6 +176,7 @@ struct no_model_s {
         for (auto& b : mean) b.release();
         for (auto& b : h) b.release();
         for (auto& b : gh) b.release();
+        for (auto& b : positive) b.release();
         ws.release(); row_loss.release(); stats.release();
     }
 };
@@ -283,6 +285,7 @@ extern "C" int32_t no_model_create(no_graph_t g, int32_t n_layers, const int32_t
         NO_CHECK(m->mean[l - 1].alloc((size_t)H.n_dst_cap * m->dims[l - 1]));
         NO_CHECK(m->h[l - 1].alloc((size_t)H.n_dst_cap * m->dims[l]));
         NO_CHECK(m->gh[l - 1].alloc((size_t)H.n_dst_cap * m->dims[l]));
+        if (l < L && m->dims[l] % 4 == 0) NO_CHECK(m->positive[l - 1].alloc((size_t)H.n_dst_cap * (m->dims[l] / 4)));
         m->ws_off[l - 1] = ws_bytes;
         ws_bytes += carve_workspace(nullptr, H.n_dst_cap, m->dims[l - 1], m->dims[l], true).bytes;
     }
@@ -623,11 +626,11 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
                                   NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1, d_features, m->arch,
                                   (l == 1 && used_cache) ? &reuse : nullptr, aggregated, &sw, &slots,
                                   bf16_products ? &bfp : nullptr, B, m->planes_of(0), cut_first,
-                                  d_next_seeds && next_uses_cache && aggregate_ahead ? m->ev_l1_done : nullptr));
+                                  d_next_seeds && next_uses_cache && aggregate_ahead ? m->ev_l1_done : nullptr, m->positive[0].p));
         } else if (l < L || !head)
         NO_CHECK(sage_forward(blk, x, dt, d_in, m->params.p + m->off_w_self[l - 1], m->params.p + m->off_w_neigh[l - 1],
                               m->params.p + m->off_bias[l - 1], d_out, l < L ? 1 : 0, m->mean[l - 1].p, h_out, w, st,
-                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->planes_of(l - 1)));
+                              nullptr, -1, -1, nullptr, m->arch, nullptr, false, &sw, nullptr, nullptr, B, m->planes_of(l - 1), false, nullptr, m->positive[l - 1].p));
         if (l == L && L >= 2) prof.end();
         if (l == 1 && d_next_seeds) {
             if (lookahead_early) {
@@ -706,6 +709,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
         if (l >= 2) {
             const no_block_view& blk_below = view[L - l + 1];
             below.h = m->h[l - 2].p;
+            below.positive = m->positive[l - 2].p;
             below.out_rows = (l == 2 && used_cache) ? B->compute_inv.p : nullptr;
             below.gz_out = carve_workspace(m->ws.p + m->ws_off[l - 2], blk_below.n_dst_cap, m->dims[l - 2], m->dims[l - 1], true).gz;
         }
