@@ -141,6 +141,8 @@ int32_t sample_blocks_impl(no_graph_s* g, const int32_t* d_seeds, int32_t n_seed
                            uint32_t domain, int32_t n_hops, no_cache_s* cache, int64_t step, no_blocks_s* b,
                            hipStream_t st, bool finish = true, const SideGather* gather = nullptr,
                            bool stamp_refresh = false);
+// Only the draw of hop 0 of a one-hop handle, rows d_dst (vertex ids inside the graph): its slots and its row count.
+int32_t draw_rows(no_graph_s* g, const int32_t* d_dst, int32_t n, uint64_t stream_key, uint32_t domain, no_blocks_s* b, hipStream_t st);
 int32_t blocks_finish(no_blocks_s* b, hipStream_t st, hipEvent_t done = nullptr);      // (done: recorded behind them)
 // The side tasks that may run in the next launch (of own_blocks blocks and the tasks' own) on the call's stream; they count as launched.
 void side_take(no_blocks_s* b, uint32_t own_blocks, SideTasks* side);

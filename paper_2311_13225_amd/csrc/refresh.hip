@@ -76,15 +76,19 @@ extern "C" int32_t no_refresh_hot_begin(no_cache_t c, no_graph_t g, const void* 
 
     r->snap_arch = arch;
     const bool bf16 = dt == NO_BF16 && arch == NO_ARCH_SAGE_MEAN;    // only the separate self path needs the rows' own copy
-    SideGather sg;
-    sg.table = d_features;
-    sg.row_bytes = feat_dim * (dt == NO_BF16 ? 2 : 4);
-    sg.out = r->x0.p;
-    r->blocks->count_sources = arch == NO_ARCH_GCN_SYM;
-    NO_CHECK(sample_blocks_impl(g, c->hot_ids.p, n_hot, seed + (uint64_t)version, 2u, 1, nullptr, 0, r->blocks, r->stream, true,
-                                bf16 ? &sg : nullptr));
+    // The rows are aggregated from the draw's slots, through global ids; only the symmetric normalisation needs the edges that leave each source,
+    // which come with numbered sources.
+    if (arch == NO_ARCH_GCN_SYM) {
+        r->blocks->count_sources = true;
+        NO_CHECK(sample_blocks_impl(g, c->hot_ids.p, n_hot, seed + (uint64_t)version, 2u, 1, nullptr, 0, r->blocks, r->stream, true));
+    } else {
+        NO_CHECK(draw_rows(g, c->hot_ids.p, n_hot, seed + (uint64_t)version, 2u, r->blocks, r->stream));
+        const int32_t row_bytes = feat_dim * 2;
+        if (bf16) NO_CHECK(gather_rows(d_features, row_bytes, row_bytes, c->hot_ids.p, nullptr, n_hot, r->x0.p, row_bytes, r->stream));
+    }
     no_block_view view;
     fill_block_view(r->blocks, 0, &view);
+    if (arch != NO_ARCH_GCN_SYM) view.d_src_global = c->hot_ids.p;
     view.d_indices = view.d_nbr_global;        // aggregate straight from the table through the global ids
     LayerWorkspace w;
     w.x_dst_f32 = bf16 ? r->x_f32.p : nullptr;
