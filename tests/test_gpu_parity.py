@@ -540,6 +540,15 @@ def test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out):
     assert torch.isnan(gx[n:]).all()
 
 
+@pytest.mark.parametrize("n,cap,F,d_out", [
+    (13_990, 14_000, 256, 250), (19_990, 20_000, 256, 256), (20_004, 20_004, 250, 256), (1, 20_000, 256, 256),     # input and weight gradients in one launch, or not
+    (40_000, 40_000, 100, 256), (40_010, 40_010, 100, 250),                                                     # the same with blocks of 64 rows
+    (28_000, 28_000, 64, 256), (28_010, 28_010, 63, 250)])                                                     # narrow input gradient: small tiles alone, or large ones
+def test_sage_layer_gradient_products_about_the_longest_short_launches(n, cap, F, d_out):
+    """Sizes about which a layer call stops to take small tiles for its weight gradients, beside the input gradient and alone. Bound as above."""
+    test_sage_layer_gradient_products_at_tile_edges(n, cap, F, d_out)
+
+
 def forward_layer(b, n, cap, x, w_self, w_neigh, bias, relu):
     """One layer whose row v samples itself: the mean is x, h = act(x (W_self + W_neigh) + bias)."""
     F, d_out = w_self.shape
@@ -1202,6 +1211,27 @@ def test_refresh_hot_rows_match_oracle(bf16):
     assert np.array_equal(view["version"].cpu().numpy(), ver2)
     assert_close(view["emb"].cpu().numpy(), emb2, "refreshed rows, second round")
     assert not np.array_equal(emb, emb2)
+
+
+@pytest.mark.parametrize("k", [1, 8, 9, 17, 32, 33, 64])
+@pytest.mark.parametrize("bits", [32, 64])
+def test_refresh_draws_at_the_widths_of_its_lane_groups(k, bits):
+    """Rows shorter and longer than the fanout (and, but for 64, as long), on both kinds of row pointers, against the oracle's draws."""
+    b = nb()
+    V, F, D, fan = 2500, 24, 40, (5, k)
+    src, dst, og, gg = make_graph(V, 80_000, 7, bits)
+    lens = np.diff(og.rowptr)
+    assert (lens < k).any() and (lens > k).any()
+    feat, train = si.features(V, F, 7), si.train_split(V, 0.65, 7)
+    (w_self, w_neigh, bias), = si.init_weights([F, D], 7)
+    oc = ora.select_hot(og, train, 64, fan, 1, 1.0, 3, D, 7)
+    gc = b.no_select_hot(gg, dev(train), 64, fan, 1, 1.0, 3, D, 7)
+    b.no_refresh_hot_begin(gc, gg, dev(feat), dev(w_self), dev(w_neigh), dev(bias), k, 6, 99)
+    b.no_refresh_hot_commit(gc)
+    emb, ver = ora.refresh_hot(og, feat, oc, (w_self, w_neigh, bias), k, 6, 99, feat_is_bf16=False)
+    view = b.no_cache_view(gc, V)
+    assert np.array_equal(view["version"].cpu().numpy(), ver)
+    assert_close(view["emb"].cpu().numpy(), emb, "refreshed rows")
 
 
 @pytest.mark.parametrize("form", ["sage", "gcn", "gcn_sum", "gcn_sym"])
