@@ -136,6 +136,10 @@ struct no_model_s {
         const int64_t least = (dims[l + 1] % 64 ? 400000 : 600000) / (dims[l] >= 300 ? 2 : 1) * (one ? 2 : 1);
         return work >= least || (l > 0 && planes_of(0)) ? cut_fwd[l] : nullptr;
     }
+    // The last layer goes with the loss and its own input gradients (head.hip).
+    bool last_layer_joined() const {
+        return n_layers >= 2 && no::head_takes(arch, dims[n_layers - 1], dims[n_layers], blocks->hop[0].n_src_cap);
+    }
     // sampling ahead (Section 4.2, Stage 1): a second set of blocks and destination rows filled on a stream of its
     // own while the current batch trains; created by the first call that asks for it
     no_blocks_s* blocks_alt = nullptr;
@@ -342,6 +346,13 @@ extern "C" int32_t no_model_forward_planes(no_model_t m, int32_t layer, int32_t*
     clear_error();
     NO_REQUIRE(m && planes && layer >= 1 && layer <= m->n_layers, NO_ERR_INVALID_ARG, "no_model_forward_planes: bad argument");
     *planes = m->planes_of(layer - 1) ? 1 : 0;
+    return NO_OK;
+}
+
+extern "C" int32_t no_model_last_layer_joined(no_model_t m, int32_t* joined) {
+    clear_error();
+    NO_REQUIRE(m && joined, NO_ERR_INVALID_ARG, "no_model_last_layer_joined: bad argument");
+    *joined = m->last_layer_joined() ? 1 : 0;
     return NO_OK;
 }
 
@@ -580,7 +591,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
 
     // forward
     const int32_t C = m->dims[L];
-    const bool head = L >= 2 && head_takes(m->arch, m->dims[L - 1], C, B->hop[0].n_src_cap);      // the last layer goes with the loss
+    const bool head = m->last_layer_joined();
     no_block_view view[NO_MAX_LAYERS];
     for (int32_t h = 0; h < L; ++h) fill_block_view(B, h, &view[h]);
     for (int32_t l = 1; l <= L; ++l) {

@@ -980,7 +980,7 @@ def check_step_outputs(b, model, st, r, n_layers, step, with_cache_blocks, gcn, 
 
 
 def run_steps(w, n_steps, use_cache, lr=0.05, V=None, E=None, hot_fraction=None, bits=32, presample=1,
-              n_train_presample=None, superbatch=0, arch="sage", ahead=False):
+              n_train_presample=None, superbatch=0, arch="sage", ahead=False, joined=None):
     b = nb()
     V = V or w.n_vertices
     E = E or w.n_edges
@@ -996,6 +996,7 @@ def run_steps(w, n_steps, use_cache, lr=0.05, V=None, E=None, hot_fraction=None,
     rtol = RTOL_BF16 if bf16_products else RTOL
     if gcn:
         b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
+    assert joined is None or b.no_model_last_layer_joined(model) == joined
     for l in range(w.n_layers):
         for t, a in zip(b.no_model_params(model, l + 1), weights[l]):
             t.copy_(dev(a))
@@ -1291,16 +1292,28 @@ def test_train_step_with_the_weights_of_two_layers_cut_beside_their_aggregations
     assert run_steps(w, 2, use_cache=True, lr=0.02) > 0
 
 
-@pytest.mark.parametrize("arch,batch,fanouts,hidden,classes", [
+JOINED_LAST_LAYERS = [
     ("sage", 1, (10, 5), 64, 16), ("sage", 15, (64, 2), 4, 4), ("gcn", 16, (17, 3), 8, 5), ("sage", 17, (3, 16, 2), 12, 15),    # a block's rows, short rows of few units
     ("sage", 300, (33, 3), 256, 64), ("gcn_sum", 33, (9, 3), 60, 65), ("gcn", 129, (15, 3), 128, 17), ("sage", 100, (1, 2), 252, 47),    # column groups and 16s of classes
     ("sage", 257, (7, 3), 100, 128), ("gcn", 260, (7, 3), 256, 129), ("sage", 65, (8, 4), 200, 192), ("sage", 65, (8, 4), 132, 193), ("gcn_sum", 40, (25, 3), 256, 256),
-    ("sage", 4100, (4, 2), 64, 20),                                                                                   # more row blocks than compute units
-    ("sage", 40, (8, 4), 260, 20), ("sage", 40, (8, 4), 66, 20), ("gcn", 40, (8, 4), 64, 3), ("sage", 40, (8, 4), 64, 257), ("gcn_sym", 40, (8, 4), 64, 20)])   # not in one launch
-def test_train_steps_at_the_edges_of_the_last_layers_launch(arch, batch, fanouts, hidden, classes):
+    ("sage", 4100, (4, 2), 64, 20)]                                                                                   # more row blocks than compute units
+SEPARATE_LAST_LAYERS = [("sage", 40, (8, 4), 260, 20), ("sage", 40, (8, 4), 66, 20), ("gcn", 40, (8, 4), 64, 3), ("sage", 40, (8, 4), 64, 257), ("gcn_sym", 40, (8, 4), 64, 20)]
+
+
+@pytest.mark.parametrize("arch,batch,fanouts,hidden,classes,joined", [c + (True,) for c in JOINED_LAST_LAYERS] + [c + (False,) for c in SEPARATE_LAST_LAYERS])
+def test_train_steps_at_the_edges_of_the_last_layers_launch(arch, batch, fanouts, hidden, classes, joined):
     import dataclasses
     w = dataclasses.replace(si.WORKLOADS["tiny"], batch=batch, fanouts=fanouts, hidden=hidden, n_classes=classes, feat_dim=20, staleness=2, hot_fraction=0.2)
-    run_steps(w, 2, use_cache=True, lr=0.02, arch=arch)
+    run_steps(w, 2, use_cache=True, lr=0.02, arch=arch, joined=joined)
+
+
+@pytest.mark.parametrize("arch,batch,fanouts,hidden,classes", [
+    ("sage", 1, (10, 5), 64, 16), ("sage", 17, (3, 16, 2), 12, 15), ("gcn", 129, (15, 3, 2), 128, 17), ("sage", 65, (8, 4, 3), 132, 193), ("gcn_sum", 40, (25, 3), 256, 256)])
+def test_the_last_layers_launch_takes_the_side_tasks_of_batches_prepared_ahead(arch, batch, fanouts, hidden, classes):
+    """Tasks that the sampling and the aggregation of a batch prepared ahead leave go with the launch of its last layer, whose blocks have twice their threads."""
+    import dataclasses
+    w = dataclasses.replace(si.WORKLOADS["tiny"], batch=batch, fanouts=fanouts, hidden=hidden, n_classes=classes, feat_dim=20, staleness=2, hot_fraction=0.2)
+    run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=True, joined=True)
 
 
 @pytest.mark.parametrize("forms", [("gcn", "sage"), ("sage", "gcn"), ("gcn_sym", "gcn_sum")])
