@@ -1316,6 +1316,69 @@ def test_the_last_layers_launch_takes_the_side_tasks_of_batches_prepared_ahead(a
     run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=True, joined=True)
 
 
+@pytest.mark.parametrize("arch,cap,F,hidden,classes,bf16,planes", [
+    ("sage", 40, 20, 64, 47, False, False), ("gcn", 40, 20, 252, 172, False, False),             # layer 1's product in small blocks
+    ("sage", 2500, 20, 256, 47, False, False), ("sage", 2500, 602, 256, 41, False, True),        # in tiles, on planes
+    ("sage", 2500, 20, 256, 47, True, False), ("gcn_sum", 2500, 602, 256, 256, False, False),    # with bf16 operands; one product in tiles
+    ("sage", 40, 20, 260, 47, False, False), ("sage", 40, 20, 66, 47, False, False)])            # the last layer not in one launch; decisions read from the outputs
+def test_infinities_and_nan_stay_where_they_arise_in_a_step(arch, cap, F, hidden, classes, bf16, planes):
+    """Seeds that sample nothing, so that every row is its own, and one seed (amid a block of 16 rows) whose features hold NaN or an infinity; a class that is
+    switched off. A NaN is not above 0, so that row's outputs are zeros with no gradient; an infinity is, where it is positive, and makes that row's logits NaN;
+    with a label outside the classes the row adds nothing to any gradient. What is finite in 64 bits is within the tolerance, and nothing else changes."""
+    b = nb()
+    n, V, at = 37, 30_000, 21
+    rng = np.random.default_rng(hidden + classes)
+    gcn = arch != "sage"
+    src = np.zeros(0, np.int32)
+    g = b.no_build_csr(src, src, V, 32)
+    for value, label_on, off in ((np.nan, True, None), (np.inf, True, None), (-np.inf, False, None), (1.0, True, 2)):
+        print("step", value, label_on, off, flush=True)
+        model = b.no_model_create(g, [F, hidden, classes], cap, (10, 3), b.NO_BF16 if bf16 else b.NO_F32)
+        if gcn:
+            b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
+        assert b.no_model_forward_planes(model, 1) == planes and b.no_model_last_layer_joined(model) == (hidden in (64, 252, 256))
+        weights = si.init_weights([F, hidden, classes], 5)
+        for layer in (1, 2):
+            weights[layer - 1][2][:] = rng.standard_normal(weights[layer - 1][2].shape) * 0.1
+        if off is not None:
+            weights[1][2][off] = -np.inf
+        for layer in (1, 2):
+            for t, a in zip(b.no_model_params(model, layer), weights[layer - 1]):
+                t.copy_(dev(a))
+        feat = torch.from_numpy(rng.standard_normal((V, F)).astype(np.float32))
+        seeds = rng.permutation(V)[:n].astype(np.int32)
+        lab = rng.integers(3, classes, V).astype(np.int32)
+        feat[int(seeds[at]), 7] = value
+        if not label_on:
+            lab[seeds[at]] = classes
+        feat = feat.to(torch.bfloat16) if bf16 else feat
+        st = b.no_train_step(model, g, feat.cuda(), dev(lab), dev(seeds), None, 0, 1, 0.0)
+        assert st.bad_label == (0 if label_on else 1)
+        w1 = torch.from_numpy(weights[0][0])
+        w1 = (w1.to(torch.bfloat16) if bf16 else w1).double().numpy()
+        x, w2 = feat.double().numpy()[seeds], weights[1][0].astype(np.float64)
+        with np.errstate(invalid="ignore"):
+            z1 = x @ w1 + weights[0][2]
+            h1 = np.where(z1 > 0, z1, 0.0)
+            z2 = h1 @ w2 + weights[1][2]
+            e = np.exp(z2 - z2.max(1, keepdims=True))
+            p = e / e.sum(1, keepdims=True)
+            gz2 = (p - (np.arange(classes) == lab[seeds][:, None])) / n
+            if not label_on:
+                gz2[at] = 0.0
+            gz1 = np.where(z1 > 0, gz2 @ w2.T, 0.0)
+            refs = [h1, z2, gz2.sum(0), h1.T @ gz2, gz1.sum(0)] + ([] if bf16 else [x.T @ gz1])
+        got = [b.no_model_activations(model, layer, n, n)[0] for layer in (1, 2)] + [b.no_model_grads(model, 2)[i] for i in (2, 0)]
+        got += [b.no_model_grads(model, 1)[i] for i in ((2,) if bf16 else (2, 0))]
+        assert not np.isfinite(refs[1]).all() or np.isnan(value)
+        for a, ref, what in zip(got, refs, ("h1", "logits", "gbias2", "gw2", "gbias1", "gw1")):
+            a = a.cpu().numpy()
+            assert np.array_equal(np.isnan(a), np.isnan(ref)), (what, value)
+            assert np.array_equal(np.where(np.isinf(a), np.sign(a), 0), np.where(np.isinf(ref), np.sign(ref), 0)), (what, value)
+            ok = np.isfinite(ref)
+            assert_close(a[ok], ref[ok], "%s with %s" % (what, value), RTOL_BF16 if bf16 else RTOL)
+
+
 @pytest.mark.parametrize("forms", [("gcn", "sage"), ("sage", "gcn"), ("gcn_sym", "gcn_sum")])
 def test_a_batch_prepared_for_one_layer_form_is_not_used_for_another(forms):
     b = nb()
