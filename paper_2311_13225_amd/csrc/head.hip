@@ -8,9 +8,15 @@
 // Measured on the training stream, four launches -> this, us: 1024 seeds, 2 x 256 columns, 47 classes, 9 neighbours 26 -> 14; 41 classes, 22
 // neighbours, beside the next batch's sampling 33 -> 19; 172 classes 37 -> 25; 4096 seeds 73 -> 32; 256 seeds, 2 x 64 columns, 16 classes 20 -> 10.
 //
-// Products on the fp32 instruction (v_mfma_f32_16x16x4_f32), operands straight from LDS (rows) and L2 (weights). Bound by round trips (launched
+// The logits' product on the fp32 instruction (v_mfma_f32_16x16x4_f32), the reduction dealt to the wavefronts and their parts added in pairs: relative 2-norm
+// error against 64 bits 1.2e-7 at 2 x 256 terms, as that of the launches before it or less (1.2e-7 in small blocks, 2.1e-7 in tiles). The gradients of the
+// rows in 64 bits (v_mfma_f64_16x16x4_f64, half that rate): with the chain of the fp32 instruction they were off by 0.9e-7 at 47 classes and 1.7e-7 at 172, where
+// products on pieces are by 0.6e-7 and 1.0e-7; now by their last rounding, 0.25e-7, for 1 to 3 us of a step (4096 seeds, 47 classes
+// 652.8 -> 654.9; 1024, 172 classes 221.9 -> 223.3; 1024, 41 classes, one matrix 149.0 -> 149.6).
+//
+// Operands straight from LDS (rows) and L2 (weights). Bound by round trips (launched
 // alone, 47 classes: rows 6.6 of 12.7 us, product 2.8, gradients of the rows 2.1), with 172 classes by the 64 compute units that 1024 seeds fill (product 8 of
-// 19.4 us, 5.1 of them at the instruction's rate). The reduction is dealt to the wavefronts and summed in their order. Eight wavefronts, two rows each:
+// 19.4 us, 5.1 of them at the instruction's rate). Eight wavefronts, two rows each:
 // with four, whose rows queue up, the 41 classes took 27 us, and instructions are fetched faster than used only in short code: unrolled
 // loads with 64-bit addresses and guards (16 KB) cost another 2 us.
 #include "gemm_tile.hpp"
@@ -24,6 +30,7 @@
 namespace no {
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef double doublex4 __attribute__((ext_vector_type(4)));
 
 // 16 bytes at a 4-byte aligned byte offset from a pointer that the whole wavefront shares (one instruction, no 64-bit address per lane)
 __device__ __forceinline__ float4 load4_at(const float* base, uint32_t bytes) {
@@ -193,13 +200,14 @@ __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side sid
         __syncthreads();
         if (64 * j + (2 * j32 & ~3) < C) {
             const int c = min(64 * j + (2 * j32 & ~3), C - 4) + (2 * j32 & 2);
-            float2 s = *reinterpret_cast<const float2*>(&tile[r32 * CP + 2 * j32]);
+            float2 s[NW];
 #pragma unroll
-            for (int w = 1; w < NW; ++w) {
-                const float2 t = *reinterpret_cast<const float2*>(&tile[(w * R + r32) * CP + 2 * j32]);
-                s.x += t.x; s.y += t.y;
-            }
-            const float z[2] = {s.x + bias[j][0], s.y + bias[j][1]};
+            for (int w = 0; w < NW; ++w) s[w] = *reinterpret_cast<const float2*>(&tile[(w * R + r32) * CP + 2 * j32]);
+#pragma unroll
+            for (int o = NW / 2; o > 0; o >>= 1)
+#pragma unroll
+                for (int w = 0; w < o; ++w) { s[w].x += s[w + o].x; s[w].y += s[w + o].y; }
+            const float z[2] = {s[0].x + bias[j][0], s[0].y + bias[j][1]};
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
                 Z[r32 * ZP + c + e] = z[e];
@@ -248,7 +256,7 @@ __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side sid
     __syncthreads();
     for (int t = first_tile; t < n_tiles; t += g.parts * NW) {
         const bool second = t >= per;
-        floatx4 a2[2] = {floatx4{0.f, 0.f, 0.f, 0.f}, floatx4{0.f, 0.f, 0.f, 0.f}};      // (even and odd 16s)
+        doublex4 sum = {0.0, 0.0, 0.0, 0.0};
         if (t != first_tile) request_t(t);
 #pragma unroll
         for (int q = 0; q < 4 * G; ++q) {
@@ -269,18 +277,18 @@ __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side sid
                 }
                 const float zs[4] = {z.x, z.y, z.z, z.w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) a2[q & 1] = __builtin_amdgcn_mfma_f32_16x16x4f32(zs[e], v[e], a2[q & 1], 0, 0, 0);
+                for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f64_16x16x4f64((double)zs[e], (double)v[e], sum, 0, 0, 0);
             }
         }
         const int i = (second ? t - per : t) * 16 + l16;
         if (i >= d) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int lr = 4 * quad + r;
+            const int lr = 4 * r + quad;      // (element r of a lane of this instruction: row 4 r + quad)
             if (m0 + lr >= n) continue;
             const int len = len_sh[lr];
             const float s = two ? (second ? (len > 0 ? 1.f / (float)len : 0.f) : 1.f) : g.agg_mode == AGG_SELF_MEAN ? 1.f / (float)(len + 1) : 1.f;
-            const float o = (a2[0][r] + a2[1][r]) * s;
+            const float o = (float)sum[r] * s;
             const int64_t at = (int64_t)(m0 + lr) * d + i;
             if (!second) g.grad_self[at] = o;
             if (second || !two) g.grad_mean[at] = o;

@@ -1316,6 +1316,33 @@ def test_the_last_layers_launch_takes_the_side_tasks_of_batches_prepared_ahead(a
     run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=True, joined=True)
 
 
+@pytest.mark.parametrize("arch,cap,hidden,classes", [("sage", 40, 64, 16), ("sage", 1024, 256, 172), ("gcn", 1024, 256, 64), ("gcn_sum", 200, 100, 255), ("sage", 4096, 256, 47),
+                                                     ("gcn", 4096, 252, 41)])
+def test_input_gradients_of_a_joined_last_layer_are_rounded_once(arch, cap, hidden, classes):
+    """A seed that samples nothing: the bias gradients are its row of the output gradients of both layers, and layer 1's are all kept. Sums in 64 bits of exact
+    products are off by 2^-53 of the sum of their terms' sizes a term, nothing beside the rounding to fp32 that ends them."""
+    b = nb()
+    src = np.zeros(0, np.int32)
+    g = b.no_build_csr(src, src, 5000, 32)
+    model = b.no_model_create(g, [8, hidden, classes], cap, (3, 2))
+    if arch != "sage":
+        b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
+    assert b.no_model_last_layer_joined(model)
+    rng = np.random.default_rng(classes)
+    feat, seed = torch.ones((5000, 8), device="cuda"), dev(np.array([17], np.int32))
+    for t, v in zip(b.no_model_params(model, 1), (0.0, 0.0, 1.0)):
+        t.fill_(v)
+    for step in range(4):
+        print("step", step, flush=True)
+        w = (rng.standard_normal((hidden, classes)) * 0.1).astype(np.float32)
+        b.no_model_params(model, 2)[0].copy_(dev(w))
+        lab = np.full(5000, rng.integers(classes), np.int32)
+        b.no_train_step(model, g, feat, dev(lab), seed, None, step, 1, 0.0)
+        gz2, gz1 = (b.no_model_grads(model, layer)[2].cpu().numpy().astype(np.float64) for layer in (2, 1))
+        ref, mag = w.astype(np.float64) @ gz2, np.abs(w).astype(np.float64) @ np.abs(gz2)
+        assert (np.abs(gz1 - ref) <= 2.0 ** -24 * np.abs(ref) + (classes + 1) * 2.0 ** -52 * mag).all()
+
+
 @pytest.mark.parametrize("arch,cap,F,hidden,classes,bf16,planes", [
     ("sage", 40, 20, 64, 47, False, False), ("gcn", 40, 20, 252, 172, False, False),             # layer 1's product in small blocks
     ("sage", 2500, 20, 256, 47, False, False), ("sage", 2500, 602, 256, 41, False, True),        # in tiles, on planes
