@@ -136,9 +136,9 @@ struct no_model_s {
         const int64_t least = (dims[l + 1] % 64 ? 400000 : 600000) / (dims[l] >= 300 ? 2 : 1) * (one ? 2 : 1);
         return work >= least || (l > 0 && planes_of(0)) ? cut_fwd[l] : nullptr;
     }
-    // The last layer goes with the loss and its own input gradients (head.hip).
+    // The last layer goes with the loss and its own input gradients (head.hip), unless its product is one on planes: that launch has none.
     bool last_layer_joined() const {
-        return n_layers >= 2 && no::head_takes(arch, dims[n_layers - 1], dims[n_layers], blocks->hop[0].n_src_cap);
+        return n_layers >= 2 && !planes_of(n_layers - 1) && no::head_takes(arch, dims[n_layers - 1], dims[n_layers], blocks->hop[0].n_src_cap);
     }
     // sampling ahead (Section 4.2, Stage 1): a second set of blocks and destination rows filled on a stream of its
     // own while the current batch trains; created by the first call that asks for it

@@ -1316,6 +1316,31 @@ def test_the_last_layers_launch_takes_the_side_tasks_of_batches_prepared_ahead(a
     run_steps(w, 3, use_cache=True, lr=0.02, arch=arch, ahead=True, joined=True)
 
 
+def test_a_last_layer_on_planes_is_what_the_model_says_it_is():
+    """Room for so many seeds that the last product is long enough for planes: it takes a launch of its own, and the model says so; with a little less
+    room it goes with the loss. Bound of the logits' error: as of products on pieces."""
+    b = nb()
+    V = 60_000
+    src, dst = si.random_graph_small(V, 200_000, 3)
+    g = b.no_build_csr(src, dst, V, 32)
+    for cap, planes in ((20_480, True), (20_000, False)):
+        model = b.no_model_create(g, [602, 256, 200], cap, (4, 3))
+        assert b.no_model_forward_planes(model, 1)
+        assert (b.no_model_forward_planes(model, 2), b.no_model_last_layer_joined(model)) == (planes, not planes)
+        for layer, three in enumerate(si.init_weights([602, 256, 200], 3)):
+            for t, a in zip(b.no_model_params(model, layer + 1), three):
+                t.copy_(dev(a))
+        feat, lab = dev(si.features(V, 602, 3, "f32")), dev(si.labels(V, 200, 3))
+        seeds = torch.arange(1500, dtype=torch.int32, device="cuda")
+        st = b.no_train_step(model, g, feat, lab, seeds, None, 0, 1, 0.0)
+        n1 = st.n_src[0]
+        h1, mean2 = b.no_model_activations(model, 1, n1, n1)[0], b.no_model_activations(model, 2, 1500, 1500)[1]
+        w_self, w_neigh, bias = (t.double() for t in b.no_model_params(model, 2))
+        ref = h1[:1500].double() @ w_self + mean2.double() @ w_neigh + bias
+        z = b.no_model_activations(model, 2, 1500, 1500)[0].double()
+        assert float(torch.linalg.norm(z - ref) / torch.linalg.norm(ref)) <= forward_error_bound(2 * 256)
+
+
 @pytest.mark.parametrize("arch,cap,hidden,classes", [("sage", 40, 64, 16), ("sage", 1024, 256, 172), ("gcn", 1024, 256, 64), ("gcn_sum", 200, 100, 255), ("sage", 4096, 256, 47),
                                                      ("gcn", 4096, 252, 41)])
 def test_input_gradients_of_a_joined_last_layer_are_rounded_once(arch, cap, hidden, classes):
