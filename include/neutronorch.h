@@ -311,9 +311,9 @@ int32_t no_model_activations(no_model_t m, int32_t layer, const float** d_h, con
 /* *planes = 1 if the model's steps multiply this layer's forward product on the bf16 matrix cores, every fp32 operand in three exact bf16
  * pieces (six bf16 products per fp32 one), else 0 (the fp32 instruction; bf16 operands in layer 1 on a bf16 table). */
 int32_t no_model_forward_planes(no_model_t m, int32_t layer, int32_t* planes);
-/* *joined = 1 if the model's steps make the last layer, the loss and the gradients of the last layer's inputs in one launch, else 0 (a
- * launch for each). It depends on the layer form, the sizes and the capacity. */
-int32_t no_model_last_layer_joined(no_model_t m, int32_t* joined);
+/* *joined = 1 if the model's steps over n_seeds seeds make the last layer, the loss and the gradients of the last layer's inputs in one launch,
+ * else 0 (launches of their own). It depends on the layer form, the sizes and the capacity. */
+int32_t no_model_last_layer_joined(no_model_t m, int32_t n_seeds, int32_t* joined);
 int32_t no_model_blocks(no_model_t m, no_blocks_t* blocks);   /* blocks of the last step (owned by m) */
 /* Gathered feature rows of the last step: the rows of the bottom hop's destinations [n_dst, F] (the
  * neighbour rows are read from the table by the fused layer-1 aggregation and are not materialised). */

@@ -92,7 +92,7 @@ _SIGNATURES = {
     "no_model_destroy": (_I32, [_P]),
     "no_model_profile": (_I32, [_P, _I32]),
     "no_model_forward_planes": (_I32, [_P, _I32, _P]),
-    "no_model_last_layer_joined": (_I32, [_P, _P]),
+    "no_model_last_layer_joined": (_I32, [_P, _I32, _P]),
     "no_model_stage_ms": (_I32, [_P, _P, _P]),
     "no_stage_name": (C.c_char_p, [_I32]),
     "no_debug_scan_wait": (_I32, [_I32, _I32]),
@@ -545,9 +545,9 @@ def no_model_forward_planes(m: Model, layer: int) -> bool:
     return bool(out.value)
 
 
-def no_model_last_layer_joined(m: Model) -> bool:
+def no_model_last_layer_joined(m: Model, n_seeds: int) -> bool:
     out = C.c_int32()
-    _check(lib().no_model_last_layer_joined(m.h, C.byref(out)))
+    _check(lib().no_model_last_layer_joined(m.h, n_seeds, C.byref(out)))
     return bool(out.value)
 
 

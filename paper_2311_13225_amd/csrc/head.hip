@@ -37,7 +37,7 @@ __device__ __forceinline__ float4 load4_at(const float* base, uint32_t bytes) {
     return load4_fast(reinterpret_cast<const float*>(reinterpret_cast<const char*>(base) + bytes));
 }
 
-constexpr int HEAD_ROWS = 16, HEAD_WAVES = 8, HEAD_THREADS = 64 * HEAD_WAVES;
+constexpr int HEAD_WAVES = 8, HEAD_THREADS = 64 * HEAD_WAVES;
 
 template <int G, typename Side>      // G: 64-column groups of the classes
 __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side side) {

@@ -160,11 +160,22 @@ struct HeadArgs {
     int32_t* bad_label_flag; int32_t flag_value;
     uint32_t row_blocks; int32_t parts;                                  // (set by the launch)
 };
+constexpr int32_t HEAD_ROWS = 16;      // seeds of a block
 // Which last layers take it. Rows are read in units of four columns and stand in LDS, the logits too; the symmetric normalisation
 // has weights of its own for every source.
-inline bool head_takes(int32_t arch, int32_t d, int32_t C, int32_t n_src_cap) {
-    return arch != NO_ARCH_GCN_SYM && d % 4 == 0 && d <= HEAD_MOST_COLUMNS && C >= 4 && C <= HEAD_MOST_CLASSES &&
-           (int64_t)n_src_cap * d * 4 < (1ll << 32);
+// A block's products run at a lower rate than those of the launches it replaces, whose wide ones are on the bf16 matrix cores, and it saves some 13 us
+// of launches and waits once. Up to 64 classes two blocks fit on a compute unit, and it is the faster one at any number of seeds; of more classes one
+// fits, so 256 blocks run at once and the next ones wait for them. Measured, a step of two layers without hidden rows from a cache, 256 columns, us in launches of
+// their own / in one. Two matrices, 47 classes: 4096 seeds 250 / 238, 20 K 710 / 693, 100 K 2165 / 2155; 64 classes: 10 K 427 / 425, 50 K 1399 / 1395; 128
+// classes: 1024 148 / 143, 4096 256 / 250, 4500 273 / 285, 10 K (100 classes) 448 / 455; 172 and 192: 4096 270 / 265 and 268 / 269, 4500 (192) 276 / 307, 10 K 462 / 491.
+// One matrix has half of the products: 128 classes 4096 (129) 232 / 225, 8000 322 / 320, 9000 351 / 356; 172 classes 4096 232 / 223, 5000 256 / 257, 10 K 391 / 402.
+// 256 classes, four whole tiles of the separate product: 256 columns, 512 seeds 137 / 143, 1024 161 / 163, 4096 274 / 282, one matrix 234 / 234; 192 columns
+// 1024 157 / 154, 4096 254 / 260; 128 columns 1024 146 / 140, 4096 219 / 220; against that 240 classes, 256 columns 1024 163 / 160, 4096 272 / 272.
+inline bool head_takes(int32_t arch, int32_t n, int32_t d, int32_t C, int32_t n_src_cap) {
+    if (arch == NO_ARCH_GCN_SYM || d % 4 || d > HEAD_MOST_COLUMNS || C < 4 || C > HEAD_MOST_CLASSES || (int64_t)n_src_cap * d * 4 >= (1ll << 32)) return false;
+    const bool two = !arch_is_gcn(arch);
+    if (two && d > 192 && C > 192 && C % 64 == 0) return false;
+    return C <= 64 || ceil_div(n, HEAD_ROWS) <= (!two && C <= 128 ? 512 : 256);
 }
 int32_t head_forward_backward(const HeadArgs& a, const CutJobs& cut, no_blocks_s* side_of, hipStream_t st);
 int32_t gather_rows(const void* d_table, int32_t row_bytes, int64_t table_stride, const int32_t* d_ids,

@@ -137,8 +137,8 @@ struct no_model_s {
         return work >= least || (l > 0 && planes_of(0)) ? cut_fwd[l] : nullptr;
     }
     // The last layer goes with the loss and its own input gradients (head.hip), unless its product is one on planes: that launch has none.
-    bool last_layer_joined() const {
-        return n_layers >= 2 && !planes_of(n_layers - 1) && no::head_takes(arch, dims[n_layers - 1], dims[n_layers], blocks->hop[0].n_src_cap);
+    bool last_layer_joined(int32_t n_seeds) const {
+        return n_layers >= 2 && !planes_of(n_layers - 1) && no::head_takes(arch, n_seeds, dims[n_layers - 1], dims[n_layers], blocks->hop[0].n_src_cap);
     }
     // sampling ahead (Section 4.2, Stage 1): a second set of blocks and destination rows filled on a stream of its
     // own while the current batch trains; created by the first call that asks for it
@@ -349,10 +349,10 @@ extern "C" int32_t no_model_forward_planes(no_model_t m, int32_t layer, int32_t*
     return NO_OK;
 }
 
-extern "C" int32_t no_model_last_layer_joined(no_model_t m, int32_t* joined) {
+extern "C" int32_t no_model_last_layer_joined(no_model_t m, int32_t n_seeds, int32_t* joined) {
     clear_error();
-    NO_REQUIRE(m && joined, NO_ERR_INVALID_ARG, "no_model_last_layer_joined: bad argument");
-    *joined = m->last_layer_joined() ? 1 : 0;
+    NO_REQUIRE(m && joined && n_seeds >= 1 && n_seeds <= m->n_seeds_cap, NO_ERR_INVALID_ARG, "no_model_last_layer_joined: bad argument");
+    *joined = m->last_layer_joined(n_seeds) ? 1 : 0;
     return NO_OK;
 }
 
@@ -591,7 +591,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
 
     // forward
     const int32_t C = m->dims[L];
-    const bool head = m->last_layer_joined();
+    const bool head = m->last_layer_joined(n_seeds);
     no_block_view view[NO_MAX_LAYERS];
     for (int32_t h = 0; h < L; ++h) fill_block_view(B, h, &view[h]);
     for (int32_t l = 1; l <= L; ++l) {

@@ -996,7 +996,7 @@ def run_steps(w, n_steps, use_cache, lr=0.05, V=None, E=None, hot_fraction=None,
     rtol = RTOL_BF16 if bf16_products else RTOL
     if gcn:
         b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
-    assert joined is None or b.no_model_last_layer_joined(model) == joined
+    assert joined is None or b.no_model_last_layer_joined(model, w.batch) == joined
     for l in range(w.n_layers):
         for t, a in zip(b.no_model_params(model, l + 1), weights[l]):
             t.copy_(dev(a))
@@ -1296,8 +1296,21 @@ JOINED_LAST_LAYERS = [
     ("sage", 1, (10, 5), 64, 16), ("sage", 15, (64, 2), 4, 4), ("gcn", 16, (17, 3), 8, 5), ("sage", 17, (3, 16, 2), 12, 15),    # a block's rows, short rows of few units
     ("sage", 300, (33, 3), 256, 64), ("gcn_sum", 33, (9, 3), 60, 65), ("gcn", 129, (15, 3), 128, 17), ("sage", 100, (1, 2), 252, 47),    # column groups and 16s of classes
     ("sage", 257, (7, 3), 100, 128), ("gcn", 260, (7, 3), 256, 129), ("sage", 65, (8, 4), 200, 192), ("sage", 65, (8, 4), 132, 193), ("gcn_sum", 40, (25, 3), 256, 256),
-    ("sage", 4100, (4, 2), 64, 20)]                                                                                   # more row blocks than compute units
-SEPARATE_LAST_LAYERS = [("sage", 40, (8, 4), 260, 20), ("sage", 40, (8, 4), 66, 20), ("gcn", 40, (8, 4), 64, 3), ("sage", 40, (8, 4), 64, 257), ("gcn_sym", 40, (8, 4), 64, 20)]
+    ("sage", 4100, (4, 2), 64, 20), ("sage", 4096, (4, 2), 64, 65), ("sage", 40, (8, 4), 192, 256), ("gcn", 4097, (4, 2), 64, 65)]      # about as many row blocks as fit at once; whole tiles
+SEPARATE_LAST_LAYERS = [("sage", 40, (8, 4), 260, 20), ("sage", 40, (8, 4), 66, 20), ("gcn", 40, (8, 4), 64, 3), ("sage", 40, (8, 4), 64, 257), ("gcn_sym", 40, (8, 4), 64, 20),
+                        ("sage", 4097, (4, 2), 64, 65), ("sage", 40, (8, 4), 196, 256)]      # more row blocks than fit at once; whole tiles of a wide layer
+
+
+def test_the_line_of_the_joined_last_layer_goes_by_the_seeds_of_a_step():
+    b = nb()
+    src = np.zeros(0, np.int32)
+    g = b.no_build_csr(src, src, 20_000, 32)
+    for arch, classes, most in (("sage", 64, 9000), ("sage", 65, 4096), ("sage", 192, 4096), ("gcn", 128, 8192), ("gcn_sum", 129, 4096), ("gcn", 256, 4096)):
+        model = b.no_model_create(g, [8, 256, classes], 9000, (4, 2))
+        if arch != "sage":
+            b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
+        assert b.no_model_last_layer_joined(model, most) and b.no_model_last_layer_joined(model, 1)
+        assert most == 9000 or not b.no_model_last_layer_joined(model, most + 1)
 
 
 @pytest.mark.parametrize("arch,batch,fanouts,hidden,classes,joined", [c + (True,) for c in JOINED_LAST_LAYERS] + [c + (False,) for c in SEPARATE_LAST_LAYERS])
@@ -1326,7 +1339,7 @@ def test_a_last_layer_on_planes_is_what_the_model_says_it_is():
     for cap, planes in ((20_480, True), (20_000, False)):
         model = b.no_model_create(g, [602, 256, 200], cap, (4, 3))
         assert b.no_model_forward_planes(model, 1)
-        assert (b.no_model_forward_planes(model, 2), b.no_model_last_layer_joined(model)) == (planes, not planes)
+        assert (b.no_model_forward_planes(model, 2), b.no_model_last_layer_joined(model, 1500)) == (planes, not planes)
         for layer, three in enumerate(si.init_weights([602, 256, 200], 3)):
             for t, a in zip(b.no_model_params(model, layer + 1), three):
                 t.copy_(dev(a))
@@ -1352,7 +1365,7 @@ def test_input_gradients_of_a_joined_last_layer_are_rounded_once(arch, cap, hidd
     model = b.no_model_create(g, [8, hidden, classes], cap, (3, 2))
     if arch != "sage":
         b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
-    assert b.no_model_last_layer_joined(model)
+    assert b.no_model_last_layer_joined(model, 1)
     rng = np.random.default_rng(classes)
     feat, seed = torch.ones((5000, 8), device="cuda"), dev(np.array([17], np.int32))
     for t, v in zip(b.no_model_params(model, 1), (0.0, 0.0, 1.0)):
@@ -1388,7 +1401,7 @@ def test_infinities_and_nan_stay_where_they_arise_in_a_step(arch, cap, F, hidden
         model = b.no_model_create(g, [F, hidden, classes], cap, (10, 3), b.NO_BF16 if bf16 else b.NO_F32)
         if gcn:
             b.no_model_set_arch(model, b.ARCH_OF_NAME[arch])
-        assert b.no_model_forward_planes(model, 1) == planes and b.no_model_last_layer_joined(model) == (hidden in (64, 252, 256))
+        assert b.no_model_forward_planes(model, 1) == planes and b.no_model_last_layer_joined(model, n) == (hidden in (64, 252, 256))
         weights = si.init_weights([F, hidden, classes], 5)
         for layer in (1, 2):
             weights[layer - 1][2][:] = rng.standard_normal(weights[layer - 1][2].shape) * 0.1
