@@ -50,6 +50,8 @@ struct GemmTNArgs {
 };
 
 constexpr int32_t TN_FEWEST_ROWS = 64;
+// Places of a chip for blocks of large tiles, two a compute unit, and the fewest rows of a slice that is cut to fill them (tn_plan).
+constexpr int TN_SLOTS = 512, TN_LEAST_ROWS = 128;
 
 // The number of row slices a split product over R rows really uses: the capacity-sized bound `splits`, cut down so that a
 // slice keeps about rows_per_split rows, but few_splits of them where those keep TN_FEWEST_ROWS each (a function of R and the shape alone, so
@@ -168,6 +170,7 @@ struct ReduceArgs {
 struct GradJobs {
     GemmTNArgs tn[NO_MAX_LAYERS]; ReduceArgs red[NO_MAX_LAYERS];
     int32_t n = 0;
+    bool reuses_rows = false;      // the step takes rows from a cache
 };
 
 // ev0 / ev1 (optional): events that take the product kernel's own start and end times

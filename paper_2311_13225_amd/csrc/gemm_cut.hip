@@ -357,7 +357,12 @@ struct ColumnUnit {
 // The jobs of one launch (by value in the kernel arguments): job j owns the linear block ids [end_block[j-1], end_block[j]).
 struct CutTNLaunch { GemmTNArgs job[NO_MAX_LAYERS]; uint32_t end_block[NO_MAX_LAYERS]; int32_t n; };
 
-constexpr uint32_t TN_LARGE_BLOCKS = 160;      // a job with fewer large-tile blocks takes small tiles
+// A job takes the larger tiles (fewer cuts per product) where they make blocks with products for most compute units, a function of the
+// batch's row count (backward pass of a layer, us, in large tiles / in small ones: 56 blocks, 3.4 K rows, 128 x 256: 47 / 39; 80 blocks, 5 K
+// rows, 128 x 256: 50 / 42; 112 blocks, 3.4 K rows, 256 x 256: 52 / 45; 128 blocks, 8 K rows: 128 x 256 57 / 55, 256 x 128 61 / 63; 160 blocks:
+// 5 K rows, 256 x 256 60 / 61, 10 K rows, 128 x 256 69 / 63; 256 blocks, 16 K rows: 85 / 86; 8 K rows, 256 x 256: 78 / 82), unless it is narrow (60 K
+// rows: 256 x 2 192 / 164; 256 x 16 152 / 143; 3 x 256 121 / 84); its share of the grid is sized for either.
+constexpr uint32_t TN_LARGE_BLOCKS = 160;
 constexpr int tn_shared_bytes(int T) { return 6 * T * SPITCH * 2 > T * (T + 4) * 4 ? 6 * T * SPITCH * 2 : T * (T + 4) * 4; }
 
 // Block `id` of a job: a T x T tile of one product over one slice; 2 x 2 wavefronts. Half of the threads bring a tile of A, the
@@ -609,18 +614,11 @@ static __host__ __device__ inline uint32_t tn_tiles(const GemmTNArgs& g, int T) 
 // A product with a side this short fills a quarter of a larger tile and is cut no less often in small ones.
 static __host__ __device__ inline bool tn_narrow(const GemmTNArgs& g) { return g.N <= 32 || g.Kp <= 32; }
 
-// A job takes the larger tiles (fewer cuts per product) where they make blocks with products for most compute units, a function of the
-// batch's row count (backward pass of a layer, us, in large tiles / in small ones: 56 blocks, 3.4 K rows, 128 x 256: 47 / 39; 80 blocks, 5 K
-// rows, 128 x 256: 50 / 42; 112 blocks, 3.4 K rows, 256 x 256: 52 / 45; 128 blocks, 8 K rows: 128 x 256 57 / 55, 256 x 128 61 / 63; 160 blocks:
-// 5 K rows, 256 x 256 60 / 61, 10 K rows, 128 x 256 69 / 63; 256 blocks, 16 K rows: 85 / 86; 8 K rows, 256 x 256: 78 / 82), unless it is narrow (60 K
-// rows: 256 x 2 192 / 164; 256 x 16 152 / 143; 3 x 256 121 / 84); its share of the grid is sized for either.
-
 // The slices of a job in large tiles on fp32 operands. A block alone on a compute unit takes 2.2 us a step of 32 rows, two together 2.6, so that the
 // jobs of a launch are cut, all into slices of as many rows, to fill TN_SLOTS places once: with 256 rows a slice some units had two blocks
 // and others one (sums over 90 K rows, 2 x 256 x 256, 320 blocks: 182 us; 504: 151; 13 K rows, 320: 38.6, 472: 32.0; 10 K rows, 2 x 602 x 256,
 // 400: 54.8; 500: 48.9; 25 K rows, 2 x 100 x 256, 256: 35.9; 448: 31.9). Blocks in small tiles and on bf16 operands are short: four of them count as one.
 // (A function of the row counts and shapes alone, so the order of the sums is the same in every run.)
-constexpr int TN_SLOTS = 512, TN_LEAST_ROWS = 128;
 __device__ __forceinline__ int tn_rows(const GemmTNArgs& g) { return min(*g.d_R, g.R_cap); }
 __device__ __forceinline__ int tn_plain_slices(const GemmTNArgs& g, int R) { return tn_used_splits(R, g.plain_splits, g.rows_per_split, g.few_splits); }
 __device__ __forceinline__ int tn_plan(const CutTNLaunch& launch, int job, int R, bool* large) {

@@ -597,12 +597,13 @@ int32_t layer_splits(int32_t n_dst_cap, int32_t d_in, int32_t d_out) {
 
 static inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// in_step: a step's workspace is its model's own, with room for as many slices as fill the chip with large tiles (tn_plan).
+// in_step: a step's workspace is its model's own, with room for as many slices as fill the chip with large tiles (tn_plan). It is laid out for two
+// products; one alone (GCN-style layers) takes both halves: step_splits.
 LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_t d_out, bool in_step) {
     LayerWorkspace w;
     w.splits = layer_splits(n_dst_cap, d_in, d_out);
     if (in_step) {
-        const int64_t fill = 512 / (2 * ceil_div(d_in, 128) * ceil_div(d_out, 128)), by_rows = ceil_div(n_dst_cap, 128);
+        const int64_t fill = TN_SLOTS / (2 * ceil_div(d_in, 128) * ceil_div(d_out, 128)), by_rows = ceil_div(n_dst_cap, TN_LEAST_ROWS);
         w.splits = (int32_t)std::max<int64_t>(w.splits, std::min<int64_t>(std::min(fill, by_rows), 128));
     }
     size_t off = 0;
@@ -617,6 +618,13 @@ LayerWorkspace carve_workspace(void* ws, int32_t n_dst_cap, int32_t d_in, int32_
     w.bytes = off;
     return w;
 }
+
+// The most slices of a step's weight gradients. One product alone takes both halves of the partials' room (less one slice, in whose place the word of
+// tn_used_word stands), unless the step reuses rows: the next batch's aggregation then waits for this one's layer 1 and runs beside the weight
+// gradients, in the places that a block a compute unit leaves. Measured, GCN-style steps prepared ahead, 602 x 256, us in one half / in both: 1024 seeds without
+// reuse 175.4 / 170.2, 2048 255.7 / 248.8, 4096 386.6 / 375.4, 25 K rows of a uniform graph 341 / 315 (the product alone 70.5 / 57.1); with reuse 147.6 / 151.4,
+// 197.5 / 203.6, 327.3 / 320.7.
+static int32_t step_splits(const LayerWorkspace& w, int32_t n_problems, bool reuses_rows) { return n_problems == 1 && !reuses_rows ? 2 * w.splits - 1 : w.splits; }
 
 // ------------------------------------------------------------------------ layer forward / backward
 
@@ -780,7 +788,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     if (gcn) { t.A[0] = mean; t.n_problems = 1; }
     t.G = gz; t.ldg = d_out;
     t.P = w.partials; t.Kp = d_in; t.N = d_out;
-    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = w.splits; t.plain_splits = layer_splits(n_cap, d_in, d_out);
+    t.d_R = blk.d_n_dst; t.R_cap = n_cap; t.splits = pending ? step_splits(w, t.n_problems, pending->reuses_rows) : w.splits; t.plain_splits = layer_splits(n_cap, d_in, d_out);
     t.small_up_to = pending ? 0 : n_cap;      // (a step's batch fills 15 to 45 % of the capacity; a caller's block is its own size)
     // Batches that fill a fraction of the capacity use fewer slices than the capacity-sized bound: a slice keeps at least
     // this many rows. Measured on a batch of 24 K rows (bound: 64 slices): the product takes the same time from 64 down
@@ -790,7 +798,7 @@ int32_t sage_backward(const no_block_view& blk, const void* x_src, no_dtype dt, 
     // 100 x 47: 25.5 -> 20.1, 128 x 256: 26.1 -> 24.0; 2 K rows, 64 x 64: 24.0 -> 20.4; 5 K rows: 28.9 -> 26.3).
     t.rows_per_split = 256;
     t.few_splits = (int32_t)(256 / (ceil_div(d_in, 64) * ceil_div(d_out, 64) * t.n_problems));
-    ReduceArgs r{w.partials, w.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
+    ReduceArgs r{w.partials, t.splits, d_in, d_out, gw_self, gw_neigh, gbias, lr, w_self_rw, w_neigh_rw, bias_rw, gcn ? 1 : 2};
     if (bf) { r.wt_self = bf->wt_self; r.wt_neigh = bf->wt_neigh; r.Kpad = bf->Kpad; }
     // In a layer call the weight gradients may go with the launch of the input gradient, unless the weights' planes stand where the partials
     // go or the fp32 rows are still to be made.

@@ -699,6 +699,7 @@ static int32_t train_step_impl(no_model_t m, no_graph_t g, const void* d_feature
     // their products and reductions are carried by the bottom layer's two launches, which end the step, instead of
     // adding two launches per layer to the chain of dependent kernels.
     GradJobs pending;
+    pending.reuses_rows = used_cache;
     for (int32_t l = L; l >= 1; --l) {
         const no_block_view& blk = view[L - l];
         const int32_t d_in = m->dims[l - 1], d_out = m->dims[l];
