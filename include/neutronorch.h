@@ -341,11 +341,11 @@ int32_t no_train_step(no_model_t m, no_graph_t g, const void* d_features, const 
  * training so that the two do not wait for each other). Results of the step are those of no_train_step. In
  * addition, if d_next_seeds != NULL, batch step + 1 (d_next_seeds[n_next_seeds], same seed) is prepared on the
  * model's own sampling stream (default priority) beside this step: it is sampled into a second set of blocks from
- * the step's start, and after this step's layer 1 its layer-1 aggregation runs into a second buffer (mean
- * aggregator with two or more layers), together with the copy of its reused rows out of the cache. The next call
- * uses that batch if it asks for exactly it (step + 1, the same d_next_seeds pointer and count, seed, cache and
- * d_features); otherwise it is dropped and the batch is sampled again. d_next_seeds and d_features must stay valid
- * and unchanged until then.
+ * the step's start, and its layer-1 aggregation (every layer form, models of two or more layers) runs into a second
+ * buffer, with a cache after this step's layer 1 and together with the copy of its reused rows out of the cache. The
+ * next call uses that batch if it asks for exactly it (step + 1, the same d_next_seeds pointer and count, seed, cache,
+ * d_features and layer form); otherwise it is dropped and the batch is sampled again. d_next_seeds and d_features must
+ * stay valid and unchanged until then.
  * Cache versions: the split of a batch into reused and computed vertices writes the batch's step into the version
  * of every slot the batch will recompute (the row follows when its layer 1 runs), so while a batch is prepared
  * ahead those entries of no_cache_view already read step + 1; a dropped batch's entries are restored by the call
@@ -383,16 +383,19 @@ int32_t no_model_destroy(no_model_t m);
  * Stages that are a single kernel launch: NO_STAGE_GATHER, NO_STAGE_AGG_L1, NO_STAGE_GEMM_FWD_L1,
  * NO_STAGE_GEMM_DW_L1 (which carries the upper layers' products), NO_STAGE_SAMPLE_ROWS_BOTTOM. While enabled, the side tasks
  * of the sampling (local indices, transposes, id-map wipe), which otherwise ride on later launches, are finished before the
- * end of NO_STAGE_SAMPLE, so that stage is all of the sampling work of the step. NO_STAGE_GEMM_FWD_L1 also counts the launch that
- * cuts a step's weights for its large forward products, the upper layers' among them. */
+ * end of NO_STAGE_SAMPLE, so that stage is all of the sampling work of the step. The weights of large forward products are cut by extra blocks
+ * of the layer's aggregation and count with it (NO_STAGE_AGG_L1, NO_STAGE_FWD_UPPER), but layer 1's of a batch whose aggregation was made ahead by a
+ * launch that counts with NO_STAGE_GEMM_FWD_L1. Where the last layer goes with the loss (no_model_last_layer_joined), NO_STAGE_LOSS holds its
+ * forward pass and the products of its input gradients as well, NO_STAGE_FWD_UPPER ends with the layer below it (a model of two layers: nothing) and
+ * NO_STAGE_BWD_UPPER begins with its transposed sum. */
 enum {
     NO_STAGE_SAMPLE = 0,      /* all hops: sampling, relabel, hot lookup, local indices, transposes */
     NO_STAGE_GATHER = 1,      /* feature rows of the bottom hop's sources */
     NO_STAGE_AGG_L1 = 2,      /* layer-1 mean aggregation kernel */
     NO_STAGE_GEMM_FWD_L1 = 3, /* layer-1 dense update kernel */
-    NO_STAGE_FWD_UPPER = 4,   /* cache row assembly and refresh + layers 2..L forward */
-    NO_STAGE_LOSS = 5,
-    NO_STAGE_BWD_UPPER = 6,   /* layers L..2 backward */
+    NO_STAGE_FWD_UPPER = 4,   /* layers 2..L forward (2..L-1 where the last is joined with the loss) */
+    NO_STAGE_LOSS = 5,        /* loss and its gradient; a joined last layer */
+    NO_STAGE_BWD_UPPER = 6,   /* layers L..2 backward, the input gradients' products and transposed sums */
     NO_STAGE_BWD_L1_PREP = 7, /* gradient row selection, ReLU mask */
     NO_STAGE_GEMM_DW_L1 = 8,  /* layer-1 weight-gradient kernel (split partial products) */
     NO_STAGE_BWD_L1_REDUCE = 9,

@@ -96,10 +96,13 @@ int32_t cut_weights(const float* w0, const float* w1, int32_t K, int32_t N, bool
 inline bool input_grad_takes_planes(int32_t M_cap, int32_t K, int32_t N, int32_t n_problems) {
     return ceil_div(M_cap, 64) * ceil_div(N, 64) * n_problems > 128 && K >= 8;
 }
-// Whether a forward product of about `rows` rows in a step or a bulk refresh does: from where it wins by enough to show in a step. Measured, two
+// Whether a forward product of about `rows` rows in a step or a bulk refresh does. The line lies where a launch of its own for the weights paid, as that of
+// layer 1 in a batch prepared ahead still has; the others' weights go with the aggregation now and would pay earlier (layer_takes_planes). It stays
+// there because a product's last bits turn ReLU decisions that are zero to within rounding: the step of the sparse graph, batch 1024, takes 307 us
+// with both hidden layers on planes and 317 without, but after 12 steps its parameters are off by 0.8 % from those it had. Measured, two
 // products / one, with a launch for the weights, us on the fp32 instruction / on planes: 256 columns, 9 K rows, K = 128 65.2 / 66.9; 20 K rows, K = 64 74.5 / 75.1, 100
 // 89.8 / 88.2; 90 K rows, K = 47 266 / 248; one product, 12 K rows, K = 256 32 / 37, 602 60.3 / 59.9; 20 K rows, K = 100 30.3 / 31.2, 256 44.9 / 43.3; 90 K rows, 172 columns,
-// K = 32 41 / 47, 200 117 / 109. (The step of the sparse graph, batch 1024, 307 us with both hidden layers on planes, 310 without.)
+// K = 32 41 / 47, 200 117 / 109.
 inline bool forward_takes_planes(int64_t rows, int32_t K, int32_t N, int32_t n_problems) {
     const int64_t tiles = ceil_div(rows, 64) * ceil_div(N, 64);
     if (K < 8 || N == 64 || tiles < 512 || tiles * (K + 50) < 150000) return false;

@@ -42,6 +42,7 @@ constexpr int HEAD_WAVES = 8, HEAD_THREADS = 64 * HEAD_WAVES;
 template <int G, typename Side>      // G: 64-column groups of the classes
 __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side side) {
     if (blockIdx.x >= side.first_block) {
+        // (the tasks' barriers wait for the wavefronts that have not ended: the other half of the block has no part in them)
         if (threadIdx.x < SIDE_THREADS) run_side_tasks(side);
         return;
     }

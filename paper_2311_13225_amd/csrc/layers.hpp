@@ -163,14 +163,15 @@ struct HeadArgs {
 constexpr int32_t HEAD_ROWS = 16;      // seeds of a block
 // Which last layers take it. Rows are read in units of four columns and stand in LDS, the logits too; the symmetric normalisation
 // has weights of its own for every source.
-// A block's products run at a lower rate than those of the launches it replaces, whose wide ones are on the bf16 matrix cores, and it saves some 13 us
-// of launches and waits once. Up to 64 classes two blocks fit on a compute unit, and it is the faster one at any number of seeds; of more classes one
-// fits, so 256 blocks run at once and the next ones wait for them. Measured, a step of two layers without hidden rows from a cache, 256 columns, us in launches of
-// their own / in one. Two matrices, 47 classes: 4096 seeds 250 / 238, 20 K 710 / 693, 100 K 2165 / 2155; 64 classes: 10 K 427 / 425, 50 K 1399 / 1395; 128
-// classes: 1024 148 / 143, 4096 256 / 250, 4500 273 / 285, 10 K (100 classes) 448 / 455; 172 and 192: 4096 270 / 265 and 268 / 269, 4500 (192) 276 / 307, 10 K 462 / 491.
-// One matrix has half of the products: 128 classes 4096 (129) 232 / 225, 8000 322 / 320, 9000 351 / 356; 172 classes 4096 232 / 223, 5000 256 / 257, 10 K 391 / 402.
-// 256 classes, four whole tiles of the separate product: 256 columns, 512 seeds 137 / 143, 1024 161 / 163, 4096 274 / 282, one matrix 234 / 234; 192 columns
-// 1024 157 / 154, 4096 254 / 260; 128 columns 1024 146 / 140, 4096 219 / 220; against that 240 classes, 256 columns 1024 163 / 160, 4096 272 / 272.
+// A block's products run at a lower rate than those of the launches it replaces, whose wide ones are on the bf16 matrix cores, and it saves some 12 us
+// of launches and waits once. Up to 64 classes two blocks fit on a compute unit, and it is the faster one, or as fast, at any number of seeds; of more classes
+// one fits, so 256 blocks run at once and the next ones wait for them. Measured, steps of two layers sampled in the call, without reuse, 256 columns, us in launches
+// of their own / in one. Two matrices, 47 classes: 1024 seeds 106 / 95, 4096 204 / 192, 20 K 670 / 654; 64 classes: 4096 204 / 194, 20 K 663 / 662, 50 K 1339 /
+// 1348; 128 classes: 1024 108 / 103, 4096 213 / 209, 4500 233 / 245; 172 and 192: 1024 115 / 111 and 114 / 112, 4096 226 / 220 and 220 / 222, 4500 (192) 237 / 266.
+// One matrix has half of the products: 172 classes 4096 191 / 180, 5000 212 / 217; 256 classes 4096 191 / 188; 128 classes 6000 226 / 227, 8000 277 / 277, 9000 311 /
+// 316; 80 classes 8000 277 / 270.
+// 256 classes, four whole tiles of the separate product: 256 columns, 256 seeds 81 / 86, 1024 117 / 118, 4096 226 / 232; 192 columns 1024 111 / 107, 4096 207 / 210;
+// 128 columns 2048 125 / 122, 4096 176 / 176; against that 240 classes, 256 columns 1024 117 / 116, 2048 156 / 157.
 inline bool head_takes(int32_t arch, int32_t n, int32_t d, int32_t C, int32_t n_src_cap) {
     if (arch == NO_ARCH_GCN_SYM || d % 4 || d > HEAD_MOST_COLUMNS || C < 4 || C > HEAD_MOST_CLASSES || (int64_t)n_src_cap * d * 4 >= (1ll << 32)) return false;
     const bool two = !arch_is_gcn(arch);

@@ -99,7 +99,7 @@ struct no_model_s {
     // they may not match them: weights_dirty, raised by no_model_params, through which a caller writes, and by a change of form)
     no::DevBuf<uint16_t> wt1;
     int32_t wt1_kpad = 0;
-    // the matrices cut for the large forward products, at the start of every step, and those of the layers above layer 1 for their input
+    // the matrices cut for the large forward products, in every step beside the aggregation before them, and those of the layers above layer 1 for their input
     // gradients, by extra blocks of the loss launch (cut_weights): made again in every step, so that no copy of them outlives one
     no::DevBuf<uint16_t> planes;
     uint16_t* cut_fwd[NO_MAX_LAYERS][2] = {{nullptr}};      // (NULL: no large product, in any form of the layer)
@@ -123,7 +123,8 @@ struct no_model_s {
     // Where the steps cut layer l + 1's matrices for its forward product (NULL: they do not). Beside that layer's aggregation; layer 1's of a batch
     // prepared ahead by a launch on the step's path, and sparse batches fill less of their room the larger they are, so the product has to be a
     // long one; one of a column count that is no
-    // multiple of 64, which the fp32 instruction reads one by one, need not be as long. Once layer 1's is cut, the upper layers' ride with it.
+    // multiple of 64, which the fp32 instruction reads one by one, need not be as long. Where layer 1's is long enough the upper layers' that
+    // forward_takes_planes are taken too; without it they stay on the fp32 instruction, for the reason given there.
     // Measured, us a step without / with planes. 800 K vertices, three hops, batches of 400, 1000, 2000 and 4096: 100 features, 256 columns 169 / 175,
     // 242 / 244, 350 / 352, 514 / 499; 200 columns 169 / 174, 244 / 239, 347 / 336; 256 features, 128 columns 161 / 166, 216 / 219, 300 / 291; 32
     // features, 128 columns, 1000 154 / 165. 233 K vertices, two hops, batches of 1500 and 3000: 602 features, 256 columns 233 / 227, 347 / 307; 300
