@@ -6,17 +6,17 @@
 // that nothing but weights and rows comes from memory: mean and own rows, then the logits, then their gradients stand in LDS. The
 // weights are asked for ahead of the rows, which are two dependent reads away.
 // Measured on the training stream, four launches -> this, us: 1024 seeds, 2 x 256 columns, 47 classes, 9 neighbours 26 -> 14; 41 classes, 22
-// neighbours, beside the next batch's sampling 33 -> 19; 172 classes 37 -> 25; 4096 seeds 73 -> 32; 256 seeds, 2 x 64 columns, 16 classes 20 -> 10.
+// neighbours, beside the next batch's sampling 33 -> 19; 172 classes 37 -> 25; 4096 seeds 73 -> 32; 256 seeds, 2 x 64 columns, 16 classes 20 -> 10. (With the
+// gradients of the rows on the fp32 instruction; in 64 bits 0.4 us more with 47 classes, 1.1 of 4096 seeds, 2.2 with 172 classes, 5.8 of 4096 seeds.)
 //
 // The logits' product on the fp32 instruction (v_mfma_f32_16x16x4_f32), the reduction dealt to the wavefronts and their parts added in pairs: relative 2-norm
 // error against 64 bits 1.2e-7 at 2 x 256 terms, as that of the launches before it or less (1.2e-7 in small blocks, 2.1e-7 in tiles). The gradients of the
 // rows in 64 bits (v_mfma_f64_16x16x4_f64, half that rate): with the chain of the fp32 instruction they were off by 0.9e-7 at 47 classes and 1.7e-7 at 172, where
-// products on pieces are by 0.6e-7 and 1.0e-7; now by their last rounding, 0.25e-7, for 1 to 3 us of a step (4096 seeds, 47 classes
-// 652.8 -> 654.9; 1024, 172 classes 221.9 -> 223.3; 1024, 41 classes, one matrix 149.0 -> 149.6).
+// products on pieces are by 0.6e-7 and 1.0e-7; now by their last rounding, 0.25e-7.
 //
 // Operands straight from LDS (rows) and L2 (weights). Bound by round trips (launched
-// alone, 47 classes: rows 6.6 of 12.7 us, product 2.8, gradients of the rows 2.1), with 172 classes by the 64 compute units that 1024 seeds fill (product 8 of
-// 19.4 us, 5.1 of them at the instruction's rate). Eight wavefronts, two rows each:
+// alone, 47 classes: rows 6.6 of 13.1 us, product 2.8, gradients of the rows 2.5), with 172 classes by the 64 compute units that 1024 seeds fill (product 8 of
+// 21.6 us, 5.1 of them at the instruction's rate). Eight wavefronts, two rows each:
 // with four, whose rows queue up, the 41 classes took 27 us, and instructions are fetched faster than used only in short code: unrolled
 // loads with 64-bit addresses and guards (16 KB) cost another 2 us.
 #include "gemm_tile.hpp"
