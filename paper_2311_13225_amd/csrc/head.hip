@@ -7,16 +7,17 @@
 // weights are asked for ahead of the rows, which are two dependent reads away.
 // Measured on the training stream, four launches -> this, us: 1024 seeds, 2 x 256 columns, 47 classes, 9 neighbours 26 -> 14; 41 classes, 22
 // neighbours, beside the next batch's sampling 33 -> 19; 172 classes 37 -> 25; 4096 seeds 73 -> 32; 256 seeds, 2 x 64 columns, 16 classes 20 -> 10. (With the
-// gradients of the rows on the fp32 instruction; in 64 bits 0.4 us more with 47 classes, 1.1 of 4096 seeds, 2.2 with 172 classes, 5.8 of 4096 seeds.)
+// gradients of the rows in one chain of the fp32 instruction; as they are now up to 1.1 us more up to 64 classes, 0.5 to 1.5 above.)
 //
 // The logits' product on the fp32 instruction (v_mfma_f32_16x16x4_f32), the reduction dealt to the wavefronts and their parts added in pairs: relative 2-norm
 // error against 64 bits 1.2e-7 at 2 x 256 terms, as that of the launches before it or less (1.2e-7 in small blocks, 2.1e-7 in tiles). The gradients of the
-// rows in 64 bits (v_mfma_f64_16x16x4_f64, half that rate): with the chain of the fp32 instruction they were off by 0.9e-7 at 47 classes and 1.7e-7 at 172, where
-// products on pieces are by 0.6e-7 and 1.0e-7; now by their last rounding, 0.25e-7.
+// rows in 64 bits up to 64 classes (v_mfma_f64_16x16x4_f64, half that rate); of more, where that would cost 2 to 6 us, in runs of 8 terms, or of 16 from 129 classes on, of
+// the fp32 instruction, which are added up in 64 bits beside it. Their errors, the launches before this / one chain / this, 1e-7, 256 columns, 4096 seeds: 41 classes
+// 0.57 / 0.93 / 0.25, 64 0.64 / 1.07 / 0.25, 65 0.64 / - / 0.59, 128 0.88 / - / 0.58, 129 0.87 / - / 0.81, 172 1.00 / 1.69 / 0.76, 240 1.09 / - / 0.75; 1024 seeds 0.96 to 1.17 before.
 //
 // Operands straight from LDS (rows) and L2 (weights). Bound by round trips (launched
 // alone, 47 classes: rows 6.6 of 13.1 us, product 2.8, gradients of the rows 2.5), with 172 classes by the 64 compute units that 1024 seeds fill (product 8 of
-// 21.6 us, 5.1 of them at the instruction's rate). Eight wavefronts, two rows each:
+// 20 us, 5.1 of them at the instruction's rate). Eight wavefronts, two rows each:
 // with four, whose rows queue up, the 41 classes took 27 us, and instructions are fetched faster than used only in short code: unrolled
 // loads with 64-bit addresses and guards (16 KB) cost another 2 us.
 #include "gemm_tile.hpp"
@@ -277,15 +278,27 @@ __global__ void __launch_bounds__(HEAD_THREADS) head_kernel(HeadArgs g, Side sid
                     }
                 }
                 const float zs[4] = {z.x, z.y, z.z, z.w};
+                if constexpr (G == 1) {
 #pragma unroll
-                for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f64_16x16x4f64((double)zs[e], (double)v[e], sum, 0, 0, 0);
+                    for (int e = 0; e < 4; ++e) sum = __builtin_amdgcn_mfma_f64_16x16x4f64((double)zs[e], (double)v[e], sum, 0, 0, 0);
+                } else {
+                    constexpr int RUN = G == 2 ? 2 : 4;      // (four terms each)
+#pragma unroll
+                    for (int e = 0; e < 4; e += RUN) {
+                        floatx4 run{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                        for (int i = e; i < e + RUN; ++i) run = __builtin_amdgcn_mfma_f32_16x16x4f32(zs[i], v[i], run, 0, 0, 0);
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) sum[r] += (double)run[r];
+                    }
+                }
             }
         }
         const int i = (second ? t - per : t) * 16 + l16;
         if (i >= d) continue;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-            const int lr = 4 * r + quad;      // (element r of a lane of this instruction: row 4 r + quad)
+            const int lr = G == 1 ? 4 * r + quad : 4 * quad + r;      // (element r of a lane: the 64-bit instruction's row 4 r + quad, the fp32 one's 4 quad + r)
             if (m0 + lr >= n) continue;
             const int len = len_sh[lr];
             const float s = two ? (second ? (len > 0 ? 1.f / (float)len : 0.f) : 1.f) : g.agg_mode == AGG_SELF_MEAN ? 1.f / (float)(len + 1) : 1.f;

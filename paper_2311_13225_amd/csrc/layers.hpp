@@ -166,12 +166,12 @@ constexpr int32_t HEAD_ROWS = 16;      // seeds of a block
 // A block's products run at a lower rate than those of the launches it replaces, whose wide ones are on the bf16 matrix cores, and it saves some 12 us
 // of launches and waits once. Up to 64 classes two blocks fit on a compute unit, and it is the faster one, or as fast, at any number of seeds; of more classes
 // one fits, so 256 blocks run at once and the next ones wait for them. Measured, steps of two layers sampled in the call, without reuse, 256 columns, us in launches
-// of their own / in one. Two matrices, 47 classes: 1024 seeds 106 / 95, 4096 204 / 192, 20 K 670 / 654; 64 classes: 4096 204 / 194, 20 K 663 / 662, 50 K 1339 /
-// 1348; 128 classes: 1024 108 / 103, 4096 213 / 209, 4500 233 / 245; 172 and 192: 1024 115 / 111 and 114 / 112, 4096 226 / 220 and 220 / 222, 4500 (192) 237 / 266.
-// One matrix has half of the products: 172 classes 4096 191 / 180, 5000 212 / 217; 256 classes 4096 191 / 188; 128 classes 6000 226 / 227, 8000 277 / 277, 9000 311 /
-// 316; 80 classes 8000 277 / 270.
-// 256 classes, four whole tiles of the separate product: 256 columns, 256 seeds 81 / 86, 1024 117 / 118, 4096 226 / 232; 192 columns 1024 111 / 107, 4096 207 / 210;
-// 128 columns 2048 125 / 122, 4096 176 / 176; against that 240 classes, 256 columns 1024 117 / 116, 2048 156 / 157.
+// of their own / in one. Two matrices, 47 classes: 1024 seeds 107 / 95, 4096 204 / 193, 20 K 670 / 655; 64 classes: 4096 203 / 194, 20 K 663 / 661, 50 K 1337 /
+// 1349; 128 classes: 1024 109 / 103, 4096 215 / 206, 4500 231 / 240; 172 and 192: 1024 115 / 110 and 114 / 111, 4096 227 / 216 and 219 / 217, 4500 (192) 235 / 255, 10 K
+// (172) 423 / 441. One matrix has half of the products: 172 classes 4096 191 / 179, 5000 211 / 211; 256 classes 4096 190 / 186; 128 classes 6000 227 / 223, 8000 276 /
+// 274, 9000 312 / 318; 80 classes 8000 280 / 269.
+// 256 classes, four whole tiles of the separate product: 256 columns, 256 seeds 81 / 83, 1024 116 / 116, 4096 223 / 227; 192 columns 1024 111 / 106, 4096 206 / 206;
+// 128 columns 2048 127 / 120, 4096 176 / 174; against that 240 classes, 256 columns 1024 117 / 115, 4096 230 / 223.
 inline bool head_takes(int32_t arch, int32_t n, int32_t d, int32_t C, int32_t n_src_cap) {
     if (arch == NO_ARCH_GCN_SYM || d % 4 || d > HEAD_MOST_COLUMNS || C < 4 || C > HEAD_MOST_CLASSES || (int64_t)n_src_cap * d * 4 >= (1ll << 32)) return false;
     const bool two = !arch_is_gcn(arch);
